@@ -446,8 +446,8 @@ TIG_API int tig_sep_assign(const tig_sep_config *cfg, const int32_t *src, const 
  * All of Alg. 1 up to the node masks: centrality and hubs (floor(top_k * N) of them) on the
  * device, then the edge loop on the host.  src, dst, ts: device pointers; scratch: device,
  * 256-byte aligned, tig_sep_scratch_bytes(N) bytes; every output is a HOST pointer (cent_out [N],
- * is_hub_out [N], the rest as in tig_sep_assign).  Synchronous; allocates host staging for the
- * endpoint arrays (TIG_ENOMEM if that fails).
+ * is_hub_out [N], the rest as in tig_sep_assign).  Synchronous; the endpoint arrays pass through a
+ * pinned host buffer of 4 MiB that the library keeps between calls (TIG_ENOMEM if it cannot be had).
  */
 TIG_API size_t tig_sep_scratch_bytes(int64_t num_nodes);
 TIG_API int tig_sep_partition(const tig_sep_config *cfg, const int32_t *src, const int32_t *dst, const double *ts,

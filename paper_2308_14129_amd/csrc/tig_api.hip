@@ -3,6 +3,7 @@
 
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
 
 #include "tig_internal.h"
@@ -322,6 +323,42 @@ thread_local char g_init_err[256] = "";
 }  // namespace
 
 namespace tig {
+
+static std::mutex g_stage_lock;
+static void *g_stage_kept[kPinnedStageKept];
+
+PinnedStage::PinnedStage() : ptr(nullptr)
+{
+    {
+        const std::lock_guard<std::mutex> hold(g_stage_lock);
+        for (void *&k : g_stage_kept)
+            if (k) {
+                ptr = k;
+                k = nullptr;
+                return;
+            }
+    }
+    if (hipHostMalloc(&ptr, kPinnedStageBytes, hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        ptr = nullptr;
+    }
+}
+
+PinnedStage::~PinnedStage()
+{
+    if (!ptr)
+        return;
+    {
+        const std::lock_guard<std::mutex> hold(g_stage_lock);
+        for (void *&k : g_stage_kept)
+            if (!k) {
+                k = ptr;
+                return;
+            }
+    }
+    (void)hipHostFree(ptr);
+}
+
 int fail_global(const char *what, hipError_t e)
 {
     snprintf(g_init_err, sizeof(g_init_err), "%s: %s", what, hipGetErrorString(e));

@@ -350,6 +350,18 @@ hipError_t modules_attach(const Dims &d, const tig_modules &m, const tig_weights
 // with a module selection; marks: NULL, or two events (after the overwrite, after the rest)
 hipError_t launch_modules(const Dims &d, const LaunchPlan &plan, const PackedWeights &pw, const StepArgs &a,
                           const ModParams &p, hipStream_t s, hipEvent_t *marks);
+// A pinned host buffer for copies between host and device that should not wait page by page.  Buffers
+// are kept for the next user (at most kPinnedStageKept of them; each is in one user's hands at a time, on
+// any thread); `ptr` is NULL where none could be had.  The user waits for its copies before it lets go.
+constexpr size_t kPinnedStageBytes = (size_t)4 << 20;
+constexpr int kPinnedStageKept = 2;
+struct PinnedStage {
+    void *ptr;
+    PinnedStage();
+    ~PinnedStage();
+    PinnedStage(const PinnedStage &) = delete;
+    PinnedStage &operator=(const PinnedStage &) = delete;
+};
 // records a failed HIP call of a context-free entry point (read back with tig_last_error(NULL)); returns TIG_EHIP
 int fail_global(const char *what, hipError_t e);
 

@@ -60,6 +60,25 @@ def test_assign_matches_oracle(sep, name, events, num_parts, k, lam):
     assert shared.tolist() == ref_shared and [p.tolist() for p in parts] == ref_parts
 
 
+@pytest.mark.parametrize("num_parts,lam,eps,hubs", [(2, 1.0, 1e-3, 3), (5, 1.0, 1e-3, 40), (64, 0.7, 1.0, 40), (3, 1e-16, 1e-3, 20),
+                                                    (4, 60.0, 1e-3, 30), (4, 1.0, 1e-13, 30), (1, 1.0, 1e-3, 5)])
+def test_assign_branches_match_oracle(sep, num_parts, lam, eps, hubs):
+    # sizes that drift far apart (non-hubs pile up where they reside) and come together again (hubs), balance terms
+    # that lose against a replica, beat it, or differ by less than a rounding
+    r = np.random.default_rng(num_parts * 100 + hubs)
+    n = 60
+    src = np.concatenate([np.tile([50, 52], 40), r.integers(0, 12, 1500), r.integers(0, n, 1500)]).astype(np.int32)
+    dst = np.concatenate([np.tile([51, 53], 40), r.integers(12, 24, 1500), r.integers(0, n, 1500)]).astype(np.int32)
+    dst = np.where(dst == src, (src + 1) % n, dst).astype(np.int32)
+    cent = np.bincount(src, minlength=n) + np.bincount(dst, minlength=n) + 0.0
+    hub_ids = np.arange(hubs)
+    is_hub = np.zeros(n, dtype=np.uint8)
+    is_hub[hub_ids] = 1
+    ref_part, A, sizes, _ = P.assign_stream(src, dst, n, cent, hub_ids, num_parts, lam, eps)
+    part, node_parts, part_edges = sep.assign(sep.make_config(num_parts, 0.0, 0.0, lam, eps), src, dst, n, cent, is_hub)
+    assert np.array_equal(part, ref_part) and np.array_equal(node_parts, masks(A)) and part_edges.tolist() == sizes
+
+
 def test_assign_rejects_bad_arguments(sep):
     from paper_2308_14129_amd import tig
     ok = dict(src=[0, 1], dst=[1, 2], num_nodes=3, cent=[1.0, 1.0, 1.0], is_hub=[0, 0, 0])
