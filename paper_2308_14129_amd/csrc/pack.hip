@@ -36,55 +36,75 @@ struct Carver {
     }
 };
 
-// C[i*ldc + j] = beta * C[..] + alpha * sum_k A[i*ars + k*acs] * B[k*brs + j*bcs]   (fp64 accumulate)
+// C[i*ldc + j] = c0[i] + C[..] (if add) + alpha * sum_k A[i*ars + k*acs] * B[k*brs + j*bcs]   (fp64 accumulate)
+// A preparation is a dozen of such small products and as many copies: launched one by one they took 0.45 ms
+// (launch after launch of 1 - 20 us each, five dozen in all); every stage of independent ones is one launch
+// now (blockIdx.y names the product): 0.08 ms.
+struct FoldJob {
+    double *C;
+    const void *A, *B;
+    const float *c0;     // NULL, or added per row
+    int ldc, ars, acs, brs, bcs, m, n, kdim;
+    double alpha;
+    bool a64, b64, add;  // operands in double; the previous value of C is added
+    bool b_cos;          // B is taken as cos(B)
+};
+constexpr int kMaxFoldJobs = 25;  // of four heads
+struct FoldJobs {
+    FoldJob j[kMaxFoldJobs];
+    int n;
+};
+
 template <typename TA, typename TB>
-__global__ void k_gemm64(double *C, int ldc, const TA *A, int ars, int acs, const TB *B, int brs,
-                         int bcs, int m, int n, int kdim, double alpha, double beta)
+__device__ inline double fold_dot(const TA *A, int acs, const TB *B, int brs, int kdim, bool b_cos)
 {
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= m * n)
-        return;
-    const int i = idx / n, j = idx % n;
     // four partial sums: the loads of four steps are in flight together and the adds do not wait for each other
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     int k = 0;
+    if (b_cos) {
+        for (; k < kdim; ++k)
+            acc[k < (kdim & ~3) ? k & 3 : 0] += (double)A[(size_t)k * acs] * cos((double)B[(size_t)k * brs]);
+        return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    }
     for (; k + 4 <= kdim; k += 4) {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            acc[u] += (double)A[(size_t)i * ars + (size_t)(k + u) * acs] * (double)B[(size_t)(k + u) * brs + (size_t)j * bcs];
+            acc[u] += (double)A[(size_t)(k + u) * acs] * (double)B[(size_t)(k + u) * brs];
     }
     for (; k < kdim; ++k)
-        acc[0] += (double)A[(size_t)i * ars + (size_t)k * acs] * (double)B[(size_t)k * brs + (size_t)j * bcs];
-    double *c = C + (size_t)i * ldc + j;
-    *c = (beta != 0.0 ? beta * *c : 0.0) + alpha * ((acc[0] + acc[1]) + (acc[2] + acc[3]));
+        acc[0] += (double)A[(size_t)k * acs] * (double)B[(size_t)k * brs];
+    return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
-template <typename TA, typename TB>
-hipError_t gemm64(hipStream_t s, double *C, int ldc, const TA *A, int ars, int acs, const TB *B,
-                  int brs, int bcs, int m, int n, int kdim, double alpha, double beta)
+__global__ void __launch_bounds__(kThreads) k_fold(FoldJobs jobs)
 {
-    const int total = m * n;
-    hipLaunchKernelGGL((k_gemm64<TA, TB>), dim3((total + kThreads - 1) / kThreads), dim3(kThreads), 0,
-                       s, C, ldc, A, ars, acs, B, brs, bcs, m, n, kdim, alpha, beta);
-    return hipGetLastError();
-}
-
-// out[i] = a[i] (+ b[i]) as double / as float, zero beyond n up to n_pad
-__global__ void k_vec_f32(float *out, int n_pad, int n, const double *a, const float *b, const float *c)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_pad)
+    const FoldJob &q = jobs.j[blockIdx.y];
+    const int idx = blockIdx.x * kThreads + threadIdx.x;
+    if (idx >= q.m * q.n)
         return;
-    double v = 0.0;
-    if (i < n) {
-        if (a)
-            v += a[i];
-        if (b)
-            v += (double)b[i];
-        if (c)
-            v += (double)c[i];
-    }
-    out[i] = (float)v;
+    const int i = idx / q.n, j = idx % q.n;
+    const size_t ao = (size_t)i * q.ars, bo = (size_t)j * q.bcs;
+    double v;
+    if (q.a64)
+        v = q.b64 ? fold_dot((const double *)q.A + ao, q.acs, (const double *)q.B + bo, q.brs, q.kdim, false)
+                  : fold_dot((const double *)q.A + ao, q.acs, (const float *)q.B + bo, q.brs, q.kdim, false);
+    else
+        v = q.b64 ? fold_dot((const float *)q.A + ao, q.acs, (const double *)q.B + bo, q.brs, q.kdim, false)
+                  : fold_dot((const float *)q.A + ao, q.acs, (const float *)q.B + bo, q.brs, q.kdim, q.b_cos);
+    double *c = q.C + (size_t)i * q.ldc + j;
+    double base = q.add ? *c : 0.0;
+    if (q.c0)
+        base += (double)q.c0[i];
+    *c = base + q.alpha * v;
+}
+
+hipError_t fold(hipStream_t s, const FoldJobs &jobs)
+{
+    int most = 1;
+    for (int i = 0; i < jobs.n; ++i)
+        most = jobs.j[i].m * jobs.j[i].n > most ? jobs.j[i].m * jobs.j[i].n : most;
+    hipLaunchKernelGGL(k_fold, dim3((most + kThreads - 1) / kThreads, jobs.n), dim3(kThreads), 0, s, jobs);
+    return hipGetLastError();
 }
 
 __global__ void k_to_revolutions(double *out, const float *in, int n)
@@ -92,22 +112,6 @@ __global__ void k_to_revolutions(double *out, const float *in, int n)
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n)
         out[i] = (double)in[i] / 6.283185307179586476925286766559;
-}
-
-__global__ void k_phi0(double *out, const float *time_b, int T)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < T)
-        out[i] = cos((double)time_b[i]);
-}
-
-__global__ void k_copy_block(double *D, int ld, const float *A, int lda, int rows, int cols)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= rows * cols)
-        return;
-    const int i = idx / cols, j = idx % cols;
-    D[(size_t)i * ld + j] = (double)A[(size_t)i * lda + j];
 }
 
 __device__ inline uint16_t f32_to_bf16_rne(float f)
@@ -149,14 +153,65 @@ __device__ inline void pack_element(void *out, size_t idx, int rows, int cols, i
     }
 }
 
-template <typename TS, bool BF16>
-__global__ void k_pack(void *out, const TS *W, int ld, int rows, int cols, int rows_p, int cols_p)
+// What the embedding and closing launches read, out of the folded products: prepared matrices and padded
+// vectors, one launch (blockIdx.y names the piece).
+struct PackMat {
+    void *out;
+    const void *W, *W2;      // columns >= split come from W2 (both row-major, double or float)
+    int ld, ld2, split;
+    int rows, cols, rows_p, cols_p;
+    int half, gap;           // rows >= half: taken `gap` rows earlier from W2h (a matrix of two stacked halves); 0: none
+    const void *W2h;
+    bool w64, w264;
+};
+struct PackVec {
+    float *out;
+    int n, n_pad;
+    const double *a, *a2;    // terms, each may be NULL
+    const float *b;
+};
+constexpr int kPackMats = 5, kPackVecs = 8;
+struct PackJobs {
+    PackMat m[kPackMats];
+    PackVec v[kPackVecs];
+};
+
+__device__ inline float pack_value(const void *W, size_t i, bool w64)
 {
-    const size_t total = (size_t)rows_p * cols_p;
-    const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= total)
-        return;
-    pack_element<BF16>(out, idx, rows, cols, cols_p, [&](int r, int c) { return (float)W[(size_t)r * ld + c]; });
+    return w64 ? (float)((const double *)W)[i] : ((const float *)W)[i];
+}
+
+template <bool BF16>
+__global__ void __launch_bounds__(kThreads) k_pack(PackJobs jobs)
+{
+    const size_t idx = (size_t)blockIdx.x * kThreads + threadIdx.x;
+    const int piece = blockIdx.y;
+    if (piece < kPackMats) {
+        const PackMat &q = jobs.m[piece];
+        if (idx < (size_t)q.rows_p * q.cols_p)
+            pack_element<BF16>(q.out, idx, q.rows, q.cols, q.cols_p, [&](int r, int c) {
+                if (q.half > 0) {  // two stacked halves of half - gap rows each, zero rows between and after
+                    const int h = r >= q.half ? 1 : 0, rr = h ? r - q.half : r;
+                    return rr < q.half - q.gap ? pack_value(h ? q.W2h : q.W, (size_t)rr * q.ld + c, q.w64) : 0.0f;
+                }
+                return c < q.split ? pack_value(q.W, (size_t)r * q.ld + c, q.w64)
+                                   : pack_value(q.W2, (size_t)r * q.ld2 + (c - q.split), q.w264);
+            });
+    } else {
+        const PackVec &q = jobs.v[piece - kPackMats];
+        if (idx < (size_t)q.n_pad) {
+            double v = 0.0;
+            if (idx < (size_t)q.n) {
+                if (q.a)
+                    v += q.a[idx];
+                if (q.a2)
+                    v += q.a2[idx];
+                if (q.b)
+                    v += (double)q.b[idx];
+            }
+            q.out[idx] = (float)v;
+        }
+    }
 }
 
 // Everything the state update's kernels read, prepared in one launch (a training step rebuilds it
@@ -210,21 +265,6 @@ __global__ void k_pack_gru(GruPackJob j)
     }
 }
 
-template <typename TS>
-hipError_t pack(hipStream_t s, int prec, void *out, const TS *W, int ld, int rows, int cols,
-                int rows_p, int cols_p)
-{
-    const size_t total = (size_t)rows_p * cols_p;
-    const dim3 grid((unsigned)((total + kThreads - 1) / kThreads));
-    if (prec == TIG_BF16_MFMA)
-        hipLaunchKernelGGL((k_pack<TS, true>), grid, dim3(kThreads), 0, s, out, W, ld, rows, cols,
-                           rows_p, cols_p);
-    else
-        hipLaunchKernelGGL((k_pack<TS, false>), grid, dim3(kThreads), 0, s, out, W, ld, rows, cols,
-                           rows_p, cols_p);
-    return hipGetLastError();
-}
-
 struct PackedLayout {
     double *time_w_rev, *time_b_rev;
     void *gru_Wr, *gru_Wz, *gru_Win, *gru_Whn;
@@ -273,7 +313,7 @@ PackedLayout layout(const Dims &d, void *base)
 }
 
 struct ScratchLayout {
-    double *phi0, *cQ, *A1, *a1, *G, *PR, *cvec, *gv, *dec, *decF, *bvec;
+    double *cQ, *A1, *a1, *G, *P, *cvec, *cvec2, *decF, *bvec;
     size_t bytes;
 };
 
@@ -281,17 +321,15 @@ ScratchLayout scratch_layout(const Dims &d, void *base)
 {
     Carver c(base);
     ScratchLayout S;
-    S.phi0 = c.take<double>(d.T);
     S.cQ = c.take<double>(d.da);
     S.A1 = c.take<double>((size_t)d.N1 * d.M);
     S.a1 = c.take<double>(d.N1);
     S.G = c.take<double>((size_t)d.E * d.da);
-    S.PR = c.take<double>((size_t)d.E * (d.H * d.dkvp + d.M));
+    S.P = c.take<double>((size_t)d.E * d.N1);
     S.cvec = c.take<double>(d.E);
-    S.gv = c.take<double>(d.da);
-    S.dec = c.take<double>((size_t)2 * d.Ep * d.E);
-    S.decF = c.take<double>((size_t)2 * d.Ep * d.E);
-    S.bvec = c.take<double>(d.E);
+    S.cvec2 = c.take<double>(d.E);
+    S.decF = c.take<double>((size_t)2 * d.E * d.E);
+    S.bvec = c.take<double>((size_t)2 * d.E);
     S.bytes = c.off;
     return S;
 }
@@ -351,88 +389,80 @@ hipError_t pack_weights(const Dims &d, const tig_weights &w, void *dst, void *sc
     }
 
     if (with_embed) {
-    // ---- attention query fold ---------------------------------------------------------------
-    // cQ = W_Q[:, M:] Phi(0) + b_Q
-    hipLaunchKernelGGL(k_phi0, grid(T), blk, 0, s, S.phi0, w.time_b, T);
-    hipLaunchKernelGGL(k_copy_block, grid(da), blk, 0, s, S.cQ, 1, w.b_Q, 1, da, 1);
-    TIG_TRY(hipGetLastError());
-    TIG_TRY((gemm64<float, double>(s, S.cQ, 1, w.W_Q + M, da, 1, S.phi0, 1, 1, da, 1, T, 1.0, 1.0)));
-    const double scale = 1.0 / sqrt((double)dh);
-    // The embedding kernel holds a key/value row in the order [Phi (T) | s_v (M) | e (F)] (time
-    // encoding first, so that its lanes are densely packed); the model's order is
-    // [s_v | e | Phi].  seg[] maps each run of model columns to its place in the kernel's order.
-    const int F = d.F;
-    const int seg_src[3] = {M + F, 0, M};
-    const int seg_dst[3] = {0, T, T + M};
-    const int seg_len[3] = {T, M, F};
-    for (int h = 0; h < H; ++h) {
-        const float *WK_h = w.W_K + (size_t)h * dh * dkv;   // [dh x dkv]
-        const float *WQm_h = w.W_Q + (size_t)h * dh * da;   // [dh x da], first M columns used
-        for (int g = 0; g < 3; ++g) {
-            // A1_h[j][m] = scale * sum_r W_K[h*dh + r][j] * W_Q[h*dh + r][m]
-            TIG_TRY((gemm64<float, float>(s, S.A1 + ((size_t)h * d.dkvp + seg_dst[g]) * M, M,
-                                          WK_h + seg_src[g], 1, dkv, WQm_h, da, 1, seg_len[g], M, dh,
-                                          scale, 0.0)));
-            // a1_h[j] = scale * sum_r W_K[h*dh + r][j] * cQ[h*dh + r]
-            TIG_TRY((gemm64<float, double>(s, S.a1 + (size_t)h * d.dkvp + seg_dst[g], 1, WK_h + seg_src[g],
-                                           1, dkv, S.cQ + h * dh, 1, 1, seg_len[g], 1, dh, scale, 0.0)));
+        const double scale = 1.0 / sqrt((double)dh);
+        // The embedding kernel holds a key/value row in the order [Phi (T) | s_v (M) | e (F)] (time
+        // encoding first, so that its lanes are densely packed); the model's order is
+        // [s_v | e | Phi].  seg[] maps each run of model columns to its place in the kernel's order.
+        const int F = d.F;
+        const int seg_src[3] = {M + F, 0, M};
+        const int seg_dst[3] = {0, T, T + M};
+        const int seg_len[3] = {T, M, F};
+        const int ld_m1 = da + M;
+        FoldJobs one = {}, two = {};
+        auto add = [](FoldJobs &f, double *C, int ldc, const void *A, bool a64, int ars, int acs, const void *B, bool b64, int brs,
+                      int bcs, int m, int n, int kdim, double alpha) -> FoldJob & {
+            FoldJob &q = f.j[f.n++];
+            q = FoldJob{C, A, B, nullptr, ldc, ars, acs, brs, bcs, m, n, kdim, alpha, a64, b64, false, false};
+            return q;
+        };
+        // ---- products of the weights as given ---------------------------------------------
+        {   // cQ = W_Q[:, M:] Phi(0) + b_Q
+            FoldJob &q = add(one, S.cQ, 1, w.W_Q + M, false, da, 1, w.time_b, false, 1, 1, da, 1, T, 1.0);
+            q.c0 = w.b_Q;
+            q.b_cos = true;
         }
-    }
-    TIG_TRY(pack<double>(s, d.prec, L.emb_A1, S.A1, M, d.N1, M, d.N1, d.Mq));
-    hipLaunchKernelGGL(k_vec_f32, grid(d.N1), blk, 0, s, L.emb_a1, d.N1, d.N1, (const double *)S.a1,
-                       (const float *)nullptr, (const float *)nullptr);
-    TIG_TRY(hipGetLastError());
-
-    // ---- value / out-projection / merge layer-1 fold ---------------------------------------
-    // G = W_m1[:, :da] W_O   [E x da]
-    const int ld_m1 = da + M;
-    TIG_TRY((gemm64<float, float>(s, S.G, da, w.W_m1, ld_m1, 1, w.W_O, da, 1, E, da, da, 1.0, 0.0)));
-    const int ldPR = H * d.dkvp + M;
-    for (int h = 0; h < H; ++h) {
-        // P_h = G[:, h*dh:(h+1)*dh] W_V[h*dh:(h+1)*dh, :]   [E x dkv]
-        for (int g = 0; g < 3; ++g)
-            TIG_TRY((gemm64<double, float>(s, S.PR + (size_t)h * d.dkvp + seg_dst[g], ldPR, S.G + h * dh,
-                                           da, 1, w.W_V + (size_t)h * dh * dkv + seg_src[g], dkv, 1, E,
-                                           seg_len[g], dh, 1.0, 0.0)));
-    }
-    hipLaunchKernelGGL(k_copy_block, grid((size_t)E * M), blk, 0, s, S.PR + (size_t)H * d.dkvp, ldPR,
-                       w.W_m1 + da, ld_m1, E, M);
-    TIG_TRY(hipGetLastError());
-    TIG_TRY(pack<double>(s, d.prec, L.emb_PR, S.PR, ldPR, E, ldPR, d.Ep, d.K2));
-    // c = b_m1 + W_m1a b_O + G b_V ;  c0 = b_m1
-    TIG_TRY((gemm64<float, float>(s, S.cvec, 1, w.W_m1, ld_m1, 1, w.b_O, 1, 1, E, 1, da, 1.0, 0.0)));
-    TIG_TRY((gemm64<double, float>(s, S.cvec, 1, S.G, da, 1, w.b_V, 1, 1, E, 1, da, 1.0, 1.0)));
-    hipLaunchKernelGGL(k_vec_f32, grid(d.Ep), blk, 0, s, L.emb_c, d.Ep, E, (const double *)S.cvec, w.b_m1,
-                       (const float *)nullptr);
-    hipLaunchKernelGGL(k_vec_f32, grid(d.Ep), blk, 0, s, L.emb_c0, d.Ep, E, (const double *)nullptr,
-                       w.b_m1, (const float *)nullptr);
-    TIG_TRY(hipGetLastError());
-
-    // ---- merge layer 2 and decoder -----------------------------------------------------------
-    TIG_TRY(pack<float>(s, d.prec, L.emb_Wm2, w.W_m2, E, E, E, d.Ep, d.Ek));
-    hipLaunchKernelGGL(k_vec_f32, grid(d.Ep), blk, 0, s, L.emb_bm2, d.Ep, E, (const double *)nullptr,
-                       w.b_m2, (const float *)nullptr);
-    // decoder layer 1 split by operand: rows 0..E-1 <- W_d1[:, :E], rows Ep..Ep+E-1 <- W_d1[:, E:]
-    hipLaunchKernelGGL(k_copy_block, grid((size_t)E * E), blk, 0, s, S.dec, E, w.W_d1, 2 * E, E, E);
-    hipLaunchKernelGGL(k_copy_block, grid((size_t)E * E), blk, 0, s, S.dec + (size_t)d.Ep * E, E,
-                       w.W_d1 + E, 2 * E, E, E);
-    TIG_TRY(hipGetLastError());
-    TIG_TRY(pack<double>(s, d.prec, L.dec_W, S.dec, E, 2 * d.Ep, E, 2 * d.Ep, d.Ek));
-    hipLaunchKernelGGL(k_vec_f32, grid(d.Ep), blk, 0, s, L.dec_b1, d.Ep, E, (const double *)nullptr,
-                       w.b_d1, (const float *)nullptr);
-    // The same layer applied to h1 directly (merge layer 2 folded in), for launches whose row tiles
-    // are whole roles: W_d1a W_m2, W_d1b W_m2 and b_d1 + (W_d1a + W_d1b) b_m2.
-    TIG_TRY((gemm64<double, float>(s, S.decF, E, S.dec, E, 1, w.W_m2, E, 1, 2 * d.Ep, E, E, 1.0, 0.0)));
-    TIG_TRY((gemm64<double, float>(s, S.bvec, 1, S.dec, E, 1, w.b_m2, 1, 1, E, 1, E, 1.0, 0.0)));
-    TIG_TRY((gemm64<double, float>(s, S.bvec, 1, S.dec + (size_t)d.Ep * E, E, 1, w.b_m2, 1, 1, E, 1, E, 1.0, 1.0)));
-    TIG_TRY(pack<double>(s, d.prec, L.dec_WF, S.decF, E, 2 * d.Ep, E, 2 * d.Ep, d.Ek));
-    hipLaunchKernelGGL(k_vec_f32, grid(d.Ep), blk, 0, s, L.dec_b1f, d.Ep, E, (const double *)S.bvec, w.b_d1,
-                       (const float *)nullptr);
-    hipLaunchKernelGGL(k_vec_f32, grid(d.Ep), blk, 0, s, L.dec_w2, d.Ep, E, (const double *)nullptr,
-                       w.w_d2, (const float *)nullptr);
-    hipLaunchKernelGGL(k_vec_f32, grid(1), blk, 0, s, L.dec_b2, 1, 1, (const double *)nullptr, w.b_d2,
-                       (const float *)nullptr);
-    TIG_TRY(hipGetLastError());
+        for (int h = 0; h < H; ++h)  // A1_h[j][m] = scale * sum_r W_K[h*dh + r][j] * W_Q[h*dh + r][m]
+            for (int g = 0; g < 3; ++g)
+                add(one, S.A1 + ((size_t)h * d.dkvp + seg_dst[g]) * M, M, w.W_K + (size_t)h * dh * dkv + seg_src[g], false, 1, dkv,
+                    w.W_Q + (size_t)h * dh * da, false, da, 1, seg_len[g], M, dh, scale);
+        // G = W_m1[:, :da] W_O   [E x da]
+        add(one, S.G, da, w.W_m1, false, ld_m1, 1, w.W_O, false, da, 1, E, da, da, 1.0);
+        // c = b_m1 + W_m1a b_O + G b_V (first term here)
+        add(one, S.cvec, 1, w.W_m1, false, ld_m1, 1, w.b_O, false, 1, 1, E, 1, da, 1.0);
+        // The first decoder layer applied to h1 directly (merge layer 2 folded in), for launches whose row
+        // tiles are whole roles: W_d1a W_m2, W_d1b W_m2 and b_d1 + (W_d1a + W_d1b) b_m2.
+        for (int half = 0; half < 2; ++half) {
+            add(one, S.decF + (size_t)half * E * E, E, w.W_d1 + half * E, false, 2 * E, 1, w.W_m2, false, E, 1, E, E, E, 1.0);
+            add(one, S.bvec + (size_t)half * E, 1, w.W_d1 + half * E, false, 2 * E, 1, w.b_m2, false, 1, 1, E, 1, E, 1.0);
+        }
+        TIG_TRY(fold(s, one));
+        // ---- products of those ------------------------------------------------------------
+        for (int h = 0; h < H; ++h)
+            for (int g = 0; g < 3; ++g) {
+                // a1_h[j] = scale * sum_r W_K[h*dh + r][j] * cQ[h*dh + r]
+                add(two, S.a1 + (size_t)h * d.dkvp + seg_dst[g], 1, w.W_K + (size_t)h * dh * dkv + seg_src[g], false, 1, dkv,
+                    S.cQ + h * dh, true, 1, 1, seg_len[g], 1, dh, scale);
+                // P_h = G[:, h*dh:(h+1)*dh] W_V[h*dh:(h+1)*dh, :]   [E x dkv]
+                add(two, S.P + (size_t)h * d.dkvp + seg_dst[g], d.N1, S.G + h * dh, true, da, 1,
+                    w.W_V + (size_t)h * dh * dkv + seg_src[g], false, dkv, 1, E, seg_len[g], dh, 1.0);
+            }
+        add(two, S.cvec2, 1, S.G, true, da, 1, w.b_V, false, 1, 1, E, 1, da, 1.0);
+        TIG_TRY(fold(s, two));
+        // ---- into the kernels' layouts ----------------------------------------------------
+        PackJobs pj = {};
+        pj.m[0] = PackMat{L.emb_A1, S.A1, nullptr, M, 0, M, d.N1, M, d.N1, d.Mq, 0, 0, nullptr, true, false};
+        pj.m[1] = PackMat{L.emb_PR, S.P, w.W_m1 + da, d.N1, ld_m1, d.N1, E, d.N1 + M, d.Ep, d.K2, 0, 0, nullptr, true, false};
+        pj.m[2] = PackMat{L.emb_Wm2, w.W_m2, nullptr, E, 0, E, E, E, d.Ep, d.Ek, 0, 0, nullptr, false, false};
+        // decoder layer 1 split by operand: rows 0..E-1 <- W_d1[:, :E], rows Ep..Ep+E-1 <- W_d1[:, E:]
+        pj.m[3] = PackMat{L.dec_W, w.W_d1, nullptr, 2 * E, 0, E, 2 * d.Ep, E, 2 * d.Ep, d.Ek, d.Ep, d.Ep - E, w.W_d1 + E, false, false};
+        pj.m[4] = PackMat{L.dec_WF, S.decF, nullptr, E, 0, E, 2 * d.Ep, E, 2 * d.Ep, d.Ek, d.Ep, d.Ep - E, S.decF + (size_t)E * E, true, false};
+        pj.v[0] = PackVec{L.emb_a1, d.N1, d.N1, S.a1, nullptr, nullptr};
+        pj.v[1] = PackVec{L.emb_c, E, d.Ep, S.cvec, S.cvec2, w.b_m1};
+        pj.v[2] = PackVec{L.emb_c0, E, d.Ep, nullptr, nullptr, w.b_m1};
+        pj.v[3] = PackVec{L.emb_bm2, E, d.Ep, nullptr, nullptr, w.b_m2};
+        pj.v[4] = PackVec{L.dec_b1, E, d.Ep, nullptr, nullptr, w.b_d1};
+        pj.v[5] = PackVec{L.dec_b1f, E, d.Ep, S.bvec, S.bvec + E, w.b_d1};
+        pj.v[6] = PackVec{L.dec_w2, E, d.Ep, nullptr, nullptr, w.w_d2};
+        pj.v[7] = PackVec{L.dec_b2, 1, 1, nullptr, nullptr, w.b_d2};
+        size_t most = d.N1;
+        for (const PackMat &q : pj.m)
+            most = (size_t)q.rows_p * q.cols_p > most ? (size_t)q.rows_p * q.cols_p : most;
+        const dim3 g3((unsigned)((most + kThreads - 1) / kThreads), kPackMats + kPackVecs);
+        if (d.prec == TIG_BF16_MFMA)
+            hipLaunchKernelGGL(k_pack<true>, g3, blk, 0, s, pj);
+        else
+            hipLaunchKernelGGL(k_pack<false>, g3, blk, 0, s, pj);
+        TIG_TRY(hipGetLastError());
     }
 
     pw->time_w_rev = L.time_w_rev;

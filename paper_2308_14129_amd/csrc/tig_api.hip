@@ -299,12 +299,61 @@ RawWeights raw_weights_layout(const Dims &d, void *base)
     return R;
 }
 
+// Scratch during tig_init: [flags | raw weights | fold scratch | adjacency sort].  The pieces do not share
+// memory, so that the weights' host side runs while the device builds the adjacency.
+size_t init_fold_offset(const Dims &d) { return 256 + raw_weights_layout(d, nullptr).bytes; }
+size_t init_sort_offset(const Dims &d) { return init_fold_offset(d) + align_up(pack_scratch_bytes(d)); }
+
 size_t init_scratch_bytes(const Dims &d, int64_t N, int64_t E)
 {
-    // [flags | raw weights | fold scratch]  and, after that is consumed, the adjacency sort
-    const size_t a = 256 + raw_weights_layout(d, nullptr).bytes + pack_scratch_bytes(d);
-    const size_t b = csr_build_scratch_bytes(E, N);
-    return a > b ? a : b;
+    return init_sort_offset(d) + csr_build_scratch_bytes(E, N);
+}
+
+// Copies the caller's weight arrays (host or device) to their places in R.  Host arrays pass through a
+// pinned buffer as one range (array by array from pageable memory each copy waits for its own staging:
+// 0.75 ms for twenty-two arrays of 1.6 MB together, now 0.1 ms).
+// The last range may still be on its way when this returns: `stage` is kept until the stream is done.
+hipError_t copy_weights_in(const Dims &d, const tig_weights &w, const RawWeights &R, const PinnedStage &stage, hipStream_t s)
+{
+    WeightField f[32];
+    const int n = weight_fields(d, f);
+    hipError_t e = hipSuccess;
+    char *range_dst = nullptr;  // the range collected so far: stage.ptr[0, range) -> range_dst
+    size_t range = 0;
+    bool used = false;
+    auto flush = [&]() -> hipError_t {
+        hipError_t r = hipSuccess;
+        if (range > 0)
+            r = hipMemcpyAsync(range_dst, stage.ptr, range, hipMemcpyHostToDevice, s);
+        used = used || range > 0;
+        range = 0;
+        return r;
+    };
+    for (int i = 0; i < n && e == hipSuccess; ++i) {
+        const float *src = w.*(f[i].member);
+        char *dst = (char *)(R.w.*(f[i].member));
+        const size_t bytes = sizeof(float) * f[i].count;
+        hipPointerAttribute_t at;
+        const bool host = stage.ptr && hipPointerGetAttributes(&at, src) == hipSuccess && at.type != hipMemoryTypeDevice &&
+                          at.type != hipMemoryTypeManaged && bytes <= kPinnedStageBytes;
+        if (!host) {
+            (void)hipGetLastError();
+            e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDefault, s);
+            continue;
+        }
+        if (range > 0 && (size_t)(dst - range_dst) + bytes > kPinnedStageBytes) {
+            if ((e = flush()) != hipSuccess || (e = hipStreamSynchronize(s)) != hipSuccess)
+                break;
+        }
+        if (range == 0) {
+            if (used && (e = hipStreamSynchronize(s)) != hipSuccess)  // (the buffer is read by an earlier copy)
+                break;
+            range_dst = dst;
+        }
+        memcpy((char *)stage.ptr + (dst - range_dst), src, bytes);
+        range = (size_t)(dst - range_dst) + bytes;
+    }
+    return e == hipSuccess ? flush() : e;
 }
 
 int fail(tig_ctx *ctx, int status, const char *what, hipError_t e = hipSuccess)
@@ -357,6 +406,50 @@ PinnedStage::~PinnedStage()
             }
     }
     (void)hipHostFree(ptr);
+}
+
+// The two hint words of a context (see tig_ctx): places of one pinned page that contexts take and give back
+// (a page of its own per context cost 0.2 ms of tig_init and tig_destroy).  A step still running when its
+// context is destroyed may write a hint into a place that another context has taken: hints shape launches,
+// never results.  No place left, or no page: the context does without.
+constexpr int kHintPlaces = 64, kHintWords = 16;
+static std::mutex g_hint_lock;
+static int32_t *g_hint_host, *g_hint_dev;
+static unsigned long long g_hint_taken;
+
+static void hint_words_take(int32_t **host, int32_t **dev)
+{
+    *host = *dev = nullptr;
+    const std::lock_guard<std::mutex> hold(g_hint_lock);
+    if (!g_hint_host) {
+        void *h = nullptr, *d = nullptr;
+        if (hipHostMalloc(&h, 4 * kHintWords * kHintPlaces, hipHostMallocMapped | hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            return;
+        }
+        if (hipHostGetDevicePointer(&d, h, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            (void)hipHostFree(h);
+            return;
+        }
+        g_hint_host = (int32_t *)h;
+        g_hint_dev = (int32_t *)d;
+    }
+    if (~g_hint_taken == 0ull)
+        return;
+    const int k = __builtin_ctzll(~g_hint_taken);
+    g_hint_taken |= 1ull << k;
+    *host = g_hint_host + k * kHintWords;
+    *dev = g_hint_dev + k * kHintWords;
+    (*host)[0] = (*host)[1] = 0;
+}
+
+static void hint_words_give(int32_t *host)
+{
+    if (!host)
+        return;
+    const std::lock_guard<std::mutex> hold(g_hint_lock);
+    g_hint_taken &= ~(1ull << ((host - g_hint_host) / kHintWords));
 }
 
 int fail_global(const char *what, hipError_t e)
@@ -472,39 +565,32 @@ int tig_init(const tig_config *cfg, const tig_graph *graph, const tig_weights *w
         INIT_TRY(hipMemcpyAsync(L.edge_feat, graph->edge_feat, sizeof(float) * (size_t)E * d.F,
                                 hipMemcpyDefault, s), "copy edge_feat");
     }
-    // validation on the device
+    // validation on the device; the adjacency and the prepared weights do not wait for its verdict (their
+    // kernels stay inside their arrays whatever the ids are)
     int32_t *flags = (int32_t *)scratch;
     INIT_TRY(launch_fill_zero(flags, 256, s), "clear flags");
     INIT_TRY(launch_validate_graph(L.src, L.dst, L.ts, E, N, flags, s), "validate");
-    int32_t hflags[4] = {0, 0, 0, 0};
-    INIT_TRY(hipMemcpyAsync(hflags, flags, sizeof(hflags), hipMemcpyDeviceToHost, s), "read flags");
-    INIT_TRY(hipStreamSynchronize(s), "sync");
-    if (hflags[0] || hflags[1] || hflags[2]) {
-        delete ctx;
-        return hflags[0] ? TIG_ERANGE : (hflags[1] ? TIG_EUNSORTED : TIG_ESELFLOOP);
-    }
-
-    // weights: stage raw fp32 copies, then fold / pad / reorder
-    ctx->has_model = weights != nullptr;
-    if (weights) {
-        char *wbase = (char *)scratch + 256;
-        RawWeights R = raw_weights_layout(d, wbase);
-        for (int i = 0; i < nwf; ++i)
-            INIT_TRY(hipMemcpyAsync((void *)(R.w.*(wf[i].member)), weights->*(wf[i].member),
-                                    sizeof(float) * wf[i].count, hipMemcpyDefault, s), "copy weights");
-        INIT_TRY(pack_weights(d, R.w, L.packed, wbase + R.bytes, &ctx->pw, s), "pack weights");
-        INIT_TRY(hipStreamSynchronize(s), "sync");
-    }
 
     // temporal adjacency
-    INIT_TRY(csr_build(L.src, L.dst, L.ts, E, N, L.indptr, L.csr, L.pos, scratch, scratch_bytes, s), "adjacency build");
+    INIT_TRY(csr_build(L.src, L.dst, L.ts, E, N, L.indptr, L.csr, L.pos, (char *)scratch + init_sort_offset(d),
+                       scratch_bytes - init_sort_offset(d), s), "adjacency build");
+
+    // weights: raw fp32 copies (while the device builds the adjacency), then fold / pad / reorder
+    const PinnedStage stage;
+    ctx->has_model = weights != nullptr;
+    if (weights) {
+        const RawWeights R = raw_weights_layout(d, (char *)scratch + 256);
+        INIT_TRY(copy_weights_in(d, *weights, R, stage, s), "copy weights");
+        INIT_TRY(pack_weights(d, R.w, L.packed, (char *)scratch + init_fold_offset(d), &ctx->pw, s), "pack weights");
+    }
 
     // state after a reset
     INIT_TRY(launch_fill_zero(L.mem, sizeof(float) * (size_t)N * d.M, s), "zero memory");
     INIT_TRY(launch_fill_zero(L.lu, sizeof(double) * (size_t)N, s), "zero last_update");
     INIT_TRY(launch_fill_zero(L.key[0], sizeof(unsigned long long) * (size_t)N, s), "zero keys");
     INIT_TRY(launch_fill_zero(L.key[1], sizeof(unsigned long long) * (size_t)N, s), "zero keys");
-    INIT_TRY(hipStreamSynchronize(s), "sync");
+    int32_t hflags[4] = {0, 0, 0, 0};
+    INIT_TRY(hipMemcpyAsync(hflags, flags, sizeof(hflags), hipMemcpyDeviceToHost, s), "read flags");
 
     // per-step intermediates: counters and the claim table start from zero
     ctx->S = step_scratch(d, scratch);
@@ -515,17 +601,12 @@ int tig_init(const tig_config *cfg, const tig_graph *graph, const tig_weights *w
     }
     INIT_TRY(launch_fill_zero(ctx->S.tab, sizeof(unsigned long long) * (size_t)ctx->S.tab_slots, s), "clear claim table");
     INIT_TRY(hipStreamSynchronize(s), "sync");
-#undef INIT_TRY
-    if (hipHostMalloc((void **)&ctx->rows_seen_host, 64, hipHostMallocMapped) == hipSuccess) {
-        ctx->rows_seen_host[0] = ctx->rows_seen_host[1] = 0;
-        if (hipHostGetDevicePointer((void **)&ctx->rows_seen_dev, ctx->rows_seen_host, 0) != hipSuccess) {
-            (void)hipHostFree(ctx->rows_seen_host);
-            ctx->rows_seen_host = ctx->rows_seen_dev = nullptr;
-        }
-    } else {
-        (void)hipGetLastError();
-        ctx->rows_seen_host = ctx->rows_seen_dev = nullptr;
+    if (hflags[0] || hflags[1] || hflags[2]) {
+        delete ctx;
+        return hflags[0] ? TIG_ERANGE : (hflags[1] ? TIG_EUNSORTED : TIG_ESELFLOOP);
     }
+#undef INIT_TRY
+    hint_words_take(&ctx->rows_seen_host, &ctx->rows_seen_dev);
     *out = ctx;
     return TIG_OK;
 }
@@ -1232,8 +1313,7 @@ void tig_destroy(tig_ctx *ctx)
     if (ctx->have_marks)
         for (int i = 0; i <= kNumStepKernels; ++i)
             (void)hipEventDestroy(ctx->marks[i]);
-    if (ctx->rows_seen_host)
-        (void)hipHostFree(ctx->rows_seen_host);
+    hint_words_give(ctx->rows_seen_host);
     if (ctx->have_train_side) {
         (void)hipStreamSynchronize(ctx->train_side.stream);
         for (int i = 0; i < kTrainForks; ++i)
