@@ -9,6 +9,8 @@
 
 #include <hip/hip_runtime.h>
 #include <rocprim/device/device_radix_sort.hpp>
+#include <rocprim/iterator/counting_iterator.hpp>
+#include <rocprim/iterator/transform_iterator.hpp>
 
 #include "tig_internal.h"
 
@@ -36,33 +38,42 @@ __global__ void k_validate(const int32_t *__restrict__ src, const int32_t *__res
     }
 }
 
-__global__ void k_fill_pairs(const int32_t *__restrict__ src, const int32_t *__restrict__ dst,
-                             int64_t num_entries, uint32_t *__restrict__ keys,
-                             uint32_t *__restrict__ vals)
+// Endpoint of entry i = 2 * eid + role: what the sort reads as its keys (no array of pairs is written first).
+struct EntryNode {
+    const int32_t *src, *dst;
+    __device__ uint32_t operator()(uint32_t i) const { return (uint32_t)((i & 1u) ? dst : src)[i >> 1]; }
+};
+
+// The event as one 16-byte record, so that an adjacency entry costs one random read.
+struct __attribute__((aligned(16))) EventRecord {
+    int32_t src, dst;
+    double ts;
+};
+
+__global__ void k_event_records(const int32_t *__restrict__ src, const int32_t *__restrict__ dst,
+                                const double *__restrict__ ts, int64_t num_events, EventRecord *__restrict__ rec)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < num_entries; i += stride) {
-        const int64_t e = i >> 1;
-        keys[i] = (uint32_t)((i & 1) ? dst[e] : src[e]);
-        vals[i] = (uint32_t)i;
-    }
+    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < num_events; e += stride)
+        rec[e] = EventRecord{src[e], dst[e], ts[e]};
 }
 
-__global__ void k_fill_csr(const int32_t *__restrict__ src, const int32_t *__restrict__ dst,
-                           const double *__restrict__ ts, int64_t num_entries,
+// Bound by the random accesses: beyond the few heaviest nodes, consecutive entries of a list are events far
+// apart, so every entry is a memory line of its own for its event and another for its `pos`.
+__global__ void k_fill_csr(const EventRecord *__restrict__ rec, int64_t num_entries,
                            const uint32_t *__restrict__ vals_sorted, CsrEntry *__restrict__ csr,
                            int32_t *__restrict__ pos)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < num_entries; p += stride) {
         const uint32_t i = vals_sorted[p];
-        const int32_t e = (int32_t)(i >> 1);
-        CsrEntry ent;
-        ent.nbr = (i & 1) ? src[e] : dst[e];
-        ent.eid = e;
-        ent.ts = ts[e];
-        csr[p] = ent;
+        const EventRecord r = rec[i >> 1];
         pos[i] = (int32_t)p;  // where entry 2*eid + role sits in the adjacency array
+        CsrEntry ent;
+        ent.nbr = (i & 1) ? r.src : r.dst;
+        ent.eid = (int32_t)(i >> 1);
+        ent.ts = r.ts;
+        csr[p] = ent;
     }
 }
 
@@ -102,9 +113,12 @@ int key_bits(int64_t num_nodes)
     return bits;
 }
 
-// Upper bound on rocPRIM's temporary storage for the in-place (double-buffer) pair sort: its
-// per-block digit counters.  Checked against the real requirement in csr_build.
-size_t sort_temp_bound(int64_t num_entries) { return (size_t)num_entries * 4 + ((size_t)64 << 20); }
+// Upper bound on rocPRIM's temporary storage for the pair sort: the second pair of arrays its passes
+// alternate with and its per-block digit counters.  Checked against the real requirement in csr_build.
+size_t sort_temp_bound(int64_t num_entries) { return (size_t)num_entries * 12 + ((size_t)64 << 20); }
+
+using EntryIndex = rocprim::counting_iterator<uint32_t>;
+using EntryKeys = rocprim::transform_iterator<EntryIndex, EntryNode, uint32_t>;
 
 }  // namespace
 
@@ -123,7 +137,7 @@ size_t csr_build_scratch_bytes(int64_t num_events, int64_t num_nodes)
     const int64_t n2 = 2 * num_events;
     if (n2 == 0)
         return 256;
-    return 4 * align_up(sizeof(uint32_t) * (size_t)n2) + align_up(sort_temp_bound(n2));
+    return 2 * align_up(sizeof(uint32_t) * (size_t)n2) + align_up(sort_temp_bound(n2));
 }
 
 hipError_t csr_build(const int32_t *src, const int32_t *dst, const double *ts, int64_t num_events,
@@ -138,33 +152,29 @@ hipError_t csr_build(const int32_t *src, const int32_t *dst, const double *ts, i
     const int bits = key_bits(num_nodes);
     const size_t seg = align_up(sizeof(uint32_t) * (size_t)n2);
     char *base = (char *)scratch;
-    rocprim::double_buffer<uint32_t> keys((uint32_t *)(base), (uint32_t *)(base + seg));
-    rocprim::double_buffer<uint32_t> vals((uint32_t *)(base + 2 * seg), (uint32_t *)(base + 3 * seg));
-    void *temp = base + 4 * seg;
+    uint32_t *const keys = (uint32_t *)base, *const vals = (uint32_t *)(base + seg);
+    void *temp = base + 2 * seg;
+    const EntryIndex entries(0u);
+    const EntryKeys nodes(entries, EntryNode{src, dst});
     size_t temp_bytes = 0;
-    hipError_t err = rocprim::radix_sort_pairs(nullptr, temp_bytes, keys, vals, (size_t)n2, 0u,
+    hipError_t err = rocprim::radix_sort_pairs(nullptr, temp_bytes, nodes, keys, entries, vals, (size_t)n2, 0u,
                                                (unsigned)bits, s);
     if (err != hipSuccess)
         return err;
-    if (temp_bytes > sort_temp_bound(n2))
+    if (temp_bytes > sort_temp_bound(n2) || sizeof(EventRecord) * (size_t)num_events > sort_temp_bound(n2))
         return hipErrorOutOfMemory;
-
-    hipLaunchKernelGGL(k_fill_pairs, dim3(grid_for(n2)), dim3(kThreads), 0, s, src, dst, n2,
-                       keys.current(), vals.current());
-    err = hipGetLastError();
-    if (err != hipSuccess)
-        return err;
     // stable: entries of one node keep their input order, i.e. ascending event id
-    err = rocprim::radix_sort_pairs(temp, temp_bytes, keys, vals, (size_t)n2, 0u, (unsigned)bits, s);
+    err = rocprim::radix_sort_pairs(temp, temp_bytes, nodes, keys, entries, vals, (size_t)n2, 0u, (unsigned)bits, s);
     if (err != hipSuccess)
         return err;
-    hipLaunchKernelGGL(k_fill_csr, dim3(grid_for(n2)), dim3(kThreads), 0, s, src, dst, ts, n2,
-                       (const uint32_t *)vals.current(), csr, pos);
+    EventRecord *const rec = (EventRecord *)temp;  // (the sort is done with it)
+    hipLaunchKernelGGL(k_event_records, dim3(grid_for(num_events)), dim3(kThreads), 0, s, src, dst, ts, num_events, rec);
+    hipLaunchKernelGGL(k_fill_csr, dim3(grid_for(n2)), dim3(kThreads), 0, s, rec, n2, vals, csr, pos);
     err = hipGetLastError();
     if (err != hipSuccess)
         return err;
     hipLaunchKernelGGL(k_indptr, dim3(grid_for(num_nodes + 1)), dim3(kThreads), 0, s,
-                       (const uint32_t *)keys.current(), n2, num_nodes, indptr);
+                       (const uint32_t *)keys, n2, num_nodes, indptr);
     return hipGetLastError();
 }
 
