@@ -102,7 +102,9 @@ __device__ inline void tile_gemm2(floatx4 &acc1, floatx4 &acc2, const char *A, i
     }
 }
 
-template <int PREC>
+// MOD: the state update of a module selection (mean messages, the plain recurrent cell, library exp / tanh);
+// an instance of its own, so that the headline's carries none of it (in one kernel it cost a step 2 us).
+template <int PREC, bool MOD>
 __global__ void __launch_bounds__(kGruThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))  // 128 registers: two workgroups per unit
 k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
 {
@@ -209,6 +211,7 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                     const float *self = a.mem + (size_t)u * g.M;
                     const float *other = a.mem + (size_t)o * g.M;
                     const float *feat = a.edge_feat + (size_t)(gj.first_eid + row_e[r]) * g.F;
+                    const float *mean = MOD && a.mean_msg ? a.mean_msg + (size_t)row_i[r] * (g.M + g.T + g.F) : nullptr;
                     dt[i] = live ? row_t[r] - a.lu[u] : 0.0;  // since the node's last update
 #pragma unroll
                     for (int k = 0; k < kAhead; ++k) {
@@ -217,6 +220,8 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                         if (live && j < g.Dmsg) {
                             if (j < g.M)
                                 v[i][k] = self[j];
+                            else if (MOD && mean)  // (uniform)
+                                v[i][k] = mean[j - g.M];
                             else if (j < 2 * g.M)
                                 v[i][k] = other[j - g.M];
                             else if (j >= 2 * g.M + g.T)
@@ -233,7 +238,7 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                         const int j = base + lane + kWave * k;
                         if (j < g.Kg) {
                             float x = v[i][k];
-                            if (live && j >= 2 * g.M && j < 2 * g.M + g.T)
+                            if (live && !(MOD && a.mean_msg) && j >= 2 * g.M && j < 2 * g.M + g.T)
                                 x = time_enc(tw_tab[2 * (j - 2 * g.M)], tw_tab[2 * (j - 2 * g.M) + 1], dt[i]);
                             P::store_a(X + (size_t)r * g.ldx, j, x);
                         }
@@ -268,7 +273,12 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                 const int per = (kblocks + ksplit - 1) / ksplit;
                 const int kb_lo = ks * per;
                 const int kb_hi = kblocks < kb_lo + per ? kblocks : kb_lo + per;
-                if (half == 0)
+                if (MOD && a.upd == kUpdModuleRnn) {  // one gate: the halves of a pair split its k range once more
+                    floatx4 one[1] = {acc1};
+                    const int mid = kb_lo + (kb_hi - kb_lo + 1) / 2, lo = half ? mid : kb_lo, hi = half ? kb_hi : mid;
+                    tile_gemm<PREC, 1, 4>(one, X, g.ldx, lo, w.gru_Wr, kblocks, lo, hi - lo, ct);
+                    acc1 = one[0];
+                } else if (half == 0)
                     tile_gemm2<PREC, 3>(acc1, acc2, X, g.ldx, w.gru_Wr, w.gru_Wz, kblocks, kblocks, kb_lo, kb_hi, ct);
                 else  // input part over the whole message, hidden part over s_self (the first Khn k's)
                     tile_gemm2<PREC, 3>(acc1, acc2, X, g.ldx, w.gru_Win, w.gru_Whn, kblocks, kblocks_hn, kb_lo,
@@ -301,12 +311,22 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                     const bool pre = idx < kGruThreads;  // the preloaded biases are this element's
                     const float br = pre ? pb[0] : w.gru_br[col], bz = pre ? pb[1] : w.gru_bz[col];
                     const float bin = pre ? pb[2] : w.gru_bin[col], bhn = pre ? pb[3] : w.gru_bhn[col];
-                    const float r = 1.0f / (1.0f + __expf(-(sr + br)));
-                    const float z = 1.0f / (1.0f + __expf(-(sz + bz)));
                     const float h = P::load_elem(X + (size_t)row * g.ldx, col);  // s_self
-                    const float x = sin_ + bin + r * (shn + bhn);
-                    const float e2 = __expf(2.0f * x);          // tanh(x) = 1 - 2 / (e^{2x} + 1)
-                    const float n = 1.0f - 2.0f / (e2 + 1.0f);
+                    float r, z, n;
+                    if (!MOD) {
+                        r = 1.0f / (1.0f + __expf(-(sr + br)));
+                        z = 1.0f / (1.0f + __expf(-(sz + bz)));
+                        const float x = sin_ + bin + r * (shn + bhn);
+                        const float e2 = __expf(2.0f * x);          // tanh(x) = 1 - 2 / (e^{2x} + 1)
+                        n = 1.0f - 2.0f / (e2 + 1.0f);
+                    } else if (a.upd == kUpdModuleGru) {
+                        r = 1.0f / (1.0f + expf(-(sr + br)));
+                        z = 1.0f / (1.0f + expf(-(sz + bz)));
+                        n = tanhf(sin_ + bin + r * (shn + bhn));
+                    } else {  // s = tanh(W_i m + b_i + W_h s' + b_h): both halves' sums make up the one gate
+                        r = z = 0.0f;
+                        n = tanhf(sr + sin_ + br);
+                    }
                     a.staging[(size_t)row_i[row] * g.M + col] = (1.0f - z) * n + z * h;
                     if (a.gru_gates) {  // (uniform) a training step keeps the gates for its backward pass
                         float *go = a.gru_gates + (size_t)(r0 + row) * 4 * g.M + col;
@@ -343,9 +363,11 @@ GruParams gru_params(const Dims &d)
     return g;
 }
 
-const void *gru_kernel(const Dims &d)
+const void *gru_kernel(const Dims &d, int upd)
 {
-    return d.prec == TIG_BF16_MFMA ? (const void *)k_gru<TIG_BF16_MFMA> : (const void *)k_gru<TIG_FP32>;
+    if (d.prec == TIG_BF16_MFMA)  // (module selections run in fp32 contexts)
+        return (const void *)k_gru<TIG_BF16_MFMA, false>;
+    return upd == kUpdGru ? (const void *)k_gru<TIG_FP32, false> : (const void *)k_gru<TIG_FP32, true>;
 }
 
 // GRU workgroups and column slices for a batch of `count` events with about `wins_est` winners.
@@ -388,7 +410,12 @@ int gru_lds_bytes(const Dims &d)
 
 hipError_t prepare_gru(const Dims &d, const LaunchPlan &plan)
 {
-    return hipFuncSetAttribute(gru_kernel(d), hipFuncAttributeMaxDynamicSharedMemorySize, gru_lds_bytes(d));
+    for (int upd : {kUpdGru, kUpdModuleGru}) {
+        const hipError_t e = hipFuncSetAttribute(gru_kernel(d, upd), hipFuncAttributeMaxDynamicSharedMemorySize, gru_lds_bytes(d));
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
 }
 
 // Ahead of the embedding launch: the GRU of the batch this step applies and, if asked for, the
@@ -414,7 +441,7 @@ hipError_t launch_gru(const Dims &d, const LaunchPlan &plan, const PackedWeights
     if (blocks == 0)
         return hipSuccess;  // nothing to apply, nothing to finish
     void *args[] = {&aa, &gj, &ww, &g, &dp};
-    return hipLaunchKernel(gru_kernel(d), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
+    return hipLaunchKernel(gru_kernel(d, a.upd), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
 }
 
 // The closing launch of a step: scores and embedding rows of its events, inspection outputs, the
@@ -443,7 +470,7 @@ hipError_t launch_closing(const Dims &d, const LaunchPlan &plan, const PackedWei
     int blocks = g.n_gru + p.n_event_blocks + p.n_expand_blocks + p.n_fin_row_blocks + p.n_fin_slot_blocks;
     blocks = blocks > 0 ? blocks : 1;  // (block 0 clears the counter whatever else there is to do)
     void *args[] = {&aa, &gj, &ww, &g, &p};
-    return hipLaunchKernel(gru_kernel(d), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
+    return hipLaunchKernel(gru_kernel(d, a.upd), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
 }
 
 }  // namespace tig

@@ -3,13 +3,15 @@
 // be chosen from ... GRU, RNN", the embedding function f is "identity, time projection or
 // attention"; Sec. II-A: nodes may carry static features), device side.  gfx950 only, fp32.
 //
-// A context with an attached module selection runs its batch step here instead of in the fused
-// kernels of the headline instance (last message, GRU, attention), in plain per-row kernels:
-//   k_mod_update   one workgroup per node of the applied batch: aggregated message (the last one, or
-//                  the mean of all the node's messages of the batch, every one built from the memory
-//                  at the start of the step), then the GRU or the plain recurrent cell -> staged row
-//   k_mod_commit   memory overwrite M <- s_i(t) and last_update, after every message has been built
-//   k_mod_simple   identity / time-projection embedding of every query, straight to the output
+// A context with an attached module selection runs its state update in k_gru (message build and gates on
+// the matrix cores; the plain recurrent cell is a one-gate product there) and, with one attention layer
+// and no node features, the fused embedding and closing launches of the headline instance.  The rest:
+//   k_mod_msgsum / k_mod_mean   mean aggregator: sums of all the node's messages of the batch (either role,
+//                  every one built from the memory at the start of the step), then their means
+//   k_mod_final    the last launch of a step without the fused ones: identity / time-projection embedding of
+//                  sixteen events' queries (or their rows out of the attention layers), both logits on the
+//                  matrix cores, beside it the memory overwrite and the preparation of the batch expected next
+//   k_mod_commit   memory overwrite M <- s_i(t) and last_update ahead of attention layers that read the table
 //   k_mr_items / k_mr_attn + k_rowgemm   attention embedding with node features and / or two stacked
 //                  layers: every layer product as one contraction over all items of the layer, the
 //                  attention core per item in its re-associated form (stated above k_mr_items); a
@@ -18,10 +20,6 @@
 //                  neighbourhood): the K most recent events, before the QUERY's time, of every
 //                  neighbour of every distinct query; the first layer then runs over each used
 //                  (query, neighbour) pair and each query itself, the second layer over those rows
-//   k_mod_decode   eight events per workgroup: both logits (and, for the attention embedding, the
-//                  per-query embedding rows out of the distinct rows)
-// Weight matrices are read through transposed copies ([in x out]) so that a thread that owns an
-// output reads consecutive addresses.
 #include <hip/hip_runtime.h>
 
 #include "kernels_common.h"
@@ -35,12 +33,11 @@ namespace {
 
 constexpr int kModThreads = 256;
 constexpr int kModWaves = kModThreads / kWave;
-constexpr int kEV = 8;   // events per decoder workgroup
 
 struct ModDims {
-    int M, T, F, E, K, H, da, dh, dkv, Dmsg;
-    int G;  // gate blocks of the state update: 3 (GRU: r, z, n) or 1 (plain recurrent cell)
-    int agg, upd, emb;
+    int M, T, F, E, K, H, da, dh, dkv;
+    int Ep, Ek;  // E padded to the decoder's output tiles / to its k-blocks
+    int emb;
 };
 
 // The dimensions the second layer sees: its input rows are E wide.
@@ -55,19 +52,7 @@ ModDims second_layer_dims(ModDims d)
 
 ModDims mod_dims(const Dims &d, const ModParams &p)
 {
-    return ModDims{d.M, d.T, d.F, d.E, d.K, d.H, d.da, d.dh, d.dkv, d.Dmsg, p.upd == TIG_UPD_GRU ? 3 : 1, p.agg, p.upd, p.emb};
-}
-
-// y[j] = bias[j] + sum_i WT[i * out + j] * x[i]   (x, y in LDS)
-__device__ inline void matvec_t(const float *WT, int in, int out, const float *x, const float *bias, float *y)
-{
-    for (int j = threadIdx.x; j < out; j += kModThreads) {
-        float acc = bias ? bias[j] : 0.0f;
-#pragma unroll 16
-        for (int i = 0; i < in; ++i)  // (unrolled: sixteen independent loads in flight, not one per step)
-            acc += WT[(size_t)i * out + j] * x[i];
-        y[j] = acc;
-    }
+    return ModDims{d.M, d.T, d.F, d.E, d.K, d.H, d.da, d.dh, d.dkv, d.Ep, d.Ek, p.emb};
 }
 
 // r_i(t): the state row the embedding module reads for node v (memory row plus the static feature
@@ -90,7 +75,7 @@ __device__ inline float repr_elem(const StepArgs &a, const ModParams &p, int M, 
 // up: a workgroup first collects its kMsgEntries entries' rows in an LDS table of kMsgSlots rows
 // (direct-mapped by accumulation row; a row whose place is taken goes to memory directly) and adds
 // every table row to memory once, dealt out over the node's kAccCopies copies.  The rows in memory
-// are all zero between steps: k_mod_update clears what it has read.
+// are all zero between steps: k_mod_mean clears what it has read.
 constexpr int kMsgThreads = 1024, kMsgEntries = 64, kMsgSlots = 16;
 
 __global__ void __launch_bounds__(kMsgThreads) k_mod_msgsum(StepArgs a, ModDims d, ModParams p)
@@ -161,78 +146,33 @@ __global__ void __launch_bounds__(kMsgThreads) k_mod_msgsum(StepArgs a, ModDims 
     }
 }
 
-// Aggregated message + state update of one node of the applied batch (the batch's winner list names
-// each node once, with its last event).
-__global__ void __launch_bounds__(kModThreads) k_mod_update(StepArgs a, ModDims d, ModParams p)
+// Mean aggregator, second half: the means of one updated node's message columns (one wavefront per winner).
+__global__ void __launch_bounds__(kModThreads) k_mod_mean(StepArgs a, ModDims d, ModParams p)
 {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int M = d.M, T = d.T, F = d.F, D = d.Dmsg, GM = d.G * d.M;
-    const int rest = M + T + F;                 // message columns that differ between a node's messages
-    float *msg = (float *)smem;                 // [D]
-    float *h = msg + D;                         // [M]
-    float *gi = h + M;                          // [GM]
-    float *gh = gi + GM;                        // [GM]
-
+    const int rest = d.M + d.T + d.F;
     int n_win = *a.n_win;
     n_win = n_win < 2 * a.msg_count ? n_win : 2 * a.msg_count;
-    const int r = (int)blockIdx.x;
+    const int r = (int)blockIdx.x * kModWaves + wave_id();
     if (r >= n_win)
         return;
-    const WinDesc w = a.win[r];
-    if (w.node < 0 || (int64_t)w.node >= a.num_nodes || w.other < 0 || (int64_t)w.other >= a.num_nodes ||
-        w.entry < 0 || w.entry >= 2 * a.msg_count)
+    const int entry = a.win[r].entry;
+    if (entry < 0 || entry >= 2 * a.msg_count)
         return;  // (not a descriptor of this batch)
-    for (int j = threadIdx.x; j < M; j += kModThreads) {
-        const float v = a.mem[(size_t)w.node * M + j];
-        h[j] = v;
-        msg[j] = v;
-    }
-    if (d.agg == TIG_AGG_LAST) {
-        const double lu0 = a.lu[w.node];
-        const int64_t eid = a.msg_first_eid + (w.entry >> 1);
-        for (int j = threadIdx.x; j < rest; j += kModThreads) {
-            float v;
-            if (j < M)
-                v = a.mem[(size_t)w.other * M + j];
-            else if (j < M + T)
-                v = time_enc(p.time_w_rev[j - M], p.time_b_rev[j - M], w.t - lu0);
-            else
-                v = a.edge_feat[(size_t)eid * F + (j - M - T)];
-            msg[M + j] = v;
-        }
-    } else {
-        double *acc = p.acc + (size_t)w.entry * kAccCopies * rest;
-        const int n = p.acc_cnt[w.entry];
-        const double inv = 1.0 / (double)(n > 0 ? n : 1);
-        for (int j = threadIdx.x; j < rest; j += kModThreads) {
-            double sum = 0.0;
+    double *acc = p.acc + (size_t)entry * kAccCopies * rest;
+    const int n = p.acc_cnt[entry];
+    const double inv = 1.0 / (double)(n > 0 ? n : 1);
+    for (int j = lane_id(); j < rest; j += kWave) {
+        double sum = 0.0;
 #pragma unroll
-            for (int c = 0; c < kAccCopies; ++c) {  // (fixed order: the result does not depend on the adds' order beyond fp64 rounding)
-                sum += acc[(size_t)c * rest + j];
-                acc[(size_t)c * rest + j] = 0.0;
-            }
-            msg[M + j] = (float)(sum * inv);
-        }
-        __syncthreads();  // (every thread has read the count)
-        if (threadIdx.x == 0)
-            p.acc_cnt[w.entry] = 0;
+        for (int c = 0; c < kAccCopies; ++c)  // (fixed order: the result does not depend on the adds' order beyond fp64 rounding)
+            sum += acc[(size_t)c * rest + j];
+#pragma unroll
+        for (int c = 0; c < kAccCopies; ++c)
+            acc[(size_t)c * rest + j] = 0.0;
+        p.mean_msg[(size_t)entry * rest + j] = (float)(sum * inv);
     }
-    __syncthreads();
-    matvec_t(p.T_i, D, GM, msg, p.b_i, gi);
-    matvec_t(p.T_h, M, GM, h, p.b_h, gh);
-    __syncthreads();
-    for (int j = threadIdx.x; j < M; j += kModThreads) {
-        float out;
-        if (d.upd == TIG_UPD_GRU) {
-            const float rr = 1.0f / (1.0f + expf(-(gi[j] + gh[j])));
-            const float zz = 1.0f / (1.0f + expf(-(gi[M + j] + gh[M + j])));
-            const float nn = tanhf(gi[2 * M + j] + rr * gh[2 * M + j]);
-            out = (1.0f - zz) * nn + zz * h[j];
-        } else {
-            out = tanhf(gi[j] + gh[j]);
-        }
-        a.staging[(size_t)w.entry * M + j] = out;
-    }
+    if (lane_id() == 0)
+        p.acc_cnt[entry] = 0;
 }
 
 __global__ void __launch_bounds__(kModThreads) k_mod_commit(StepArgs a, int M)
@@ -241,39 +181,23 @@ __global__ void __launch_bounds__(kModThreads) k_mod_commit(StepArgs a, int M)
 }
 
 // ------------------------------------------------------------------------------------------
-// Identity / time-projection embedding: emb[q] = r_u(t), or (1 + (t - last_update[u]) w_p) * r_u(t),
-// for the queries [sources | destinations | negatives]; also the winner flags out.
-__global__ void __launch_bounds__(kModThreads) k_mod_simple(StepArgs a, ModDims d, ModParams p)
-{
-    const int M = d.M;
-    const size_t n = (size_t)a.roles * a.count * M;
-    const size_t idx = (size_t)blockIdx.x * kModThreads + threadIdx.x;
-    if (idx < (size_t)2 * a.count && a.out_is_winner && a.win_flags)
-        a.out_is_winner[idx] = a.win_flags[idx];
-    if (idx >= n)
-        return;
-    const int q = (int)(idx / M), j = (int)(idx - (size_t)q * M);
-    const int role = q / a.count, b = q - role * a.count;
-    const int64_t e = a.first_eid + b;
-    const int32_t u = role == 0 ? a.src[e] : (role == 1 ? a.dst[e] : a.neg[b]);
-    float v = repr_elem(a, p, M, u, j);
-    if (d.emb == TIG_EMB_TIME_PROJECTION && u >= 0 && (int64_t)u < a.num_nodes)
-        v = (float)((1.0 + (a.ts[e] - a.lu[u]) * (double)p.time_proj_w[j]) * (double)v);
-    a.emb[idx] = v;
-}
-
-// ------------------------------------------------------------------------------------------
 // Two layers: the neighbour tables of the second hop.  One workgroup per query row (distinct source /
 // destination queries, then the negatives, whose own table is looked up first): wavefront w takes the
 // neighbours k = w, w + waves, ... and looks up the K most recent events of neighbour k before the
 // QUERY's time into row q * K + k of the second-hop tables.
-__global__ void __launch_bounds__(kModThreads) k_mod_hop2(StepArgs a, ModDims d, ModParams p)
+__global__ void __launch_bounds__(kModThreads) k_mod_hop2(StepArgs a, ModDims d, ModParams p, int msg_count, int n_commit)
 {
     __shared__ int s_cnt;
+    if ((int)blockIdx.x < n_commit) {  // the memory overwrite (nothing of this launch reads the memory)
+        StepArgs c = a;
+        c.msg_count = msg_count;
+        overwrite_memory(c, d.M, (int)(blockIdx.x * kModWaves + threadIdx.x / kWave), n_commit * kModWaves);
+        return;
+    }
     int n_u = *a.qs.n_u;
     n_u = n_u < 2 * a.count ? n_u : 2 * a.count;
     const int n_rows = n_u + (a.roles == 3 ? a.count : 0);
-    const int x = (int)blockIdx.x;
+    const int x = (int)blockIdx.x - n_commit;
     if (x >= n_rows)
         return;
     const int K = d.K;
@@ -596,80 +520,160 @@ __device__ inline int mod_row_of_entry(const QuerySet &qs, int i, int entries)
     return s >= 0 && s < entries ? s : 0;
 }
 
-// Both logits of kEV events.  from_rows: the embeddings are the distinct rows of the query set (and
-// are copied out per query here); else they are already in the output, [sources | destinations |
-// negatives].
-__global__ void __launch_bounds__(kModThreads) k_mod_decode(StepArgs a, ModDims d, ModParams p, int from_rows)
+// The last launch of a step: the preparation of the batch expected next (workgroups of 1024 threads, as
+// winners_block and dedup_block want), the memory overwrite, and workgroups of sixteen events (embedding
+// rows into LDS and out, both logits).
+//   ROWS   the embeddings are the distinct rows of the query set (attention layers; the memory has been
+//          overwritten by an earlier launch)
+//   else   identity / time projection: emb = r_u(t), or (1 + (t - last_update[u]) w_p) * r_u(t), from the
+//          state as this step leaves it -- the staged row and the winning event's time for a node
+//          the step updates (the overwrite runs beside this), the memory row and last_update for the others
+// First decoder layer on the matrix cores: the sixteen sources against the weights' first half, the
+// sixteen destinations and sixteen negatives against the second, an output tile of sixteen columns per
+// wavefront.  Bound by latency (ids -> keys -> rows, then the weights' first touch): 1000 events of 100
+// columns in 7 us; a workgroup of eight events with the weights read once per event column took 24 us
+// after a launch of 4 us for the rows.
+constexpr int kFinEvents = 16, kFinThreads = 1024, kFinWaves = kFinThreads / kWave;
+
+struct FinalParams {
+    int n_side;    // workgroups that prepare the next batch (first: they take the longest)
+    int n_commit;  // then: of the memory overwrite; the ones beyond take sixteen events each
+    int applied;   // events of the applied batch (0: none)
+    int ldr;       // LDS row stride of the embedding rows, bytes
+    int32_t *clear;  // a counter that block 0 sets to 0, or NULL
+};
+
+template <bool ROWS>
+__global__ void __launch_bounds__(kFinThreads) k_mod_final(StepArgs a, ModDims d, ModParams p, PackedWeights w, FinalParams f)
 {
+    using P = Prec<TIG_FP32>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int E = d.E, B = a.count, roles = a.roles;
-    float *em = (float *)smem;            // [kEV][3][E]
-    float *part = em + kEV * 3 * E;       // [kEV][2][waves]
-    const int b0 = (int)blockIdx.x * kEV;
-    const int nev = B - b0 < kEV ? B - b0 : kEV;
-    for (int idx = threadIdx.x; idx < nev * roles * E; idx += kModThreads) {
-        const int ev = idx / (roles * E), rem = idx - ev * roles * E;
-        const int r = rem / E, j = rem - r * E;
-        const int b = b0 + ev;
-        float v;
-        if (from_rows) {
-            const int row = r < 2 ? mod_row_of_entry(a.qs, 2 * b + r, 2 * B) : 2 * B + b;
-            v = a.emb_u[(size_t)row * E + j];
-            a.emb[((size_t)r * B + b) * E + j] = v;
-        } else {
-            v = a.emb[((size_t)r * B + b) * E + j];
+    int x = (int)blockIdx.x;
+    if (x == 0 && threadIdx.x == 0) {
+        if (f.clear)
+            *f.clear = 0;
+        if (a.rows_seen && f.applied > 0)
+            a.rows_seen[1] = *a.n_win;  // (a hint for the host)
+    }
+    if (x < f.n_side) {
+        if (a.sel.count > 0) {
+            if (x == 0) {
+                winners_block(a, a.sel, smem);
+                return;
+            }
+            --x;
         }
-        em[(ev * 3 + r) * E + j] = v;
+        if (a.ded.count > 0 && x < a.ded.n_wgs)
+            dedup_block(a, a.ded, d.K, x, smem);
+        return;
+    }
+    x -= f.n_side;
+    if (x < f.n_commit) {
+        overwrite_memory(a, d.M, x * kFinWaves + wave_id(), f.n_commit * kFinWaves);
+        return;
+    }
+    x -= f.n_commit;
+    const int E = d.E, B = a.count, roles = a.roles;
+    char *em = smem;                                              // [3 roles x 16 events] rows of ldr bytes
+    int32_t *row_ref = (int32_t *)(em + (size_t)3 * kFinEvents * f.ldr);  // [48] row to read
+    int32_t *row_node = row_ref + 3 * kFinEvents;                 // [48] node, or -1
+    double *row_dt = (double *)(row_node + 3 * kFinEvents);       // [48] t - last_update
+    float *part = (float *)(row_dt + 3 * kFinEvents);             // [output tiles][2][16]
+    const int b0 = x * kFinEvents;
+    const int lane = lane_id(), wave = wave_id();
+    if ((int)threadIdx.x < 3 * kFinEvents) {
+        const int role = (int)threadIdx.x / kFinEvents, b = b0 + (int)threadIdx.x % kFinEvents;
+        int32_t ref = kRefNone, u = -1;
+        double dt = 0.0;
+        if (b < B && role < roles) {
+            if (ROWS) {
+                ref = role < 2 ? mod_row_of_entry(a.qs, 2 * b + role, 2 * B) : 2 * B + b;
+            } else {
+                const int64_t e = a.first_eid + b;
+                u = role == 0 ? a.src[e] : (role == 1 ? a.dst[e] : a.neg[b]);
+                const double t = a.ts[e];
+                if (u < 0 || (int64_t)u >= a.num_nodes)
+                    u = -1;
+                if (u >= 0) {
+                    const unsigned long long key = a.msg_count > 0 ? a.msg_key[u] : 0ull;
+                    const double lu = a.lu[u];
+                    ref = ref_of_key(ref_ctx(a), u, key);
+                    dt = t - (ref >= 0 ? lu : a.ts[a.msg_first_eid + (~ref >> 1)]);
+                }
+            }
+            if (role < 2 && a.out_is_winner && a.win_flags)
+                a.out_is_winner[2 * b + role] = a.win_flags[2 * b + role];
+        }
+        row_ref[threadIdx.x] = ref;
+        row_node[threadIdx.x] = u;
+        row_dt[threadIdx.x] = dt;
     }
     __syncthreads();
-    float sp[kEV], sn[kEV];
+    for (int j0 = 0; j0 < d.Ek; j0 += 2 * kWave) {  // (all of a wavefront's rows in flight together)
+        float v[3][2], nf[3][2];
+        int32_t node[3];
+        double dt[3];
 #pragma unroll
-    for (int ev = 0; ev < kEV; ++ev)
-        sp[ev] = sn[ev] = 0.0f;
-    // (no condition inside the loops: events beyond the batch repeat event 0, a step without negatives
-    // reads the destination row twice; both results are dropped below)
-    const int noff = roles == 3 ? 2 * E : E;
-    for (int j = threadIdx.x; j < E; j += kModThreads) {
-        float ya[kEV], yb[kEV], yn[kEV];
+        for (int i = 0; i < 3; ++i) {
+            const int32_t ref = __builtin_amdgcn_readfirstlane(row_ref[wave + i * kFinWaves]);
+            node[i] = __builtin_amdgcn_readfirstlane(row_node[wave + i * kFinWaves]);
+            dt[i] = row_dt[wave + i * kFinWaves];
+            const float *row = ROWS ? a.emb_u + (size_t)(ref > 0 ? ref : 0) * E
+                                    : (ref >= 0 ? a.mem + (size_t)ref * E : a.staging + (size_t)(ref == kRefNone ? 0 : ~ref) * E);
+            const __amdgpu_buffer_rsrc_t rr =
+                __builtin_amdgcn_make_buffer_rsrc((void *)row, 0, ref == kRefNone ? 0 : E * 4, kBufferFlags);
+            const bool has_nf = !ROWS && p.node_feat && node[i] >= 0;  // (uniform)
+            const float *feat = has_nf ? p.node_feat + (size_t)node[i] * E : row;
+            const __amdgpu_buffer_rsrc_t rf = __builtin_amdgcn_make_buffer_rsrc((void *)feat, 0, has_nf ? E * 4 : 0, kBufferFlags);
 #pragma unroll
-        for (int ev = 0; ev < kEV; ++ev)
-            ya[ev] = yb[ev] = yn[ev] = 0.0f;
-#pragma unroll 10
-        for (int i = 0; i < E; ++i) {  // (unrolled: the weight loads of ten steps are in flight together)
-            const float wa = p.T_d1[(size_t)i * E + j], wb = p.T_d1[(size_t)(E + i) * E + j];
-#pragma unroll
-            for (int ev = 0; ev < kEV; ++ev) {
-                const float *row = em + (ev < nev ? ev : 0) * 3 * E;
-                ya[ev] = fmaf(wa, row[i], ya[ev]);
-                yb[ev] = fmaf(wb, row[E + i], yb[ev]);
-                yn[ev] = fmaf(wb, row[noff + i], yn[ev]);
+            for (int k = 0; k < 2; ++k) {
+                v[i][k] = buffer_load_f32(rr, (uint32_t)(j0 + lane + kWave * k) * 4u);
+                nf[i][k] = ROWS ? 0.0f : buffer_load_f32(rf, (uint32_t)(j0 + lane + kWave * k) * 4u);
             }
         }
-        const float b1 = p.b_d1[j], w2 = p.w_d2[j];
 #pragma unroll
-        for (int ev = 0; ev < kEV; ++ev) {
-            sp[ev] += w2 * fmaxf(ya[ev] + yb[ev] + b1, 0.0f);
-            sn[ev] += w2 * fmaxf(ya[ev] + yn[ev] + b1, 0.0f);
-        }
-    }
+        for (int i = 0; i < 3; ++i) {
+            const int r = wave + i * kFinWaves, b = b0 + wave;  // (kFinWaves = kFinEvents: row i of the wavefront has role i)
 #pragma unroll
-    for (int ev = 0; ev < kEV; ++ev) {
-        const float s1 = wave_sum_uniform(sp[ev]), s2 = wave_sum_uniform(sn[ev]);
-        if (lane_id() == 0) {
-            part[(ev * 2 + 0) * kModWaves + wave_id()] = s1;
-            part[(ev * 2 + 1) * kModWaves + wave_id()] = s2;
+            for (int k = 0; k < 2; ++k) {
+                const int j = j0 + lane + kWave * k;
+                float y = ROWS ? v[i][k] : v[i][k] + nf[i][k];
+                if (!ROWS && d.emb == TIG_EMB_TIME_PROJECTION && node[i] >= 0 && j < E)
+                    y = (float)((1.0 + dt[i] * (double)p.time_proj_w[j]) * (double)y);
+                if (j < d.Ek)
+                    P::store_a(em + (size_t)r * f.ldr, j, y);
+                if (j < E && b < B && i < roles)
+                    a.emb[((size_t)i * B + b) * E + j] = y;
+            }
         }
     }
     __syncthreads();
-    if ((int)threadIdx.x < nev * 2) {
-        const int ev = threadIdx.x >> 1, pr = threadIdx.x & 1;
-        float s = p.b_d2[0];
-        for (int w = 0; w < kModWaves; ++w)
-            s += part[(ev * 2 + pr) * kModWaves + w];
-        if (pr == 0)
-            a.score_pos[b0 + ev] = s;
-        else if (roles == 3)
-            a.score_neg[b0 + ev] = s;
+    const int nE = d.Ep / 16, kb = d.Ek / P::KB;
+    for (int nt = wave; nt < nE; nt += kFinWaves) {
+        floatx4 src[1] = {floatx4{0, 0, 0, 0}}, oth[2] = {floatx4{0, 0, 0, 0}, floatx4{0, 0, 0, 0}};
+        const int col = nt * 16 + (lane & 15);
+        const float b1 = w.dec_b1[col], w2 = w.dec_w2[col];  // (0 in the padding)
+        tile_gemm<TIG_FP32, 1, 4>(src, em, f.ldr, 0, w.dec_W, kb, 0, kb, nt);
+        tile_gemm<TIG_FP32, 2, 4>(oth, em + (size_t)kFinEvents * f.ldr, f.ldr, 0, w.dec_W, kb, 0, kb, nE + nt);
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float y = row_sum_all(w2 * fmaxf(src[0][v] + oth[q][v] + b1, 0.0f));
+                if ((lane & 15) == 0)
+                    part[(nt * 2 + q) * kFinEvents + 4 * (lane >> 4) + v] = y;
+            }
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < 2 * kFinEvents) {
+        const int q = (int)threadIdx.x / kFinEvents, ev = (int)threadIdx.x % kFinEvents;
+        float sum = w.dec_b2[0];
+        for (int nt = 0; nt < nE; ++nt)
+            sum += part[(nt * 2 + q) * kFinEvents + ev];
+        if (b0 + ev < B && q == 0)
+            a.score_pos[b0 + ev] = sum;
+        else if (b0 + ev < B && roles == 3)
+            a.score_neg[b0 + ev] = sum;
     }
 }
 
@@ -691,24 +695,12 @@ __global__ void k_mod_revolutions(double *out, const float *in, int n)
 
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
-int update_lds(const ModDims &d) { return (d.Dmsg + d.M + 2 * d.G * d.M) * 4; }
-
 int msgsum_lds(const ModDims &d) { return kMsgSlots * (d.M + d.T + d.F) * 8 + 2 * kMsgSlots * 4; }
 
-int decode_lds(const ModDims &d) { return (kEV * 3 * d.E + kEV * 2 * kModWaves) * 4; }
-
-// One matrix of the workspace: raw copy (kept for nothing but the transpose) and its transpose.
-struct MatJob {
-    const float *src;     // caller's [rows x cols]
-    const float **dst_t;  // where the transposed copy's pointer goes
-    int rows, cols;
-};
-
-struct VecJob {
-    const float *src;
-    const float **dst;
-    size_t n;
-};
+int final_lds(const ModDims &d)
+{
+    return 3 * kFinEvents * lds_row_bytes(d.Ek) + 3 * kFinEvents * 16 + d.Ep / 16 * 2 * kFinEvents * 4;
+}
 
 }  // namespace
 
@@ -723,7 +715,7 @@ static size_t mod_layout(const Dims &d, int agg, int upd, int emb, int layers, b
         off += align_up(count * elem);
         return q;
     };
-    const size_t M = d.M, T = d.T, E = d.E, D = d.Dmsg, G = upd == TIG_UPD_GRU ? 3 : 1;
+    const size_t M = d.M, T = d.T, E = d.E;
     const bool attn = emb == TIG_EMB_ATTENTION;
     ModParams q = {};
     q.agg = agg;
@@ -732,11 +724,7 @@ static size_t mod_layout(const Dims &d, int agg, int upd, int emb, int layers, b
     q.layers = layers == 2 ? 2 : 1;
     q.time_w_rev = (const double *)take(T, 8);
     q.time_b_rev = (const double *)take(T, 8);
-    q.b_i = (const float *)take(G * M, 4);
-    q.b_h = (const float *)take(G * M, 4);
-    q.T_i = (const float *)take(D * G * M, 4);
-    q.T_h = (const float *)take(M * G * M, 4);
-    size_t biggest = D * G * M;
+    size_t biggest = T;
     if (attn) {
         for (int l = 0; l < q.layers; ++l) {
             // layer l reads rows of width in_w: the state width, then the first layer's width
@@ -748,20 +736,13 @@ static size_t mod_layout(const Dims &d, int agg, int upd, int emb, int layers, b
             A.b_O = (const float *)take(a_w, 4);
             A.b_m1 = (const float *)take(E, 4);
             A.b_m2 = (const float *)take(E, 4);
-            A.T_Q = (const float *)take(a_w * a_w, 4);
             A.T_K = (const float *)take(kv_w * a_w, 4);
-            A.T_V = (const float *)take(kv_w * a_w, 4);
-            A.T_O = (const float *)take(a_w * a_w, 4);
-            A.T_m1 = (const float *)take((a_w + in_w) * E, 4);
-            A.T_m2 = (const float *)take(E * E, 4);
             A.N_Q = (const float *)take(a_w * a_w, 4);
             A.N_V = (const float *)take(a_w * kv_w, 4);
             A.N_O = (const float *)take(a_w * a_w, 4);
             A.N_m1 = (const float *)take(E * (a_w + in_w), 4);
             A.N_m2 = (const float *)take(E * E, 4);
-            const size_t c[] = {a_w * a_w, kv_w * a_w, (a_w + in_w) * E, E * E};
-            for (size_t v : c)
-                biggest = v > biggest ? v : biggest;
+            biggest = kv_w * a_w > biggest ? kv_w * a_w : biggest;
         }
         if (q.layers == 2) {
             const size_t R2 = (size_t)3 * d.max_batch * d.K;  // rows of the second-hop tables
@@ -795,18 +776,14 @@ static size_t mod_layout(const Dims &d, int agg, int upd, int emb, int layers, b
             q.mr_n = (int32_t *)take(64, 4);
         }
     }
-    q.b_d1 = (const float *)take(E, 4);
-    q.w_d2 = (const float *)take(E, 4);
-    q.b_d2 = (const float *)take(1, 4);
-    q.T_d1 = (const float *)take(2 * E * E, 4);
-    biggest = 2 * E * E > biggest ? 2 * E * E : biggest;
     if (emb == TIG_EMB_TIME_PROJECTION)
         q.time_proj_w = (const float *)take(M, 4);
     if (agg == TIG_AGG_MEAN) {
         q.acc = (double *)take((size_t)2 * d.max_batch * kAccCopies * (M + T + d.F), 8);
         q.acc_cnt = (int32_t *)take((size_t)2 * d.max_batch, 4);
+        q.mean_msg = (float *)take((size_t)2 * d.max_batch * (M + T + d.F), 4);
     }
-    float *stage = (float *)take(biggest > T ? biggest : T, 4);
+    float *stage = (float *)take(biggest, 4);
     float *nf = node_feat ? (float *)take((size_t)num_nodes * M, 4) : nullptr;
     q.node_feat = nf;
     q.fused_embed = attn && !node_feat && q.layers == 1;
@@ -836,7 +813,7 @@ bool modules_supported(const Dims &d, const tig_modules &m)
         return false;
     if (m.num_layers == 2 && (m.embedding != TIG_EMB_ATTENTION || (d.E + d.T) % d.H != 0 || d.K + 1 > kWave))
         return false;
-    return d.prec == TIG_FP32 && update_lds(md) <= 160 * 1024 && msgsum_lds(md) <= 64 * 1024 && decode_lds(md) <= 160 * 1024 && d.K <= kModThreads &&
+    return d.prec == TIG_FP32 && msgsum_lds(md) <= 64 * 1024 && final_lds(md) <= 160 * 1024 && d.K <= kModThreads &&
            (m.embedding != TIG_EMB_ATTENTION || (d.H <= kMrMaxHeads && d.H * d.K <= kWave && d.dkv <= kMrCC * kWave &&
                                                   d.E + d.F + d.T <= kMrCC * kWave));
 }
@@ -849,7 +826,7 @@ hipError_t modules_attach(const Dims &d, const tig_modules &m, const tig_weights
     mod_layout(d, m.aggregator, m.updater, m.embedding, m.num_layers, m.node_feat != nullptr, num_nodes, (char *)workspace, &p,
                &stage, &nf);
     const ModDims md = mod_dims(d, p);
-    const int M = d.M, T = d.T, E = d.E, D = d.Dmsg, GM = md.G * d.M;
+    const int M = d.M, T = d.T, E = d.E;
     hipError_t e;
     auto vec = [&](const float *dst, const float *src, size_t n) -> hipError_t {
         return hipMemcpyAsync((void *)dst, src, 4 * n, hipMemcpyDefault, s);
@@ -875,10 +852,6 @@ hipError_t modules_attach(const Dims &d, const tig_modules &m, const tig_weights
         return e
     MOD_TRY(rev(p.time_w_rev, w.time_w));
     MOD_TRY(rev(p.time_b_rev, w.time_b));
-    MOD_TRY(vec(p.b_i, w.b_i, GM));
-    MOD_TRY(vec(p.b_h, w.b_h, GM));
-    MOD_TRY(mat(p.T_i, w.W_i, GM, D));
-    MOD_TRY(mat(p.T_h, w.W_h, GM, M));
     if (m.embedding == TIG_EMB_ATTENTION) {
         // the second layer's matrices have the first layer's roles with E-wide input rows
         tig_layer_weights first = {};
@@ -894,12 +867,7 @@ hipError_t modules_attach(const Dims &d, const tig_modules &m, const tig_weights
             MOD_TRY(vec(A.b_O, src.b_O, a_w));
             MOD_TRY(vec(A.b_m1, src.b_m1, E));
             MOD_TRY(vec(A.b_m2, src.b_m2, E));
-            MOD_TRY(mat(A.T_Q, src.W_Q, a_w, a_w));
             MOD_TRY(mat(A.T_K, src.W_K, a_w, kv_w));
-            MOD_TRY(mat(A.T_V, src.W_V, a_w, kv_w));
-            MOD_TRY(mat(A.T_O, src.W_O, a_w, a_w));
-            MOD_TRY(mat(A.T_m1, src.W_m1, E, a_w + in_w));
-            MOD_TRY(mat(A.T_m2, src.W_m2, E, E));
             MOD_TRY(vec(A.N_Q, src.W_Q, (size_t)a_w * a_w));
             MOD_TRY(vec(A.N_V, src.W_V, (size_t)a_w * kv_w));
             MOD_TRY(vec(A.N_O, src.W_O, (size_t)a_w * a_w));
@@ -907,10 +875,6 @@ hipError_t modules_attach(const Dims &d, const tig_modules &m, const tig_weights
             MOD_TRY(vec(A.N_m2, src.W_m2, (size_t)E * E));
         }
     }
-    MOD_TRY(vec(p.b_d1, w.b_d1, E));
-    MOD_TRY(vec(p.w_d2, w.w_d2, E));
-    MOD_TRY(vec(p.b_d2, w.b_d2, 1));
-    MOD_TRY(mat(p.T_d1, w.W_d1, E, 2 * E));
     if (m.embedding == TIG_EMB_TIME_PROJECTION)
         MOD_TRY(vec(p.time_proj_w, m.time_proj_w, M));
     if (nf)
@@ -919,57 +883,52 @@ hipError_t modules_attach(const Dims &d, const tig_modules &m, const tig_weights
         MOD_TRY(launch_fill_zero(p.acc, (size_t)2 * d.max_batch * kAccCopies * (M + T + d.F) * 8, s));
         MOD_TRY(launch_fill_zero(p.acc_cnt, (size_t)2 * d.max_batch * 4, s));
     }
-    MOD_TRY(hipFuncSetAttribute((const void *)k_mod_update, hipFuncAttributeMaxDynamicSharedMemorySize, update_lds(md)));
     MOD_TRY(hipFuncSetAttribute((const void *)k_mod_msgsum, hipFuncAttributeMaxDynamicSharedMemorySize, msgsum_lds(md)));
-    MOD_TRY(hipFuncSetAttribute((const void *)k_mod_decode, hipFuncAttributeMaxDynamicSharedMemorySize, decode_lds(md)));
+    const int fin = final_lds(md) > kOneLds ? final_lds(md) : kOneLds;
+    MOD_TRY(hipFuncSetAttribute((const void *)k_mod_final<true>, hipFuncAttributeMaxDynamicSharedMemorySize, fin));
+    MOD_TRY(hipFuncSetAttribute((const void *)k_mod_final<false>, hipFuncAttributeMaxDynamicSharedMemorySize, fin));
 #undef MOD_TRY
     *out = p;
     return hipStreamSynchronize(s);
 }
 
-// Everything of a step after the selection (and, for the attention embedding, the query
-// preparation): state update, memory overwrite, embedding, decoder, inspection outputs.
-// `marks`: NULL, or two events recorded after the state update + overwrite and after the rest.
+// Mean aggregator: the message columns of the applied batch's nodes into p.mean_msg, ahead of k_gru.
+hipError_t launch_mean_messages(const Dims &d, const StepArgs &a, const ModParams &p, hipStream_t s)
+{
+    const ModDims md = mod_dims(d, p);
+    hipLaunchKernelGGL(k_mod_msgsum, dim3((2 * a.msg_count + kMsgEntries - 1) / kMsgEntries), dim3(kMsgThreads), msgsum_lds(md), s,
+                       a, md, p);
+    hipLaunchKernelGGL(k_mod_mean, dim3((2 * a.msg_count + kModWaves - 1) / kModWaves), dim3(kModThreads), 0, s, a, md, p);
+    return hipGetLastError();
+}
+
+// Everything of a step after the state update (k_gru) of a selection that the fused launches do not
+// cover: memory overwrite, embedding, decoder, inspection outputs, the next batch's preparation.
 hipError_t launch_modules(const Dims &d, const LaunchPlan &plan, const PackedWeights &pw, const StepArgs &a,
-                          const ModParams &p, hipStream_t s, hipEvent_t *marks)
+                          const ModParams &p, hipStream_t s, int *launches)
 {
     const ModDims md = mod_dims(d, p);
     hipError_t e;
-    if (a.msg_count > 0) {
-        if (p.agg == TIG_AGG_MEAN)
-            hipLaunchKernelGGL(k_mod_msgsum, dim3((2 * a.msg_count + kMsgEntries - 1) / kMsgEntries), dim3(kMsgThreads),
-                               msgsum_lds(md), s, a, md, p);
-        hipLaunchKernelGGL(k_mod_update, dim3(2 * a.msg_count), dim3(kModThreads), update_lds(md), s, a, md, p);
-        if ((e = hipGetLastError()) != hipSuccess)
-            return e;
-    }
-    if (p.fused_embed) {
-        // attention without node features: the fused kernels of the headline instance embed and decode,
-        // reading updated nodes' rows from the staged rows (the memory overwrite runs beside them)
-        if (marks && (e = hipEventRecord(marks[0], s)) != hipSuccess)
-            return e;
-        StepArgs f = a;
-        f.finish_here = 1;
-        if ((e = launch_gru(d, plan, pw, f, s, false)) != hipSuccess || (e = launch_embed(d, plan, pw, f, s)) != hipSuccess ||
-            (e = launch_closing(d, plan, pw, f, GruAhead{}, s)) != hipSuccess)
-            return e;
-        return marks ? hipEventRecord(marks[1], s) : hipSuccess;
-    }
-    if (a.msg_count > 0) {
-        hipLaunchKernelGGL(k_mod_commit, dim3(64), dim3(kModThreads), 0, s, a, d.M);
-        if ((e = hipGetLastError()) != hipSuccess)
-            return e;
-    }
-    if (marks && (e = hipEventRecord(marks[0], s)) != hipSuccess)
-        return e;
-    // from here on every state row is read from the memory table: nothing is "applied" any more
+    const int B = a.count;
+    FinalParams fp = {};
+    const int n_events = (B + kFinEvents - 1) / kFinEvents;
+    fp.ldr = lds_row_bytes(d.Ek);
+    fp.applied = a.msg_count;
+    const int side = fp.n_side = (a.sel.count > 0 ? 1 : 0) + (a.ded.count > 0 ? a.ded.n_wgs : 0);
+    const int fin_lds = side > 0 && final_lds(md) < kOneLds ? kOneLds : final_lds(md);
+    // about four winners per wavefront at the winner count recent steps had
+    const int most = 2 * a.msg_count;
+    const int wins = a.wins_est > 0 && a.wins_est < most ? a.wins_est : most;
+    // from here on the attention layers read every state row from the memory table: nothing is "applied" any more
     StepArgs b = a;
     b.msg_count = 0;
-    const int B = a.count;
     if (p.emb == TIG_EMB_ATTENTION) {
-        b.finish_here = 1;  // slots of the query set (its row references all name memory rows)
-        if ((e = launch_gru(d, plan, pw, b, s)) != hipSuccess)
-            return e;
+        const int n_commit = a.msg_count > 0 ? 64 : 0;
+        if (n_commit > 0 && p.layers != 2) {
+            hipLaunchKernelGGL(k_mod_commit, dim3(n_commit), dim3(kModThreads), 0, s, a, d.M);
+            if ((e = hipGetLastError()) != hipSuccess)
+                return e;
+        }
         // one attention layer + merge MLP over all items of `mode`: item list and query rows, the layer's
         // products as contractions over the items, the attention core per item in between
         auto layer_pass = [&](const ModDims &ld, const AttnLayer &A, int mode) {
@@ -1042,28 +1001,32 @@ hipError_t launch_modules(const Dims &d, const LaunchPlan &plan, const PackedWei
             if ((e = launch_fill_zero(p.mr_n, 4, s)) != hipSuccess ||
                 (e = launch_fill_zero(p.mr_tab, ((size_t)p.mr_tab_mask + 1) * 4, s)) != hipSuccess)
                 return e;
-            hipLaunchKernelGGL(k_mod_hop2, dim3(3 * B), dim3(kModThreads), 0, s, b, md, p);
+            hipLaunchKernelGGL(k_mod_hop2, dim3(3 * B + n_commit), dim3(kModThreads), 0, s, b, md, p, a.msg_count, n_commit);
             layer_pass(md, p.L[0], kMrFirst);
             layer_pass(md2, p.L[1], kMrSecond);
         } else {
             layer_pass(md, p.L[0], kMrSingle);
         }
-        hipLaunchKernelGGL(k_mod_decode, dim3((B + kEV - 1) / kEV), dim3(kModThreads), decode_lds(md), s, b, md, p, 1);
+        fp.clear = b.qs.n_u;  // (for the set's next preparation)
+        hipLaunchKernelGGL(k_mod_final<true>, dim3(side + n_events), dim3(kFinThreads), fin_lds, s, b, md, p, pw, fp);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
-        // inspection outputs; the query set's counter is cleared for its next preparation
-        if ((e = launch_closing(d, plan, pw, b, GruAhead{}, s, false)) != hipSuccess)
-            return e;
-    } else {
-        const size_t n = (size_t)a.roles * B * d.M;
-        hipLaunchKernelGGL(k_mod_simple, dim3((unsigned)((n + kModThreads - 1) / kModThreads)), dim3(kModThreads), 0, s, b, md, p);
-        hipLaunchKernelGGL(k_mod_decode, dim3((B + kEV - 1) / kEV), dim3(kModThreads), decode_lds(md), s, b, md, p, 0);
-        if ((e = hipGetLastError()) != hipSuccess)
-            return e;
+        *launches += p.layers == 2 ? 2 + 1 + 2 * 8 + 1 : (n_commit > 0 ? 1 : 0) + 8 + 1;
+        if (wants_inspection(a)) {  // (the winner flags are out)
+            StepArgs c = b;
+            c.out_is_winner = nullptr;
+            if (wants_inspection(c)) {
+                *launches += 1;
+                return launch_closing(d, plan, pw, c, GruAhead{}, s, false);
+            }
+        }
+        return hipSuccess;
     }
-    if (marks && (e = hipEventRecord(marks[1], s)) != hipSuccess)
-        return e;
-    return hipSuccess;
+    fp.n_commit = a.msg_count > 0 ? (wins + 4 * kFinWaves - 1) / (4 * kFinWaves) : 0;
+    fp.n_commit = fp.n_commit > 16 ? 16 : fp.n_commit;
+    hipLaunchKernelGGL(k_mod_final<false>, dim3(side + fp.n_commit + n_events), dim3(kFinThreads), fin_lds, s, a, md, p, pw, fp);
+    *launches += 1;
+    return hipGetLastError();
 }
 
 }  // namespace tig

@@ -225,6 +225,7 @@ struct GruPackJob {
     void *Wr, *Wz, *Win, *Whn;
     float *br, *bz, *bin, *bhn;
     int M, T, Dmsg, Ng, Kg, Khn;
+    bool rnn;  // one gate only (pieces 0, 1, 2 and 6)
 };
 
 template <bool BF16>
@@ -232,6 +233,8 @@ __global__ void k_pack_gru(GruPackJob j)
 {
     const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int piece = blockIdx.y, M = j.M, D = j.Dmsg;
+    if (j.rnn && piece > 2 && piece != 6)
+        return;
     if (piece < 2) {
         if (idx < (size_t)j.T)
             (piece ? j.time_b_rev : j.time_w_rev)[idx] = (double)(piece ? j.time_b : j.time_w)[idx] / 6.283185307179586476925286766559;
@@ -350,6 +353,7 @@ hipError_t pack_weights(const Dims &d, const tig_weights &w, void *dst, void *sc
                         PackedWeights *pw, hipStream_t s, int parts)
 {
     const bool with_gru = (parts & kPackGru) != 0, with_embed = (parts & kPackEmbed) != 0;
+    const bool with_dec = (parts & kPackDec) != 0;
     const PackedLayout L = layout(d, dst);
     const ScratchLayout S = scratch_layout(d, scratch);
     const int M = d.M, T = d.T, E = d.E, H = d.H, da = d.da, dh = d.dh, dkv = d.dkv;
@@ -377,6 +381,7 @@ hipError_t pack_weights(const Dims &d, const tig_weights &w, void *dst, void *sc
         j.W_i = w.W_i, j.W_h = w.W_h, j.b_i = w.b_i, j.b_h = w.b_h;
         j.Wr = L.gru_Wr, j.Wz = L.gru_Wz, j.Win = L.gru_Win, j.Whn = L.gru_Whn;
         j.br = L.gru_br, j.bz = L.gru_bz, j.bin = L.gru_bin, j.bhn = L.gru_bhn;
+        j.rnn = (parts & kPackRnn) != 0;
         j.M = M, j.T = T, j.Dmsg = Dmsg, j.Ng = d.Ng, j.Kg = d.Kg, j.Khn = d.Khn;
         size_t most = (size_t)d.Ng * (d.Kg > d.Khn ? d.Kg : d.Khn);
         most = most > (size_t)T ? most : (size_t)T;
@@ -462,6 +467,15 @@ hipError_t pack_weights(const Dims &d, const tig_weights &w, void *dst, void *sc
             hipLaunchKernelGGL(k_pack<true>, g3, blk, 0, s, pj);
         else
             hipLaunchKernelGGL(k_pack<false>, g3, blk, 0, s, pj);
+        TIG_TRY(hipGetLastError());
+    } else if (with_dec) {
+        PackJobs pj = {};
+        pj.m[3] = PackMat{L.dec_W, w.W_d1, nullptr, 2 * E, 0, E, 2 * d.Ep, E, 2 * d.Ep, d.Ek, d.Ep, d.Ep - E, w.W_d1 + E, false, false};
+        pj.v[4] = PackVec{L.dec_b1, E, d.Ep, nullptr, nullptr, w.b_d1};
+        pj.v[6] = PackVec{L.dec_w2, E, d.Ep, nullptr, nullptr, w.w_d2};
+        pj.v[7] = PackVec{L.dec_b2, 1, 1, nullptr, nullptr, w.b_d2};
+        const dim3 g3((unsigned)(((size_t)2 * d.Ep * d.Ek + kThreads - 1) / kThreads), kPackMats + kPackVecs);
+        hipLaunchKernelGGL(d.prec == TIG_BF16_MFMA ? k_pack<true> : k_pack<false>, g3, blk, 0, s, pj);
         TIG_TRY(hipGetLastError());
     }
 

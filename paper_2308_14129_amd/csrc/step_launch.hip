@@ -72,10 +72,14 @@ hipError_t launch_step(const Dims &d, const LaunchPlan &plan, const PackedWeight
     }
     if ((e = stamp()) != hipSuccess)
         return e;
-    if (sp.mods) {
-        if ((e = launch_modules(d, plan, pw, a, *sp.mods, s, marks ? marks + mark : nullptr)) != hipSuccess)
+    if (sp.mods && sp.mods->agg == TIG_AGG_MEAN && a.msg_count > 0 && (e = launch_mean_messages(d, a, *sp.mods, s)) != hipSuccess)
+        return e;
+    if (sp.mods && !sp.mods->fused_embed) {
+        if (sp.gru_now && (e = launch_gru(d, plan, pw, a, s)) != hipSuccess)
             return e;
-        mark += marks ? 2 : 0;
+        if ((e = stamp()) != hipSuccess || (e = launch_modules(d, plan, pw, a, *sp.mods, s, sp.mod_launches)) != hipSuccess ||
+            (e = stamp()) != hipSuccess)
+            return e;
         return stamp();
     }
     if (sp.train && sp.train_side && (sp.side_sel || sp.side_ded)) {

@@ -654,9 +654,8 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
         return fail(ctx, TIG_EINVAL, "tig_step: the context was created without weights and no module selection is attached");
     if (general && (use_static || train))
         return fail(ctx, TIG_EINVAL, "tig_step_static / tig_train_step: the context runs an attached module selection");
-    // a training step or a step of a module selection has no embedding launch to carry a later
-    // step's preparation (a training step runs it on its second stream instead, see side_prep)
-    const bool solo = train || general;
+    const bool fused = !general || ctx->mods.fused_embed;  // the embedding and closing launches run this step
+    const bool mean = general && ctx->mods.agg == TIG_AGG_MEAN;
     const bool wants_queries = !general || ctx->mods.emb == TIG_EMB_ATTENTION;
     StepScratch st = ctx->S;
     if (use_static) {
@@ -710,9 +709,17 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
         a.wins_est = wins > 0 ? wins + wins / 8 : 0;
     }
 
-    // What the embedding launch can do on the side for a later step (never for a static call).
+    if (general) {
+        a.upd = ctx->mods.upd == TIG_UPD_RNN ? kUpdModuleRnn : kUpdModuleGru;
+        a.mean_msg = mean ? ctx->mods.mean_msg : nullptr;
+    }
+
+    // What the embedding launch -- or a module selection's last launch -- can do on the side for a later
+    // step (never for a static call; a training step runs it on its second stream, see side_prep).
     const bool one_wg = winners_in_one_launch(count);
-    const int spare = use_static || solo ? 0 : embed_spare_workgroups(d, ctx->plan, a.roles, count);
+    const int spare = use_static || train ? 0
+                      : fused              ? embed_spare_workgroups(d, ctx->plan, a.roles, count)
+                                           : 1 + prepare_workgroups(count, true);
     uint32_t epoch = ctx->epoch;
     bool clear_tab = use_static;  // the static array's table holds claims of unknown epochs
     auto next_epoch = [&]() -> uint32_t {
@@ -730,15 +737,15 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
     DedupJob ded_now = {}, ded_side = {};
     // a training step has no embedding launch to carry such work: it goes to the step's second stream
     const bool side_prep = train && ctx->have_train_side;
-    int launches = 2;  // embedding, closing
+    int launches = fused ? 2 : 0;  // embedding, closing
 
     // ---- the distinct queries of this batch: prepared by the previous step's embedding launch if
     // that step guessed this batch (it reads the event stream and the adjacency only), else now
-    const bool q_ready = !use_static && !general && ctx->ahead_q_valid && ctx->ahead_q_first == first &&
+    const bool q_ready = !use_static && wants_queries && ctx->ahead_q_valid && ctx->ahead_q_first == first &&
                          ctx->ahead_q_count == count;
     const int qi = use_static ? 0 : (q_ready ? ctx->qcur ^ 1 : ctx->qcur);
     a.qs = st.qs[qi];
-    a.finish_here = !(q_ready && ctx->ahead_q_finished);
+    a.finish_here = wants_queries && !(q_ready && ctx->ahead_q_finished);
     if (!q_ready && wants_queries) {
         ded_now = make_dedup(st, st.qs[qi], first, count, next_epoch(), one_wg);
         sp.prep_ded = &ded_now;
@@ -749,7 +756,7 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
     bool w_ready = false;
     if (!d.deferred) {
         // this batch's: selected ahead like the queries, else now
-        w_ready = !use_static && !solo && ctx->ahead_w_valid && ctx->ahead_w_first == first &&
+        w_ready = !use_static && !train && ctx->ahead_w_valid && ctx->ahead_w_first == first &&
                   ctx->ahead_w_count == count;
         wi = use_static ? 0 : (w_ready ? ctx->wcur ^ 1 : ctx->wcur);
         a.msg_first_eid = first;
@@ -770,7 +777,8 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
         a.win_flags = st.flags[wi ^ 1];
         const SelectJob mine = SelectJob{first, count, st.win[wi ^ 1], st.n_win[wi ^ 1], st.flags[wi ^ 1],
                                          ctx->key[wi ^ 1]};
-        if (spare > 0 && one_wg) {
+        // (a module selection's last launch copies the flags out itself: they have to be there before it)
+        if (spare > 0 && one_wg && (fused || !a.out_is_winner)) {
             a.sel = mine;
         } else if (side_prep && one_wg) {
             sel_side = mine;
@@ -787,12 +795,13 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
     // the batch (and the memory has not changed since), else now, together with what is left of
     // this step's query preparation
     // (a training step runs it itself: its backward pass reads the gates that this launch leaves)
-    const bool g_ready = !use_static && !general && !train && ctx->ahead_g_valid && a.msg_count > 0 && ctx->ahead_g_first == a.msg_first_eid &&
+    const bool g_ready = !use_static && fused && !mean && !train && ctx->ahead_g_valid && a.msg_count > 0 && ctx->ahead_g_first == a.msg_first_eid &&
                          ctx->ahead_g_count == a.msg_count && !a.finish_here && (d.deferred || w_ready);
-    sp.gru_now = !general && !g_ready && (a.msg_count > 0 || a.finish_here);
+    sp.gru_now = !g_ready && (a.msg_count > 0 || a.finish_here);
     if (general) {
         sp.mods = &ctx->mods;
-        launches += ctx->mods.fused_embed ? 2 : (wants_queries ? 4 : 2);  // update[, overwrite][, finishing pass], embedding, decoder / closing
+        sp.mod_launches = &launches;
+        launches += mean && a.msg_count > 0 ? 2 : 0;
     }
     if (sp.big_sel)
         launches += 2;
@@ -810,10 +819,11 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
         const int64_t left = ctx->num_events - next_first;
         const int32_t guess = left < count ? (int32_t)left : count;
         if (winners_in_one_launch(guess)) {
-            a.ded = make_dedup(st, st.qs[qi ^ 1], next_first, guess, next_epoch(), true);
+            if (wants_queries)
+                a.ded = make_dedup(st, st.qs[qi ^ 1], next_first, guess, next_epoch(), true);
             // that set's counter was cleared by the closing launch of the step that used the set,
             // unless this step did not take the set prepared for it
-            if (!q_ready)
+            if (wants_queries && !q_ready)
                 sp.clear_first = st.qs[qi ^ 1].n_u;
             if (!d.deferred)
                 a.sel = SelectJob{next_first, guess, st.win[wi ^ 1], st.n_win[wi ^ 1], st.flags[wi ^ 1],
@@ -821,7 +831,7 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
             // The decode launch finishes that preparation: row references against the batch the NEXT
             // step applies -- the guessed batch itself, or in the deferred order this step's batch
             // (selected into the other list by now, by the embedding launch or up front).
-            a.fin_count = guess;
+            a.fin_count = fused ? guess : 0;
             a.fin_msg_first_eid = d.deferred ? first : next_first;
             a.fin_msg_count = d.deferred ? count : guess;
             a.fin_msg_key = ctx->key[wi ^ 1];
@@ -843,7 +853,7 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
     // ---- The closing launch also runs the GRU of the batch the next step applies, once that batch's
     // winners are known: in the update-first order the guessed batch (selected by this step's
     // embedding launch), in the deferred order this step's own batch (whatever comes next).
-    if (!use_static && !solo) {
+    if (!use_static && !train && fused && !mean) {
         if (!d.deferred && a.sel.count > 0)
             sp.ahead = GruAhead{a.sel.first_eid, a.sel.count, st.win[wi ^ 1], st.n_win[wi ^ 1]};
         else if (d.deferred)
@@ -876,7 +886,7 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
     // bit i: the interval between marks i and i + 1 held a kernel (a module selection's kernels fill
     // intervals 3 and 4)
     ctx->last_ran = (sp.big_sel ? 3u : 0u) | ((sp.prep_sel || sp.prep_ded) ? 4u : 0u) |
-                    ((sp.mods || sp.gru_now) ? 8u : 0u) | 16u | ((sp.mods || (train && !wants_inspection(a))) ? 0u : 32u);
+                    (sp.gru_now ? 8u : 0u) | 16u | ((!fused || (train && !wants_inspection(a))) ? 0u : 32u);
     if (e != hipSuccess) {
         // kernels of this step may already be enqueued: nothing prepared ahead is trusted any more,
         // and the model state is undefined until tig_reset / tig_state_import
@@ -1081,24 +1091,29 @@ int tig_modules_attach(tig_ctx *ctx, const tig_modules *modules, const tig_weigh
     ModParams mp;
     if (e == hipSuccess)
         e = modules_attach(ctx->d, *modules, w, ctx->num_nodes, workspace, &mp, ctx->stream);
-    if (e == hipSuccess && mp.fused_embed) {
-        // the fused embedding / closing kernels run this selection's attention: their prepared weights
-        // are folded from `weights` as in tig_init (staged through the scratch workspace, whose
-        // per-step counters and claim table are then put back to their resting state)
+    if (e == hipSuccess) {
+        // the prepared weights of the launches that the selection shares with the headline instance -- state
+        // update; decoder, or all of the fused embedding -- are folded from `weights` as in tig_init (staged
+        // through the scratch workspace, whose per-step counters and claim table are then put back to
+        // their resting state)
         hipStream_t s = ctx->stream;
-        char *wbase = (char *)ctx->scratch + 256;
-        RawWeights R = raw_weights_layout(ctx->d, wbase);
+        const bool rnn = mp.upd == TIG_UPD_RNN;
+        const Dims &d = ctx->d;
+        const RawWeights R = raw_weights_layout(d, (char *)ctx->scratch + 256);
         WeightField wf[32];
-        const int nwf = weight_fields(ctx->d, wf);
+        const int nwf = weight_fields(d, wf);
         for (int i = 0; i < nwf && e == hipSuccess; ++i) {
-            if (wf[i].member == &tig_weights::W_i || wf[i].member == &tig_weights::b_i ||
-                wf[i].member == &tig_weights::W_h || wf[i].member == &tig_weights::b_h)
-                continue;  // the state update has kernels of its own
-            e = hipMemcpyAsync((void *)(R.w.*(wf[i].member)), w.*(wf[i].member), sizeof(float) * wf[i].count,
-                               hipMemcpyDefault, s);
+            const float *tig_weights::*m = wf[i].member;
+            const bool gated = m == &tig_weights::W_i || m == &tig_weights::b_i || m == &tig_weights::W_h || m == &tig_weights::b_h;
+            const bool shared = gated || m == &tig_weights::time_w || m == &tig_weights::time_b || m == &tig_weights::W_d1 ||
+                                m == &tig_weights::b_d1 || m == &tig_weights::w_d2 || m == &tig_weights::b_d2;
+            if (!shared && !mp.fused_embed)
+                continue;  // (attention and merge weights: not read, or read by kernels of their own)
+            e = hipMemcpyAsync((void *)(R.w.*m), w.*m, sizeof(float) * wf[i].count / (gated && rnn ? 3 : 1), hipMemcpyDefault, s);
         }
         if (e == hipSuccess)
-            e = pack_weights(ctx->d, R.w, ctx->packed, wbase + R.bytes, &ctx->pw, s, kPackEmbed);
+            e = pack_weights(d, R.w, ctx->packed, (char *)ctx->scratch + init_fold_offset(d), &ctx->pw, s,
+                             kPackGru | (rnn ? kPackRnn : 0) | (mp.fused_embed ? kPackEmbed : kPackDec));
         for (int i = 0; i < 2 && e == hipSuccess; ++i) {
             e = launch_fill_zero(ctx->S.n_win[i], 4, s);
             if (e == hipSuccess)

@@ -92,6 +92,10 @@ struct QuerySet {
     int32_t *n_u;       // [1]
 };
 
+// The state update a step runs in k_gru: the headline GRU; the GRU or the plain recurrent cell of a module
+// selection (library exp / tanh).
+enum UpdateKind { kUpdGru = 0, kUpdModuleGru = 1, kUpdModuleRnn = 2 };
+
 // Last-message selection of one batch (count 0: nothing to do).  Besides the compacted winner
 // list it leaves key[node] = the winning entry's 64-bit (time, event id, role) key.  There are two
 // winner lists (the one a step applies and the one selected meanwhile), each with a key array of
@@ -146,6 +150,8 @@ struct StepArgs {
     // intermediates (device)
     QuerySet qs;     // distinct queries of this batch
     float *staging;  // [2*msg_count x M] new memory rows of the winners, by entry 2b+role
+    int upd;         // UpdateKind of the state update
+    const float *mean_msg;  // NULL, or [2*msg_count x (M + T + F)]: the mean aggregator's message columns behind s_self, by winning entry
     float *gru_gates;  // NULL, or [2*msg_count x 4 x M]: r, z, n and the hidden half of n's pre-activation of winner r of the list (a training step's backward pass reads them)
     float *emb_u;    // [R x E] embedding of every distinct query
     float *dec_a;    // [R x Ep] first decoder layer, source half, of every distinct query
@@ -195,7 +201,9 @@ size_t packed_weights_bytes(const Dims &d);
 // parts: kPackGru = the state update's matrices (W_i / W_h are read), kPackEmbed = attention, merge
 // MLP and decoder; the time-encoding parameters go with either.  A part that is left out keeps what
 // `dst` holds (zeros after tig_init's clear for a context whose state update runs elsewhere).
-enum PackParts { kPackGru = 1, kPackEmbed = 2, kPackAll = 3 };
+// kPackDec: of the decoder, layer 1 by operand half and the vectors (a module selection's decoder); kPackRnn:
+// with kPackGru, W_i / W_h / b_i / b_h are the plain recurrent cell's (one gate, in the r gate's place).
+enum PackParts { kPackGru = 1, kPackEmbed = 2, kPackAll = 3, kPackDec = 4, kPackRnn = 8 };
 hipError_t pack_weights(const Dims &d, const tig_weights &w_dev_f32, void *dst, void *scratch,
                         PackedWeights *pw, hipStream_t s, int parts = kPackAll);
 
@@ -263,7 +271,8 @@ struct StepPlan {
     const DedupJob *side_ded;
     int32_t *clear_first;       // a counter to clear ahead of everything, or NULL
     GruAhead ahead;             // GRU workgroups of the closing launch
-    const struct ModParams *mods;  // a context with a module selection: its kernels instead of GRU, embedding and closing launches
+    const struct ModParams *mods;  // a context with a module selection, or NULL
+    int *mod_launches;             // ... where launch_modules adds its launches
 };
 // does the step copy neighbour lists or winner flags out
 inline bool wants_inspection(const StepArgs &a)
@@ -313,15 +322,14 @@ float *train_gates_buffer(const Dims &d, void *workspace);
 // Module selection of a context and its weights: transposed copies ([in x out]) in the attached workspace.
 constexpr int kAccCopies = 8;  // accumulation rows per node of the mean aggregator (entries are dealt out to them: less same-address traffic)
 struct AttnLayer {
-    const float *T_Q, *T_K, *T_V, *T_O, *b_Q, *b_K, *b_V, *b_O;  // attention
-    const float *T_m1, *T_m2, *b_m1, *b_m2;    // merge MLP
+    const float *T_K, *b_Q, *b_K, *b_V, *b_O;  // attention (W_K transposed)
+    const float *b_m1, *b_m2;                  // merge MLP
     const float *N_Q, *N_V, *N_O, *N_m1, *N_m2;  // the matrices as given ([out x in]) for the contractions over all rows
 };
 struct ModParams {
     int agg, upd, emb;                         // tig_aggregator, tig_updater, tig_embedding
     int layers;                                // attention embedding: 1 or 2 stacked layers
     const double *time_w_rev, *time_b_rev;     // [T] time-encoding frequency / phase in revolutions
-    const float *T_i, *T_h, *b_i, *b_h;        // state update: [D_msg x GM], [M x GM], [GM], [GM] (G = 3 GRU, 1 RNN)
     AttnLayer L[2];                            // first layer (input width M) and second (input width E)
     QuerySet hop2;                             // two layers: neighbour tables of (neighbour k of query row q, t_q) at row q * K + k
     float *h1;                                 // two layers: first-layer rows [3 * max_batch x (K + 1) x E], one per item in the items' order
@@ -335,21 +343,22 @@ struct ModParams {
     int32_t *mr_n;                             // [1] items of the first layer (cleared every step)
     uint32_t *mr_tab;                          // first layer: claims of equal (node, t) pairs, 1 + the claimant's (x, j) index, 0 = empty (cleared every step)
     uint32_t mr_tab_mask;                      // its size - 1 (a power of two)
-    const float *T_d1, *b_d1, *w_d2, *b_d2;    // decoder: [2E x E], [E], [E], [1]
     const float *node_feat;                    // [N x M] or NULL
     const float *time_proj_w;                  // [M] or NULL
     bool fused_embed;                          // attention without node features: the fused embedding / closing launches run it
     double *acc;                               // mean aggregator: [2 * max_batch x kAccCopies x (M + T + F)] message sums by winning entry, zero between steps
     int32_t *acc_cnt;                          // ... and the number of messages in each
+    float *mean_msg;                           // ... and the means, [2 * max_batch x (M + T + F)] by winning entry
 };
 size_t modules_workspace_bytes(const Dims &d, const tig_modules &m, int64_t num_nodes);
 bool modules_supported(const Dims &d, const tig_modules &m);
 hipError_t modules_attach(const Dims &d, const tig_modules &m, const tig_weights &w, int64_t num_nodes, void *workspace,
                           ModParams *out, hipStream_t s);
-// state update, memory overwrite, embedding, decoder and inspection outputs of a step of a context
-// with a module selection; marks: NULL, or two events (after the overwrite, after the rest)
+hipError_t launch_mean_messages(const Dims &d, const StepArgs &a, const ModParams &p, hipStream_t s);
+// everything after the state update of a step of a context with a module selection that the fused launches
+// do not cover; adds the launches it made to *launches
 hipError_t launch_modules(const Dims &d, const LaunchPlan &plan, const PackedWeights &pw, const StepArgs &a,
-                          const ModParams &p, hipStream_t s, hipEvent_t *marks);
+                          const ModParams &p, hipStream_t s, int *launches);
 // A pinned host buffer for copies between host and device that should not wait page by page.  Buffers
 // are kept for the next user (at most kPinnedStageKept of them; each is in one user's hands at a time, on
 // any thread); `ptr` is NULL where none could be had.  The user waits for its copies before it lets go.

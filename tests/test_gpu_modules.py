@@ -121,6 +121,31 @@ def test_c1_from_reset_and_ragged(name, node_feat):
     c.close()
 
 
+@pytest.mark.parametrize("order", ["update_first", "deferred"])
+@pytest.mark.parametrize("name,dims,batch", [("jodie_like", dict(mem_dim=37, time_dim=11, feat_dim=5), 33),
+                                             ("mean_rnn_projection", dict(mem_dim=130, time_dim=20, feat_dim=3), 999),
+                                             ("last_rnn_attention", dict(mem_dim=33, time_dim=15, emb_dim=50), 137),
+                                             ("mean_gru_identity", dict(mem_dim=16, time_dim=4, feat_dim=1), 1)])
+def test_steps_that_prepare_each_other(name, dims, batch, order):
+    """Without inspection outputs every step's winners (and queries) come from the step before; row widths around
+    the tiles' edges, batches that leave tiles ragged, a gap in the stream."""
+    c = Case(S.WORKLOADS["c1_tiny"].scaled(**dims), INSTANCES[name], False, order=order, max_batch=batch)
+    st = O.OracleState.zeros(c.g.num_nodes, c.w.mem_dim)
+    c.ctx.reset()
+    for first in [0, batch, 2 * batch, 3 * batch + 50, 4 * batch + 50]:
+        neg = S.make_negatives(c.w, c.g, first, batch)
+        ref = G.step(st, c.g.src, c.g.dst, c.g.ts, c.g.edge_feat, c.W, first, batch, neg, c.w.num_neighbors, c.w.num_heads,
+                     c.mods, index=c.ix, deferred=c.deferred)
+        out = c.ctx.alloc_outputs(batch)
+        c.ctx.step(first, batch, c.torch.from_numpy(neg).to("cuda:0"), out)
+        for k in ("emb", "score_pos", "score_neg"):
+            gate(getattr(out, k).cpu().numpy(), ref[k], TOL, k)
+    mem, lu = c.ctx.state_export()
+    np.testing.assert_array_equal(lu, st.last_update)
+    gate(mem, st.mem, TOL, "mem")
+    c.close()
+
+
 @pytest.mark.parametrize("name", ["jodie_like", "mean_gru_attention", "mean_rnn_projection"])
 def test_c1_deferred_order(name):
     c = Case(S.WORKLOADS["c1_tiny"], INSTANCES[name], True, order="deferred")
