@@ -188,20 +188,17 @@ def mfma_flops(w, rows_u, winners, precision):
     return issued, useful
 
 
-def train_flops(w, rows, pairs, winners):
-    """Multiply-adds x 2 of the contractions of one training step as the kernels run them (attention
-    core re-associated: every product over queries, events or winners): forward, backward, weight gradients."""
+def train_flops(w, rows, winners):
+    """Multiply-adds x 2 of the contractions over rows of one training step as the kernels run them (on folded
+    weights; every product over distinct queries or winners): forward, backward, weight gradients."""
     M, T, E, F, H = w.mem_dim, w.time_dim, w.emb_dim, w.feat_dim, w.num_heads
-    da, dkv, D = M + T, M + F + T, 2 * M + T + F
+    N1, D = H * (M + F + T), 2 * M + T + F
 
     def mm(r, n, k):
         return 2.0 * r * n * k
-    fwd = mm(rows, da, da) + mm(rows, dkv, da) + mm(rows, da, dkv) + mm(rows, da, da) + mm(rows, E, da + M) + \
-        mm(rows, E, E) + mm(pairs, E, 2 * E) + mm(winners, 3 * M, D) + mm(winners, 3 * M, M)
-    bwd = mm(pairs, 2 * E, E) + mm(rows, E, E) + mm(rows, da + M, E) + mm(rows, da, da) + mm(rows, dkv, da) + \
-        mm(rows, da, dkv) + mm(rows, da, da) + mm(winners, T, 3 * M)
-    wgr = mm(pairs, E, 2 * E) + mm(pairs, 1, E) + mm(rows, E, E) + mm(rows, E, da + M) + 2 * mm(rows, da, da) + \
-        2 * mm(rows, da, dkv) + mm(winners, 3 * M, D) + mm(winners, 3 * M, M)
+    fwd = mm(rows, N1, M) + mm(rows, E, N1 + M) + 3 * mm(rows, E, E) + mm(winners, 3 * M, D) + mm(winners, M, M)
+    bwd = 3 * mm(rows, E, E) + mm(rows, N1 + M, E) + mm(rows, M, N1) + mm(winners, T, 3 * M)
+    wgr = mm(rows, N1, M) + mm(rows, E, N1 + M) + 3 * mm(rows, E, E) + mm(winners, 3 * M, D) + mm(winners, 3 * M, M)
     return fwd + bwd + wgr
 
 
@@ -234,7 +231,7 @@ def bench_train(S, tig, torch, w, g, weights, B, batches, negs, negs_np, mem0, l
             "order": "deferred", "dtype": "f32", "lr": 1e-4, "workspace_GB": round(ws_bytes / 1e9, 2),
             "loss_first_last": [round(float(losses[0].item()), 5), round(float(losses[-1].item()), 5)]}
     if rows_per_step and winners_per_step:
-        fl = train_flops(w, rows_per_step, 2 * B, winners_per_step)
+        fl = train_flops(w, rows_per_step, winners_per_step)
         rep_["contraction_GFLOP_per_step"] = round(fl / 1e9, 2)
         rep_["fp32_mfma_frac_of_peak"] = round(fl / (dt / n) / 1e12 / FP32_MFMA_PEAK_TFLOPS, 4)
     if cpu_steps > 0:

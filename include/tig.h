@@ -254,28 +254,22 @@ TIG_API int tig_step_static(tig_ctx *ctx, const tig_batch *batch, const tig_out 
 
 /* Size of the training workspace of a configuration (device memory the caller allocates):
  * master weights, gradients and the buffers of the backward pass, about
- * 12 * max_batch * ((2 * num_neighbors + 4 * num_heads) * (mem + feat + time) + 14 * (mem + time)) bytes
- * (the raw key / value rows of the neighbour slots and their gradients, and per-query rows).
+ * 36 * max_batch * (num_heads * (mem + feat + time) + 2 * emb + 3 * mem + time + feat) bytes, and up to 40 MB of
+ * partial sums where the rows of the weight gradients are split over workgroups.
  * TIG_EINVAL for a precision other than TIG_FP32 or a row shape the backward kernels cannot hold
  * (more than 4 heads, heads * neighbours above 64, key / value rows above 512 columns). */
 TIG_API int tig_train_workspace_bytes(const tig_config *cfg, size_t *bytes);
 
 /* Makes a context trainable: `weights` (host or device, as in tig_init; normally the same values)
  * become the master weights in `workspace` (device, 256-byte aligned, owned by the caller until
- * tig_destroy), and the context's prepared weights are rebuilt from them.  Synchronous.
- * The first call on a context also creates one HIP stream (default priority, non-blocking) and a few
- * events, which tig_destroy releases: no device memory, but host-side runtime objects. */
+ * tig_destroy), and the context's prepared weights are rebuilt from them.  Synchronous. */
 TIG_API int tig_train_attach(tig_ctx *ctx, const tig_weights *weights, void *workspace, size_t workspace_bytes);
 
 /* One training step on a batch: the step of tig_step (same outputs, same state update, in the
  * context's message order), the loss, the gradient of every weight, and the SGD update with
  * learning rate lr >= 0 (0: gradients only, weights untouched).  batch->neg_dst is required.
- * loss_out: device pointer to one float, or NULL.  Enqueued on the context's stream; the weight-gradient
- * contractions run on the stream that tig_train_attach created, ordered against the context's stream
- * by events on both ends (they start when their inputs are complete and the context's stream waits for
- * them ahead of the update), so whatever the caller orders against the context's stream -- later
- * calls, copies, events -- sees the finished step.  On that stream the call also prepares the queries
- * of the batch it expects next (the same number of events, continuing where this one ends), as tig_step
+ * loss_out: device pointer to one float, or NULL.  Enqueued on the context's stream.  The call also prepares
+ * the queries of the batch it expects next (the same number of events, continuing where this one ends), as tig_step
  * does; a following tig_step or tig_train_step on another batch prepares its own. */
 TIG_API int tig_train_step(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, float lr, float *loss_out);
 

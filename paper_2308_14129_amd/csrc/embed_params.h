@@ -1,0 +1,37 @@
+// Launch parameters of the embedding kernels and the choice among their instances (host side).
+#pragma once
+
+#include "tig_internal.h"
+
+namespace tig {
+
+struct EmbedParams {
+    int M, T, F, E, K;
+    int dkv, dkvp, Mq, N1, K2, Ep, Ek;
+    int row_bytes;  // LDS bytes per query row of the main buffer: [q~ / kvbar (N1) | s_u (Mq)]
+    int ld1;        // row stride of the E-wide buffers, bytes
+    int off_h1, off_meta;  // byte offsets in LDS
+    int n_tiles;    // workgroups that take row tiles
+    int n_commit;   // then: workgroups of the memory overwrite; the ones beyond prepare the next batch
+    // bit n set: register n of a key/value row (dims 64 n .. 64 n + 63 of [Phi | s_v | e]) holds
+    // at least one dim of the time encoding / of the neighbour's memory / of the edge feature
+    int phi_regs, mem_regs, feat_regs;
+};
+
+inline int npl_for(const Dims &d)
+{
+    const int need = (d.dkvp + 63) / 64;
+    int npl = 1;
+    while (npl < need)
+        npl *= 2;
+    return npl;
+}
+
+// must agree with EmbedShape (heads other than 1 and 2 run the 4-head kernels)
+inline int embed_threads(const Dims &d) { return npl_for(d) >= 8 && d.H > 2 ? 512 : 1024; }
+
+const void *embed_kernel_bf16(const Dims &d, int mt);
+const void *embed_kernel_fp32(const Dims &d, int mt);
+const void *embed_kernel_train(const Dims &d, int mt);
+
+}  // namespace tig

@@ -1,0 +1,15 @@
+// The embedding kernels: the forward pass of a training step (embed_tile.h).
+#include "embed_tile.h"
+
+namespace tig {
+
+#ifdef TIG_PHASE_CLOCKS
+extern "C" __attribute__((visibility("default"))) int tig_debug_phase_clocks_train(unsigned long long *out, int n)
+{
+    return (int)hipMemcpyFromSymbol(out, HIP_SYMBOL(g_phase_clocks), sizeof(unsigned long long) * (size_t)n);
+}
+#endif
+
+const void *embed_kernel_train(const Dims &d, int mt) { return pick<TIG_FP32, true>(d, mt); }
+
+}  // namespace tig

@@ -102,12 +102,15 @@ __device__ inline void tile_gemm2(floatx4 &acc1, floatx4 &acc2, const char *A, i
     }
 }
 
-// MOD: the state update of a module selection (mean messages, the plain recurrent cell, library exp / tanh);
-// an instance of its own, so that the headline's carries none of it (in one kernel it cost a step 2 us).
-template <int PREC, bool MOD>
+// KIND: an ordinary step; the state update of a module selection (mean messages, the plain recurrent cell, library
+// exp / tanh); a training step, which keeps what its backward pass reads.  Instances of their own, so that the
+// ordinary one carries nothing of the others (in one kernel they cost a step 2 us and 1 us).
+enum GruKind { kGruPlain, kGruModules, kGruTraining };
+template <int PREC, GruKind KIND>
 __global__ void __launch_bounds__(kGruThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))  // 128 registers: two workgroups per unit
 k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
 {
+    constexpr bool MOD = KIND == kGruModules, TRAIN = KIND == kGruTraining;
     TIG_MARK(0);
     if (blockIdx.x == 0 && threadIdx.x == 0 && g.clear)
         *g.clear = 0;
@@ -241,6 +244,8 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                             if (live && !(MOD && a.mean_msg) && j >= 2 * g.M && j < 2 * g.M + g.T)
                                 x = time_enc(tw_tab[2 * (j - 2 * g.M)], tw_tab[2 * (j - 2 * g.M) + 1], dt[i]);
                             P::store_a(X + (size_t)r * g.ldx, j, x);
+                            if (TRAIN && live && ct_lo == 0 && j < g.Dmsg)
+                                a.gru_msg[(size_t)(r0 + r) * g.Dmsg + j] = x;
                         }
                     }
                 }
@@ -328,8 +333,9 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                         n = tanhf(sr + sin_ + br);
                     }
                     a.staging[(size_t)row_i[row] * g.M + col] = (1.0f - z) * n + z * h;
-                    if (a.gru_gates) {  // (uniform) a training step keeps the gates for its backward pass
+                    if (TRAIN) {
                         float *go = a.gru_gates + (size_t)(r0 + row) * 4 * g.M + col;
+                        a.d_staging[(size_t)row_i[row] * g.M + col] = 0.0f;
                         go[0] = r;
                         go[g.M] = z;
                         go[2 * g.M] = n;
@@ -363,11 +369,13 @@ GruParams gru_params(const Dims &d)
     return g;
 }
 
-const void *gru_kernel(const Dims &d, int upd)
+const void *gru_kernel(const Dims &d, int upd, bool train)
 {
+    if (train)
+        return (const void *)k_gru<TIG_FP32, kGruTraining>;
     if (d.prec == TIG_BF16_MFMA)  // (module selections run in fp32 contexts)
-        return (const void *)k_gru<TIG_BF16_MFMA, false>;
-    return upd == kUpdGru ? (const void *)k_gru<TIG_FP32, false> : (const void *)k_gru<TIG_FP32, true>;
+        return (const void *)k_gru<TIG_BF16_MFMA, kGruPlain>;
+    return upd == kUpdGru ? (const void *)k_gru<TIG_FP32, kGruPlain> : (const void *)k_gru<TIG_FP32, kGruModules>;
 }
 
 // GRU workgroups and column slices for a batch of `count` events with about `wins_est` winners.
@@ -410,8 +418,9 @@ int gru_lds_bytes(const Dims &d)
 
 hipError_t prepare_gru(const Dims &d, const LaunchPlan &plan)
 {
-    for (int upd : {kUpdGru, kUpdModuleGru}) {
-        const hipError_t e = hipFuncSetAttribute(gru_kernel(d, upd), hipFuncAttributeMaxDynamicSharedMemorySize, gru_lds_bytes(d));
+    for (int i = 0; i < 3; ++i) {
+        const void *const kernel = gru_kernel(d, i == 1 ? kUpdModuleGru : kUpdGru, i == 2 && d.prec == TIG_FP32);
+        const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, gru_lds_bytes(d));
         if (e != hipSuccess)
             return e;
     }
@@ -441,7 +450,7 @@ hipError_t launch_gru(const Dims &d, const LaunchPlan &plan, const PackedWeights
     if (blocks == 0)
         return hipSuccess;  // nothing to apply, nothing to finish
     void *args[] = {&aa, &gj, &ww, &g, &dp};
-    return hipLaunchKernel(gru_kernel(d, a.upd), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
+    return hipLaunchKernel(gru_kernel(d, a.upd, a.gru_gates != nullptr), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
 }
 
 // The closing launch of a step: scores and embedding rows of its events, inspection outputs, the
@@ -470,7 +479,7 @@ hipError_t launch_closing(const Dims &d, const LaunchPlan &plan, const PackedWei
     int blocks = g.n_gru + p.n_event_blocks + p.n_expand_blocks + p.n_fin_row_blocks + p.n_fin_slot_blocks;
     blocks = blocks > 0 ? blocks : 1;  // (block 0 clears the counter whatever else there is to do)
     void *args[] = {&aa, &gj, &ww, &g, &p};
-    return hipLaunchKernel(gru_kernel(d, a.upd), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
+    return hipLaunchKernel(gru_kernel(d, a.upd, false), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
 }
 
 }  // namespace tig

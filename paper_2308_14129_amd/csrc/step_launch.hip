@@ -82,28 +82,15 @@ hipError_t launch_step(const Dims &d, const LaunchPlan &plan, const PackedWeight
             return e;
         return stamp();
     }
-    if (sp.train && sp.train_side && (sp.side_sel || sp.side_ded)) {
-        // beside the step, ordered after whatever this step prepared for itself (the jobs share the
-        // claim table); the step's stream waits for the side stream ahead of its update
-        const TrainSide &ts = *sp.train_side;
-        const SelectJob no_sel = {};
-        const DedupJob no_ded = {};
-        if ((e = hipEventRecord(ts.fork[kTrainForks - 1], s)) != hipSuccess ||
-            (e = hipStreamWaitEvent(ts.stream, ts.fork[kTrainForks - 1], 0)) != hipSuccess ||
-            (e = launch_prepare(a, sp.side_sel ? *sp.side_sel : no_sel, sp.side_ded ? *sp.side_ded : no_ded, d.K,
-                                ts.stream)) != hipSuccess)
-            return e;
-    }
     if (sp.gru_now && (e = launch_gru(d, plan, pw, a, s)) != hipSuccess)
         return e;
     if ((e = stamp()) != hipSuccess)
         return e;
     if (sp.train) {
-        if ((e = launch_train(d, a, sp.train_ws, sp.packed, sp.pw_out, sp.lr, sp.loss_out, s, sp.train_side)) != hipSuccess ||
-            (e = stamp()) != hipSuccess)
+        if ((e = launch_train(d, plan, a, sp.train_ws, pw, sp.lr, sp.loss_out, sp.train_launches, s)) != hipSuccess || (e = stamp()) != hipSuccess)
             return e;
         // inspection outputs, if any are asked for (the training step has cleared its query set's counter)
-        if (wants_inspection(a) && (e = launch_closing(d, plan, *sp.pw_out, a, GruAhead{}, s, false)) != hipSuccess)
+        if (wants_inspection(a) && (e = launch_closing(d, plan, pw, a, GruAhead{}, s, false)) != hipSuccess)
             return e;
         return stamp();
     }

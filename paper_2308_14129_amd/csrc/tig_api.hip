@@ -89,8 +89,6 @@ struct tig_ctx {
     void *static_scratch;  // this device's copy of g_static_scratch
     bool embed_stale;      // training steps have moved the master weights since the attention / merge / decoder weights were last folded
     void *train_ws;        // training workspace (master weights, gradients, the backward pass's buffers), or NULL
-    TrainSide train_side;  // side stream and events of the training step's weight-gradient contractions
-    bool have_train_side;
     bool has_model;        // tig_init was given weights (the headline instance's prepared weights exist)
     void *mods_ws;         // workspace of an attached module selection, or NULL
     ModParams mods;        // ... and its parameters
@@ -715,9 +713,9 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
     }
 
     // What the embedding launch -- or a module selection's last launch -- can do on the side for a later
-    // step (never for a static call; a training step runs it on its second stream, see side_prep).
+    // step (never for a static call).
     const bool one_wg = winners_in_one_launch(count);
-    const int spare = use_static || train ? 0
+    const int spare = use_static ? 0
                       : fused              ? embed_spare_workgroups(d, ctx->plan, a.roles, count)
                                            : 1 + prepare_workgroups(count, true);
     uint32_t epoch = ctx->epoch;
@@ -733,11 +731,9 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
     };
 
     StepPlan sp = {};
-    SelectJob sel_now = {}, sel_side = {};
-    DedupJob ded_now = {}, ded_side = {};
-    // a training step has no embedding launch to carry such work: it goes to the step's second stream
-    const bool side_prep = train && ctx->have_train_side;
-    int launches = fused ? 2 : 0;  // embedding, closing
+    SelectJob sel_now = {};
+    DedupJob ded_now = {};
+    int launches = train ? 0 : fused ? 2 : 0;  // embedding, closing (a training step counts its own)
 
     // ---- the distinct queries of this batch: prepared by the previous step's embedding launch if
     // that step guessed this batch (it reads the event stream and the adjacency only), else now
@@ -756,7 +752,7 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
     bool w_ready = false;
     if (!d.deferred) {
         // this batch's: selected ahead like the queries, else now
-        w_ready = !use_static && !train && ctx->ahead_w_valid && ctx->ahead_w_first == first &&
+        w_ready = !use_static && ctx->ahead_w_valid && ctx->ahead_w_first == first &&
                   ctx->ahead_w_count == count;
         wi = use_static ? 0 : (w_ready ? ctx->wcur ^ 1 : ctx->wcur);
         a.msg_first_eid = first;
@@ -780,9 +776,6 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
         // (a module selection's last launch copies the flags out itself: they have to be there before it)
         if (spare > 0 && one_wg && (fused || !a.out_is_winner)) {
             a.sel = mine;
-        } else if (side_prep && one_wg) {
-            sel_side = mine;
-            sp.side_sel = &sel_side;
         } else {
             sel_now = mine;
             (one_wg ? sp.prep_sel : sp.big_sel) = &sel_now;
@@ -831,25 +824,12 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
             // The decode launch finishes that preparation: row references against the batch the NEXT
             // step applies -- the guessed batch itself, or in the deferred order this step's batch
             // (selected into the other list by now, by the embedding launch or up front).
-            a.fin_count = fused ? guess : 0;
+            a.fin_count = fused && !train ? guess : 0;
             a.fin_msg_first_eid = d.deferred ? first : next_first;
             a.fin_msg_count = d.deferred ? count : guess;
             a.fin_msg_key = ctx->key[wi ^ 1];
         }
     }
-    if (side_prep && next_first < ctx->num_events) {
-        const int64_t left = ctx->num_events - next_first;
-        const int32_t guess = left < count ? (int32_t)left : count;
-        if (winners_in_one_launch(guess)) {
-            // (the step that takes the set finishes it: slots, row references)
-            ded_side = make_dedup(st, st.qs[qi ^ 1], next_first, guess, next_epoch(), true);
-            sp.side_ded = &ded_side;
-            if (!q_ready)
-                sp.clear_first = st.qs[qi ^ 1].n_u;
-        }
-    }
-    if (sp.side_sel || sp.side_ded)
-        launches += 1;
     // ---- The closing launch also runs the GRU of the batch the next step applies, once that batch's
     // winners are known: in the update-first order the guessed batch (selected by this step's
     // embedding launch), in the deferred order this step's own batch (whatever comes next).
@@ -859,7 +839,7 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
         else if (d.deferred)
             sp.ahead = GruAhead{first, count, st.win[wi ^ 1], st.n_win[wi ^ 1]};
     }
-    if (clear_tab && !sp.prep_ded && (a.ded.count > 0 || sp.side_ded)) {
+    if (clear_tab && !sp.prep_ded && a.ded.count > 0) {
         // the epoch wrapped and only the side job uses the table: clear it ahead of everything
         const hipError_t e = launch_fill_zero(st.tab, sizeof(unsigned long long) * (size_t)st.tab_slots, ctx->stream);
         if (e != hipSuccess)
@@ -874,13 +854,11 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
     }
     if (train) {
         sp.train = true;
+        sp.train_launches = &launches;
         sp.train_ws = ctx->train_ws;
-        sp.packed = ctx->packed;
-        sp.pw_out = &ctx->pw;
         sp.lr = train->lr;
         sp.loss_out = train->loss_out;
-        sp.train_side = ctx->have_train_side ? &ctx->train_side : nullptr;
-        a.gru_gates = train_gates_buffer(d, ctx->train_ws);
+        train_step_args(d, ctx->train_ws, &a);
     }
     const hipError_t e = launch_step(d, ctx->plan, ctx->pw, a, sp, ctx->stream, marks);
     // bit i: the interval between marks i and i + 1 held a kernel (a module selection's kernels fill
@@ -909,11 +887,10 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
         return TIG_OK;  // the context's own lists and sets are untouched: winners and queries prepared ahead stay usable
     ctx->epoch = epoch;
     ctx->qcur = qi;
-    const DedupJob &ded_ahead = sp.side_ded ? ded_side : a.ded;
-    ctx->ahead_q_valid = ded_ahead.count > 0;
+    ctx->ahead_q_valid = a.ded.count > 0;
     ctx->ahead_q_finished = a.fin_count > 0;
-    ctx->ahead_q_first = ded_ahead.first_eid;
-    ctx->ahead_q_count = ded_ahead.count;
+    ctx->ahead_q_first = a.ded.first_eid;
+    ctx->ahead_q_count = a.ded.count;
     if (d.deferred) {
         ctx->wcur = wi ^ 1;  // the list just selected is the one the next step applies
         ctx->pend_valid = true;
@@ -971,23 +948,7 @@ int tig_train_attach(tig_ctx *ctx, const tig_weights *weights, void *workspace, 
         return fail(ctx, TIG_EINVAL, "tig_train_attach: training needs an fp32 context whose rows fit the backward kernels");
     if (workspace_bytes < train_workspace_bytes(ctx->d))
         return fail(ctx, TIG_ENOSPACE, "tig_train_attach: workspace too small");
-    hipError_t e = prepare_train(ctx->d);
-    if (e == hipSuccess && !ctx->have_train_side) {
-        // (default priority; non-blocking: no implicit ordering against the legacy default stream)
-        TrainSide ts = {};
-        int made = 0;
-        e = hipStreamCreateWithFlags(&ts.stream, hipStreamNonBlocking);
-        for (; e == hipSuccess && made <= kTrainForks; ++made)
-            e = hipEventCreateWithFlags(made < kTrainForks ? &ts.fork[made] : &ts.join, hipEventDisableTiming);
-        if (e == hipSuccess) {
-            ctx->train_side = ts;
-            ctx->have_train_side = true;
-        } else if (ts.stream) {
-            for (int i = 0; i < made - 1; ++i)
-                (void)hipEventDestroy(i < kTrainForks ? ts.fork[i] : ts.join);
-            (void)hipStreamDestroy(ts.stream);
-        }
-    }
+    hipError_t e = prepare_train(ctx->d, ctx->plan);
     if (e == hipSuccess)
         e = train_attach(ctx->d, *weights, workspace, ctx->packed, &ctx->pw, ctx->stream);
     if (e == hipSuccess)
@@ -1329,13 +1290,6 @@ void tig_destroy(tig_ctx *ctx)
         for (int i = 0; i <= kNumStepKernels; ++i)
             (void)hipEventDestroy(ctx->marks[i]);
     hint_words_give(ctx->rows_seen_host);
-    if (ctx->have_train_side) {
-        (void)hipStreamSynchronize(ctx->train_side.stream);
-        for (int i = 0; i < kTrainForks; ++i)
-            (void)hipEventDestroy(ctx->train_side.fork[i]);
-        (void)hipEventDestroy(ctx->train_side.join);
-        (void)hipStreamDestroy(ctx->train_side.stream);
-    }
     delete ctx;
 }
 

@@ -122,6 +122,14 @@ struct DedupJob {
     int32_t n_wgs;              // workgroups that share the job
 };
 
+// What the forward pass of a training step keeps per row of the query set (S NULL: an ordinary step).
+struct TrainFwd {
+    float *S;         // [R x (M + 1)] own state row, then 1 if the row has neighbours
+    float *QT, *KVB;  // [R x N1] q~ and the weighted sums of the key / value rows, in the kernels' column order
+    float *H1;        // [R x E]
+    float *DA, *DB;   // [R x E] cleared: gradients of the decoder's source / second-operand half of the row
+};
+
 struct StepArgs {
     // graph (device)
     const int32_t *src, *dst;
@@ -152,7 +160,6 @@ struct StepArgs {
     float *staging;  // [2*msg_count x M] new memory rows of the winners, by entry 2b+role
     int upd;         // UpdateKind of the state update
     const float *mean_msg;  // NULL, or [2*msg_count x (M + T + F)]: the mean aggregator's message columns behind s_self, by winning entry
-    float *gru_gates;  // NULL, or [2*msg_count x 4 x M]: r, z, n and the hidden half of n's pre-activation of winner r of the list (a training step's backward pass reads them)
     float *emb_u;    // [R x E] embedding of every distinct query
     float *dec_a;    // [R x Ep] first decoder layer, source half, of every distinct query
     float *dec_b;    // [R x Ep] the same, second-operand half
@@ -177,6 +184,11 @@ struct StepArgs {
     int32_t *out_nbr_node, *out_nbr_eid, *out_nbr_cnt;  // optional
     double *out_nbr_ts;                                 // optional
     uint8_t *out_is_winner;                             // optional
+    // a training step (gru_gates NULL: an ordinary step): what its backward pass reads
+    float *gru_gates;  // [2*msg_count x 4 x M] r, z, n and the hidden half of n's pre-activation of winner r of the list
+    float *gru_msg;    // [2*msg_count x D_msg] the message row of winner r
+    float *d_staging;  // [2*msg_count x M] gradients of the staged rows, cleared by the GRU launch
+    TrainFwd tr;
 };
 
 struct LaunchPlan {
@@ -211,7 +223,7 @@ bool plan_launch(const Dims &d, int lds_limit, LaunchPlan *plan);
 int gru_lds_bytes(const Dims &d);
 int embed_lds_bytes(const Dims &d, int mt);
 hipError_t prepare_gru(const Dims &d, const LaunchPlan &plan);
-hipError_t prepare_embed(const Dims &d, const LaunchPlan &plan);
+hipError_t prepare_embed(const Dims &d, const LaunchPlan &plan, bool train = false);
 hipError_t prepare_small();
 bool winners_in_one_launch(int count);
 // batches above the one-workgroup limit: keys to the per-node array, then winners + flags
@@ -257,18 +269,12 @@ struct StepPlan {
     const DedupJob *prep_ded;   // query preparation inside the prepare launch, or NULL
     bool clear_tab;             // clear prep_ded's claim table first
     bool gru_now;               // the GRU launch ahead of the embedding
-    // a training step: forward in direct form, loss, backward and SGD instead of the embedding launch
+    // a training step: forward with its intermediates kept, loss, backward and SGD instead of embedding and closing
     bool train;
+    int *train_launches;  // kernels of the training step, counted here
     void *train_ws;
-    void *packed;
-    PackedWeights *pw_out;
     float lr;
     float *loss_out;
-    const struct TrainSide *train_side;  // NULL, or the side stream of the weight-gradient contractions
-    // a training step with a side stream: preparation that nothing of this step reads (this batch's
-    // selection in the deferred order, the next batch's queries), launched on that stream; or NULL
-    const SelectJob *side_sel;
-    const DedupJob *side_ded;
     int32_t *clear_first;       // a counter to clear ahead of everything, or NULL
     GruAhead ahead;             // GRU workgroups of the closing launch
     const struct ModParams *mods;  // a context with a module selection, or NULL
@@ -297,27 +303,17 @@ hipError_t launch_sync_shared(const SyncArgs &a, hipStream_t s);
 // ---- training step (train.hip) ----
 size_t train_workspace_bytes(const Dims &d);
 bool train_supported(const Dims &d);
-hipError_t prepare_train(const Dims &d);
+hipError_t prepare_train(const Dims &d, const LaunchPlan &plan);
 hipError_t train_attach(const Dims &d, const tig_weights &w, void *workspace, void *packed, PackedWeights *pw,
                         hipStream_t s);
 hipError_t train_copy_out(const Dims &d, void *workspace, bool grads, const tig_weights &out, hipStream_t s);
-// A second stream for the weight-gradient contractions of a training step: they depend on nothing
-// but their own (delta, input) rows, so they run beside the rest of the backward pass; `fork[i]` is
-// recorded on the step's stream when the rows of group i are complete, `join` on the side stream
-// after the last contraction (the step's stream waits for it ahead of the update).
-constexpr int kTrainForks = 7;  // (the last one: the preparation launched beside the step)
-struct TrainSide {
-    hipStream_t stream;
-    hipEvent_t fork[kTrainForks], join;
-};
-// side: NULL = everything on s
-hipError_t launch_train(const Dims &d, const StepArgs &a, void *workspace, void *packed, PackedWeights *pw, float lr,
-                        float *loss_out, hipStream_t s, const TrainSide *side);
-// after training steps with lr != 0 only the state update's prepared weights follow the masters: this
-// re-folds the rest (attention, merge MLP, decoder) for the fused inference kernels
+// the arrays that a training step's GRU and embedding launches leave for its backward pass
+void train_step_args(const Dims &d, void *workspace, StepArgs *a);
+hipError_t launch_train(const Dims &d, const LaunchPlan &plan, const StepArgs &a, void *workspace, const PackedWeights &pw, float lr,
+                        float *loss_out, int *launches, hipStream_t s);
+// after training steps with lr != 0 the prepared weights follow the masters in single precision: this folds
+// those of the inference kernels again, in double precision
 hipError_t train_refold_embed(const Dims &d, void *workspace, void *packed, PackedWeights *pw, hipStream_t s);
-// where the step's GRU launch leaves the gates of the applied winners for the backward pass
-float *train_gates_buffer(const Dims &d, void *workspace);
 // ---- other instances of the general architecture (modules.hip) ----
 // Module selection of a context and its weights: transposed copies ([in x out]) in the attached workspace.
 constexpr int kAccCopies = 8;  // accumulation rows per node of the mean aggregator (entries are dealt out to them: less same-address traffic)

@@ -49,7 +49,7 @@ def main():
         return c
 
     us = lambda ticks: ticks * 0.01
-    c = clocks("tig_debug_phase_clocks", 1024)
+    c = clocks("tig_debug_phase_clocks_" + prec, 1024)
     tile = (c[:, 5] > 0) & (c[:, 0] > 0) & (c[:, 7] == 0)
     side = (c[:, 7] > 0) & (c[:, 0] > 0) & (c[:, 5] == 0)
     ct = c[tile]

@@ -225,6 +225,18 @@ def test_four_heads_gradients():
     run_training(b, [(6000, 150), (6150, 150)], 0.01, "update_first", warm_at=6000, then_eval=1)
 
 
+@pytest.mark.parametrize("dims,count", [
+    (dict(mem_dim=2, time_dim=2, feat_dim=1, emb_dim=1, num_neighbors=1, num_heads=2), 33),       # narrower than any tile or load
+    (dict(mem_dim=7, time_dim=130, feat_dim=5, emb_dim=33, num_neighbors=5, num_heads=1), 97),    # ragged widths, T > 128
+    (dict(mem_dim=48, time_dim=20, feat_dim=3, emb_dim=140, num_neighbors=16, num_heads=4), 64),  # all lanes hold a slot
+    (dict(mem_dim=128, time_dim=128, feat_dim=256, emb_dim=512, num_neighbors=4, num_heads=1), 40),  # the widest rows
+    (dict(mem_dim=21, time_dim=13, feat_dim=6, emb_dim=35, num_neighbors=6, num_heads=2), 801),   # rows split over the XCDs
+])
+def test_gradients_at_the_edges_of_the_kernels(dims, count):
+    b = Bundle(S.WORKLOADS["c1_tiny"].scaled(**dims))
+    run_training(b, [(4000, count), (4000 + count, count // 2)], 0.0, "deferred", warm_at=4000)
+
+
 def test_training_needs_fp32_negatives_and_a_workspace(c1):
     import torch
     from paper_2308_14129_amd import tig
