@@ -18,6 +18,8 @@ struct EmbedParams {
     int phi_regs, mem_regs, feat_regs;
 };
 
+enum EmbedMode { kEmbedStep = 0, kEmbedTrain = 1, kEmbedLayer = 2 };
+
 inline int npl_for(const Dims &d)
 {
     const int need = (d.dkvp + 63) / 64;
@@ -33,5 +35,6 @@ inline int embed_threads(const Dims &d) { return npl_for(d) >= 8 && d.H > 2 ? 51
 const void *embed_kernel_bf16(const Dims &d, int mt);
 const void *embed_kernel_fp32(const Dims &d, int mt);
 const void *embed_kernel_train(const Dims &d, int mt);
+const void *embed_kernel_layer(const Dims &d, int mt);
 
 }  // namespace tig

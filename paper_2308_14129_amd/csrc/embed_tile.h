@@ -26,8 +26,11 @@
 // destinations, first in the set) over all tiles.  Workgroups beyond the tiles and the memory
 // overwrite prepare the batch expected next: one selects its last-message winners, the others
 // merge and look up its queries.
-// TRAIN: the forward pass of a training step, which also keeps what the backward pass reads (state rows,
-// q~, kvbar, h1 per row of the query set).
+// MODE (EmbedMode): an ordinary step; the forward pass of a training step (TRAIN), which also keeps what the
+// backward pass reads (state rows, q~, kvbar, h1 per row of the query set); one attention layer of a stack (LAYER):
+// every row of the set, the negatives' too, has its neighbours and references already, the "memory" is the table
+// of rows the layer reads, and a workgroup takes tile after tile (the rows can be many times those of a batch: a
+// workgroup per possible tile, at one per compute unit, would queue behind the tiles in use).
 #pragma once
 
 #include <type_traits>
@@ -88,10 +91,12 @@ constexpr int regs_touching(int lo, int hi, int dims)
     return m;
 }
 
-template <int PREC, bool TRAIN, int MT, int NPL, int H, int SHAPE>
-__global__ void __launch_bounds__((EmbedShape<NPL, H>::kThreads))
-k_embed(StepArgs a, PackedWeights w, EmbedParams p)
+// one tile of ROWS query rows: rows pass, pass + n_passes, ...
+template <int PREC, int MODE, int MT, int NPL, int H, int SHAPE>
+__device__ inline __attribute__((always_inline)) void embed_rows(const StepArgs &a, const PackedWeights &w, const EmbedParams &p, char *smem, int pass, int n_passes,
+                                                                int n_u, int n_rows)
 {
+    constexpr bool TRAIN = MODE == kEmbedTrain, LAYER = MODE == kEmbedLayer;
     using P = Prec<PREC>;
     using SH = RowShape<SHAPE>;
     // segment sizes and segment-to-register maps of a key/value row, as phase C uses them
@@ -107,39 +112,6 @@ k_embed(StepArgs a, PackedWeights w, EmbedParams p)
     constexpr int ROWS = 16 * MT;
     constexpr int KC = NPL >= 8 ? 5 : (NPL == 4 ? 10 : 16);      // neighbour rows in flight
     constexpr int NPHI = NPL;  // registers that may hold time-encoding dims (T <= 64 * NPL)
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    if ((int)blockIdx.x >= p.n_tiles) {
-        int x = (int)blockIdx.x - p.n_tiles;
-        if (x < p.n_commit) {
-            overwrite_memory(a, p.M, x * kEmbedWaves + wave_id(), p.n_commit * kEmbedWaves);
-            return;
-        }
-        x -= p.n_commit;
-        // The workgroups beyond, on compute units this launch leaves idle (launched only with
-        // 1024 threads): last-message selection and query preparation for a later step.
-        if constexpr (kEmbedThreads == kScatterThreads) {
-            TIG_MARK(0);
-            if (x == 0 && threadIdx.x == 0 && a.rows_seen) {
-                // hints for the host (stores to its memory take a while: from a workgroup that ends
-                // long before the launch does)
-                a.rows_seen[0] = *a.qs.n_u + (a.roles == 3 ? a.count : 0);  // (a hint: not clamped)
-                if (a.msg_count > 0)
-                    a.rows_seen[1] = *a.n_win;
-            }
-            if (a.sel.count > 0) {
-                if (x == 0) {
-                    winners_block(a, a.sel, smem);
-                    TIG_MARK(7);
-                    return;
-                }
-                --x;
-            }
-            if (a.ded.count > 0 && x < a.ded.n_wgs)
-                dedup_block(a, a.ded, p.K, x, smem);
-            TIG_MARK(7);
-        }
-        return;
-    }
     char *rowbuf = smem;
     char *h1buf = smem + p.off_h1;
     int *row_q = (int *)(smem + p.off_meta);  // [ROWS] row of the query set or -1
@@ -153,20 +125,13 @@ k_embed(StepArgs a, PackedWeights w, EmbedParams p)
     const int lane = lane_id();
     const int wave = wave_id();
     const int mem_off = 4 * p.N1;
-    int n_u = *a.qs.n_u;  // distinct source / destination queries; the negatives' rows follow at 2 * count
-    n_u = n_u < 2 * a.count ? n_u : 2 * a.count;
-    const int neg_row0 = 2 * a.count;
-    const int n_rows = n_u + (a.roles == 3 ? a.count : 0);
-    const int n_passes = (n_rows + ROWS - 1) / ROWS;
+    const int neg_row0 = 2 * a.count;  // (the negatives' rows of the set)
     // a row reference that is neither a memory row nor a staged row of the applied batch reads as none
     auto checked_ref = [&](int32_t ref) -> int32_t {
         const bool ok = ref >= 0 ? (int64_t)ref < a.num_nodes : (ref != kRefNone && ~ref < 2 * a.msg_count);
         return ok ? ref : kRefNone;
     };
 
-    const int pass = (int)blockIdx.x;
-    if (pass >= n_passes)
-        return;  // fewer distinct queries than the grid was sized for
     TIG_MARK(0);
     // ---- A. query rows ------------------------------------------------------------------------
     // Every load of this phase is unconditional (an index that does not apply is replaced by one that
@@ -180,16 +145,16 @@ k_embed(StepArgs a, PackedWeights w, EmbedParams p)
     if (threadIdx.x < ROWS) {
         const int r = threadIdx.x;
         const int x = pass + n_passes * r;
-        const bool is_rep = x < n_u, is_neg = !is_rep && x < n_rows;
+        const bool is_rep = x < n_u || (LAYER && x < n_rows), is_neg = !is_rep && x < n_rows;
         // a negative: node and time from the call.  For now the reference is the node's own memory
         // row; the gather below checks whether this step updates the node.
-        const int b = is_neg ? x - n_u : 0, qq = is_rep ? x : 0;
+        const int b = is_neg ? x - n_u : 0, qq = !is_rep ? 0 : (LAYER && x >= n_u ? neg_row0 + (x - n_u) : x);
         const int32_t *ref_p = is_neg ? a.neg + b : a.qs.self_ref + qq;
         const double *t_p = is_neg ? a.ts + a.first_eid + b : a.qs.t + qq;
         int32_t ref = *ref_p;
         double t = *t_p;
         int cnt = a.qs.cnt[qq];
-        int q = is_rep ? x : neg_row0 + b;
+        int q = is_rep ? qq : neg_row0 + b;
         if (is_neg) {
             ref = ref >= 0 ? ref : kRefNone;
             cnt = 0;
@@ -241,7 +206,7 @@ k_embed(StepArgs a, PackedWeights w, EmbedParams p)
         for (int i = 0; i < kRowsPerWave; ++i) {
             const int r = wave + i * kEmbedWaves;
             const int ref = __builtin_amdgcn_readfirstlane(r < ROWS ? row_ref[r] : kRefNone);
-            const bool is_neg = r < ROWS && __builtin_amdgcn_readfirstlane(row_q[r < ROWS ? r : 0]) >= neg_row0;
+            const bool is_neg = !LAYER && r < ROWS && __builtin_amdgcn_readfirstlane(row_q[r < ROWS ? r : 0]) >= neg_row0;
             src_row[i] = row_rsrc(ref);
 #pragma unroll
             for (int u = 0; u < kAhead; ++u)
@@ -324,7 +289,7 @@ k_embed(StepArgs a, PackedWeights w, EmbedParams p)
         dt = 0.0;
         if (r < ROWS) {
             const int q = row_q[r];
-            if (q >= 0 && q < neg_row0 && lane < row_cnt[r]) {
+            if (q >= 0 && (LAYER || q < neg_row0) && lane < row_cnt[r]) {
                 v = a.qs.ref[(size_t)q * p.K + lane];  // row reference of the neighbour's state
                 e = a.qs.eid[(size_t)q * p.K + lane];
                 dt = row_t[r] - a.qs.ts[(size_t)q * p.K + lane];
@@ -426,7 +391,7 @@ k_embed(StepArgs a, PackedWeights w, EmbedParams p)
             if (q_cur < 0)
                 continue;
             int cnt;
-            if (q_cur >= neg_row0 && !__builtin_amdgcn_readfirstlane(row_todo[r_cur])) {
+            if (!LAYER && q_cur >= neg_row0 && !__builtin_amdgcn_readfirstlane(row_todo[r_cur])) {
                 // a negative without history: its (empty) row of the query set is written here, where
                 // nothing waits for the stores
                 if (lane < p.K) {
@@ -443,7 +408,7 @@ k_embed(StepArgs a, PackedWeights w, EmbedParams p)
                     a.qs.t[q_cur] = row_t[r_cur];
                 }
                 cnt = 0;
-            } else if (q_cur >= neg_row0) {
+            } else if (!LAYER && q_cur >= neg_row0) {
                 // a negative: its neighbours are looked up now (slot k lands in lane k)
                 double ts_k;
                 cnt = finish_negative(a, p.K, q_cur - neg_row0, nb_vc, nb_ec, ts_k);
@@ -793,7 +758,7 @@ k_embed(StepArgs a, PackedWeights w, EmbedParams p)
     // share the reads of h1.
     {
         const int nE = p.Ep / 16, kbE = p.Ek / P::KB;
-        const int n_out = 3 * nE;
+        const int n_out = LAYER && !a.dec_a ? nE : 3 * nE;  // (only the last layer's rows go on to the decoder)
         auto put = [&](const floatx4 (&acc)[MT], int ot) {
             const int grp = ot / nE;  // 0: embedding, 1: source half, 2: second-operand half
             const int col = (ot - grp * nE) * 16 + (lane & 15);
@@ -836,13 +801,79 @@ k_embed(StepArgs a, PackedWeights w, EmbedParams p)
     TIG_MARK(5);
 }
 
-template <int PREC, bool TRAIN, int MT, int NPL>
+static_assert(sizeof(StepArgs) % alignof(PackedWeights) == 0 && (sizeof(StepArgs) + sizeof(PackedWeights)) % alignof(EmbedParams) == 0,
+              "the kernel's arguments follow each other without gaps");
+
+template <int PREC, int MODE, int MT, int NPL, int H, int SHAPE>
+__global__ void __launch_bounds__((EmbedShape<NPL, H>::kThreads))
+k_embed(StepArgs a, PackedWeights w, EmbedParams p)
+{
+    constexpr int kEmbedThreads = EmbedShape<NPL, H>::kThreads;
+    constexpr int kEmbedWaves = EmbedShape<NPL, H>::kWaves;
+    constexpr int ROWS = 16 * MT;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    if ((int)blockIdx.x >= p.n_tiles) {
+        int x = (int)blockIdx.x - p.n_tiles;
+        if (x < p.n_commit) {
+            overwrite_memory(a, p.M, x * kEmbedWaves + wave_id(), p.n_commit * kEmbedWaves);
+            return;
+        }
+        x -= p.n_commit;
+        // The workgroups beyond, on compute units this launch leaves idle (launched only with
+        // 1024 threads): last-message selection and query preparation for a later step.
+        if constexpr (kEmbedThreads == kScatterThreads) {
+            TIG_MARK(0);
+            if (x == 0 && threadIdx.x == 0 && a.rows_seen) {
+                // hints for the host (stores to its memory take a while: from a workgroup that ends
+                // long before the launch does)
+                a.rows_seen[0] = *a.qs.n_u + (a.roles == 3 ? a.count : 0);  // (a hint: not clamped)
+                if (a.msg_count > 0)
+                    a.rows_seen[1] = *a.n_win;
+            }
+            if (a.sel.count > 0) {
+                if (x == 0) {
+                    winners_block(a, a.sel, smem);
+                    TIG_MARK(7);
+                    return;
+                }
+                --x;
+            }
+            if (a.ded.count > 0 && x < a.ded.n_wgs)
+                dedup_block(a, a.ded, p.K, x, smem);
+            TIG_MARK(7);
+        }
+        return;
+    }
+    int n_u = *a.qs.n_u;  // distinct source / destination queries; the negatives' rows follow at 2 * count
+    n_u = n_u < 2 * a.count ? n_u : 2 * a.count;
+    const int n_rows = n_u + (a.roles == 3 ? a.count : 0);
+    const int n_passes = (n_rows + ROWS - 1) / ROWS;
+    if constexpr (MODE == kEmbedLayer) {
+        for (int pass = (int)blockIdx.x; pass < n_passes; pass += p.n_tiles) {
+            // The arguments are read again for every tile, from a pointer that the compiler cannot see through: what it
+            // takes out of the loop otherwise (every address that does not depend on the tile) needs 250 registers
+            // and 824 bytes of scratch per lane (105 us for the first layer of 4000 events).
+            typedef const __attribute__((address_space(4))) char *Args;
+            Args at = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(at));
+            const StepArgs &ta = *(const StepArgs *)at;
+            const PackedWeights &tw = *(const PackedWeights *)(at + sizeof(StepArgs));
+            const EmbedParams &tp = *(const EmbedParams *)(at + sizeof(StepArgs) + sizeof(PackedWeights));
+            embed_rows<PREC, MODE, MT, NPL, H, SHAPE>(ta, tw, tp, smem, pass, n_passes, n_u, n_rows);
+            __syncthreads();  // (the next tile's rows take this one's place in LDS)
+        }
+    } else if ((int)blockIdx.x < n_passes) {  // (there may be fewer distinct queries than the grid was sized for)
+        embed_rows<PREC, MODE, MT, NPL, H, SHAPE>(a, w, p, smem, (int)blockIdx.x, n_passes, n_u, n_rows);
+    }
+}
+
+template <int PREC, int MODE, int MT, int NPL>
 const void *pick_h(int H)
 {
     switch (H) {
-    case 1: return (const void *)k_embed<PREC, TRAIN, MT, NPL, 1, 0>;
-    case 2: return (const void *)k_embed<PREC, TRAIN, MT, NPL, 2, 0>;
-    default: return (const void *)k_embed<PREC, TRAIN, MT, NPL, 4, 0>;
+    case 1: return (const void *)k_embed<PREC, MODE, MT, NPL, 1, 0>;
+    case 2: return (const void *)k_embed<PREC, MODE, MT, NPL, 2, 0>;
+    default: return (const void *)k_embed<PREC, MODE, MT, NPL, 4, 0>;
     }
 }
 
@@ -854,15 +885,15 @@ constexpr int npl_of_dims(int dims)
     return npl;
 }
 
-template <int PREC, bool TRAIN, int SHAPE>
+template <int PREC, int MODE, int SHAPE>
 const void *pick_fixed(int mt)
 {
     using SH = RowShape<SHAPE>;
     constexpr int NPL = npl_of_dims(SH::T + SH::M + SH::F);
     switch (mt) {
-    case 1: return (const void *)k_embed<PREC, TRAIN, 1, NPL, SH::H, SHAPE>;
-    case 2: return (const void *)k_embed<PREC, TRAIN, 2, NPL, SH::H, SHAPE>;
-    default: return (const void *)k_embed<PREC, TRAIN, 3, NPL, SH::H, SHAPE>;
+    case 1: return (const void *)k_embed<PREC, MODE, 1, NPL, SH::H, SHAPE>;
+    case 2: return (const void *)k_embed<PREC, MODE, 2, NPL, SH::H, SHAPE>;
+    default: return (const void *)k_embed<PREC, MODE, 3, NPL, SH::H, SHAPE>;
     }
 }
 
@@ -873,37 +904,37 @@ bool shape_is(const Dims &d)
     return d.T == SH::T && d.M == SH::M && d.F == SH::F && d.H == SH::H;
 }
 
-template <int PREC, bool TRAIN, int MT>
+template <int PREC, int MODE, int MT>
 const void *pick_npl(int npl, int H)
 {
     switch (npl) {
-    case 1: return pick_h<PREC, TRAIN, MT, 1>(H);
-    case 2: return pick_h<PREC, TRAIN, MT, 2>(H);
-    case 4: return pick_h<PREC, TRAIN, MT, 4>(H);
-    default: return pick_h<PREC, TRAIN, MT, 8>(H);
+    case 1: return pick_h<PREC, MODE, MT, 1>(H);
+    case 2: return pick_h<PREC, MODE, MT, 2>(H);
+    case 4: return pick_h<PREC, MODE, MT, 4>(H);
+    default: return pick_h<PREC, MODE, MT, 8>(H);
     }
 }
 
-template <int PREC, bool TRAIN>
+template <int PREC, int MODE>
 const void *pick_mt(int mt, int npl, int H)
 {
     switch (mt) {
-    case 1: return pick_npl<PREC, TRAIN, 1>(npl, H);
-    case 2: return pick_npl<PREC, TRAIN, 2>(npl, H);
-    default: return pick_npl<PREC, TRAIN, 3>(npl, H);
+    case 1: return pick_npl<PREC, MODE, 1>(npl, H);
+    case 2: return pick_npl<PREC, MODE, 2>(npl, H);
+    default: return pick_npl<PREC, MODE, 3>(npl, H);
     }
 }
 
-template <int PREC, bool TRAIN>
+template <int PREC, int MODE>
 const void *pick(const Dims &d, int mt)
 {
     if (shape_is<1>(d))
-        return pick_fixed<PREC, TRAIN, 1>(mt);
+        return pick_fixed<PREC, MODE, 1>(mt);
     if (shape_is<2>(d))
-        return pick_fixed<PREC, TRAIN, 2>(mt);
+        return pick_fixed<PREC, MODE, 2>(mt);
     if (shape_is<3>(d))
-        return pick_fixed<PREC, TRAIN, 3>(mt);
-    return pick_mt<PREC, TRAIN>(mt, npl_for(d), d.H);
+        return pick_fixed<PREC, MODE, 3>(mt);
+    return pick_mt<PREC, MODE>(mt, npl_for(d), d.H);
 }
 
 }  // namespace

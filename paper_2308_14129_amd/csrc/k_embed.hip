@@ -70,6 +70,28 @@ static int embed_tiles(const LaunchPlan &plan, int rows, int units)
     return plan.emb_mt;
 }
 
+// Most 16-row tiles per workgroup that LDS holds for one layer of a stack (0: none).
+int layer_tiles(const Dims &d, int lds_limit)
+{
+    int mt = d.dkvp <= 512 ? 3 : 0;
+    while (mt > 0 && embed_lds_bytes(d, mt) > lds_limit)
+        --mt;
+    return mt;
+}
+
+hipError_t prepare_embed_layer(const Dims &d, int most_mt)
+{
+    for (int mt = 1; mt <= most_mt; ++mt) {
+        const int own = embed_lds_bytes(d, mt);
+        const int lds = embed_threads(d) == kScatterThreads && own < kOneLds ? kOneLds : own;
+        const hipError_t e =
+            hipFuncSetAttribute(embed_kernel_layer(d, mt), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess)
+            return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t prepare_embed(const Dims &d, const LaunchPlan &plan, bool train)
 {
     for (int mt = 1; mt <= plan.emb_mt; ++mt) {
@@ -137,6 +159,29 @@ hipError_t launch_embed(const Dims &d, const LaunchPlan &plan, const PackedWeigh
     const int own = embed_lds_bytes(d, mt);
     const int lds = a.sel.count > 0 && own < kOneLds ? kOneLds : (own < kPrepLds ? kPrepLds : own);
     return hipLaunchKernel(embed_kernel(d, mt, train), dim3(p.n_tiles + extra), dim3(threads), args, (size_t)lds, s);
+}
+
+// One attention layer over the rows of a.qs (d, pw: the layer's); a.rows_est (0: unknown) sizes the tiles.  The grid
+// fills the compute units once, its workgroups take tile after tile.
+hipError_t launch_embed_layer(const Dims &d, int most_mt, int num_cus, const PackedWeights &pw, const StepArgs &a, hipStream_t s)
+{
+    StepArgs aa = a;
+    PackedWeights ww = pw;
+    const int extra = (a.sel.count > 0 ? 1 : 0) + (a.ded.count > 0 ? a.ded.n_wgs : 0);
+    const int cus = num_cus > 0 ? num_cus : 256;
+    const int units = cus - extra > 16 ? cus - extra : 16;
+    const int most = a.roles * a.count;
+    const int rows = a.rows_est > 0 && a.rows_est < most ? a.rows_est : most;
+    LaunchPlan plan = {};
+    plan.emb_mt = most_mt;
+    const int mt = embed_tiles(plan, rows, units);
+    EmbedParams p = embed_params(d, mt);
+    p.n_tiles = (most + 16 * mt - 1) / (16 * mt);
+    p.n_tiles = p.n_tiles < units ? p.n_tiles : units;
+    void *args[] = {&aa, &ww, &p};
+    const int own = embed_lds_bytes(d, mt);
+    const int lds = a.sel.count > 0 && own < kOneLds ? kOneLds : (own < kPrepLds ? kPrepLds : own);
+    return hipLaunchKernel(embed_kernel_layer(d, mt), dim3(p.n_tiles + extra), dim3(embed_threads(d)), args, (size_t)lds, s);
 }
 
 }  // namespace tig

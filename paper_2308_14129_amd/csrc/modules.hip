@@ -4,16 +4,17 @@
 // attention"; Sec. II-A: nodes may carry static features), device side.  gfx950 only, fp32.
 //
 // A context with an attached module selection runs its state update in k_gru (message build and gates on
-// the matrix cores; the plain recurrent cell is a one-gate product there) and, with one attention layer
-// and no node features, the fused embedding and closing launches of the headline instance.  The rest:
+// the matrix cores; the plain recurrent cell is a one-gate product there) and, with attention and no node
+// features, the fused embedding (two layers: k_two_*, then one launch per layer) and closing launches of the
+// headline instance.  The rest:
 //   k_mod_msgsum / k_mod_mean   mean aggregator: sums of all the node's messages of the batch (either role,
 //                  every one built from the memory at the start of the step), then their means
 //   k_mod_final    the last launch of a step without the fused ones: identity / time-projection embedding of
 //                  sixteen events' queries (or their rows out of the attention layers), both logits on the
 //                  matrix cores, beside it the memory overwrite and the preparation of the batch expected next
 //   k_mod_commit   memory overwrite M <- s_i(t) and last_update ahead of attention layers that read the table
-//   k_mr_items / k_mr_attn + k_rowgemm   attention embedding with node features and / or two stacked
-//                  layers: every layer product as one contraction over all items of the layer, the
+//   k_mr_items / k_mr_attn + k_rowgemm   attention embedding with node features, or second-layer rows that
+//                  do not fit the fused kernel's tiles: every layer product as one contraction over all items of the layer, the
 //                  attention core per item in its re-associated form (stated above k_mr_items); a
 //                  negative's neighbours are looked up by k_mr_items
 //   k_mod_hop2     two stacked attention layers (the embedding module's sum over the 2-hop temporal
@@ -223,7 +224,162 @@ __global__ void __launch_bounds__(kModThreads) k_mod_hop2(StepArgs a, ModDims d,
 }
 
 // ------------------------------------------------------------------------------------------
-// The attention embedding as contractions over all ITEMS of a layer at once (an item is a distinct
+// Two layers without node features: the rows of the first layer -- every distinct (node, time) among the queries
+// and their neighbours at the queries' times -- as a query set of their own, so that either layer is one launch
+// of the embedding kernel (embed_tile.h, LAYER; the second with the first's rows as its "memory").  4000 events of
+// 100 columns: 337 -> 126 us a step (46 + 39 us of it the layers); with the products of both layers as launches over
+// all rows (k_mr_*, below, which remain for node features and for rows that the embedding kernel's tiles do not hold) every
+// intermediate of every row went through memory, and the host issued 22 launches a step.
+//   k_two_negatives  memory overwrite; the negatives' own neighbours, one wavefront each
+//   k_two_claim      equal pairs merged, one wavefront per query: the rows' (node, time), and for every (query,
+//                    slot) its row or the (query, slot) that represents the pair
+//   k_two_lookup     the rows' neighbours, one wavefront each; the references of the queries' slots into the rows
+// Bound by chains of dependent reads (claims; the search for t in a hub's list): as many wavefronts as the
+// chip holds, and none waits for another's chain.
+constexpr int kTwoWaves = 8, kTwoThreads = kTwoWaves * kWave;
+
+__device__ inline int two_rows(const StepArgs &a, int &n_u)
+{
+    n_u = *a.qs.n_u;
+    n_u = n_u < 0 ? 0 : (n_u < 2 * a.count ? n_u : 2 * a.count);
+    return n_u + (a.roles == 3 ? a.count : 0);
+}
+
+__device__ inline int two_query_row(const StepArgs &a, int n_u, int x) { return x < n_u ? x : 2 * a.count + (x - n_u); }
+
+__device__ inline int two_slots(const StepArgs &a, int K, int q)
+{
+    const int c = a.qs.cnt[q];
+    return c < 0 ? 0 : (c > K ? K : c);
+}
+
+__global__ void __launch_bounds__(kTwoThreads) k_two_negatives(StepArgs a, int M, int K, int n_commit)
+{
+    int x = (int)blockIdx.x;
+    if (x < n_commit) {
+        if (x == 0 && threadIdx.x == 0 && a.rows_seen)
+            a.rows_seen[1] = *a.n_win;  // (a hint for the host)
+        overwrite_memory(a, M, x * kTwoWaves + wave_id(), n_commit * kTwoWaves);
+        return;
+    }
+    const int b = (x - n_commit) * kTwoWaves + wave_id();
+    if (b >= a.count)
+        return;
+    const int32_t u = a.neg[b];
+    int32_t nbr, eid;
+    double ts;
+    (void)nbr_lookup_wave(a, K, u, a.ts[a.first_eid + b], -1, a.qs, 2 * a.count + b, nbr, eid, ts);
+}
+
+// Pair (u, t) of (query x, slot j) = index `dense` claims a place of the table (open addressing; a place
+// changes once per epoch); returns the index that represents the pair.
+__device__ inline int two_claim(const StepArgs &a, const ModParams &p, int K, int n_u, int n_rows, uint32_t epoch, int dense, int32_t u, double t)
+{
+    const unsigned long long mine = ((unsigned long long)epoch << 32) | (uint32_t)dense;
+    uint32_t h = query_hash(u, t) & p.claim_mask;
+    for (uint32_t probes = 0; probes <= p.claim_mask; ++probes) {
+        unsigned long long cur = __hip_atomic_load(&p.claim[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if ((uint32_t)(cur >> 32) != epoch) {
+            const unsigned long long old = atomicCAS(&p.claim[h], cur, mine);
+            if (old == cur)
+                return dense;
+            cur = old;
+        }
+        const int other = (int)(uint32_t)cur;
+        const int xo = other / (K + 1), jo = other - xo * (K + 1);
+        if (other >= 0 && xo < n_rows) {
+            const int qo = two_query_row(a, n_u, xo);
+            const int32_t uo = jo < K ? a.qs.nbr[(size_t)qo * K + jo] : a.qs.node[qo];
+            if (uo == u && a.qs.t[qo] == t)
+                return other;
+        }
+        h = (h + 1) & p.claim_mask;
+    }
+    return dense;
+}
+
+__global__ void __launch_bounds__(kTwoThreads) k_two_claim(StepArgs a, ModParams p, int K, uint32_t epoch)
+{
+    __shared__ int s_items[kTwoWaves], s_base;
+    int n_u;
+    const int n_rows = two_rows(a, n_u), lane = lane_id(), wave = wave_id();
+    int32_t *counter = p.it.n_u + (epoch & 1u);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        p.it.n_u[(epoch & 1u) ^ 1u] = 0;  // (the next step's)
+        if (a.rows_seen)
+            a.rows_seen[2] = n_rows;      // (a hint for the host)
+    }
+    const int x = (int)blockIdx.x * kTwoWaves + wave;
+    const bool valid = x < n_rows;  // (uniform over the wavefront)
+    const int q = valid ? two_query_row(a, n_u, x) : 0;
+    const int cnt = valid ? two_slots(a, K, q) : 0;
+    // lane j < cnt: slot j; lane K: the query itself
+    const bool cand = valid && (lane < cnt || lane == K);
+    const double t = a.qs.t[q];
+    int32_t u = -1;
+    int rep = -1;
+    const int dense = x * (K + 1) + lane;
+    if (cand) {
+        u = lane < K ? a.qs.nbr[(size_t)q * K + lane] : a.qs.node[q];
+        rep = two_claim(a, p, K, n_u, n_rows, epoch, dense, u, t);
+    }
+    const bool is_row = cand && rep == dense;
+    const unsigned long long m = __ballot(is_row);
+    if (lane == 0)
+        s_items[wave] = __popcll(m);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int total = 0;
+        for (int i = 0; i < kTwoWaves; ++i)
+            total += s_items[i];
+        s_base = total > 0 ? atomicAdd(counter, total) : 0;
+    }
+    __syncthreads();
+    int row = s_base + __popcll(m & ((1ull << lane) - 1ull));
+    for (int i = 0; i < wave; ++i)
+        row += s_items[i];
+    if (is_row && row >= 0 && row < 3 * a.count * (K + 1)) {  // (always, with a counter that started at 0)
+        p.it.node[row] = u;
+        p.it.t[row] = t;
+        p.mr_ci[dense] = row;
+    } else if (cand) {
+        p.mr_ci[dense] = -rep - 1;
+    }
+}
+
+__global__ void __launch_bounds__(kTwoThreads) k_two_lookup(StepArgs a, ModParams p, int K, uint32_t epoch, int n_refs)
+{
+    int n_u;
+    const int n_rows = two_rows(a, n_u), most = 3 * a.count * (K + 1);
+    if ((int)blockIdx.x < n_refs) {  // the references, a thread each
+        const int n = n_rows * (K + 1);
+        for (int i = (int)blockIdx.x * kTwoThreads + (int)threadIdx.x; i < n; i += n_refs * kTwoThreads) {
+            const int x = i / (K + 1), j = i - x * (K + 1), q = two_query_row(a, n_u, x);
+            if (j < K && j >= two_slots(a, K, q))
+                continue;
+            int c = p.mr_ci[i];
+            if (c < 0 && -c - 1 < n)
+                c = p.mr_ci[-c - 1];
+            c = c >= 0 && c < most ? c : 0;
+            if (j < K)
+                p.ref2[(size_t)q * K + j] = c;
+            else
+                p.self2[q] = c;
+        }
+        return;
+    }
+    int n = p.it.n_u[epoch & 1u];
+    n = n < 0 ? 0 : (n < most ? n : most);
+    const int step = ((int)gridDim.x - n_refs) * kTwoWaves;
+    for (int r = ((int)blockIdx.x - n_refs) * kTwoWaves + wave_id(); r < n; r += step) {
+        int32_t nbr, eid;
+        double ts;
+        (void)nbr_lookup_wave(a, K, p.it.node[r], p.it.t[r], -1, p.it, r, nbr, eid, ts);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// With node features: the attention embedding as contractions over all ITEMS of a layer at once (an item is a distinct
 // query or, in the first of two layers, neighbour j of a distinct query at the query's time): every
 // layer product is one k_rowgemm launch over the items instead of one pass over the weight matrices
 // per item (forty thousand workgroups streaming 0.7 MB each from L2 bounded the per-item kernel),
@@ -704,10 +860,30 @@ int final_lds(const ModDims &d)
 
 }  // namespace
 
+constexpr int kModLdsLimit = 160 * 1024;
+
+// The dimensions the second layer sees (embedding part): its input rows are E wide.
+static Dims second_layer_dims(const Dims &d)
+{
+    Dims o = d;
+    o.M = d.E;
+    o.da = o.M + o.T;
+    o.dh = o.da / o.H;
+    o.dkv = o.M + o.F + o.T;
+    o.dkvp = round_up(o.dkv, o.KB);
+    o.Mq = round_up(o.M, o.KB);
+    o.N1 = o.H * o.dkvp;
+    o.K2 = o.N1 + o.Mq;
+    return o;
+}
+
+bool two_layers_fused(const ModParams &p) { return p.fused_embed && p.layers == 2; }
+
 // Layout of the attached workspace: [vectors | transposed matrices | raw staging of one matrix |
 // node features].  Fills `p` when base != NULL.
 static size_t mod_layout(const Dims &d, int agg, int upd, int emb, int layers, bool node_feat, int64_t num_nodes, char *base,
-                         ModParams *p, float **raw_stage, float **nf_dst)
+                         ModParams *p, float **raw_stage, float **nf_dst, void **pack2 = nullptr, void **fold2 = nullptr,
+                         float **raw2 = nullptr)
 {
     size_t off = 0;
     auto take = [&](size_t count, size_t elem) -> void * {
@@ -722,11 +898,19 @@ static size_t mod_layout(const Dims &d, int agg, int upd, int emb, int layers, b
     q.upd = upd;
     q.emb = emb;
     q.layers = layers == 2 ? 2 : 1;
+    q.fused_embed = attn && !node_feat && q.layers == 1;
     q.time_w_rev = (const double *)take(T, 8);
     q.time_b_rev = (const double *)take(T, 8);
     size_t biggest = T;
+    const Dims d2 = second_layer_dims(d);
+    if (attn && !node_feat && q.layers == 2) {
+        q.d2 = d2;
+        q.mt[0] = layer_tiles(d, kModLdsLimit);
+        q.mt[1] = layer_tiles(d2, kModLdsLimit);
+        q.fused_embed = q.mt[0] > 0 && q.mt[1] > 0;
+    }
     if (attn) {
-        for (int l = 0; l < q.layers; ++l) {
+        for (int l = 0; l < q.layers && !q.fused_embed; ++l) {
             // layer l reads rows of width in_w: the state width, then the first layer's width
             const size_t in_w = l == 0 ? M : E, a_w = in_w + T, kv_w = in_w + d.F + T;
             AttnLayer &A = q.L[l];
@@ -744,7 +928,34 @@ static size_t mod_layout(const Dims &d, int agg, int upd, int emb, int layers, b
             A.N_m2 = (const float *)take(E * E, 4);
             biggest = kv_w * a_w > biggest ? kv_w * a_w : biggest;
         }
-        if (q.layers == 2) {
+        if (q.layers == 2 && q.fused_embed) {
+            const size_t R = (size_t)3 * d.max_batch, items = R * (d.K + 1);
+            QuerySet &it = q.it;
+            it.node = it.self_ref = (int32_t *)take(items, 4);  // (no batch is applied any more: a reference is the node)
+            it.t = (double *)take(items, 8);
+            it.cnt = (int32_t *)take(items, 4);
+            it.nbr = it.ref = (int32_t *)take(items * d.K, 4);
+            it.eid = (int32_t *)take(items * d.K, 4);
+            it.ts = (double *)take(items * d.K, 8);
+            it.n_u = (int32_t *)take(64, 4);  // two counters: a step's, by its epoch's parity, and the next one's
+            q.h1 = (float *)take(items * E, 4);
+            q.mr_ci = (int32_t *)take(items, 4);
+            q.ref2 = (int32_t *)take(R * d.K, 4);
+            q.self2 = (int32_t *)take(R, 4);
+            size_t slots = 1024;
+            while (slots < 2 * items)
+                slots *= 2;
+            q.claim = (unsigned long long *)take(slots, 8);
+            q.claim_mask = (uint32_t)(slots - 1);
+            void *packed = take(packed_weights_bytes(d2), 1);
+            void *fold = take(pack_scratch_bytes(d2), 1);
+            // the layer's weights as given, each padded to 64 floats
+            const size_t a2 = d2.da, raw = 2 * a2 * a2 + 2 * a2 * d2.dkv + E * (a2 + E) + 3 * E * E + 4 * a2 + 4 * E + 1 + 2 * T + 18 * 64;
+            float *as_given = (float *)take(raw, 4);
+            if (pack2)
+                *pack2 = packed, *fold2 = fold, *raw2 = as_given;
+            q.fused_embed = true;
+        } else if (q.layers == 2) {
             const size_t R2 = (size_t)3 * d.max_batch * d.K;  // rows of the second-hop tables
             q.hop2.node = (int32_t *)take(R2, 4);
             q.hop2.t = (double *)take(R2, 8);
@@ -760,7 +971,7 @@ static size_t mod_layout(const Dims &d, int agg, int upd, int emb, int layers, b
             q.mr_tab = (uint32_t *)take(slots, 4);
             q.mr_tab_mask = (uint32_t)(slots - 1);
         }
-        {   // the items' matrices: widths of the wider layer
+        if (!q.fused_embed) {  // the items' matrices: widths of the wider layer
             const size_t items = (size_t)3 * d.max_batch * (q.layers == 2 ? d.K + 1 : 1);
             const size_t in_w = q.layers == 2 && E > M ? E : M, a_w = in_w + T, kv_w = in_w + d.F + T;
             q.mr_qin = (float *)take(items * a_w, 4);
@@ -786,7 +997,6 @@ static size_t mod_layout(const Dims &d, int agg, int upd, int emb, int layers, b
     float *stage = (float *)take(biggest, 4);
     float *nf = node_feat ? (float *)take((size_t)num_nodes * M, 4) : nullptr;
     q.node_feat = nf;
-    q.fused_embed = attn && !node_feat && q.layers == 1;
     if (p)
         *p = q;
     if (raw_stage)
@@ -823,8 +1033,10 @@ hipError_t modules_attach(const Dims &d, const tig_modules &m, const tig_weights
 {
     ModParams p;
     float *stage = nullptr, *nf = nullptr;
+    void *packed2 = nullptr, *fold2 = nullptr;
+    float *raw2 = nullptr;
     mod_layout(d, m.aggregator, m.updater, m.embedding, m.num_layers, m.node_feat != nullptr, num_nodes, (char *)workspace, &p,
-               &stage, &nf);
+               &stage, &nf, &packed2, &fold2, &raw2);
     const ModDims md = mod_dims(d, p);
     const int M = d.M, T = d.T, E = d.E;
     hipError_t e;
@@ -852,7 +1064,7 @@ hipError_t modules_attach(const Dims &d, const tig_modules &m, const tig_weights
         return e
     MOD_TRY(rev(p.time_w_rev, w.time_w));
     MOD_TRY(rev(p.time_b_rev, w.time_b));
-    if (m.embedding == TIG_EMB_ATTENTION) {
+    if (m.embedding == TIG_EMB_ATTENTION && !p.fused_embed) {
         // the second layer's matrices have the first layer's roles with E-wide input rows
         tig_layer_weights first = {};
         first.W_Q = w.W_Q, first.b_Q = w.b_Q, first.W_K = w.W_K, first.b_K = w.b_K, first.W_V = w.W_V, first.b_V = w.b_V;
@@ -887,6 +1099,33 @@ hipError_t modules_attach(const Dims &d, const tig_modules &m, const tig_weights
     const int fin = final_lds(md) > kOneLds ? final_lds(md) : kOneLds;
     MOD_TRY(hipFuncSetAttribute((const void *)k_mod_final<true>, hipFuncAttributeMaxDynamicSharedMemorySize, fin));
     MOD_TRY(hipFuncSetAttribute((const void *)k_mod_final<false>, hipFuncAttributeMaxDynamicSharedMemorySize, fin));
+    if (two_layers_fused(p)) {
+        // the second layer's prepared weights: its matrices and the decoder's as given, through a device copy
+        float *at = raw2;
+        auto dev = [&](const float *src, size_t n) -> const float * {
+            float *dst = at;
+            at += align_up(n, 64);
+            if (e == hipSuccess)
+                e = vec(dst, src, n);
+            return dst;
+        };
+        const tig_layer_weights &l = *m.layer2;
+        const size_t da2 = p.d2.da, dkv2 = p.d2.dkv, E_ = E;
+        tig_weights w2 = {};
+        e = hipSuccess;
+        w2.W_Q = dev(l.W_Q, da2 * da2), w2.b_Q = dev(l.b_Q, da2), w2.W_K = dev(l.W_K, da2 * dkv2), w2.b_K = dev(l.b_K, da2);
+        w2.W_V = dev(l.W_V, da2 * dkv2), w2.b_V = dev(l.b_V, da2), w2.W_O = dev(l.W_O, da2 * da2), w2.b_O = dev(l.b_O, da2);
+        w2.W_m1 = dev(l.W_m1, E_ * (da2 + E_)), w2.b_m1 = dev(l.b_m1, E_), w2.W_m2 = dev(l.W_m2, E_ * E_), w2.b_m2 = dev(l.b_m2, E_);
+        w2.W_d1 = dev(w.W_d1, 2 * E_ * E_), w2.b_d1 = dev(w.b_d1, E_), w2.w_d2 = dev(w.w_d2, E_), w2.b_d2 = dev(w.b_d2, 1);
+        w2.time_w = dev(w.time_w, T), w2.time_b = dev(w.time_b, T);
+        if (e != hipSuccess)
+            return e;
+        MOD_TRY(launch_fill_zero(packed2, packed_weights_bytes(p.d2), s));
+        MOD_TRY(pack_weights(p.d2, w2, packed2, fold2, &p.pw2, s, kPackEmbed));
+        MOD_TRY(clear_two_layers(p, s));
+        MOD_TRY(prepare_embed_layer(d, p.mt[0]));
+        MOD_TRY(prepare_embed_layer(p.d2, p.mt[1]));
+    }
 #undef MOD_TRY
     *out = p;
     return hipStreamSynchronize(s);
@@ -1027,6 +1266,59 @@ hipError_t launch_modules(const Dims &d, const LaunchPlan &plan, const PackedWei
     hipLaunchKernelGGL(k_mod_final<false>, dim3(side + fp.n_commit + n_events), dim3(kFinThreads), fin_lds, s, a, md, p, pw, fp);
     *launches += 1;
     return hipGetLastError();
+}
+
+hipError_t clear_two_layers(const ModParams &p, hipStream_t s)
+{
+    const hipError_t e = launch_fill_zero(p.it.n_u, 64 * 4, s);
+    return e != hipSuccess ? e : launch_fill_zero(p.claim, ((size_t)p.claim_mask + 1) * 8, s);
+}
+
+hipError_t launch_two_layers(const Dims &d, int num_cus, const PackedWeights &pw, const StepArgs &a, const ModParams &p, uint32_t epoch,
+                             const int32_t *seen, hipStream_t s, int *launches)
+{
+    const int B = a.count, K = d.K;
+    const int rows = a.roles * B, cus = num_cus > 0 ? num_cus : 256;
+    // a wavefront of the overwrite takes about four winners, at the winner count recent steps had
+    const int most = 2 * a.msg_count;
+    const int wins = a.wins_est > 0 && a.wins_est < most ? a.wins_est : most;
+    const int n_commit = (wins + 4 * kTwoWaves - 1) / (4 * kTwoWaves);
+    const int n_neg = a.roles == 3 ? (B + kTwoWaves - 1) / kTwoWaves : 0;
+    if (n_commit + n_neg > 0)
+        hipLaunchKernelGGL(k_two_negatives, dim3(n_commit + n_neg), dim3(kTwoThreads), 0, s, a, d.M, K, n_commit);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(k_two_claim, dim3((rows + kTwoWaves - 1) / kTwoWaves), dim3(kTwoThreads), 0, s, a, p, K, epoch);
+    if ((e = hipGetLastError()) != hipSuccess)
+        return e;
+    const int n_refs = cus / 4 > 0 ? cus / 4 : 1;
+    hipLaunchKernelGGL(k_two_lookup, dim3(n_refs + 3 * cus), dim3(kTwoThreads), 0, s, a, p, K, epoch, n_refs);
+    if ((e = hipGetLastError()) != hipSuccess)
+        return e;
+    // the first layer reads the memory as overwritten; the next batch's preparation runs beside it
+    const int items = rows * (K + 1);
+    StepArgs one = a;
+    one.msg_count = 0;
+    one.qs = p.it;
+    one.qs.n_u = p.it.n_u + (epoch & 1u);
+    one.count = (items + 1) / 2;
+    one.roles = 2;
+    one.emb_u = p.h1;
+    one.dec_a = one.dec_b = nullptr;
+    if ((e = launch_embed_layer(d, p.mt[0], num_cus, pw, one, s)) != hipSuccess)
+        return e;
+    StepArgs two = a;
+    two.msg_count = 0;
+    two.mem = p.h1;
+    two.num_nodes = items;
+    two.qs.ref = p.ref2;
+    two.qs.self_ref = p.self2;
+    two.sel.count = two.ded.count = 0;
+    const int n = seen ? ((const volatile int32_t *)seen)[2] : 0;
+    two.rows_est = n > 0 ? n + n / 8 : 0;
+    *launches += 3 + (n_commit + n_neg > 0 ? 1 : 0);  // (beyond embedding and closing launch)
+    return launch_embed_layer(p.d2, p.mt[1], num_cus, p.pw2, two, s);
 }
 
 }  // namespace tig

@@ -94,6 +94,17 @@ hipError_t launch_step(const Dims &d, const LaunchPlan &plan, const PackedWeight
             return e;
         return stamp();
     }
+    if (sp.mods && two_layers_fused(*sp.mods)) {
+        PackedWeights last = sp.mods->pw2;  // (the closing launch: the state update's weights and the decoder's)
+        last.gru_Wr = pw.gru_Wr, last.gru_Wz = pw.gru_Wz, last.gru_Win = pw.gru_Win, last.gru_Whn = pw.gru_Whn;
+        last.gru_br = pw.gru_br, last.gru_bz = pw.gru_bz, last.gru_bin = pw.gru_bin, last.gru_bhn = pw.gru_bhn;
+        if (sp.mod_clear && (e = clear_two_layers(*sp.mods, s)) != hipSuccess)
+            return e;
+        if ((e = launch_two_layers(d, plan.num_cus, pw, a, *sp.mods, sp.mod_epoch, sp.seen, s, sp.mod_launches)) != hipSuccess ||
+            (e = stamp()) != hipSuccess || (e = launch_closing(d, plan, last, a, sp.ahead, s)) != hipSuccess)
+            return e;
+        return stamp();
+    }
     if ((e = launch_embed(d, plan, pw, a, s)) != hipSuccess || (e = stamp()) != hipSuccess)
         return e;
     if ((e = launch_closing(d, plan, pw, a, sp.ahead, s)) != hipSuccess || (e = stamp()) != hipSuccess)

@@ -92,6 +92,8 @@ struct tig_ctx {
     bool has_model;        // tig_init was given weights (the headline instance's prepared weights exist)
     void *mods_ws;         // workspace of an attached module selection, or NULL
     ModParams mods;        // ... and its parameters
+    uint32_t mod_epoch;  // epoch of the latest step of two fused layers
+    bool mod_clean;      // its claims and counters are as that step left them
     // Two pinned host words that the device can write: every step leaves its numbers of distinct
     // query rows and of winners there, and later calls shape their launches by them (hints that
     // may be a few steps old; results do not depend on them).  NULL if the allocation failed.
@@ -794,6 +796,13 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
     if (general) {
         sp.mods = &ctx->mods;
         sp.mod_launches = &launches;
+        sp.seen = ctx->rows_seen_host;
+        if (two_layers_fused(ctx->mods)) {
+            sp.mod_clear = !ctx->mod_clean || ctx->mod_epoch == 0xFFFFFFFFu;
+            ctx->mod_epoch = sp.mod_clear ? 1u : ctx->mod_epoch + 1u;
+            sp.mod_epoch = ctx->mod_epoch;
+            ctx->mod_clean = false;  // (until the step's launches are made)
+        }
         launches += mean && a.msg_count > 0 ? 2 : 0;
     }
     if (sp.big_sel)
@@ -861,6 +870,7 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
         train_step_args(d, ctx->train_ws, &a);
     }
     const hipError_t e = launch_step(d, ctx->plan, ctx->pw, a, sp, ctx->stream, marks);
+    ctx->mod_clean = e == hipSuccess;
     // bit i: the interval between marks i and i + 1 held a kernel (a module selection's kernels fill
     // intervals 3 and 4)
     ctx->last_ran = (sp.big_sel ? 3u : 0u) | ((sp.prep_sel || sp.prep_ded) ? 4u : 0u) |
@@ -1089,6 +1099,7 @@ int tig_modules_attach(tig_ctx *ctx, const tig_modules *modules, const tig_weigh
         return fail(ctx, TIG_EHIP, "tig_modules_attach", e);
     ctx->mods = mp;
     ctx->mods_ws = workspace;
+    ctx->mod_clean = false;
     // nothing prepared by earlier steps of another model is trusted
     ctx->ahead_g_valid = false;
     ctx->ahead_w_valid = false;

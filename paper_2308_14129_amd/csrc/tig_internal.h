@@ -220,10 +220,12 @@ hipError_t pack_weights(const Dims &d, const tig_weights &w_dev_f32, void *dst, 
                         PackedWeights *pw, hipStream_t s, int parts = kPackAll);
 
 bool plan_launch(const Dims &d, int lds_limit, LaunchPlan *plan);
+int layer_tiles(const Dims &d, int lds_limit);
 int gru_lds_bytes(const Dims &d);
 int embed_lds_bytes(const Dims &d, int mt);
 hipError_t prepare_gru(const Dims &d, const LaunchPlan &plan);
 hipError_t prepare_embed(const Dims &d, const LaunchPlan &plan, bool train = false);
+hipError_t prepare_embed_layer(const Dims &d, int most_mt);
 hipError_t prepare_small();
 bool winners_in_one_launch(int count);
 // batches above the one-workgroup limit: keys to the per-node array, then winners + flags
@@ -248,6 +250,7 @@ hipError_t launch_gru(const Dims &d, const LaunchPlan &plan, const PackedWeights
 // selection and query preparation for the batch expected next
 hipError_t launch_embed(const Dims &d, const LaunchPlan &plan, const PackedWeights &pw, const StepArgs &a,
                         hipStream_t s);
+hipError_t launch_embed_layer(const Dims &d, int most_mt, int num_cus, const PackedWeights &pw, const StepArgs &a, hipStream_t s);
 // scores and per-query embeddings from the distinct rows, optional inspection outputs, finishing pass
 // of the batch prepared ahead, GRU of the batch the next step applies
 hipError_t launch_closing(const Dims &d, const LaunchPlan &plan, const PackedWeights &pw, const StepArgs &a,
@@ -279,6 +282,9 @@ struct StepPlan {
     GruAhead ahead;             // GRU workgroups of the closing launch
     const struct ModParams *mods;  // a context with a module selection, or NULL
     int *mod_launches;             // ... where launch_modules adds its launches
+    uint32_t mod_epoch;            // two fused layers: the step's epoch
+    bool mod_clear;                // ... and whether claims and counters have to be cleared first
+    const int32_t *seen;           // the context's hint words (host), or NULL
 };
 // does the step copy neighbour lists or winner flags out
 inline bool wants_inspection(const StepArgs &a)
@@ -342,6 +348,14 @@ struct ModParams {
     const float *node_feat;                    // [N x M] or NULL
     const float *time_proj_w;                  // [M] or NULL
     bool fused_embed;                          // attention without node features: the fused embedding / closing launches run it
+    // two layers as fused launches (fused_embed; the second layer's rows fit its tiles)
+    Dims d2;                                   // dimensions the second layer sees: its input rows are E wide
+    int mt[2];                                 // most 16-row tiles per workgroup of either layer
+    PackedWeights pw2;                         // the second layer's prepared weights, the decoder folded with them
+    QuerySet it;                               // the first layer's rows: every distinct (node, time) of the queries and their neighbours
+    int32_t *ref2, *self2;                     // references of the query set's rows into the first layer's rows
+    unsigned long long *claim;                 // claims of equal pairs: epoch << 32 | (x, j) index
+    uint32_t claim_mask;
     double *acc;                               // mean aggregator: [2 * max_batch x kAccCopies x (M + T + F)] message sums by winning entry, zero between steps
     int32_t *acc_cnt;                          // ... and the number of messages in each
     float *mean_msg;                           // ... and the means, [2 * max_batch x (M + T + F)] by winning entry
@@ -350,6 +364,11 @@ size_t modules_workspace_bytes(const Dims &d, const tig_modules &m, int64_t num_
 bool modules_supported(const Dims &d, const tig_modules &m);
 hipError_t modules_attach(const Dims &d, const tig_modules &m, const tig_weights &w, int64_t num_nodes, void *workspace,
                           ModParams *out, hipStream_t s);
+bool two_layers_fused(const ModParams &p);
+hipError_t clear_two_layers(const ModParams &p, hipStream_t s);
+// embedding rows of two stacked layers (memory overwrite first); `epoch`: new for every call, never 0
+hipError_t launch_two_layers(const Dims &d, int num_cus, const PackedWeights &pw, const StepArgs &a, const ModParams &p, uint32_t epoch,
+                             const int32_t *seen, hipStream_t s, int *launches);
 hipError_t launch_mean_messages(const Dims &d, const StepArgs &a, const ModParams &p, hipStream_t s);
 // everything after the state update of a step of a context with a module selection that the fused launches
 // do not cover; adds the launches it made to *launches

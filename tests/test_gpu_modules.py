@@ -199,6 +199,35 @@ def test_c1_two_layers_deferred_order():
     c.close()
 
 
+@pytest.mark.parametrize("order", ["update_first", "deferred"])
+@pytest.mark.parametrize("name,dims,batch", [
+    ("headline", dict(), 1),                                              # one event: fewer rows than a tile
+    ("last_rnn_attention", dict(mem_dim=33, time_dim=15, emb_dim=49, feat_dim=5, num_neighbors=7), 137),
+    ("mean_gru_attention", dict(num_heads=1, mem_dim=65, emb_dim=31), 1000),
+    ("headline", dict(num_heads=4, num_neighbors=15, emb_dim=64), 999),   # rows of both layers beyond one pass of the grid
+    # the second layer's rows do not fit the embedding kernel's tiles: products over all rows instead
+    ("headline", dict(num_heads=4, mem_dim=16, time_dim=100, feat_dim=160, emb_dim=252), 50)])
+def test_two_layers_that_prepare_each_other(name, dims, batch, order):
+    """Without inspection outputs the winners, queries and (but for the mean) staged rows come from the step before;
+    a gap in the stream, row widths around the tiles' edges, a step without negatives at the end."""
+    c = Case(S.WORKLOADS["c1_tiny"].scaled(**dims), INSTANCES[name], False, order=order, max_batch=batch, layers=2)
+    st = O.OracleState.zeros(c.g.num_nodes, c.w.mem_dim)
+    c.ctx.reset()
+    for n, first in enumerate([0, batch, 2 * batch, 3 * batch + 50, 4 * batch + 50]):
+        print(f"two layers {name} {dims} first={first} count={batch}", flush=True)
+        neg = S.make_negatives(c.w, c.g, first, batch) if n < 4 else None
+        ref = G.step(st, c.g.src, c.g.dst, c.g.ts, c.g.edge_feat, c.W, first, batch, neg, c.w.num_neighbors, c.w.num_heads,
+                     c.mods, index=c.ix, deferred=c.deferred)
+        out = c.ctx.alloc_outputs(batch, with_neg=n < 4)
+        c.ctx.step(first, batch, c.torch.from_numpy(neg).to("cuda:0") if n < 4 else None, out)
+        for k in ("emb", "score_pos", "score_neg")[:3 if n < 4 else 2]:
+            gate(getattr(out, k).cpu().numpy(), ref[k], TOL, k)
+    mem, lu = c.ctx.state_export()
+    np.testing.assert_array_equal(lu, st.last_update)
+    gate(mem, st.mem, TOL, "mem")
+    c.close()
+
+
 def test_c2_two_layers_wide_rows_emb_narrower_than_memory():
     """E = 100 != M = 172: the second layer's rows have a width of their own."""
     w = S.WORKLOADS["c2_bipartite_medium"]
