@@ -135,7 +135,7 @@ __device__ inline float wave_max_uniform(float v)
 constexpr int kBackThreads = 512;
 template <int NPL, int H>
 struct BackShape {
-    static constexpr int KC = NPL >= 8 && H >= 4 ? 6 : 10;  // neighbour rows in registers at a time
+    static constexpr int KC = NPL >= 6 && H >= 4 ? 6 : 10;  // neighbour rows in registers at a time
 };
 
 // acc[j] += A[16 mt ..][k-blocks a_kb0 .. + n) x W[nt[j]]^T over W's k-blocks [w_kb0, w_kb0 + n), for NT output tiles
@@ -740,10 +740,12 @@ BackParams back_params(const Dims &d, int mt, int lds_limit, int *lds)
 
 constexpr int kBackLds = 160 * 1024;
 
+// 64-column pieces of a row the kernel is compiled for.  Above four, one too many costs: at 444 columns and two heads
+// eight pieces spilled 69 registers, seven spill 31; six pieces fit.
 int back_npl(const Dims &d)
 {
     const int need = (d.dkvp + 63) / 64;
-    return need <= 2 ? 2 : (need <= 4 ? 4 : 8);
+    return need <= 2 ? 2 : (need <= 4 ? 4 : (need <= 6 ? 6 : need));
 }
 
 template <int MT, int NPL, int NPHI>
@@ -761,6 +763,8 @@ const void *pick_back(const Dims &d)
     switch (back_npl(d)) {
     case 2: return pick_back_h<MT, 2, 2>(d.H);
     case 4: return few ? pick_back_h<MT, 4, 2>(d.H) : pick_back_h<MT, 4, 4>(d.H);
+    case 6: return few ? pick_back_h<MT, 6, 2>(d.H) : pick_back_h<MT, 8, 8>(d.H);
+    case 7: return few ? pick_back_h<MT, 7, 2>(d.H) : pick_back_h<MT, 8, 8>(d.H);
     default: return few ? pick_back_h<MT, 8, 2>(d.H) : pick_back_h<MT, 8, 8>(d.H);
     }
 }
