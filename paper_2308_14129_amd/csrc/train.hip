@@ -894,7 +894,10 @@ hipError_t train_attach(const Dims &d, const tig_weights &w, void *workspace, vo
     hipLaunchKernelGGL(k_tr_phi0, dim3((d.T + 255) / 256), dim3(256), 0, s, L.w.time_b, L.phi0, d.T);
     if (e == hipSuccess)
         e = hipGetLastError();
-    return e == hipSuccess ? fold_weights(d, L, *pw, s) : e;
+    // (single precision, for the backward pass's copies; the forward pass and ordinary steps start from foldings in double)
+    if (e == hipSuccess)
+        e = fold_weights(d, L, *pw, s);
+    return e == hipSuccess ? pack_weights(d, L.w, packed, L.pack_scratch, pw, s, kPackEmbed) : e;
 }
 
 // The masters (or gradients) lie in one range: through a pinned buffer to host destinations in pieces (one
