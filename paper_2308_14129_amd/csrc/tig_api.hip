@@ -565,14 +565,13 @@ int tig_init(const tig_config *cfg, const tig_graph *graph, const tig_weights *w
         INIT_TRY(hipMemcpyAsync(L.edge_feat, graph->edge_feat, sizeof(float) * (size_t)E * d.F,
                                 hipMemcpyDefault, s), "copy edge_feat");
     }
-    // validation on the device; the adjacency and the prepared weights do not wait for its verdict (their
-    // kernels stay inside their arrays whatever the ids are)
+    // validation on the device, with the adjacency; nothing waits for its verdict (the kernels stay inside their
+    // arrays whatever the ids are)
     int32_t *flags = (int32_t *)scratch;
     INIT_TRY(launch_fill_zero(flags, 256, s), "clear flags");
-    INIT_TRY(launch_validate_graph(L.src, L.dst, L.ts, E, N, flags, s), "validate");
 
     // temporal adjacency
-    INIT_TRY(csr_build(L.src, L.dst, L.ts, E, N, L.indptr, L.csr, L.pos, (char *)scratch + init_sort_offset(d),
+    INIT_TRY(csr_build(L.src, L.dst, L.ts, E, N, L.indptr, L.csr, L.pos, flags, (char *)scratch + init_sort_offset(d),
                        scratch_bytes - init_sort_offset(d), s), "adjacency build");
 
     // weights: raw fp32 copies (while the device builds the adjacency), then fold / pad / reorder

@@ -199,12 +199,11 @@ struct LaunchPlan {
 };
 
 // ---- launchers (each returns the hipError_t of the launch) -------------------------------
-hipError_t launch_validate_graph(const int32_t *src, const int32_t *dst, const double *ts,
-                                 int64_t num_events, int64_t num_nodes, int32_t *flags,
-                                 hipStream_t s);
+// adjacency and, along the way, validation of the graph (flags[0..2], cleared by the caller: id out of range, times not
+// sorted, self-loop; nothing leaves its array whatever the ids are)
 size_t csr_build_scratch_bytes(int64_t num_events, int64_t num_nodes);
 hipError_t csr_build(const int32_t *src, const int32_t *dst, const double *ts, int64_t num_events,
-                     int64_t num_nodes, int64_t *indptr, CsrEntry *csr, int32_t *pos, void *scratch,
+                     int64_t num_nodes, int64_t *indptr, CsrEntry *csr, int32_t *pos, int32_t *flags, void *scratch,
                      size_t scratch_bytes, hipStream_t s);
 
 size_t pack_scratch_bytes(const Dims &d);
