@@ -91,12 +91,64 @@ constexpr int regs_touching(int lo, int hi, int dims)
     return m;
 }
 
-// one tile of ROWS query rows: rows pass, pass + n_passes, ...
+static_assert(sizeof(StepArgs) % alignof(PackedWeights) == 0 && (sizeof(StepArgs) + sizeof(PackedWeights)) % alignof(EmbedParams) == 0,
+              "the kernel's arguments follow each other without gaps");
+
 template <int PREC, int MODE, int MT, int NPL, int H, int SHAPE>
-__device__ inline __attribute__((always_inline)) void embed_rows(const StepArgs &a, const PackedWeights &w, const EmbedParams &p, char *smem, int pass, int n_passes,
-                                                                int n_u, int n_rows)
+__global__ void __launch_bounds__((EmbedShape<NPL, H>::kThreads))
+k_embed(StepArgs a_, PackedWeights w_, EmbedParams p_)
 {
     constexpr bool TRAIN = MODE == kEmbedTrain, LAYER = MODE == kEmbedLayer;
+    constexpr int kEmbedThreads = EmbedShape<NPL, H>::kThreads;
+    constexpr int kEmbedWaves = EmbedShape<NPL, H>::kWaves;
+    constexpr int ROWS = 16 * MT;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    if ((int)blockIdx.x >= p_.n_tiles) {
+        int x = (int)blockIdx.x - p_.n_tiles;
+        if (x < p_.n_commit) {
+            overwrite_memory(a_, p_.M, x * kEmbedWaves + wave_id(), p_.n_commit * kEmbedWaves);
+            return;
+        }
+        x -= p_.n_commit;
+        // The workgroups beyond, on compute units this launch leaves idle (launched only with
+        // 1024 threads): last-message selection and query preparation for a later step.
+        if constexpr (kEmbedThreads == kScatterThreads) {
+            TIG_MARK(0);
+            if (x == 0 && threadIdx.x == 0 && a_.rows_seen) {
+                // hints for the host (stores to its memory take a while: from a workgroup that ends
+                // long before the launch does)
+                a_.rows_seen[0] = *a_.qs.n_u + (a_.roles == 3 ? a_.count : 0);  // (a hint: not clamped)
+                if (a_.msg_count > 0)
+                    a_.rows_seen[1] = *a_.n_win;
+            }
+            if (a_.sel.count > 0) {
+                if (x == 0) {
+                    winners_block(a_, a_.sel, smem);
+                    TIG_MARK(7);
+                    return;
+                }
+                --x;
+            }
+            if (a_.ded.count > 0 && x < a_.ded.n_wgs)
+                dedup_block(a_, a_.ded, p_.K, x, smem);
+            TIG_MARK(7);
+        }
+        return;
+    }
+    int pass = (int)blockIdx.x;
+next_tile:
+    // LAYER: the arguments are read again for every tile, from a pointer that the compiler cannot see through: what it
+    // takes out of the loop otherwise (every address that does not depend on the tile) needs 250 registers and
+    // 824 bytes of scratch per lane (105 us for the first layer of 4000 events, 46 this way).
+    typedef const __attribute__((address_space(4))) char *Args;
+    Args at = nullptr;
+    if constexpr (LAYER) {
+        at = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(at));
+    }
+    const StepArgs &a = LAYER ? *(const StepArgs *)at : a_;
+    const PackedWeights &w = LAYER ? *(const PackedWeights *)(at + sizeof(StepArgs)) : w_;
+    const EmbedParams &p = LAYER ? *(const EmbedParams *)(at + sizeof(StepArgs) + sizeof(PackedWeights)) : p_;
     using P = Prec<PREC>;
     using SH = RowShape<SHAPE>;
     // segment sizes and segment-to-register maps of a key/value row, as phase C uses them
@@ -107,9 +159,6 @@ __device__ inline __attribute__((always_inline)) void embed_rows(const StepArgs 
     const int mem_regs = SH::kFixed ? regs_touching(SH::T, SH::T + SH::M, kWave * NPL) : p.mem_regs;
     const int feat_regs =
         SH::kFixed ? regs_touching(SH::T + SH::M, SH::T + SH::M + SH::F, kWave * NPL) : p.feat_regs;
-    constexpr int kEmbedThreads = EmbedShape<NPL, H>::kThreads;
-    constexpr int kEmbedWaves = EmbedShape<NPL, H>::kWaves;
-    constexpr int ROWS = 16 * MT;
     constexpr int KC = NPL >= 8 ? 5 : (NPL == 4 ? 10 : 16);      // neighbour rows in flight
     constexpr int NPHI = NPL;  // registers that may hold time-encoding dims (T <= 64 * NPL)
     char *rowbuf = smem;
@@ -125,7 +174,13 @@ __device__ inline __attribute__((always_inline)) void embed_rows(const StepArgs 
     const int lane = lane_id();
     const int wave = wave_id();
     const int mem_off = 4 * p.N1;
-    const int neg_row0 = 2 * a.count;  // (the negatives' rows of the set)
+    int n_u = *a.qs.n_u;  // distinct source / destination queries; the negatives' rows follow at 2 * count
+    n_u = n_u < 2 * a.count ? n_u : 2 * a.count;
+    const int neg_row0 = 2 * a.count;
+    const int n_rows = n_u + (a.roles == 3 ? a.count : 0);
+    const int n_passes = (n_rows + ROWS - 1) / ROWS;
+    if (pass >= n_passes)
+        return;  // fewer distinct queries than the grid was sized for
     // a row reference that is neither a memory row nor a staged row of the applied batch reads as none
     auto checked_ref = [&](int32_t ref) -> int32_t {
         const bool ok = ref >= 0 ? (int64_t)ref < a.num_nodes : (ref != kRefNone && ~ref < 2 * a.msg_count);
@@ -799,71 +854,10 @@ __device__ inline __attribute__((always_inline)) void embed_rows(const StepArgs 
         }
     }
     TIG_MARK(5);
-}
-
-static_assert(sizeof(StepArgs) % alignof(PackedWeights) == 0 && (sizeof(StepArgs) + sizeof(PackedWeights)) % alignof(EmbedParams) == 0,
-              "the kernel's arguments follow each other without gaps");
-
-template <int PREC, int MODE, int MT, int NPL, int H, int SHAPE>
-__global__ void __launch_bounds__((EmbedShape<NPL, H>::kThreads))
-k_embed(StepArgs a, PackedWeights w, EmbedParams p)
-{
-    constexpr int kEmbedThreads = EmbedShape<NPL, H>::kThreads;
-    constexpr int kEmbedWaves = EmbedShape<NPL, H>::kWaves;
-    constexpr int ROWS = 16 * MT;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    if ((int)blockIdx.x >= p.n_tiles) {
-        int x = (int)blockIdx.x - p.n_tiles;
-        if (x < p.n_commit) {
-            overwrite_memory(a, p.M, x * kEmbedWaves + wave_id(), p.n_commit * kEmbedWaves);
-            return;
-        }
-        x -= p.n_commit;
-        // The workgroups beyond, on compute units this launch leaves idle (launched only with
-        // 1024 threads): last-message selection and query preparation for a later step.
-        if constexpr (kEmbedThreads == kScatterThreads) {
-            TIG_MARK(0);
-            if (x == 0 && threadIdx.x == 0 && a.rows_seen) {
-                // hints for the host (stores to its memory take a while: from a workgroup that ends
-                // long before the launch does)
-                a.rows_seen[0] = *a.qs.n_u + (a.roles == 3 ? a.count : 0);  // (a hint: not clamped)
-                if (a.msg_count > 0)
-                    a.rows_seen[1] = *a.n_win;
-            }
-            if (a.sel.count > 0) {
-                if (x == 0) {
-                    winners_block(a, a.sel, smem);
-                    TIG_MARK(7);
-                    return;
-                }
-                --x;
-            }
-            if (a.ded.count > 0 && x < a.ded.n_wgs)
-                dedup_block(a, a.ded, p.K, x, smem);
-            TIG_MARK(7);
-        }
-        return;
-    }
-    int n_u = *a.qs.n_u;  // distinct source / destination queries; the negatives' rows follow at 2 * count
-    n_u = n_u < 2 * a.count ? n_u : 2 * a.count;
-    const int n_rows = n_u + (a.roles == 3 ? a.count : 0);
-    const int n_passes = (n_rows + ROWS - 1) / ROWS;
-    if constexpr (MODE == kEmbedLayer) {
-        for (int pass = (int)blockIdx.x; pass < n_passes; pass += p.n_tiles) {
-            // The arguments are read again for every tile, from a pointer that the compiler cannot see through: what it
-            // takes out of the loop otherwise (every address that does not depend on the tile) needs 250 registers
-            // and 824 bytes of scratch per lane (105 us for the first layer of 4000 events).
-            typedef const __attribute__((address_space(4))) char *Args;
-            Args at = (Args)__builtin_amdgcn_kernarg_segment_ptr();
-            asm volatile("" : "+s"(at));
-            const StepArgs &ta = *(const StepArgs *)at;
-            const PackedWeights &tw = *(const PackedWeights *)(at + sizeof(StepArgs));
-            const EmbedParams &tp = *(const EmbedParams *)(at + sizeof(StepArgs) + sizeof(PackedWeights));
-            embed_rows<PREC, MODE, MT, NPL, H, SHAPE>(ta, tw, tp, smem, pass, n_passes, n_u, n_rows);
-            __syncthreads();  // (the next tile's rows take this one's place in LDS)
-        }
-    } else if ((int)blockIdx.x < n_passes) {  // (there may be fewer distinct queries than the grid was sized for)
-        embed_rows<PREC, MODE, MT, NPL, H, SHAPE>(a, w, p, smem, (int)blockIdx.x, n_passes, n_u, n_rows);
+    if constexpr (LAYER) {
+        pass += p.n_tiles;
+        __syncthreads();  // (the next tile's rows take this one's place in LDS)
+        goto next_tile;
     }
 }
 
