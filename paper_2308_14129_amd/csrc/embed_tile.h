@@ -99,6 +99,9 @@ __global__ void __launch_bounds__((EmbedShape<NPL, H>::kThreads))
 k_embed(StepArgs a_, PackedWeights w_, EmbedParams p_)
 {
     constexpr bool TRAIN = MODE == kEmbedTrain, LAYER = MODE == kEmbedLayer;
+    // A training step evaluates the softmax as k_tr_back does, with expf and a division; an ordinary step with the
+    // hardware's exponential and reciprocal.
+    const auto soft_exp = [](float x) -> float { return TRAIN ? expf(x) : __expf(x); };
     constexpr int kEmbedThreads = EmbedShape<NPL, H>::kThreads;
     constexpr int kEmbedWaves = EmbedShape<NPL, H>::kWaves;
     constexpr int ROWS = 16 * MT;
@@ -642,7 +645,7 @@ next_tile:
                         max_row_bcast15(m);  // rows 1 and 3 now hold the maximum of their head
                         const float m0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), 31));
                         const float m1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(m), 63));
-                        const float e = __expf(S[h / 2] - (lane < 32 ? m0 : m1));
+                        const float e = soft_exp(S[h / 2] - (lane < 32 ? m0 : m1));
                         float sum = row_sum_all(e);
                         add_row_bcast15(sum);
                         den[h] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sum), 31));
@@ -670,7 +673,7 @@ next_tile:
                         mnew = fmaxf(mnew, sc[kk][h]);
                     float dsum = 0.0f;
                     if constexpr (!FULL) {
-                        const float corr = __expf(mx[h] - mnew);  // first chunk: exp(-inf) = 0
+                        const float corr = soft_exp(mx[h] - mnew);  // first chunk: exp(-inf) = 0
                         dsum = den[h] * corr;
 #pragma unroll
                         for (int n = 0; n < NPL; ++n)
@@ -679,7 +682,7 @@ next_tile:
 #pragma unroll
                     for (int kk = 0; kk < KC; ++kk) {
                         if (FULL || c0 + kk < cnt) {  // scalar
-                            const float pk = __expf(sc[kk][h] - mnew);
+                            const float pk = soft_exp(sc[kk][h] - mnew);
                             dsum += pk;
 #pragma unroll
                             for (int n = 0; n < NPL; ++n)
@@ -699,7 +702,8 @@ next_tile:
             // kvbar overwrites q~ in place (as matrix-core operand elements)
 #pragma unroll
             for (int h = 0; h < H; ++h) {
-                const float inv = cnt > 0 ? __builtin_amdgcn_rcpf(den[h]) : 0.0f;  // den >= 1; 1 ulp
+                // (den >= 1; the hardware's reciprocal is within 1 ulp)
+                const float inv = cnt == 0 ? 0.0f : TRAIN ? 1.0f / den[h] : __builtin_amdgcn_rcpf(den[h]);
 #pragma unroll
                 for (int n = 0; n < NPL; ++n) {
                     const int j = lane + kWave * n;
@@ -760,7 +764,7 @@ next_tile:
                 }
                 const int kb0 = my_ks * kb_half;
                 const int nkb = (kbT - kb0) < kb_half ? (kbT - kb0) : kb_half;
-                tile_gemm<PREC, MT, (MT <= 2 ? 5 : 4)>(acc, rowbuf, p.row_bytes, kb0, w.emb_PR, kbT, kb0, nkb, my_nt);
+                tile_gemm<PREC, MT, (MT <= 2 ? 5 : 4), TRAIN>(acc, rowbuf, p.row_bytes, kb0, w.emb_PR, kbT, kb0, nkb, my_nt);
             }
             if (ksplit == 2) {
                 if (on && my_ks == 1) {

@@ -20,7 +20,7 @@ struct TrainArrays {
     // per applied winner r, and per entry of the applied batch
     float *MSG, *GATES, *DGI, *DGH, *D_STAG;
     // sums over rows, added up with atomics and cleared by the update that reads them
-    float *TACC;                        // [2T] time-encoding gradients [frequencies | phases]
+    double *TACC;                       // [2T] time-encoding gradients [frequencies | phases]
     float *WACC;                        // [E + 1] gradients of w_d2, b_d2
     // transposed weights, prepared like the forward kernels' (lane-ordered, padded with zeros)
     float *Wd1T;                        // [Ep x 2Ek]   W_d1[k][n], W_d1[k][E + n]

@@ -35,32 +35,46 @@ namespace {
 // change, and the vector unit has nothing to do beside the products (with an address per lane and 4-byte loads the
 // instructions for these were what bound these kernels).  Rows and columns beyond a matrix may read any element
 // in bounds; they reach results that nobody stores.
-// sum[i]: the sums of a's values, per lane.
+// sum[i]: the sums of a's values, per lane.  Products are summed sixteen rows at a time and those sums added up (in one
+// chain over a wavefront's 150 rows gradients were up to 1.6 times as far from 64 bits as in the step in direct form;
+// in parts, with the column sums in double, they are below it everywhere).
 template <int N>
 struct __attribute__((packed, aligned(4))) Floats {
     float v[N];
 };
 
-template <int MI>
+template <int MI, int kU>  // kU: k-steps of 4 whose loads are issued together
 __device__ inline void multiply(const float *A, const float *B, int sa, int sb, int ao, int bo, int n, floatx4 (&acc)[MI][2],
-                                float (&sum)[MI])
+                                double (&sum)[MI])
 {
-    constexpr int kU = 8;  // k-steps of 4 whose loads are issued together
+    constexpr int kPart = 4;  // k-steps whose products are summed on their own
     const int g = lane_id() >> 4;
     using VA = Floats<MI>;
     using VB = Floats<2>;
     auto products = [&](VA (&av)[kU], VB (&bv)[kU], int k) {
 #pragma unroll
-        for (int u = 0; u < kU; ++u)
-            if (k + 4 * u < n) {  // (uniform)
+        for (int u0 = 0; u0 < kU; u0 += kPart) {
+            floatx4 part[MI][2] = {};
+            float ps[MI] = {};
 #pragma unroll
-                for (int i = 0; i < MI; ++i) {
-                    sum[i] += av[u].v[i];
+            for (int u = u0; u < u0 + kPart; ++u)
+                if (k + 4 * u < n) {  // (uniform)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u].v[i], bv[u].v[j], acc[i][j], 0, 0, 0);
+                    for (int i = 0; i < MI; ++i) {
+                        ps[i] += av[u].v[i];
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u].v[i], bv[u].v[j], part[i][j], 0, 0, 0);
+                    }
                 }
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                sum[i] += (double)ps[i];
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    acc[i][j] += part[i][j];
             }
+        }
     };
     int k = 0;
     for (; k + 4 * kU <= n; k += 4 * kU) {
@@ -99,6 +113,7 @@ __device__ inline void multiply(const float *A, const float *B, int sa, int sb, 
 // wavefronts takes one block of 16 * MI x 32 of one C over all of its rows (no atomics, no cleared targets), the
 // wavefronts split the rows and add their blocks up in LDS.  csum: also the column sums of A (the bias gradient
 // that goes with a weight gradient), by the workgroups of the first block column.
+// The wavefronts' and XCDs' parts are added in double.
 // Bound by the matrix units of the compute unit a block lies on: blocks of 64 rows where these fill the chip, of 32
 // otherwise.  A block's operands are read to the end of a lane's two or four columns, up to 12 bytes
 // beyond the last row: in the workspace, where every array is followed by another.  SPLIT: many rows and few blocks -- every XCD takes an eighth of the rows (and reads
@@ -149,11 +164,14 @@ __device__ inline void store_block(const WgradJob &q, int m0, int n0, int e, flo
     }
 }
 
+// Registers: with parts, four wavefronts per SIMD spilled (12 registers with loads four deep, 106 with eight: 33 and 80 us at
+// 5700 rows of 100 columns).  SPLIT launches more workgroups than fit at once: three wavefronts, four deep (30 us, as
+// without parts); the others two, eight deep.
 template <int MI, bool SPLIT>
-__global__ void __launch_bounds__(kWgWaves *kWave, 4) k_tr_wgrad(StepArgs a, WgradJobs jobs)
+__global__ void __launch_bounds__(kWgWaves *kWave, SPLIT ? 3 : 2) k_tr_wgrad(StepArgs a, WgradJobs jobs)
 {
     __shared__ float red[kWgWaves][MI * 512];
-    __shared__ float reds[kWgWaves][MI][kWave];
+    __shared__ double reds[kWgWaves][MI][kWave];
     const int block = SPLIT ? (int)blockIdx.x / kXcds : (int)blockIdx.x;
     const int ji = job_of_block(jobs.first, block);
     const WgradJob q = jobs.j[ji];
@@ -179,10 +197,10 @@ __global__ void __launch_bounds__(kWgWaves *kWave, 4) k_tr_wgrad(StepArgs a, Wgr
     const int k_lo = (SPLIT ? (int)blockIdx.x % kXcds * kWgWaves + w : w) * sub, k_hi = k_lo + sub < rows ? k_lo + sub : rows;
     const bool with_sum = q.csum != nullptr && n0 == 0;  // (uniform over the workgroup)
     floatx4 acc[MI][2];
-    float sum[MI];
+    double sum[MI];
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-        sum[i] = 0.0f;
+        sum[i] = 0.0;
         acc[i][0] = acc[i][1] = floatx4{0, 0, 0, 0};
     }
     const int c = lane & 15, g = lane >> 4, mm = m0 + MI * c, nn = n0 + 2 * c;
@@ -194,7 +212,7 @@ __global__ void __launch_bounds__(kWgWaves *kWave, 4) k_tr_wgrad(StepArgs a, Wgr
             continue;
         const size_t row = (size_t)lo + (part ? gap : 0);
         const float *A = q.A + row * q.lda, *B = q.B + row * q.ldb;
-        multiply<MI>(A, B, q.lda, q.ldb, ao, bo, hi - lo, acc, sum);
+        multiply<MI, SPLIT ? 4 : 8>(A, B, q.lda, q.ldb, ao, bo, hi - lo, acc, sum);
     }
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
@@ -207,22 +225,24 @@ __global__ void __launch_bounds__(kWgWaves *kWave, 4) k_tr_wgrad(StepArgs a, Wgr
     }
     __syncthreads();
     for (int e = threadIdx.x; e < MI * 512; e += kWgWaves * kWave) {
-        float x = 0.0f;
+        double sum_e = 0.0;
 #pragma unroll
         for (int ww = 0; ww < kWgWaves; ++ww)
-            x += red[ww][e];
+            sum_e += (double)red[ww][e];
+        const float x = (float)sum_e;
         if (SPLIT)
             jobs.part[(size_t)blockIdx.x * kPartFloats + e] = x;
         else
             store_block<MI>(q, m0, n0, e, x);
     }
     if (with_sum && threadIdx.x < 16 * MI && m0 + (int)threadIdx.x < q.Mo) {
-        float x = 0.0f;
+        double sum_m = 0.0;
 #pragma unroll
         for (int ww = 0; ww < kWgWaves; ++ww)
 #pragma unroll
             for (int gg = 0; gg < 4; ++gg)
-                x += reds[ww][threadIdx.x % MI][16 * gg + threadIdx.x / MI];
+                sum_m += reds[ww][threadIdx.x % MI][16 * gg + threadIdx.x / MI];
+        const float x = (float)sum_m;
         if (SPLIT)
             jobs.part[(size_t)blockIdx.x * kPartFloats + 512 * MI + threadIdx.x] = x;
         else
@@ -243,20 +263,19 @@ __global__ void __launch_bounds__(512) k_tr_wgrad_sum(WgradJobs jobs)
 #pragma unroll
     for (int x = 0; x < kXcds; ++x)
         p[x] = *(const float4 *)(part + (size_t)x * kPartFloats + e);
-    float4 sum = p[0];
+    double sum[4] = {};
 #pragma unroll
-    for (int x = 1; x < kXcds; ++x)
-        sum.x += p[x].x, sum.y += p[x].y, sum.z += p[x].z, sum.w += p[x].w;
-    store_block<4>(q, m0, n0, e, sum.x);
-    store_block<4>(q, m0, n0, e + 1, sum.y);
-    store_block<4>(q, m0, n0, e + 2, sum.z);
-    store_block<4>(q, m0, n0, e + 3, sum.w);
+    for (int x = 0; x < kXcds; ++x)
+        sum[0] += (double)p[x].x, sum[1] += (double)p[x].y, sum[2] += (double)p[x].z, sum[3] += (double)p[x].w;
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+        store_block<4>(q, m0, n0, e + v, (float)sum[v]);
     if (q.csum && n0 == 0 && threadIdx.x < 64 && m0 + (int)threadIdx.x < q.Mo) {
-        float x = 0.0f;
+        double x = 0.0;
 #pragma unroll
         for (int i = 0; i < kXcds; ++i)
-            x += part[(size_t)i * kPartFloats + 2048 + threadIdx.x];
-        q.csum[m0 + threadIdx.x] = x;
+            x += (double)part[(size_t)i * kPartFloats + 2048 + threadIdx.x];
+        q.csum[m0 + threadIdx.x] = (float)x;
     }
 }
 
@@ -265,6 +284,9 @@ __global__ void __launch_bounds__(512) k_tr_wgrad_sum(WgradJobs jobs)
 // wavefronts per 32 x 32 block of a C, the wavefronts split k.  Results go to a plain matrix and / or, as
 // element (r, c) of a prepared operand or of its transpose, straight into the kernels' lane-ordered layout.
 // Beside them plain copies into such layouts.  Latency: a launch is one round of loads and two LDS steps.
+// Products and sums in double: the foldings are what every row of the next step is multiplied by, and a gradient passes
+// through two of these products (in single precision, 35 instead of 43 us for the four launches at 172 state columns and 25
+// instead of 29 at 100, gradients came out up to 1.7 times as far from 64 bits).
 //
 // Columns of a key / value row have two orders: the model's [s | e | Phi] and the kernels' [Phi | s | e];
 // a job names, per operand index, which way it is mapped.
@@ -275,7 +297,7 @@ struct SmallJob {
     float *pk, *pkT;           // element (pk_r + m, pk_c + n) of pk, element (pkT_r + n, pkT_c + m) of pkT
     int ars, acs, brs, bcs, us, vs, ldc, split;
     int m, n, k;
-    float alpha, u_scale;
+    double alpha, u_scale;
     int pk_kbs, pk_r, pk_c, pkT_kbs, pkT_r, pkT_c;  // (no narrow fields: those are not scalar loads)
     int am, bn;                // IndexMap of A's row, of B's column (and of v)
     int k_at;                  // A's k is k + a_k[0] and B's k + b_k[0] below this k, + [1] from it on
@@ -313,7 +335,7 @@ __device__ inline size_t packed_index(int r, int c, int kbs)  // fp32 operand, 1
 __device__ inline void element(int e, int m0, int n0, int &mm, int &nn)
 {
     const int l = e & (kWave - 1), v = (e / kWave) & 3, j = (e / (4 * kWave)) & 1, i = e / (8 * kWave);
-    mm = m0 + 16 * i + 4 * (l >> 4) + v;
+    mm = m0 + 16 * i + 4 * v + (l >> 4);  // (products of doubles: a lane's rows are four apart)
     nn = n0 + 16 * j + (l & 15);
 }
 
@@ -337,9 +359,11 @@ struct __attribute__((packed, aligned(4))) Four {
 // The wavefront's part k_lo <= k < k_hi of a block.  Of sixteen k, lane group g takes the four from 4 g on, so that an
 // operand with consecutive k in memory (AV, BV: and with k in fours) is one load of 16 bytes where it would be four
 // of 4 bytes in sixteen cache lines each, which bound these products (172 x 272 x 272: 9 us).
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
 template <bool AV, bool BV>
 __device__ inline void small_multiply(const SmallJob &q, const int (&ao)[2], const int (&bo)[2], int k_lo, int k_hi,
-                                      floatx4 (&acc)[2][2])
+                                      doublex4 (&acc)[2][2])
 {
     constexpr int kS = 2;  // steps of 16 k whose loads are issued together
     const int g = lane_id() >> 4;
@@ -387,18 +411,18 @@ __device__ inline void small_multiply(const SmallJob &q, const int (&ao)[2], con
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const bool on = k + 16 * u + 4 * g + e < k_hi;
-                float x[2], y[2];
+                double x[2], y[2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
-                    x[i] = on ? av[u][i].v[e] : 0.0f;
-                    y[i] = on ? bv[u][i].v[e] : 0.0f;
+                    x[i] = (double)(on ? av[u][i].v[e] : 0.0f);
+                    y[i] = (double)(on ? bv[u][i].v[e] : 0.0f);
                 }
                 if (k + 16 * u + e < k_hi)  // (uniform)
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
 #pragma unroll
                         for (int j = 0; j < 2; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[j], acc[i][j], 0, 0, 0);
+                            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[i], y[j], acc[i][j], 0, 0, 0);
             }
     }
 }
@@ -420,10 +444,10 @@ __global__ void __launch_bounds__(kSmallThreads, 4) k_tr_small(SmallJobs jobs, C
     const int tiles_n = (q.n + 31) / 32, tile = block - jobs.first[ji];
     const int m0 = (tile / tiles_n) * 32, n0 = (tile % tiles_n) * 32;
     int ao[2], bo[2];
-    floatx4 acc[2][2];
+    doublex4 acc[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        acc[i][0] = acc[i][1] = floatx4{0, 0, 0, 0};
+        acc[i][0] = acc[i][1] = doublex4{0, 0, 0, 0};
         const int mm = m0 + 16 * i + c, nn = n0 + 16 * i + c;
         ao[i] = map_index(mm < q.m ? mm : 0, q.am, T, MF) * q.ars;
         bo[i] = map_index(nn < q.n ? nn : 0, q.bn, T, MF) * q.bcs;
@@ -455,7 +479,7 @@ __global__ void __launch_bounds__(kSmallThreads, 4) k_tr_small(SmallJobs jobs, C
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
-                red[w][((i * 2 + j) * 4 + v) * kWave + lane] = acc[i][j][v];
+                red[w][((i * 2 + j) * 4 + v) * kWave + lane] = (float)acc[i][j][v];
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kSmallPer; ++r) {
@@ -464,15 +488,16 @@ __global__ void __launch_bounds__(kSmallThreads, 4) k_tr_small(SmallJobs jobs, C
         element(e, m0, n0, mm, nn);
         if (mm >= q.m || nn >= q.n)
             continue;
-        float sum = 0.0f;
+        double total = 0.0;
 #pragma unroll
         for (int ww = 0; ww < kSmallWaves; ++ww)
-            sum += red[ww][e];
-        sum *= q.alpha;
+            total += (double)red[ww][e];
+        total *= q.alpha;
         if (q.u)
-            sum += q.u_scale * eu[r] * ev[r];
+            total += q.u_scale * (double)eu[r] * (double)ev[r];
         if (q.add)
-            sum += ea[r];
+            total += (double)ea[r];
+        const float sum = (float)total;
         if (q.C) {
             if (nn < q.split)
                 q.C[(size_t)mm * q.ldc + nn] = sum;
@@ -522,7 +547,8 @@ struct UpdateJob {
     float *P, *G;
     size_t n_params;
     float lr;
-    float *TACC, *WACC;
+    double *TACC;
+    float *WACC;
     float *phi0;         // [T] Phi(0), which the query row carries
     const float *dphi0;  // [T] its gradient
 };
@@ -544,10 +570,8 @@ __global__ void __launch_bounds__(256) k_tr_update(StepArgs a, UpdateJob u)
         float g = u.G[i];
         const size_t T = (size_t)u.T, tail = u.n_params - (size_t)(u.E + 1);
         if (i < 2 * T) {  // the first two arrays: frequencies, phases (Phi(0)_j = cos(b_j))
-            g = u.TACC[i];
-            if (i >= T)
-                g -= (float)sin((double)u.P[i]) * u.dphi0[i - T];
-            u.TACC[i] = 0.0f;
+            g = (float)(u.TACC[i] - (i >= T ? sin((double)u.P[i]) * (double)u.dphi0[i - T] : 0.0));
+            u.TACC[i] = 0.0;
             u.G[i] = g;
         } else if (i >= tail) {  // the last two: w_d2, b_d2
             g = u.WACC[i - tail];
@@ -643,7 +667,7 @@ static TrainLayout train_layout(const Dims &d, void *base)
     L.zero_lo = off;
     L.G = take(n);
     TrainArrays &t = L.t;
-    t.TACC = take(2 * T);
+    t.TACC = (double *)take(2 * 2 * T);
     t.WACC = take(E + 1);
     t.Wd1T = take((size_t)d.Ep * 2 * d.Ek);
     t.Wm2T = take((size_t)d.Ep * d.Ek);
@@ -721,14 +745,14 @@ struct SmallList {
     }
     // C[m x n] = alpha A B, A(i, k) = A[i * ars + k * acs], B(k, j) = B[k * brs + j * bcs]
     SmallJob &add(float *C, int ldc, const float *A, int ars, int acs, const float *B, int brs, int bcs, int m, int n, int k,
-                  float alpha = 1.0f)
+                  double alpha = 1.0)
     {
         jobs.first[jobs.n] = jobs.tiles;
         SmallJob &q = jobs.j[jobs.n++];
         q = SmallJob{};
         q.A = A, q.B = B, q.C = C;
         q.ars = ars, q.acs = acs, q.brs = brs, q.bcs = bcs, q.ldc = ldc, q.split = n;
-        q.m = m, q.n = n, q.k = k, q.alpha = alpha, q.u_scale = 1.0f, q.k_at = k;
+        q.m = m, q.n = n, q.k = k, q.alpha = alpha, q.u_scale = 1.0, q.k_at = k;
         jobs.tiles += ((m + 31) / 32) * ((n + 31) / 32);
         return q;
     }
@@ -753,7 +777,7 @@ hipError_t fold_weights(const Dims &d, const TrainLayout &L, const PackedWeights
     const TrainArrays &t = L.t;
     const int M = d.M, T = d.T, F = d.F, E = d.E, H = d.H, da = d.da, dh = d.dh, dkv = d.dkv, D = d.Dmsg;
     const int kbM = d.Mq / 16, kbN = d.N1 / 16, kbE = d.Ek / 16, kbK2 = d.K2 / 16, ld_m1 = da + M;
-    const float scale = 1.0f / sqrtf((float)dh);
+    const double scale = 1.0 / sqrt((double)dh);
     SmallList one(d), two(d);
     one.add(L.Gm, da, w.W_m1, ld_m1, 1, w.W_O, da, 1, E, da, da);
     for (int h = 0; h < H; ++h) {  // A1_h = scale W_K,h^T W_Q,h[:, :M]; rows in the kernels' column order
@@ -829,7 +853,7 @@ hipError_t unfold_gradients(const Dims &d, const TrainLayout &L, hipStream_t s)
 {
     const tig_weights &w = L.w, &g = L.g;
     const int M = d.M, T = d.T, E = d.E, H = d.H, da = d.da, dh = d.dh, dkv = d.dkv, ld_m1 = da + M, ldA = M + 1;
-    const float scale = 1.0f / sqrtf((float)dh);
+    const double scale = 1.0 / sqrt((double)dh);
     SmallList one(d), two(d);
     for (int h = 0; h < H; ++h) {
         const float *WK = w.W_K + (size_t)h * dh * dkv, *WV = w.W_V + (size_t)h * dh * dkv, *WQ = w.W_Q + (size_t)h * dh * da;
@@ -894,7 +918,8 @@ hipError_t train_attach(const Dims &d, const tig_weights &w, void *workspace, vo
     hipLaunchKernelGGL(k_tr_phi0, dim3((d.T + 255) / 256), dim3(256), 0, s, L.w.time_b, L.phi0, d.T);
     if (e == hipSuccess)
         e = hipGetLastError();
-    // (single precision, for the backward pass's copies; the forward pass and ordinary steps start from foldings in double)
+    // (for the backward pass's copies; the forward pass and ordinary steps start from foldings in double throughout, where
+    // fold_weights rounds G and cQ once in between)
     if (e == hipSuccess)
         e = fold_weights(d, L, *pw, s);
     return e == hipSuccess ? pack_weights(d, L.w, packed, L.pack_scratch, pw, s, kPackEmbed) : e;

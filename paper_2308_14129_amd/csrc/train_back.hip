@@ -141,6 +141,7 @@ struct BackShape {
 // acc[j] += A[16 mt ..][k-blocks a_kb0 .. + n) x W[nt[j]]^T over W's k-blocks [w_kb0, w_kb0 + n), for NT output tiles
 // that share the reads of A.  With eight wavefronts on a unit a product is as long as its round trips to L2, so up to
 // DEPTH blocks of every tile's weights are requested together (a block beyond n repeats the last and is not used).
+// Products are summed two blocks (32 terms) at a time, see tile_gemm's PARTS.
 template <int MT, int NT, int DEPTH>
 __device__ inline void tile_gemm_deep(floatx4 (&acc)[NT][MT], const char *A, int lda, int a_kb0, const void *W, int w_kblocks,
                                       int w_kb0, int n, const int (&nt)[NT])
@@ -159,16 +160,27 @@ __device__ inline void tile_gemm_deep(floatx4 (&acc)[NT][MT], const char *A, int
                 b[j][u] = P::load_w(W, ((size_t)nt[j] * w_kblocks + w_kb0 + kc) * kWave + lane);
         }
 #pragma unroll
-        for (int u = 0; u < DEPTH; ++u)
-            if (kb + u < n) {  // (uniform)
+        for (int u0 = 0; u0 < DEPTH; u0 += 2) {
+            if (kb + u0 >= n)  // (uniform)
+                break;
+            floatx4 part[NT][MT] = {};
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const frag a = P::load_a(ap + (size_t)mt * 16 * lda, a_kb0 + kb + u, g);
+            for (int u = u0; u < u0 + 2 && u < DEPTH; ++u)
+                if (kb + u < n) {  // (uniform)
 #pragma unroll
-                    for (int j = 0; j < NT; ++j)
-                        P::mma(acc[j][mt], a, b[j][u]);
+                    for (int mt = 0; mt < MT; ++mt) {
+                        const frag a = P::load_a(ap + (size_t)mt * 16 * lda, a_kb0 + kb + u, g);
+#pragma unroll
+                        for (int j = 0; j < NT; ++j)
+                            P::mma(part[j][mt], a, b[j][u]);
+                    }
                 }
-            }
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+                    acc[j][mt] += part[j][mt];
+        }
     }
 }
 
@@ -362,11 +374,13 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
     };
     auto staged = [&](int32_t ref) -> int { return ref < 0 && ref != kRefNone && ~ref < 2 * a.msg_count ? ~ref : -1; };
     TIG_MARK(3);
-    float gw[NPHI], gb[NPHI];        // time-encoding gradients of the lane's dims, over all rows of the wavefront
+    // time-encoding gradients of the lane's dims, over all rows of the wavefront (in double: some hundred terms, whose
+    // sizes differ as the time differences do)
+    double gw[NPHI], gb[NPHI];
     double tw_reg[NPHI], tb_reg[NPHI];  // ... and its parameters
 #pragma unroll
     for (int n = 0; n < NPHI; ++n) {
-        gw[n] = gb[n] = 0.0f;
+        gw[n] = gb[n] = 0.0;
         const int j = lane + kWave * n < p.T ? lane + kWave * n : 0;
         tw_reg[n] = tw_tab[2 * j];
         tb_reg[n] = tw_tab[2 * j + 1];
@@ -546,8 +560,8 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
 #pragma unroll
                         for (int n = 0; n < NPHI; ++n) {
                             const float v = -time_enc_sin(tw_reg[n], tb_reg[n], dt) * dk[n];
-                            gw[n] += (float)dt * v;  // (lanes beyond T are dropped at the end)
-                            gb[n] += v;
+                            gw[n] += dt * (double)v;  // (lanes beyond T are dropped at the end)
+                            gb[n] += (double)v;
                         }
                     }
             }
@@ -604,7 +618,7 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
         if (srow >= 0)
             atomicAdd(&t.D_STAG[(size_t)srow * p.M + i % p.M], (float)tab[i]);
     }
-    float *red = (float *)X;  // [waves x T], frequencies first, then phases
+    double *red = (double *)X;  // [waves x T], frequencies first, then phases
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
 #pragma unroll
@@ -615,7 +629,7 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
         }
         __syncthreads();
         for (int j = threadIdx.x; j < p.T; j += kThreads) {
-            float sum = 0.0f;
+            double sum = 0.0;
             for (int v = 0; v < kWaves; ++v)
                 sum += red[v * p.T + j];
             atomicAdd(&t.TACC[half * p.T + j], sum);
@@ -695,7 +709,7 @@ __global__ void __launch_bounds__(kGbThreads) k_tr_gru_back(StepArgs a, PackedWe
     for (int nt = wave; nt < p.Tp / 16; nt += kGbWaves) {
         floatx4 acc[1] = {floatx4{0, 0, 0, 0}};
         const int kb = p.Kp / Prec<TIG_FP32>::KB;
-        tile_gemm<TIG_FP32, 1, 4>(acc, X, p.ldx, 0, t.WiT, kb, 0, kb, nt);
+        tile_gemm<TIG_FP32, 1, 4, true>(acc, X, p.ldx, 0, t.WiT, kb, 0, kb, nt);
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             ((float *)(DP + (size_t)(4 * (lane >> 4) + v) * p.ldp))[nt * 16 + (lane & 15)] = acc[0][v];
@@ -703,13 +717,13 @@ __global__ void __launch_bounds__(kGbThreads) k_tr_gru_back(StepArgs a, PackedWe
     __syncthreads();
     for (int j = threadIdx.x; j < T; j += kGbThreads) {
         const double w_rev = w.time_w_rev[j], b_rev = w.time_b_rev[j];
-        float gw = 0.0f, gb = 0.0f;
+        double gw = 0.0, gb = 0.0;
 #pragma unroll
         for (int i = 0; i < kGbRows; ++i) {  // (rows beyond the winners hold zeros)
             const double dt = row_dt[i];
             const float v = -time_enc_sin(w_rev, b_rev, dt) * ((const float *)(DP + (size_t)i * p.ldp))[j];
-            gw += (float)dt * v;
-            gb += v;
+            gw += dt * (double)v;
+            gb += (double)v;
         }
         atomicAdd(&t.TACC[j], gw);
         atomicAdd(&t.TACC[T + j], gb);
