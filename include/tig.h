@@ -370,7 +370,8 @@ TIG_API int tig_reset(tig_ctx *ctx);
 TIG_API int tig_state_export(tig_ctx *ctx, float *mem_out, double *last_update_out);
 TIG_API int tig_state_import(tig_ctx *ctx, const float *mem_in, const double *last_update_in);
 
-/* Frees the host-side context.  Device buffers belong to the caller and are not touched. */
+/* Waits for the context's stream (which still has to exist) and frees the host-side context: when it returns, no
+ * step reads or writes the workspaces any more.  Device buffers belong to the caller and are not touched. */
 TIG_API void tig_destroy(tig_ctx *ctx);
 
 /* Static text for a status code / detail of the last failure on this context ("" if none);

@@ -409,9 +409,9 @@ PinnedStage::~PinnedStage()
 }
 
 // The two hint words of a context (see tig_ctx): places of one pinned page that contexts take and give back
-// (a page of its own per context cost 0.2 ms of tig_init and tig_destroy).  A step still running when its
-// context is destroyed may write a hint into a place that another context has taken: hints shape launches,
-// never results.  No place left, or no page: the context does without.
+// (a page of its own per context cost 0.2 ms of tig_init and tig_destroy).  tig_destroy waits for the
+// context's steps, which write them, before it gives the place back.  No place left, or no page: the context
+// does without.
 constexpr int kHintPlaces = 64, kHintWords = 16;
 static std::mutex g_hint_lock;
 static int32_t *g_hint_host, *g_hint_dev;
@@ -525,6 +525,7 @@ int tig_init(const tig_config *cfg, const tig_graph *graph, const tig_weights *w
         hipError_t e_ = (expr);                                                             \
         if (e_ != hipSuccess) {                                                             \
             snprintf(g_init_err, sizeof(g_init_err), "%s: %s", what, hipGetErrorString(e_)); \
+            (void)hipStreamSynchronize(s); /* copies from `stage` and into `hflags` may be on their way */ \
             delete ctx;                                                                     \
             return TIG_EHIP;                                                                \
         }                                                                                   \
@@ -1296,6 +1297,8 @@ void tig_destroy(tig_ctx *ctx)
 {
     if (!ctx)
         return;
+    // steps may be running: the caller gives the workspaces to someone else after this call
+    (void)hipStreamSynchronize(ctx->stream);
     if (ctx->have_marks)
         for (int i = 0; i <= kNumStepKernels; ++i)
             (void)hipEventDestroy(ctx->marks[i]);

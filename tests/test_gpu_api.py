@@ -251,3 +251,34 @@ def test_all_equal_timestamps_give_empty_neighbourhoods():
     assert int(out.nbr_cnt.abs().sum()) == 0 and int((out.nbr_node != -1).sum()) == 0
     ctx.close()
     run(b, "fp32", [(1000, 100)], locked=False, warm_at=1000)
+
+
+@pytest.mark.parametrize("train", [False, True])
+def test_closing_waits_for_the_contexts_stream(c1, train):
+    # the workspaces go back to the allocator when a context is closed: its step must have ended, on whatever stream
+    import torch
+    from paper_2308_14129_amd import tig
+    w, g, W = c1.w, c1.g, c1.W
+    neg = torch.from_numpy(S.make_negatives(w, g, 0, 200)).to("cuda:0")
+    cfg = tig.make_config(w.mem_dim, w.time_dim, w.feat_dim, w.emb_dim, w.num_neighbors, w.num_heads, 200)
+    got = []
+    for stream in (None, torch.cuda.Stream()):
+        torch.cuda.synchronize()
+        ctx = tig.TigContext(cfg, g.num_nodes, g.src, g.dst, g.ts, g.edge_feat, W, stream=stream)
+        if train:
+            ctx.train_attach(W)
+        out = ctx.alloc_outputs(200)
+        x = torch.full((8192, 8192), 1e-4, device="cuda:0")
+        torch.cuda.synchronize()
+        with torch.cuda.stream(ctx.stream):
+            for _ in range(10):
+                x = x @ x  # some 100 ms in front of the step
+        if train:
+            ctx.train_step(0, 200, neg, out, 0.0)
+        else:
+            ctx.step(0, 200, neg, out)
+        assert not ctx.stream.query()
+        ctx.close()
+        assert ctx.stream.query()
+        got.append(out.emb.cpu().numpy())
+    assert np.array_equal(got[0], got[1])
