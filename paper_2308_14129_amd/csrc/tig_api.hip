@@ -336,9 +336,10 @@ hipError_t copy_weights_in(const Dims &d, const tig_weights &w, const RawWeights
         hipPointerAttribute_t at;
         const bool host = stage.ptr && hipPointerGetAttributes(&at, src) == hipSuccess && at.type != hipMemoryTypeDevice &&
                           at.type != hipMemoryTypeManaged && bytes <= kPinnedStageBytes;
-        if (!host) {
+        if (!host) {  // (ends the range: its bytes lie between the host arrays')
             (void)hipGetLastError();
-            e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDefault, s);
+            if ((e = flush()) == hipSuccess)
+                e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDefault, s);
             continue;
         }
         if (range > 0 && (size_t)(dst - range_dst) + bytes > kPinnedStageBytes) {

@@ -282,3 +282,22 @@ def test_closing_waits_for_the_contexts_stream(c1, train):
         assert ctx.stream.query()
         got.append(out.emb.cpu().numpy())
     assert np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("on_device", [lambda i: i % 2 == 1, lambda i: i % 2 == 0, lambda i: i % 5 == 3, lambda i: True])
+def test_weights_on_host_and_device_side_by_side(c1, on_device):
+    # every weight pointer is a host or a device array: any mixture gives the context that host arrays alone give
+    import torch
+    w, g, W = c1.w, c1.g, c1.W
+    neg = torch.from_numpy(S.make_negatives(w, g, 0, 200)).to("cuda:0")
+    mixed = {k: torch.from_numpy(v).to("cuda:0") if on_device(i) else v for i, (k, v) in enumerate(W.items())}
+    got = []
+    for weights in (W, mixed):
+        ctx = make_ctx(w, g, weights, "fp32")
+        out = ctx.alloc_outputs(200)
+        ctx.step(0, 200, neg, out)
+        mem, _ = ctx.state_export()
+        got.append((out.emb.cpu().numpy(), out.score_pos.cpu().numpy(), out.score_neg.cpu().numpy(), mem))
+        ctx.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
