@@ -262,8 +262,10 @@ namespace {
 // Terms that are evaluated are the IEEE operations of Eq. 3-6 in their order, so the partitions are the
 // same bit for bit; an edge that the sets do not cover (sizes spread over kLevels values or more, terms
 // so close that rounding could make two sizes equal, centralities that are not finite and non-negative)
-// is decided by the plain evaluation (best_plain).  Measured (EPYC host of the MI355X, 4 M events, 1 M nodes,
-// 8 partitions): 36 -> 5.3 ns per edge; 5 partitions and mostly non-hubs 20 -> 6.5; 16 partitions 49 -> 6.6.
+// is decided by the plain evaluation (best_plain), and while the sizes are spread that far only their extremes are
+// kept.  Measured (EPYC host of the MI355X, 4 M events, 1 M nodes, 8 partitions): 36 -> 5.3 ns per edge; 5 partitions
+// and mostly non-hubs 20 -> 6.5; 16 partitions 49 -> 6.6.  Without hubs the sizes are spread from the start: 9 ns at 8
+// partitions as before (2 M events, another host), 91 with the sets rebuilt for every edge.
 class EdgeLoop {
 public:
     EdgeLoop(const tig_sep_config &cfg, int64_t num_nodes, const double *cent, const uint8_t *is_hub, uint64_t *A)
@@ -286,6 +288,10 @@ public:
             size_[p] = 0;
         for (int g = 0; g < kLevels; ++g)
             terms_[g].den = -1.0;
+        for (uint64_t &l : level_)
+            l = 0;
+        base_ = 0;
+        mx_ = mn_ = 0;
         levels_from_sizes();
     }
 
@@ -355,10 +361,15 @@ public:
             mx_ = mx;
             mn_ = mn;
             base_ = (int)(lev - level_);
-            if (base_ >= kRing || mx_ - mn_ >= kLevels)
+            if (base_ >= kRing && mx_ - mn_ < kLevels)
                 levels_from_sizes();
-            // one edge of any kind
-            if (e < n) {
+            // one edge of any kind, or all of them while the sizes are too far apart for the sets
+            while (e < n) {
+                if (e + kAhead < n) {
+                    const uint32_t pi = (uint32_t)src[e + kAhead], pj = (uint32_t)dst[e + kAhead];
+                    __builtin_prefetch(A + (pi < N ? pi : 0));
+                    __builtin_prefetch(A + (pj < N ? pj : 0));
+                }
                 const int64_t i = src[e], j = dst[e];
                 if (i < 0 || i >= N_ || j < 0 || j >= N_)
                     return false;
@@ -370,6 +381,8 @@ public:
                     grow(p);
                 }
                 ++e;
+                if (easy && mx_ - mn_ < kLevels)
+                    break;
             }
         }
         return true;
@@ -491,8 +504,15 @@ private:
     void grow(int p)
     {
         const int64_t sz = size_[p]++;
-        if (mx_ - mn_ >= kLevels || sz + 1 - mn_ >= kLevels) {
-            levels_from_sizes();
+        if (mx_ - mn_ >= kLevels) {  // only the extremes, until the sizes are close enough for the sets again
+            mx_ = sz + 1 > mx_ ? sz + 1 : mx_;
+            if (sz == mn_) {
+                mn_ = size_[0];
+                for (int q = 1; q < P_; ++q)
+                    mn_ = size_[q] < mn_ ? size_[q] : mn_;
+                if (mx_ - mn_ < kLevels)
+                    levels_from_sizes();
+            }
             return;
         }
         uint64_t *lev = level_ + base_;
@@ -502,24 +522,19 @@ private:
         mx_ += sz == mx_;
         if (lev[0] == 0) {
             ++mn_;
-            if (++base_ >= kRing)
+            if (++base_ >= kRing && mx_ - mn_ < kLevels)
                 levels_from_sizes();
         }
     }
 
+    // the sets of sizes that lie within kLevels values (mx_ and mn_ are kept by the callers)
     void levels_from_sizes()
     {
-        mx_ = mn_ = size_[0];
-        for (int p = 1; p < P_; ++p) {
-            mx_ = size_[p] > mx_ ? size_[p] : mx_;
-            mn_ = size_[p] < mn_ ? size_[p] : mn_;
-        }
+        for (int k = 0; k <= kLevels; ++k)  // (all others are zero)
+            level_[base_ + k] = 0;
         base_ = 0;
-        for (int k = 0; k < kRing + kLevels + 1; ++k)
-            level_[k] = 0;
         for (int p = 0; p < P_; ++p)
-            if (size_[p] - mn_ < kLevels)
-                level_[size_[p] - mn_] |= 1ull << p;
+            level_[size_[p] - mn_] |= 1ull << p;
     }
 
     const int P_;

@@ -79,6 +79,50 @@ def test_assign_branches_match_oracle(sep, num_parts, lam, eps, hubs):
     assert np.array_equal(part, ref_part) and np.array_equal(node_parts, masks(A)) and part_edges.tolist() == sizes
 
 
+@pytest.mark.parametrize("num_parts,pile", [(2, 17), (3, 40), (7, 16), (16, 30)])
+def test_sizes_that_drift_apart_and_come_together_again(sep, num_parts, pile):
+    # blocks of events between two resident non-hubs (one partition grows by `pile`), and of events between hubs, which
+    # the balance term sends to the small partitions until all sizes are close again
+    r = np.random.default_rng(num_parts)
+    hubs = np.arange(30)
+    src, dst = [], []
+    for k in range(25):
+        src += [40 + 2 * (k % 5)] * pile + r.integers(0, 30, num_parts * pile + k).tolist()
+        dst += [41 + 2 * (k % 5)] * pile + r.integers(0, 29, num_parts * pile + k).tolist()
+    src, dst = np.array(src, dtype=np.int32), np.array(dst, dtype=np.int32)
+    dst = np.where(dst == src, 29, dst).astype(np.int32)
+    src = np.where(dst == src, 0, src).astype(np.int32)
+    n = 60
+    cent = np.bincount(src, minlength=n) + np.bincount(dst, minlength=n) + 0.0
+    is_hub = (np.arange(n) < 30).astype(np.uint8)
+    for lam in (1.0, 8.0):  # (8: a partition that is small enough beats one with both replicas)
+        ref_part, A, sizes, _ = P.assign_stream(src, dst, n, cent, hubs, num_parts, lam, 1e-3)
+        part, node_parts, part_edges = sep.assign(sep.make_config(num_parts, 0.0, 0.0, lam, 1e-3), src, dst, n, cent, is_hub)
+        assert np.array_equal(part, ref_part) and np.array_equal(node_parts, masks(A)) and part_edges.tolist() == sizes
+
+
+def test_a_stream_without_hubs_costs_no_more_than_one_with(sep):
+    # without hubs the sizes are far apart from the start: an edge of such a stream took seven times as long as one of
+    # the same stream with hubs while the sets of sizes were rebuilt for each (0.8 times as long without that)
+    import time
+    r = np.random.default_rng(1)
+    n, events = 100_000, 300_000
+    cdf = np.cumsum(np.arange(1, n + 1) ** -1.5)
+    src, dst = (np.searchsorted(cdf, r.random(events) * cdf[-1]).astype(np.int32) for _ in range(2))
+    dst = np.where(dst == src, (src + 1) % n, dst).astype(np.int32)
+    cent = np.bincount(src, minlength=n) + np.bincount(dst, minlength=n) + 0.0
+    seconds = []
+    for hubs in (0, n // 100):
+        is_hub = (np.arange(n) < hubs).astype(np.uint8)
+        runs = []
+        for _ in range(7):
+            start = time.perf_counter()
+            sep.assign(sep.make_config(16, 0.0, 0.0), src, dst, n, cent, is_hub)
+            runs.append(time.perf_counter() - start)
+        seconds.append(min(runs))
+    assert seconds[0] < 3.0 * seconds[1], seconds
+
+
 def test_assign_rejects_bad_arguments(sep):
     from paper_2308_14129_amd import tig
     ok = dict(src=[0, 1], dst=[1, 2], num_nodes=3, cent=[1.0, 1.0, 1.0], is_hub=[0, 0, 0])
