@@ -291,7 +291,7 @@ __device__ inline unsigned long long winner_key(double t, int32_t eid, int role)
 // with W's k-block w_kb0+i.  W: lane-ordered blocks, `w_kblocks` per output tile.
 // Weight operands come from L2 and the loop is latency-bound, so up to DEPTH operand loads are
 // issued before the first MFMA of a group.
-// PARTS (training step): every group is summed on its own and added to acc, not all products one after the other (the
+// PARTS (training step, layers of a stack): every group is summed on its own and added to acc, not all products one after the other (the
 // rounding of a chain grows with its length; embeddings of 30 shapes: 2.9e-7 off 64 bits in one chain of up to 400
 // terms, 2.2e-7 in parts of 64 or 80, and 1 us of 45 more).
 template <int PREC, int MT, int DEPTH, bool PARTS = false>
