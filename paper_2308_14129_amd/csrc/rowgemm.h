@@ -1,5 +1,5 @@
-// A layer product over all rows of a step at once on the matrix cores (fp32 16x16x4), shared by the
-// training step and the attention embedding of the module instances.  gfx950 only.
+// A layer product over all rows of a step at once on the matrix cores (fp32 16x16x4): the attention embedding of the
+// module selections, where it does not run in the embedding kernel.  gfx950 only.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -21,34 +21,22 @@ __device__ inline int row_count(const RowCount &rc)
     return r < 0 ? 0 : (r < rc.rows_max ? (int)r : rc.rows_max);
 }
 
-// A layer product over all rows at once: C[r][n] = f(sum_k A[r][k] W[n][k] (+ sum_k A2[r][k] W2[n][k]) + bias[n])
-// on the matrix cores (fp32 16x16x4).  A and W are both k-contiguous: a forward product takes the
-// weight matrix as stored ([out x in]), a backward product dX = dY W its transposed copy
-// ([in x out]).  A workgroup takes 32 rows; each of its four wavefronts one block of 32 columns
+// A layer product over all rows at once: C[r][n] = f(sum_k A[r][k] W[n][k] + bias[n])
+// on the matrix cores (fp32 16x16x4).  A and W are both k-contiguous.  A workgroup takes 32 rows; each of its four wavefronts one block of 32 columns
 // (blockIdx.y counts groups of four column blocks; the workgroups stride over the row blocks).  A lane
 // loads four consecutive k of its row per step (k = k0 + 4 g + v for lane group g: the four groups
 // cover 16 k, and the v-th products of a step pair the same k in both operands).
 struct RowGemm {
-    const float *A, *W, *A2, *W2, *bias;
+    const float *A, *W, *bias;
     float *C;
-    int lda, ldw, lda2, ldw2, ldc;
-    int N, Kd, Kd2;
+    int lda, ldw, ldc;
+    int N, Kd;
     RowCount rc;
     int relu;                // f = max(., 0)
-    const float *gate;       // NULL, or: the result is kept where gate[row][n] > 0, else 0
-    int ldg;
     const int32_t *rowmask;  // NULL, or: rows with rowmask[row] == 0 give 0 (no bias)
     const int32_t *remap_nu; // NULL, or: output row of r is r below min(*remap_nu, remap_2b), else remap_2b + (r - that)
     int remap_2b;
-    int vecA, vecW, vecA2, vecW2;  // operand rows are 16-byte aligned: four k in one load
-    // two products that share A in one launch: columns n >= n_split (n_split > 0) take the weight rows
-    // W_hi[n - n_split] and bias_hi[n - n_split] and go to C_hi[row][n - n_split]; rowmask then covers
-    // the columns below n_split only
-    int n_split;
-    const float *W_hi, *bias_hi;
-    float *C_hi;
-    int ldc_hi;
-    int ldw_hi, Kd_hi;  // 0: as W; else the rows of W_hi are Kd_hi <= Kd long (A's columns beyond count as 0 for them)
+    int vecA, vecW;          // operand rows are 16-byte aligned: four k in one load
     // a batch of products in one launch (one per attention head): product z = blockIdx.z reads A + z * zA,
     // W + z * zW, bias + z * zBias and writes C + z * zC (element offsets)
     int zA, zW, zC, zBias;
@@ -84,13 +72,12 @@ __device__ inline floatx4 load_k4(const float *row, int k, int Kd, bool ok, int 
 // acc += the part over k in [k_lo, k_hi) (k_lo a multiple of 16) of one block of 32 rows x 32 columns
 // of product z of p, by one wavefront: rows r0 .., columns 32 tn ..
 template <bool VEC>
-__device__ inline void rowgemm_accumulate(const RowGemm &p, int rows, int r0, int tn, int z, int pass, int k_lo, int k_hi,
+__device__ inline void rowgemm_accumulate(const RowGemm &p, int rows, int r0, int tn, int z, int k_lo, int k_hi,
                                           floatx4 (&acc)[2][2])
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int c = lane & 15, g = lane >> 4;
     const int n0 = tn * 32;
-    const int split = p.n_split > 0 ? p.n_split : p.N;
     // the two rows whose operand this lane loads (rows r0 + c and r0 + 16 + c)
     size_t arow[2];
     bool aok[2];
@@ -101,21 +88,15 @@ __device__ inline void rowgemm_accumulate(const RowGemm &p, int rows, int r0, in
         arow[i] = (size_t)(ok ? r : 0);
         aok[i] = ok;
     }
-    const float *A = pass ? p.A2 : p.A + (size_t)z * p.zA, *W = pass ? p.W2 : p.W + (size_t)z * p.zW;
-    const int lda = pass ? p.lda2 : p.lda, ldw = pass ? p.ldw2 : p.ldw, Kd = pass ? p.Kd2 : p.Kd;
-    const int vA = pass ? p.vecA2 : p.vecA, vW = pass ? p.vecW2 : p.vecW;
-    const float *ar[2] = {A + arow[0] * lda, A + arow[1] * lda};
+    const float *A = p.A + (size_t)z * p.zA, *W = p.W + (size_t)z * p.zW;
+    const int Kd = p.Kd;
+    const float *ar[2] = {A + arow[0] * p.lda, A + arow[1] * p.lda};
     const int nn0 = n0 + c, nn1 = n0 + 16 + c;
     const bool wok[2] = {nn0 < p.N, nn1 < p.N};
     const float *wr[2];
-    int wkd[2];  // length of the lane's weight rows
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int nn = wok[i] ? (i ? nn1 : nn0) : 0;
-        const bool hi = nn >= split;  // (no second pass with a split)
-        wr[i] = hi ? p.W_hi + (size_t)(nn - split) * (p.ldw_hi ? p.ldw_hi : ldw) : W + (size_t)nn * ldw;
-        wkd[i] = hi && p.Kd_hi ? p.Kd_hi : Kd;
-    }
+    for (int i = 0; i < 2; ++i)
+        wr[i] = W + (size_t)(wok[i] ? (i ? nn1 : nn0) : 0) * p.ldw;
     const int k_end = k_hi < Kd ? k_hi : Kd;
     constexpr int kU = 4;  // steps of 16 k whose loads are issued together
     for (int k0 = k_lo; k0 < k_end; k0 += 16 * kU) {
@@ -126,8 +107,8 @@ __device__ inline void rowgemm_accumulate(const RowGemm &p, int rows, int r0, in
             const bool on = k0 + 16 * u < k_end;  // (uniform)
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                av[u][i] = load_k4<VEC>(ar[i], kk, Kd, aok[i] && on, vA);
-                wv[u][i] = load_k4<VEC>(wr[i], kk, wkd[i], wok[i] && on, vW);
+                av[u][i] = load_k4<VEC>(ar[i], kk, Kd, aok[i] && on, p.vecA);
+                wv[u][i] = load_k4<VEC>(wr[i], kk, Kd, wok[i] && on, p.vecW);
             }
         }
 #pragma unroll
@@ -146,12 +127,12 @@ __device__ inline void rowgemm_accumulate(const RowGemm &p, int rows, int r0, in
 }
 
 // Epilogue of one 16 x 16 sub-block (i, j) of a block: the lane holds rows 16 i + 4 g + v (v = 0..3) of
-// column 16 j + c.  What the epilogue reads (bias, gate, row mask) is loaded unconditionally -- from a
+// column 16 j + c.  What the epilogue reads (bias, row mask) is loaded unconditionally -- from a
 // valid address where the product has no such input, the value then plays no part -- and ahead of
 // the first store, so that a sub-block costs one round trip (a load inside a branch is waited for at
 // the end of the branch: one round trip per load).
 struct RowGemmEpi {
-    float bias, gate[4];
+    float bias;
     int32_t mask[4];
 };
 
@@ -168,25 +149,20 @@ __device__ inline int rowgemm_out_row(const RowGemm &p, int r, int nu)
     return p.remap_nu ? (r < nu ? r : p.remap_2b + (r - nu)) : r;
 }
 
-__device__ inline RowGemmEpi rowgemm_epi_load(const RowGemm &p, int rows, int r0, int tn, int z, int i, int j, int nu)
+__device__ inline RowGemmEpi rowgemm_epi_load(const RowGemm &p, int rows, int r0, int tn, int z, int i, int j)
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int c = lane & 15, g = lane >> 4;
-    const int split = p.n_split > 0 ? p.n_split : p.N;
     const int n = tn * 32 + 16 * j + c;
     const int nc = n < p.N ? n : 0;
-    const bool hi = nc >= split;
-    const float *bptr = hi ? p.bias_hi : (p.bias ? p.bias + (size_t)z * p.zBias : nullptr);
     RowGemmEpi e;
-    e.bias = (bptr ? bptr : p.W)[bptr ? (hi ? nc - split : nc) : 0] * (bptr ? 1.0f : 0.0f);
-    const float *gp = p.gate ? p.gate : p.W;
+    e.bias = (p.bias ? p.bias + (size_t)z * p.zBias : p.W)[p.bias ? nc : 0] * (p.bias ? 1.0f : 0.0f);
     const int32_t *mp = p.rowmask ? p.rowmask : (const int32_t *)p.W;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int r = r0 + 16 * i + 4 * g + v;
         const int rc = r < rows ? r : 0;
         e.mask[v] = mp[p.rowmask ? rc : 0];
-        e.gate[v] = gp[p.gate ? (size_t)rowgemm_out_row(p, rc, nu) * p.ldg + nc : 0];
     }
     return e;
 }
@@ -196,11 +172,9 @@ __device__ inline void rowgemm_epi_store(const RowGemm &p, int rows, int r0, int
 {
     const int lane = threadIdx.x & (kWave - 1);
     const int c = lane & 15, g = lane >> 4;
-    const int split = p.n_split > 0 ? p.n_split : p.N;
     const int n = tn * 32 + 16 * j + c;
     if (n >= p.N)
         return;
-    const bool hi = n >= split;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int r = r0 + 16 * i + 4 * g + v;
@@ -210,13 +184,8 @@ __device__ inline void rowgemm_epi_store(const RowGemm &p, int rows, int r0, int
         float val = acc[v] + e.bias;
         if (p.relu)
             val = fmaxf(val, 0.0f);
-        const bool gated_off = (p.gate != nullptr) & !(e.gate[v] > 0.0f);
-        const bool dead = (p.rowmask != nullptr) & (e.mask[v] == 0) & !hi;
-        val = (gated_off | dead) ? 0.0f : val;
-        if (hi)
-            p.C_hi[(size_t)orow * p.ldc_hi + (n - split)] = val;
-        else
-            p.C[(size_t)z * p.zC + (size_t)orow * p.ldc + n] = val;
+        val = ((p.rowmask != nullptr) & (e.mask[v] == 0)) ? 0.0f : val;
+        p.C[(size_t)z * p.zC + (size_t)orow * p.ldc + n] = val;
     }
 }
 
@@ -230,14 +199,13 @@ __device__ inline void rowgemm_tile(const RowGemm &p, int rows, int r0, int tn, 
         for (int j = 0; j < 2; ++j)
             acc[i][j] = floatx4{0, 0, 0, 0};
     const int nu = rowgemm_remap_count(p);
-    for (int pass = 0; pass < (p.A2 ? 2 : 1); ++pass)
-        rowgemm_accumulate<VEC>(p, rows, r0, tn, z, pass, 0, pass ? p.Kd2 : p.Kd, acc);
+    rowgemm_accumulate<VEC>(p, rows, r0, tn, z, 0, p.Kd, acc);
     RowGemmEpi e[2][2];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-            e[i][j] = rowgemm_epi_load(p, rows, r0, tn, z, i, j, nu);
+            e[i][j] = rowgemm_epi_load(p, rows, r0, tn, z, i, j);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -266,8 +234,8 @@ __global__ void __launch_bounds__(256) k_rowgemm_ks(RowGemm p)
             for (int j = 0; j < 2; ++j)
                 acc[i][j] = floatx4{0, 0, 0, 0};
         // (what this wavefront's sub-block (w / 2, w % 2) needs for its epilogue is requested ahead of the products)
-        const RowGemmEpi e = rowgemm_epi_load(p, rows, r0, tn, z, w >> 1, w & 1, nu);
-        rowgemm_accumulate<VEC>(p, rows, r0, tn, z, 0, w * kq, (w + 1) * kq, acc);
+        const RowGemmEpi e = rowgemm_epi_load(p, rows, r0, tn, z, w >> 1, w & 1);
+        rowgemm_accumulate<VEC>(p, rows, r0, tn, z, w * kq, (w + 1) * kq, acc);
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -300,8 +268,7 @@ __global__ void __launch_bounds__(256) k_rowgemm(RowGemm p)
 
 inline bool rowgemm_all_vec(const RowGemm &g)
 {
-    return g.vecA && g.vecW && g.Kd % 4 == 0 && g.Kd_hi % 4 == 0 && g.ldw_hi % 4 == 0 &&
-           (!g.A2 || (g.vecA2 && g.vecW2 && g.Kd2 % 4 == 0));
+    return g.vecA && g.vecW && g.Kd % 4 == 0;
 }
 
 // (the row count is known on the device only: at most 1024 row blocks are launched and stride)
@@ -309,7 +276,7 @@ inline void launch_rowgemm(const RowGemm &g, int nz, hipStream_t s)
 {
     const int row_blocks = (g.rc.rows_max + 31) / 32, tiles_n = (g.N + 31) / 32;
     const int gx = row_blocks < 1024 ? (row_blocks > 0 ? row_blocks : 1) : 1024;
-    if (!g.A2 && g.Kd >= 64 && row_blocks <= 512) {  // few rows: four wavefronts per block, each a quarter of k
+    if (g.Kd >= 64 && row_blocks <= 512) {  // few rows: four wavefronts per block, each a quarter of k
         const dim3 grid(gx, tiles_n, nz);
         if (rowgemm_all_vec(g))
             hipLaunchKernelGGL(k_rowgemm_ks<true>, grid, dim3(256), 0, s, g);
