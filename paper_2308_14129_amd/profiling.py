@@ -27,11 +27,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 # (a name that is the beginning of another comes after it: the first match names the kernel)
 STEP_KERNELS = ("k_scatter", "k_select", "k_prepare", "k_gru", "k_embed", "k_centrality", "k_topk_keys", "k_topk_flags",
-                "k_tr_gather", "k_rowgemm", "k_tr_attn_fwd", "k_tr_attn_bwd", "k_tr_scatter", "k_tr_pairs", "k_tr_logit",
-                "k_tr_pair_scatter", "k_tr_gru_gates", "k_tr_gru_time", "k_gemm_tn", "k_colsum", "k_gemm64",
-                "k_pack_gru", "k_pack", "k_transpose", "k_tr_update",
-                "k_mod_msgsum", "k_mod_update", "k_mod_commit", "k_mod_simple", "k_mod_hop2", "k_mr_items", "k_mr_attn",
-                "k_mod_decode")
+                "k_rowgemm_ks", "k_rowgemm", "k_tr_back", "k_tr_decode", "k_tr_gru_back", "k_tr_phi0", "k_tr_small",
+                "k_tr_update", "k_tr_wgrad_sum", "k_tr_wgrad", "k_fold", "k_pack_gru", "k_pack",
+                "k_mod_msgsum", "k_mod_mean", "k_mod_final", "k_mod_commit", "k_mod_hop2", "k_mod_transpose", "k_mod_revolutions",
+                "k_mr_items", "k_mr_attn", "k_two_claim", "k_two_lookup", "k_two_negatives")
 COPY_KIB = 256 * 1024  # one calibration copy reads and writes this much
 XCDS = 8                # accelerator dies of one MI355X
 
