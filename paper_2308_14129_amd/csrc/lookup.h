@@ -20,7 +20,7 @@ namespace tig {
 // query's own event in u's list (everything from there on has time >= t), or -1 if unknown.
 // my_nbr / my_eid / my_ts: the slot this lane wrote (lanes below K; -1, -1, 0.0 for an unused
 // slot and for the other lanes).  Returns the number of filled slots.
-__device__ inline int nbr_lookup_wave(const StepArgs &a, int K, int32_t u, double t, int64_t own_pos,
+__device__ inline int nbr_lookup_wave(const StepBase &a, int K, int32_t u, double t, int64_t own_pos,
                                       const QuerySet &qs, int row, int32_t &my_nbr, int32_t &my_eid, double &my_ts)
 {
     my_nbr = -1;

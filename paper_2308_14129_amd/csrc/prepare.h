@@ -31,7 +31,7 @@ __device__ inline uint32_t query_hash(int32_t u, double t)
     return h;
 }
 
-__device__ inline void entry_query(const StepArgs &a, int64_t first_eid, int i, int32_t &u, double &t)
+__device__ inline void entry_query(const StepBase &a, int64_t first_eid, int i, int32_t &u, double &t)
 {
     const int64_t eid = first_eid + (i >> 1);
     u = (i & 1) ? a.dst[eid] : a.src[eid];
@@ -43,7 +43,7 @@ __device__ inline void entry_query(const StepArgs &a, int64_t first_eid, int i, 
 // A slot changes once per job, from empty to claimed, and the compare-and-swap decides who
 // claimed it, so a stale read of "empty" only costs the failed swap.  The probe count is bounded
 // by the table size; if that bound were ever hit the entry simply represents itself.
-__device__ inline int claim_query(const StepArgs &a, const DedupJob &j, int i, int32_t u, double t)
+__device__ inline int claim_query(const StepBase &a, const DedupJob &j, int i, int32_t u, double t)
 {
     const int entries = 2 * j.count;
     const unsigned long long mine = ((unsigned long long)j.epoch << 32) | (uint32_t)i;
@@ -75,7 +75,7 @@ __device__ inline int claim_query(const StepArgs &a, const DedupJob &j, int i, i
 // representatives among them are compacted, take consecutive rows of the query set (one atomic
 // per workgroup), and the wavefronts look up their neighbours.  smem: kPrepLds bytes.
 // ceil(2 * count / n_wgs) must not exceed kPrepThreads.
-__device__ inline void dedup_block(const StepArgs &a, const DedupJob &j, int K, int wg, char *smem)
+__device__ inline void dedup_block(const StepBase &a, const DedupJob &j, int K, int wg, char *smem)
 {
     int *list = (int *)smem;            // [kPrepThreads] thread index of the n-th representative
     int *s_cnt = list + kPrepThreads;   // [waves] representatives per wavefront, then their prefix
@@ -144,7 +144,7 @@ struct RefCtx {
     int32_t count;                  // 0: the step applies nothing
 };
 
-__device__ inline RefCtx ref_ctx(const StepArgs &a)
+__device__ inline RefCtx ref_ctx(const StepBase &a)
 {
     return RefCtx{a.num_nodes, a.msg_key, a.msg_first_eid, a.msg_count};
 }
@@ -203,7 +203,7 @@ __device__ inline void finish_row(const RefCtx &c, const QuerySet &qs, int K, in
 
 // Returns the number of filled slots; my_ref / my_eid / my_ts: slot `lane` of the row (lanes
 // below K), as written to the query set.
-__device__ inline int finish_negative(const StepArgs &a, int K, int b, int32_t &my_ref, int32_t &my_eid,
+__device__ inline int finish_negative(const StepBase &a, int K, int b, int32_t &my_ref, int32_t &my_eid,
                                       double &my_ts)
 {
     int32_t my_nbr;

@@ -21,7 +21,10 @@ namespace {
 
 constexpr int kHashSlots = 2048;       // k_scatter: power of two, 2 x entries per workgroup
 
-__global__ void __launch_bounds__(kScatterThreads) k_prepare(StepArgs a, SelectJob sel, DedupJob ded, int K)
+// (The kernels here take the arguments without a training step's: at 812 bytes of arguments the launch record of k_prepare
+// fell into a size that the host's allocator had to search for after a context's preparation, and the first step of a
+// context took 20 us longer on the host, 50 instead of 30.)
+__global__ void __launch_bounds__(kScatterThreads) k_prepare(StepBase a, SelectJob sel, DedupJob ded, int K)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     int x = (int)blockIdx.x;
@@ -41,7 +44,7 @@ __global__ void __launch_bounds__(kScatterThreads) k_prepare(StepArgs a, SelectJ
 // table (hub nodes take thousands of entries per batch, and same-address device atomics
 // serialise), and finally one atomicMax per distinct node of the workgroup goes to memory.
 // Keys left in the array by earlier batches are smaller than any key of this one.
-__global__ void __launch_bounds__(kScatterThreads) k_scatter(StepArgs a, SelectJob j)
+__global__ void __launch_bounds__(kScatterThreads) k_scatter(StepBase a, SelectJob j)
 {
     __shared__ int32_t t_node[kHashSlots];
     __shared__ unsigned long long t_key[kHashSlots];
@@ -70,7 +73,7 @@ __global__ void __launch_bounds__(kScatterThreads) k_scatter(StepArgs a, SelectJ
 // Larger batches, part 2: an entry supplies its node's message iff the node's key is the entry's
 // own.  Winners are compacted through an atomic counter; their order is irrelevant (rows are
 // independent).
-__global__ void __launch_bounds__(256) k_select(StepArgs a, SelectJob j)
+__global__ void __launch_bounds__(256) k_select(StepBase a, SelectJob j)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     bool win = false;

@@ -130,7 +130,7 @@ struct TrainFwd {
     float *DA, *DB;   // [R x E] cleared: gradients of the decoder's source / second-operand half of the row
 };
 
-struct StepArgs {
+struct StepBase {
     // graph (device)
     const int32_t *src, *dst;
     const double *ts;
@@ -184,6 +184,9 @@ struct StepArgs {
     int32_t *out_nbr_node, *out_nbr_eid, *out_nbr_cnt;  // optional
     double *out_nbr_ts;                                 // optional
     uint8_t *out_is_winner;                             // optional
+};
+
+struct StepArgs : StepBase {
     // a training step (gru_gates NULL: an ordinary step): what its backward pass reads
     float *gru_gates;  // [2*msg_count x 4 x M] r, z, n and the hidden half of n's pre-activation of winner r of the list
     float *gru_msg;    // [2*msg_count x D_msg] the message row of winner r

@@ -87,7 +87,7 @@ __device__ inline void table_insert_max(int32_t *t_node, unsigned long long *t_k
 // Besides the winner list and the per-entry flags, every winner leaves its key in key[node]: a
 // later lookup of "was this node updated by batch (first_eid, count), and by which entry" reads
 // key[node] and checks that the event id inside lies in the batch (keys of other batches do not).
-__device__ inline void winners_block(const StepArgs &g, const SelectJob &a, char *smem)
+__device__ inline void winners_block(const StepBase &g, const SelectJob &a, char *smem)
 {
     unsigned long long *t_key = (unsigned long long *)smem;   // [kOneSlots]
     int32_t *t_node = (int32_t *)(smem + kOneSlots * 8);      // [kOneSlots]
@@ -191,7 +191,7 @@ __device__ inline void winners_block(const StepArgs &g, const SelectJob &a, char
 // Wavefront `w` of `n_waves` takes winner after winner.  While a step runs, every reader of an
 // updated node's state takes the staged row through its row reference, never the memory row, so
 // this may run beside the embedding.
-__device__ inline void overwrite_memory(const StepArgs &a, int M, int w, int n_waves)
+__device__ inline void overwrite_memory(const StepBase &a, int M, int w, int n_waves)
 {
     const int lane = lane_id();
     int n_win = *a.n_win;
