@@ -927,6 +927,10 @@ const void *pick_mt(int mt, int npl, int H)
     }
 }
 
+// Row shapes compiled in (RowShape; any other takes the general instances, whose widths are arguments): with their widths
+// known, which register holds what is decided at compile time and the time-encoding parameters stay in registers.  They
+// bring a training step 9% at 172 and 4% at 100 state columns (20 steps 4.85 -> 4.46 and 4.59 -> 4.43 ms) and two layers
+// over 4000 events 14% (148.6 -> 128.3 us).
 template <int PREC, int MODE>
 const void *pick(const Dims &d, int mt)
 {
