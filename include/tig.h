@@ -335,17 +335,22 @@ typedef struct tig_modules {
     const tig_layer_weights *layer2; /* required iff num_layers == 2 (TIG_EMB_ATTENTION only) */
 } tig_modules;
 
-/* Size of the workspace of a module selection (device memory the caller allocates): transposed
- * copies of the weights and, if node features are given, a copy of them.  TIG_EINVAL for a
- * precision other than TIG_FP32, an unknown selector, emb_dim != mem_dim with an embedding that
- * needs it, two layers without the attention embedding or without `layer2`, or rows the kernels
- * cannot hold (attention: more than 4 heads, heads * K above 64, key / value rows above 512 columns;
- * two layers: K above 63).  The attention embedding with node features or two layers runs as
- * contractions over all items of a layer (distinct queries; first of two layers: also their used
- * neighbour slots) and keeps the items' matrices here: about items * 4 * (5 * (w + T) + 4 * H *
+/* Size of the workspace of a module selection (device memory the caller allocates): copies of the
+ * weights as the selection's kernels read them and, if node features are given, a copy of them.
+ * TIG_EINVAL for a precision other than TIG_FP32, an unknown selector, emb_dim != mem_dim with an
+ * embedding that needs it, two layers without the attention embedding or without `layer2`, or rows
+ * the kernels cannot hold (attention: more than 4 heads, heads * K above 64, key / value rows above
+ * 512 columns; two layers: K above 63).
+ * The attention embedding without node features runs in the step's own launches.  Two layers then
+ * keep a table of the distinct (node, time) pairs of the queries and their neighbours, and the
+ * claims that merge equal pairs: with rows = 3 * max_batch * (K + 1) about
+ * rows * (16 * K + 4 * E + 56) bytes (84 MB with batch 4000, K = 10, E = 100).
+ * With node features, or where a second-layer row does not fit the launches' on-chip memory, it runs
+ * as contractions over all items of a layer (distinct queries; first of two layers: also their used
+ * neighbour slots) and keeps the items' matrices: about items * 4 * (5 * (w + T) + 4 * H *
  * (w + F + T) + E) bytes with w = max(mem_dim, emb_dim) and items = 3 * max_batch * (K + 1) for two
- * layers (1 GB at 2.6 M nodes' shape with batch 4000, K = 10), 3 * max_batch for one.  Two layers also
- * add the second hop's neighbour tables and the first layer's rows:
+ * layers (1 GB with batch 4000, K = 10 and widths of 100), 3 * max_batch for one.  Two layers also add the
+ * second hop's neighbour tables and the first layer's rows:
  * 3 * max_batch * (K * K * 16 + (K + 1) * 4 * E) bytes. */
 TIG_API int tig_modules_workspace_bytes(const tig_config *cfg, const tig_modules *modules, int64_t num_nodes,
                                         size_t *bytes);

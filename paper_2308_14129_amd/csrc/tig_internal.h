@@ -319,8 +319,8 @@ hipError_t train_copy_out(const Dims &d, void *workspace, bool grads, const tig_
 void train_step_args(const Dims &d, void *workspace, StepArgs *a);
 hipError_t launch_train(const Dims &d, const LaunchPlan &plan, const StepArgs &a, void *workspace, const PackedWeights &pw, float lr,
                         float *loss_out, int *launches, hipStream_t s);
-// after training steps with lr != 0 the prepared weights follow the masters in single precision: this folds
-// those of the inference kernels again, in double precision
+// after training steps with lr != 0 the prepared weights follow the masters through fold_weights (products in double, two
+// intermediate matrices in single precision): this folds those of the inference kernels again, in double throughout
 hipError_t train_refold_embed(const Dims &d, void *workspace, void *packed, PackedWeights *pw, hipStream_t s);
 // ---- other instances of the general architecture (modules.hip) ----
 // Module selection of a context and its weights: transposed copies ([in x out]) in the attached workspace.
