@@ -227,7 +227,7 @@ __global__ void __launch_bounds__(kModThreads) k_mod_hop2(StepArgs a, ModDims d,
 // Two layers without node features: the rows of the first layer -- every distinct (node, time) among the queries
 // and their neighbours at the queries' times -- as a query set of their own, so that either layer is one launch
 // of the embedding kernel (embed_tile.h, LAYER; the second with the first's rows as its "memory").  4000 events of
-// 100 columns: 337 -> 126 us a step (46 + 39 us of it the layers); with the products of both layers as launches over
+// 100 columns: 337 -> 128 us a step (48 + 40 us of it the layers); with the products of both layers as launches over
 // all rows (k_mr_*, below, which remain for node features and for rows that the embedding kernel's tiles do not hold) every
 // intermediate of every row went through memory, and the host issued 22 launches a step.
 //   k_two_negatives  memory overwrite; the negatives' own neighbours, one wavefront each
