@@ -707,7 +707,7 @@ next_tile:
 #pragma unroll
             for (int h = 0; h < H; ++h) {
                 // (den >= 1; the hardware's reciprocal is within 1 ulp)
-                const float inv = cnt == 0 ? 0.0f : FINE ? 1.0f / den[h] : __builtin_amdgcn_rcpf(den[h]);
+                const float inv = cnt > 0 ? (FINE ? 1.0f / den[h] : __builtin_amdgcn_rcpf(den[h])) : 0.0f;
 #pragma unroll
                 for (int n = 0; n < NPL; ++n) {
                     const int j = lane + kWave * n;
