@@ -12,11 +12,15 @@ struct EmbedParams {
     int ld1;        // row stride of the E-wide buffers, bytes
     int off_h1, off_meta;  // byte offsets in LDS
     int n_tiles;    // workgroups that take row tiles
+    int spread;     // tiles the rows are spread over if they are few (tiles_in_use)
     int n_commit;   // then: workgroups of the memory overwrite; the ones beyond prepare the next batch
+    int commit_beside;  // the memory overwrite is done by those beyond, behind the query preparation
     // bit n set: register n of a key/value row (dims 64 n .. 64 n + 63 of [Phi | s_v | e]) holds
     // at least one dim of the time encoding / of the neighbour's memory / of the edge feature
     int phi_regs, mem_regs, feat_regs;
 };
+
+constexpr int kLeastRows = 8;  // of a tile that is not one of the fewest
 
 enum EmbedMode { kEmbedStep = 0, kEmbedTrain = 1, kEmbedLayer = 2 };
 

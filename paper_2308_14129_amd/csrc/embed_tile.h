@@ -21,7 +21,7 @@
 // The projections W_Q, W_K, W_V, W_O and the first merge layer are folded into A1 and P at init
 // (pack.hip), which removes the per-neighbour key/value projections.
 // The number of rows is known on the device only: the grid has a tile for every 16*MT rows the
-// batch could have, and the tiles beyond the actual row count return at once.  Row r of tile p is
+// batch could have, and the tiles beyond those in use (tiles_in_use) return at once.  Row r of tile p is
 // query row p + (number of tiles in use) * r, which spreads the heavy rows (sources /
 // destinations, first in the set) over all tiles.  Workgroups beyond the tiles and the memory
 // overwrite prepare the batch expected next: one selects its last-message winners, the others
@@ -94,6 +94,19 @@ constexpr int regs_touching(int lo, int hi, int dims)
 static_assert(sizeof(StepArgs) % alignof(PackedWeights) == 0 && (sizeof(StepArgs) + sizeof(PackedWeights)) % alignof(EmbedParams) == 0,
               "the kernel's arguments follow each other without gaps");
 
+// Tiles of at most ROWS rows that n_rows rows are dealt over: as many as there are compute units to take them (SPREAD)
+// while each gets eight rows, because the attention phase is as long as the rows of a compute unit are many (a row of
+// twenty 444-column slots is 2.7 us of a SIMD: 187 tiles of 32 rows took 30 us there, 223 of 27 take 26), while the
+// products cost the same for any number of rows.  A launch whose workgroups loop (LOOP of them) gives each equally many.
+__device__ inline int tiles_in_use(int n_rows, int rows, int spread, int loop)
+{
+    const int least = (n_rows + rows - 1) / rows, most = (n_rows + kLeastRows - 1) / kLeastRows;
+    if (loop > 0 && least > loop)
+        return (least + loop - 1) / loop * loop;
+    const int even = most < spread ? most : spread;
+    return least > even ? least : even;
+}
+
 template <int PREC, int MODE, int MT, int NPL, int H, int SHAPE>
 __global__ void __launch_bounds__((EmbedShape<NPL, H>::kThreads))
 k_embed(StepArgs a_, PackedWeights w_, EmbedParams p_)
@@ -136,8 +149,11 @@ k_embed(StepArgs a_, PackedWeights w_, EmbedParams p_)
                 }
                 --x;
             }
-            if (a_.ded.count > 0 && x < a_.ded.n_wgs)
+            if (a_.ded.count > 0 && x < a_.ded.n_wgs) {
                 dedup_block(a_, a_.ded, p_.K, x, smem);
+                if (p_.commit_beside)
+                    overwrite_memory(a_, p_.M, x * kEmbedWaves + wave_id(), a_.ded.n_wgs * kEmbedWaves);
+            }
             TIG_MARK(7);
         }
         return;
@@ -185,7 +201,7 @@ next_tile:
     n_u = n_u < 2 * a.count ? n_u : 2 * a.count;
     const int neg_row0 = 2 * a.count;
     const int n_rows = n_u + (a.roles == 3 ? a.count : 0);
-    const int n_passes = (n_rows + ROWS - 1) / ROWS;
+    const int n_passes = tiles_in_use(n_rows, ROWS, p.spread, LAYER ? p.n_tiles : 0);
     if (pass >= n_passes)
         return;  // fewer distinct queries than the grid was sized for
     // a row reference that is neither a memory row nor a staged row of the applied batch reads as none

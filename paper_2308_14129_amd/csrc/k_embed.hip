@@ -29,8 +29,8 @@ EmbedParams embed_params(const Dims &d, int mt)
     p.ld1 = lds_row_bytes(d.Ek);
     p.off_h1 = (rows * p.row_bytes + 15) / 16 * 16;
     p.off_meta = p.off_h1 + rows * p.ld1;
-    p.n_tiles = 0;
-    p.n_commit = 0;
+    p.n_tiles = p.spread = 0;
+    p.n_commit = p.commit_beside = 0;
     p.phi_regs = p.mem_regs = p.feat_regs = 0;
     for (int n = 0; n * kWave < d.dkvp; ++n) {
         const int lo = n * kWave, hi = lo + kWave;
@@ -134,10 +134,13 @@ hipError_t launch_embed(const Dims &d, const LaunchPlan &plan, const PackedWeigh
     StepArgs aa = a;
     PackedWeights ww = pw;
     const int threads = embed_threads(d);
-    // memory overwrite: about four winners per wavefront at the winner count recent steps had
+    // memory overwrite: by the workgroups that prepare the next batch's queries, if there are any (they end long before the
+    // tiles do, and every workgroup of its own takes a compute unit from these), else about four winners per wavefront
+    // at the winner count recent steps had
     int n_commit = 0;
     const bool train = a.tr.S != nullptr;  // (a training step overwrites the memory at its end)
-    if (a.msg_count > 0 && !train) {
+    const bool commit = a.msg_count > 0 && !train, beside = commit && a.ded.count > 0;
+    if (commit && !beside) {
         const int most = 2 * a.msg_count;
         const int wins = a.wins_est > 0 && a.wins_est < most ? a.wins_est : most;
         const int per_block = 4 * (threads / kWave);
@@ -153,8 +156,13 @@ hipError_t launch_embed(const Dims &d, const LaunchPlan &plan, const PackedWeigh
     const int rows = a.rows_est > 0 && a.rows_est < most ? a.rows_est : most;
     const int mt = embed_tiles(plan, rows, units);
     EmbedParams p = embed_params(d, mt);
-    p.n_tiles = (a.roles * a.count + 16 * mt - 1) / (16 * mt);  // tiles in use if no query repeats
+    // tiles in use if no query repeats (tiles_in_use)
+    const int even = (most + kLeastRows - 1) / kLeastRows < units ? (most + kLeastRows - 1) / kLeastRows : units;
+    p.spread = units;
+    p.n_tiles = (most + 16 * mt - 1) / (16 * mt);
+    p.n_tiles = p.n_tiles > even ? p.n_tiles : even;
     p.n_commit = n_commit;
+    p.commit_beside = beside ? 1 : 0;
     void *args[] = {&aa, &ww, &p};
     const int own = embed_lds_bytes(d, mt);
     const int lds = a.sel.count > 0 && own < kOneLds ? kOneLds : (own < kPrepLds ? kPrepLds : own);
@@ -176,7 +184,8 @@ hipError_t launch_embed_layer(const Dims &d, int most_mt, int num_cus, const Pac
     plan.emb_mt = most_mt;
     const int mt = embed_tiles(plan, rows, units);
     EmbedParams p = embed_params(d, mt);
-    p.n_tiles = (most + 16 * mt - 1) / (16 * mt);
+    p.spread = units;
+    p.n_tiles = (most + kLeastRows - 1) / kLeastRows;
     p.n_tiles = p.n_tiles < units ? p.n_tiles : units;
     void *args[] = {&aa, &ww, &p};
     const int own = embed_lds_bytes(d, mt);

@@ -847,15 +847,16 @@ hipError_t launch_train_back(const Dims &d, const LaunchPlan &plan, const StepAr
     // one round of workgroups if 16-row tiles of the rows recent steps had fit the compute units, else taller tiles
     const int most = 3 * a.count, rows = a.rows_est > 0 && a.rows_est < most ? a.rows_est : most;
     const int cus = plan.num_cus > 0 ? plan.num_cus : 256;
-    // (and eight rows per workgroup, one per wavefront in the attention phase, while those fit: the products' time
-    // does not depend on how many rows of a tile are in use)
     const int mt = (rows + 15) / 16 <= cus ? 1 : back_most_tiles(d);
     int lds = 0;
     StepArgs aa = a;
     PackedWeights ww = pw;
     TrainArrays tt = t;
     BackParams p = back_params(d, mt, kBackLds, &lds);
-    p.rpt = (rows + 7) / 8 <= cus ? 8 : 16 * mt;
+    // (the rows dealt evenly over the compute units, eight per workgroup -- one per wavefront in the attention phase -- at
+    // least: the products' time does not depend on how many rows of a tile are in use, the attention's does)
+    const int even = (rows + cus - 1) / cus;
+    p.rpt = even < 8 ? 8 : (even > 16 * mt ? 16 * mt : even);
     void *args[] = {&aa, &ww, &tt, &p};
     return hipLaunchKernel(back_kernel(d, mt), dim3((most + p.rpt - 1) / p.rpt), dim3(kBackThreads), args, (size_t)lds, s);
 }
