@@ -36,9 +36,9 @@ inline int npl_for(const Dims &d)
 // must agree with EmbedShape (heads other than 1 and 2 run the 4-head kernels)
 inline int embed_threads(const Dims &d) { return npl_for(d) >= 8 && d.H > 2 ? 512 : 1024; }
 
-const void *embed_kernel_bf16(const Dims &d, int mt);
-const void *embed_kernel_fp32(const Dims &d, int mt);
-const void *embed_kernel_train(const Dims &d, int mt);
-const void *embed_kernel_layer(const Dims &d, int mt);
+const void *embed_kernel_bf16(const Dims &d, int rows);
+const void *embed_kernel_fp32(const Dims &d, int rows);
+const void *embed_kernel_train(const Dims &d, int rows);
+const void *embed_kernel_layer(const Dims &d, int rows);
 
 }  // namespace tig

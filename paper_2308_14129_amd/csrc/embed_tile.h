@@ -2,7 +2,7 @@
 // the paper's Sec. II-C) and the first decoder layer (decoder g), fused in one kernel, for the
 // DISTINCT queries (node, t) of the batch (prepare.h).  gfx950 only.
 //
-// One workgroup (16 wavefronts) takes 16*MT rows of the query set at a time and keeps every
+// One workgroup (16 wavefronts) takes ROWS rows of the query set at a time and keeps every
 // intermediate of those rows in LDS:
 //   A  row descriptors: row reference of the node's state, neighbour count, time; s_u
 //   B  folded query  q~ = A1 s_u + a1                        (matrix cores; fp32 result)
@@ -20,7 +20,7 @@
 // wavefronts' rows).
 // The projections W_Q, W_K, W_V, W_O and the first merge layer are folded into A1 and P at init
 // (pack.hip), which removes the per-neighbour key/value projections.
-// The number of rows is known on the device only: the grid has a tile for every 16*MT rows the
+// The number of rows is known on the device only: the grid has a tile for every ROWS rows the
 // batch could have, and the tiles beyond those in use (tiles_in_use) return at once.  Row r of tile p is
 // query row p + (number of tiles in use) * r, which spreads the heavy rows (sources /
 // destinations, first in the set) over all tiles.  Workgroups beyond the tiles and the memory
@@ -107,7 +107,7 @@ __device__ inline int tiles_in_use(int n_rows, int rows, int spread, int loop)
     return least > even ? least : even;
 }
 
-template <int PREC, int MODE, int MT, int NPL, int H, int SHAPE>
+template <int PREC, int MODE, int ROWS, int NPL, int H, int SHAPE>
 __global__ void __launch_bounds__((EmbedShape<NPL, H>::kThreads))
 k_embed(StepArgs a_, PackedWeights w_, EmbedParams p_)
 {
@@ -121,7 +121,8 @@ k_embed(StepArgs a_, PackedWeights w_, EmbedParams p_)
     const auto soft_exp = [](float x) -> float { return FINE ? expf(x) : __expf(x); };
     constexpr int kEmbedThreads = EmbedShape<NPL, H>::kThreads;
     constexpr int kEmbedWaves = EmbedShape<NPL, H>::kWaves;
-    constexpr int ROWS = 16 * MT;
+    constexpr int MT = ROWS / 16, RG = ROWS % 16 / 4;  // blocks of 16 rows, then groups of four (TileRows)
+    using TR = TileRows<PREC, MT, RG>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     if ((int)blockIdx.x >= p_.n_tiles) {
         int x = (int)blockIdx.x - p_.n_tiles;
@@ -388,37 +389,38 @@ next_tile:
     TIG_MARK(1);
     // ---- B. folded query: q~ = A1 s_u + a1  (fp32, [H x dkvp] per row) -----------------------
     {
+        constexpr int kPairB = PREC == TIG_FP32 && ROWS <= 8 ? 4 : 2;  // k-blocks requested together
         const int ntB = p.N1 / 16, kbB = p.Mq / P::KB, a_kb0 = p.N1 / P::KB;
-        auto put = [&](const floatx4 (&acc)[MT], int nt, float bias) {
+        auto put = [&](const floatx4 (&acc)[TR::kAcc], int nt, float bias) {
             const int col = nt * 16 + (lane & 15);
+            float x[TR::kOut];
+            TR::results(acc, x);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = mt * 16 + 4 * (lane >> 4) + v;
-                    ((float *)(rowbuf + (size_t)row * p.row_bytes))[col] = acc[mt][v] + bias;
-                    if constexpr (TRAIN)
-                        if (row_q[row] >= 0)
-                            a.tr.QT[(size_t)row_q[row] * p.N1 + col] = acc[mt][v] + bias;
-                }
+            for (int o = 0; o < TR::kOut; ++o) {
+                const int row = TR::row(o);
+                ((float *)(rowbuf + (size_t)row * p.row_bytes))[col] = x[o] + bias;
+                if constexpr (TRAIN)
+                    if (row_q[row] >= 0)
+                        a.tr.QT[(size_t)row_q[row] * p.N1 + col] = x[o] + bias;
+            }
         };
         // two output tiles per pass where the wavefront has two: they share the reads of s_u
         for (int nt = wave; nt < ntB; nt += 2 * kEmbedWaves) {
             const int nt2 = nt + kEmbedWaves;
-            floatx4 acc1[MT], acc2[MT];
+            floatx4 acc1[TR::kAcc], acc2[TR::kAcc];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                acc1[mt] = floatx4{0, 0, 0, 0};
-                acc2[mt] = floatx4{0, 0, 0, 0};
+            for (int i = 0; i < TR::kAcc; ++i) {
+                acc1[i] = floatx4{0, 0, 0, 0};
+                acc2[i] = floatx4{0, 0, 0, 0};
             }
             const float bias1 = w.emb_a1[nt * 16 + (lane & 15)];
             if (nt2 < ntB) {
                 const float bias2 = w.emb_a1[nt2 * 16 + (lane & 15)];
-                tile_gemm_two<PREC, MT, 2>(acc1, acc2, rowbuf, p.row_bytes, a_kb0, w.emb_A1, kbB, kbB, nt, nt2);
+                tile_gemm_pair<PREC, MT, kPairB, RG>(acc1, acc2, rowbuf, p.row_bytes, a_kb0, w.emb_A1, w.emb_A1, kbB, nt, nt2);
                 put(acc1, nt, bias1);
                 put(acc2, nt2, bias2);
             } else {
-                tile_gemm<PREC, MT, 4>(acc1, rowbuf, p.row_bytes, a_kb0, w.emb_A1, kbB, 0, kbB, nt);
+                tile_gemm<PREC, MT, 4, false, RG>(acc1, rowbuf, p.row_bytes, a_kb0, w.emb_A1, kbB, 0, kbB, nt);
                 put(acc1, nt, bias1);
             }
         }
@@ -766,7 +768,7 @@ next_tile:
         const int ksplit = (2 * n_tiles <= kEmbedWaves && kbT >= 8) ? 2 : 1;
         const int kb_half = (kbT + ksplit - 1) / ksplit;
         float *red = (float *)h1buf;  // [ROWS][ld1/4] partial sums of the upper k half
-        floatx4 acc[MT];
+        floatx4 acc[TR::kAcc];
         int my_nt = -1, my_ks = 0;
         for (int base = 0; base < n_tiles * ksplit; base += kEmbedWaves) {  // at most one round if split
             const int unit = base + wave;
@@ -774,8 +776,8 @@ next_tile:
             my_nt = on ? unit % n_tiles : -1;
             my_ks = on ? unit / n_tiles : 0;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                acc[mt] = floatx4{0, 0, 0, 0};
+            for (int i = 0; i < TR::kAcc; ++i)
+                acc[i] = floatx4{0, 0, 0, 0};
             float c = 0.0f, c0 = 0.0f;  // requested with the first weight operands, used in the epilogue
             if (on) {
                 if (my_ks == 0) {
@@ -784,42 +786,33 @@ next_tile:
                 }
                 const int kb0 = my_ks * kb_half;
                 const int nkb = (kbT - kb0) < kb_half ? (kbT - kb0) : kb_half;
-                tile_gemm<PREC, MT, (MT <= 2 ? 5 : 4), FINE>(acc, rowbuf, p.row_bytes, kb0, w.emb_PR, kbT, kb0, nkb, my_nt);
+                tile_gemm<PREC, MT, (TR::kAcc <= 2 ? 5 : 4), FINE, RG>(acc, rowbuf, p.row_bytes, kb0, w.emb_PR, kbT, kb0, nkb, my_nt);
             }
+            float x[TR::kOut];
+            TR::results(acc, x);
+            const int col = (my_nt < 0 ? 0 : my_nt) * 16 + (lane & 15);
             if (ksplit == 2) {
                 if (on && my_ks == 1) {
-                    const int col = my_nt * 16 + (lane & 15);
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int row = mt * 16 + 4 * (lane >> 4) + v;
-                            red[(size_t)row * (p.ld1 / 4) + col] = acc[mt][v];
-                        }
+                    for (int o = 0; o < TR::kOut; ++o)
+                        red[(size_t)TR::row(o) * (p.ld1 / 4) + col] = x[o];
                 }
                 __syncthreads();
             }
             if (on && my_ks == 0) {
-                const int col = my_nt * 16 + (lane & 15);
-                float part[MT][4];
+                float part[TR::kOut];
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
+                for (int o = 0; o < TR::kOut; ++o)
+                    part[o] = ksplit == 2 ? red[(size_t)TR::row(o) * (p.ld1 / 4) + col] : 0.0f;
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int row = mt * 16 + 4 * (lane >> 4) + v;
-                        part[mt][v] = ksplit == 2 ? red[(size_t)row * (p.ld1 / 4) + col] : 0.0f;
-                    }
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int row = mt * 16 + 4 * (lane >> 4) + v;
-                        const float x = acc[mt][v] + part[mt][v] + (row_cnt[row] > 0 ? c : c0);
-                        P::store_a(h1buf + (size_t)row * p.ld1, col, fmaxf(x, 0.0f));
-                        if constexpr (TRAIN)
-                            if (row_q[row] >= 0 && col < p.E)
-                                a.tr.H1[(size_t)row_q[row] * p.E + col] = fmaxf(x, 0.0f);
-                    }
+                for (int o = 0; o < TR::kOut; ++o) {
+                    const int row = TR::row(o);
+                    const float y = x[o] + part[o] + (row_cnt[row] > 0 ? c : c0);
+                    P::store_a(h1buf + (size_t)row * p.ld1, col, fmaxf(y, 0.0f));
+                    if constexpr (TRAIN)
+                        if (row_q[row] >= 0 && col < p.E)
+                            a.tr.H1[(size_t)row_q[row] * p.E + col] = fmaxf(y, 0.0f);
+                }
             }
         }
     }
@@ -838,7 +831,7 @@ next_tile:
     {
         const int nE = p.Ep / 16, kbE = p.Ek / P::KB;
         const int n_out = LAYER && !a.dec_a ? nE : 3 * nE;  // (only the last layer's rows go on to the decoder)
-        auto put = [&](const floatx4 (&acc)[MT], int ot) {
+        auto put = [&](const floatx4 (&acc)[TR::kAcc], int ot) {
             const int grp = ot / nE;  // 0: embedding, 1: source half, 2: second-operand half
             const int col = (ot - grp * nE) * 16 + (lane & 15);
             const float bias = grp == 0 ? w.emb_bm2[col] : 0.0f;
@@ -846,33 +839,32 @@ next_tile:
             const int ld = grp == 0 ? p.E : p.Ep;
             if (grp == 0 && col >= p.E)
                 return;
+            float x[TR::kOut];
+            TR::results(acc, x);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = mt * 16 + 4 * (lane >> 4) + v;
-                    const int q = row_q[row];
-                    if (q >= 0)
-                        dst[(size_t)q * ld + col] = acc[mt][v] + bias;
-                }
+            for (int o = 0; o < TR::kOut; ++o) {
+                const int q = row_q[TR::row(o)];
+                if (q >= 0)
+                    dst[(size_t)q * ld + col] = x[o] + bias;
+            }
         };
         auto weights_of = [&](int ot) -> const void * { return ot < nE ? w.emb_Wm2 : w.dec_WF; };
         auto tile_of = [&](int ot) -> int { return ot < nE ? ot : ot - nE; };
         for (int ot = wave; ot < n_out; ot += 2 * kEmbedWaves) {
             const int ot2 = ot + kEmbedWaves;
-            floatx4 acc1[MT], acc2[MT];
+            floatx4 acc1[TR::kAcc], acc2[TR::kAcc];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                acc1[mt] = floatx4{0, 0, 0, 0};
-                acc2[mt] = floatx4{0, 0, 0, 0};
+            for (int i = 0; i < TR::kAcc; ++i) {
+                acc1[i] = floatx4{0, 0, 0, 0};
+                acc2[i] = floatx4{0, 0, 0, 0};
             }
             if (ot2 < n_out) {
-                tile_gemm_pair<PREC, MT, 4>(acc1, acc2, h1buf, p.ld1, weights_of(ot), weights_of(ot2), kbE,
-                                            tile_of(ot), tile_of(ot2));
+                tile_gemm_pair<PREC, MT, 4, RG>(acc1, acc2, h1buf, p.ld1, 0, weights_of(ot), weights_of(ot2), kbE, tile_of(ot),
+                                                tile_of(ot2));
                 put(acc1, ot);
                 put(acc2, ot2);
             } else {
-                tile_gemm<PREC, MT, 4>(acc1, h1buf, p.ld1, 0, weights_of(ot), kbE, 0, kbE, tile_of(ot));
+                tile_gemm<PREC, MT, 4, false, RG>(acc1, h1buf, p.ld1, 0, weights_of(ot), kbE, 0, kbE, tile_of(ot));
                 put(acc1, ot);
             }
         }
@@ -885,13 +877,13 @@ next_tile:
     }
 }
 
-template <int PREC, int MODE, int MT, int NPL>
+template <int PREC, int MODE, int ROWS, int NPL>
 const void *pick_h(int H)
 {
     switch (H) {
-    case 1: return (const void *)k_embed<PREC, MODE, MT, NPL, 1, 0>;
-    case 2: return (const void *)k_embed<PREC, MODE, MT, NPL, 2, 0>;
-    default: return (const void *)k_embed<PREC, MODE, MT, NPL, 4, 0>;
+    case 1: return (const void *)k_embed<PREC, MODE, ROWS, NPL, 1, 0>;
+    case 2: return (const void *)k_embed<PREC, MODE, ROWS, NPL, 2, 0>;
+    default: return (const void *)k_embed<PREC, MODE, ROWS, NPL, 4, 0>;
     }
 }
 
@@ -904,14 +896,21 @@ constexpr int npl_of_dims(int dims)
 }
 
 template <int PREC, int MODE, int SHAPE>
-const void *pick_fixed(int mt)
+const void *pick_fixed(int rows)
 {
     using SH = RowShape<SHAPE>;
     constexpr int NPL = npl_of_dims(SH::T + SH::M + SH::F);
-    switch (mt) {
-    case 1: return (const void *)k_embed<PREC, MODE, 1, NPL, SH::H, SHAPE>;
-    case 2: return (const void *)k_embed<PREC, MODE, 2, NPL, SH::H, SHAPE>;
-    default: return (const void *)k_embed<PREC, MODE, 3, NPL, SH::H, SHAPE>;
+    if constexpr (PREC == TIG_FP32)
+        switch (rows) {
+        case 4: return (const void *)k_embed<PREC, MODE, 4, NPL, SH::H, SHAPE>;
+        case 8: return (const void *)k_embed<PREC, MODE, 8, NPL, SH::H, SHAPE>;
+        case 24: return (const void *)k_embed<PREC, MODE, 24, NPL, SH::H, SHAPE>;
+        default: break;
+        }
+    switch (rows) {
+    case 16: return (const void *)k_embed<PREC, MODE, 16, NPL, SH::H, SHAPE>;
+    case 32: return (const void *)k_embed<PREC, MODE, 32, NPL, SH::H, SHAPE>;
+    default: return (const void *)k_embed<PREC, MODE, 48, NPL, SH::H, SHAPE>;
     }
 }
 
@@ -922,24 +921,31 @@ bool shape_is(const Dims &d)
     return d.T == SH::T && d.M == SH::M && d.F == SH::F && d.H == SH::H;
 }
 
-template <int PREC, int MODE, int MT>
+template <int PREC, int MODE, int ROWS>
 const void *pick_npl(int npl, int H)
 {
     switch (npl) {
-    case 1: return pick_h<PREC, MODE, MT, 1>(H);
-    case 2: return pick_h<PREC, MODE, MT, 2>(H);
-    case 4: return pick_h<PREC, MODE, MT, 4>(H);
-    default: return pick_h<PREC, MODE, MT, 8>(H);
+    case 1: return pick_h<PREC, MODE, ROWS, 1>(H);
+    case 2: return pick_h<PREC, MODE, ROWS, 2>(H);
+    case 4: return pick_h<PREC, MODE, ROWS, 4>(H);
+    default: return pick_h<PREC, MODE, ROWS, 8>(H);
     }
 }
 
 template <int PREC, int MODE>
-const void *pick_mt(int mt, int npl, int H)
+const void *pick_rows(int rows, int npl, int H)
 {
-    switch (mt) {
-    case 1: return pick_npl<PREC, MODE, 1>(npl, H);
-    case 2: return pick_npl<PREC, MODE, 2>(npl, H);
-    default: return pick_npl<PREC, MODE, 3>(npl, H);
+    if constexpr (PREC == TIG_FP32)
+        switch (rows) {
+        case 4: return pick_npl<PREC, MODE, 4>(npl, H);
+        case 8: return pick_npl<PREC, MODE, 8>(npl, H);
+        case 24: return pick_npl<PREC, MODE, 24>(npl, H);
+        default: break;
+        }
+    switch (rows) {
+    case 16: return pick_npl<PREC, MODE, 16>(npl, H);
+    case 32: return pick_npl<PREC, MODE, 32>(npl, H);
+    default: return pick_npl<PREC, MODE, 48>(npl, H);
     }
 }
 
@@ -948,15 +954,15 @@ const void *pick_mt(int mt, int npl, int H)
 // bring a training step 9% at 172 and 4% at 100 state columns (20 steps 4.85 -> 4.46 and 4.59 -> 4.43 ms) and two layers
 // over 4000 events 14% (148.6 -> 128.3 us).
 template <int PREC, int MODE>
-const void *pick(const Dims &d, int mt)
+const void *pick(const Dims &d, int rows)
 {
     if (shape_is<1>(d))
-        return pick_fixed<PREC, MODE, 1>(mt);
+        return pick_fixed<PREC, MODE, 1>(rows);
     if (shape_is<2>(d))
-        return pick_fixed<PREC, MODE, 2>(mt);
+        return pick_fixed<PREC, MODE, 2>(rows);
     if (shape_is<3>(d))
-        return pick_fixed<PREC, MODE, 3>(mt);
-    return pick_mt<PREC, MODE>(mt, npl_for(d), d.H);
+        return pick_fixed<PREC, MODE, 3>(rows);
+    return pick_rows<PREC, MODE>(rows, npl_for(d), d.H);
 }
 
 }  // namespace

@@ -9,7 +9,7 @@ namespace tig {
 
 namespace {
 
-EmbedParams embed_params(const Dims &d, int mt)
+EmbedParams embed_params(const Dims &d, int rows)
 {
     EmbedParams p;
     p.M = d.M;
@@ -24,7 +24,6 @@ EmbedParams embed_params(const Dims &d, int mt)
     p.K2 = d.K2;
     p.Ep = d.Ep;
     p.Ek = d.Ek;
-    const int rows = 16 * mt;
     p.row_bytes = lds_row_bytes(d.N1 + d.Mq);
     p.ld1 = lds_row_bytes(d.Ek);
     p.off_h1 = (rows * p.row_bytes + 15) / 16 * 16;
@@ -45,30 +44,40 @@ EmbedParams embed_params(const Dims &d, int mt)
 }
 
 // (kernels of each precision are a translation unit of their own)
-const void *embed_kernel(const Dims &d, int mt, bool train)
+const void *embed_kernel(const Dims &d, int rows, bool train)
 {
     if (train)
-        return embed_kernel_train(d, mt);
-    return d.prec == TIG_BF16_MFMA ? embed_kernel_bf16(d, mt) : embed_kernel_fp32(d, mt);
+        return embed_kernel_train(d, rows);
+    return d.prec == TIG_BF16_MFMA ? embed_kernel_bf16(d, rows) : embed_kernel_fp32(d, rows);
+}
+
+int lds_of(const Dims &d, int rows)
+{
+    const EmbedParams p = embed_params(d, rows);
+    return p.off_meta + rows * (4 * 4 + 8) + d.T * 16 + 16;
+}
+
+// Rows a workgroup's tile can have.  fp32 products keep the matrix units busy for as long as a tile has rows (172 state
+// columns: 18 of the 43 us of a launch over 600 rows, with half of every 16-row block empty), so fp32 tiles also come in 4
+// and 8 rows and in 24 (groups of four rows, Prec<TIG_FP32>::mma_four): a step of 200 events of 172 columns 54.3 -> 36.8 us, of
+// 500 57.6 -> 46.2, of 1600 92.7 -> 79.1, a training step of 200 224 -> 203.  bf16 products take a fifth of that and are bound by the
+// weights' way from L2, which is the same for any number of rows.
+constexpr int kHeights[] = {4, 8, 16, 24, 32, 48};
+bool height_of(bool fp32, int rows) { return fp32 || (rows % 16 == 0); }
+
+// The lowest tile whose workgroups, one per compute unit at hand, take `rows` query rows: a workgroup's latency grows
+// with its rows.
+int embed_height(bool fp32, int most_mt, int rows, int units)
+{
+    for (const int h : kHeights)
+        if (height_of(fp32, h) && h < 16 * most_mt && (rows + h - 1) / h <= units)
+            return h;
+    return 16 * most_mt;
 }
 
 }  // namespace
 
-int embed_lds_bytes(const Dims &d, int mt)
-{
-    const EmbedParams p = embed_params(d, mt);
-    return p.off_meta + 16 * mt * (4 * 4 + 8) + d.T * 16 + 16;
-}
-
-// 16-row tiles per workgroup for `rows` query rows.  A workgroup's latency grows with its rows,
-// so the smallest tile count is taken whose tiles, one per workgroup, fit the compute units at hand.
-static int embed_tiles(const LaunchPlan &plan, int rows, int units)
-{
-    for (int mt = 1; mt < plan.emb_mt; ++mt)
-        if ((rows + 16 * mt - 1) / (16 * mt) <= units)
-            return mt;
-    return plan.emb_mt;
-}
+int embed_lds_bytes(const Dims &d, int mt) { return lds_of(d, 16 * mt); }
 
 // Most 16-row tiles per workgroup that LDS holds for one layer of a stack (0: none).
 int layer_tiles(const Dims &d, int lds_limit)
@@ -81,11 +90,13 @@ int layer_tiles(const Dims &d, int lds_limit)
 
 hipError_t prepare_embed_layer(const Dims &d, int most_mt)
 {
-    for (int mt = 1; mt <= most_mt; ++mt) {
-        const int own = embed_lds_bytes(d, mt);
+    for (const int h : kHeights) {
+        if (!height_of(true, h) || h > 16 * most_mt)
+            continue;
+        const int own = lds_of(d, h);
         const int lds = embed_threads(d) == kScatterThreads && own < kOneLds ? kOneLds : own;
         const hipError_t e =
-            hipFuncSetAttribute(embed_kernel_layer(d, mt), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            hipFuncSetAttribute(embed_kernel_layer(d, h), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess)
             return e;
     }
@@ -94,11 +105,14 @@ hipError_t prepare_embed_layer(const Dims &d, int most_mt)
 
 hipError_t prepare_embed(const Dims &d, const LaunchPlan &plan, bool train)
 {
-    for (int mt = 1; mt <= plan.emb_mt; ++mt) {
-        const int own = embed_lds_bytes(d, mt);
+    const int most_mt = plan.emb_mt;
+    for (const int h : kHeights) {
+        if (!height_of(train || d.prec == TIG_FP32, h) || h > 16 * most_mt)
+            continue;
+        const int own = lds_of(d, h);
         const int lds = embed_threads(d) == kScatterThreads && own < kOneLds ? kOneLds : own;
         const hipError_t e =
-            hipFuncSetAttribute(embed_kernel(d, mt, train), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+            hipFuncSetAttribute(embed_kernel(d, h, train), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess)
             return e;
     }
@@ -154,19 +168,19 @@ hipError_t launch_embed(const Dims &d, const LaunchPlan &plan, const PackedWeigh
     // the grid covers the most rows the batch can have, and tiles beyond the actual count return).
     const int most = a.roles * a.count;
     const int rows = a.rows_est > 0 && a.rows_est < most ? a.rows_est : most;
-    const int mt = embed_tiles(plan, rows, units);
-    EmbedParams p = embed_params(d, mt);
+    const int height = embed_height(train || d.prec == TIG_FP32, plan.emb_mt, rows, units);
+    EmbedParams p = embed_params(d, height);
     // tiles in use if no query repeats (tiles_in_use)
     const int even = (most + kLeastRows - 1) / kLeastRows < units ? (most + kLeastRows - 1) / kLeastRows : units;
     p.spread = units;
-    p.n_tiles = (most + 16 * mt - 1) / (16 * mt);
+    p.n_tiles = (most + height - 1) / height;
     p.n_tiles = p.n_tiles > even ? p.n_tiles : even;
     p.n_commit = n_commit;
     p.commit_beside = beside ? 1 : 0;
     void *args[] = {&aa, &ww, &p};
-    const int own = embed_lds_bytes(d, mt);
+    const int own = lds_of(d, height);
     const int lds = a.sel.count > 0 && own < kOneLds ? kOneLds : (own < kPrepLds ? kPrepLds : own);
-    return hipLaunchKernel(embed_kernel(d, mt, train), dim3(p.n_tiles + extra), dim3(threads), args, (size_t)lds, s);
+    return hipLaunchKernel(embed_kernel(d, height, train), dim3(p.n_tiles + extra), dim3(threads), args, (size_t)lds, s);
 }
 
 // One attention layer over the rows of a.qs (d, pw: the layer's); a.rows_est (0: unknown) sizes the tiles.  The grid
@@ -180,17 +194,15 @@ hipError_t launch_embed_layer(const Dims &d, int most_mt, int num_cus, const Pac
     const int units = cus - extra > 16 ? cus - extra : 16;
     const int most = a.roles * a.count;
     const int rows = a.rows_est > 0 && a.rows_est < most ? a.rows_est : most;
-    LaunchPlan plan = {};
-    plan.emb_mt = most_mt;
-    const int mt = embed_tiles(plan, rows, units);
-    EmbedParams p = embed_params(d, mt);
+    const int height = embed_height(true, most_mt, rows, units);
+    EmbedParams p = embed_params(d, height);
     p.spread = units;
     p.n_tiles = (most + kLeastRows - 1) / kLeastRows;
     p.n_tiles = p.n_tiles < units ? p.n_tiles : units;
     void *args[] = {&aa, &ww, &p};
-    const int own = embed_lds_bytes(d, mt);
+    const int own = lds_of(d, height);
     const int lds = a.sel.count > 0 && own < kOneLds ? kOneLds : (own < kPrepLds ? kPrepLds : own);
-    return hipLaunchKernel(embed_kernel_layer(d, mt), dim3(p.n_tiles + extra), dim3(embed_threads(d)), args, (size_t)lds, s);
+    return hipLaunchKernel(embed_kernel_layer(d, height), dim3(p.n_tiles + extra), dim3(embed_threads(d)), args, (size_t)lds, s);
 }
 
 }  // namespace tig

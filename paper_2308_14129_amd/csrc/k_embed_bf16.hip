@@ -10,6 +10,6 @@ extern "C" __attribute__((visibility("default"))) int tig_debug_phase_clocks_bf1
 }
 #endif
 
-const void *embed_kernel_bf16(const Dims &d, int mt) { return pick<TIG_BF16_MFMA, kEmbedStep>(d, mt); }
+const void *embed_kernel_bf16(const Dims &d, int rows) { return pick<TIG_BF16_MFMA, kEmbedStep>(d, rows); }
 
 }  // namespace tig

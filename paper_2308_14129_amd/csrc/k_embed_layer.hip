@@ -3,6 +3,6 @@
 
 namespace tig {
 
-const void *embed_kernel_layer(const Dims &d, int mt) { return pick<TIG_FP32, kEmbedLayer>(d, mt); }
+const void *embed_kernel_layer(const Dims &d, int rows) { return pick<TIG_FP32, kEmbedLayer>(d, rows); }
 
 }  // namespace tig

@@ -58,6 +58,16 @@ struct Prec<TIG_FP32> {
         acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[2], b.v[2], acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[3], b.v[3], acc, 0, 0, 0);
     }
+    // Four rows: the 4x4x1 instruction's sixteen blocks take the weight operand as it lies (block l/4 of lane l: four
+    // columns, one k of the lane's four), a's row is l%4; lane group l/16 ends with its k's part of the four rows'
+    // sums (sum_groups).  A quarter of the sixteen rows' time.
+    static __device__ inline void mma_four(floatx4 &acc, const frag &a, const frag &b)
+    {
+        acc = __builtin_amdgcn_mfma_f32_4x4x1f32(a.v[0], b.v[0], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_4x4x1f32(a.v[1], b.v[1], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_4x4x1f32(a.v[2], b.v[2], acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_4x4x1f32(a.v[3], b.v[3], acc, 0, 0, 0);
+    }
 };
 
 // bf16 matrix cores with split operands: x = hi + lo, hi = bf16(x), lo = bf16(x - hi), for
@@ -286,7 +296,63 @@ __device__ inline unsigned long long winner_key(double t, int32_t eid, int role)
     return ((unsigned long long)mono << 32) | (unsigned long long)(((uint32_t)eid << 1) | (uint32_t)role);
 }
 
-// acc[mt] += A[16*mt .. 16*mt+15][k-blocks kb0 .. kb0+kblocks) x W[nt]^T.
+// Sums over the four 16-lane groups of a register quadruple: lane group g keeps the sum of register g (wave_sum_four's
+// exchanges).
+__device__ inline float sum_groups(const floatx4 &p)
+{
+    const auto ac = __builtin_amdgcn_permlane32_swap(__float_as_uint(p[0]), __float_as_uint(p[2]), false, false);
+    const auto bd = __builtin_amdgcn_permlane32_swap(__float_as_uint(p[1]), __float_as_uint(p[3]), false, false);
+    const float x = __uint_as_float(ac[0]) + __uint_as_float(ac[1]);
+    const float y = __uint_as_float(bd[0]) + __uint_as_float(bd[1]);
+    const auto xy = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(xy[0]) + __uint_as_float(xy[1]);
+}
+
+// The rows of a tile: 16 MT rows as MT blocks of the 16x16 instructions, then 4 RG rows (fp32 only) as RG groups of the
+// 4x4 ones.  acc[i]: block i < MT, row group i - MT beyond.
+template <int PREC, int MT, int RG>
+struct TileRows {
+    using P = Prec<PREC>;
+    using frag = typename P::frag;
+    static constexpr int kAcc = MT + RG;        // accumulators (of four registers) per output tile
+    static constexpr int kOut = 4 * MT + RG;    // results per lane
+    const char *a16, *a4;
+    int lda, g;
+    __device__ inline TileRows(const char *A, int lda_) : lda(lda_)
+    {
+        const int lane = lane_id();
+        g = lane >> 4;
+        a16 = A + (size_t)(lane & 15) * lda;
+        a4 = A + (size_t)(16 * MT + (lane & 3)) * lda;
+    }
+    __device__ inline frag load(int i, int kb) const
+    {
+        return P::load_a(i < MT ? a16 + (size_t)i * 16 * lda : a4 + (size_t)(i - MT) * 4 * lda, kb, g);
+    }
+    static __device__ inline void mma(int i, floatx4 &acc, const frag &a, const frag &b)
+    {
+        if constexpr (RG > 0) {
+            if (i >= MT) {
+                P::mma_four(acc, a, b);
+                return;
+            }
+        }
+        P::mma(acc, a, b);
+    }
+    // result o of the lane and its row; the column is lane % 16
+    static __device__ inline int row(int o)
+    {
+        return o < 4 * MT ? (o >> 2) * 16 + 4 * (lane_id() >> 4) + (o & 3) : 16 * MT + 4 * (o - 4 * MT) + (lane_id() >> 4);
+    }
+    static __device__ inline void results(const floatx4 (&acc)[MT + RG], float (&out)[4 * MT + RG])
+    {
+#pragma unroll
+        for (int o = 0; o < kOut; ++o)
+            out[o] = o < 4 * MT ? acc[o >> 2][o & 3] : sum_groups(acc[o < 4 * MT ? 0 : o - 3 * MT]);
+    }
+};
+
+// acc += A[the tile's rows][k-blocks kb0 .. kb0+kblocks) x W[nt]^T.
 // A: LDS rows of `lda` BYTES (4 bytes per element in either precision); A's k-block kb0+i pairs
 // with W's k-block w_kb0+i.  W: lane-ordered blocks, `w_kblocks` per output tile.
 // Weight operands come from L2 and the loop is latency-bound, so up to DEPTH operand loads are
@@ -294,28 +360,28 @@ __device__ inline unsigned long long winner_key(double t, int32_t eid, int role)
 // PARTS (training step, layers of a stack): every group is summed on its own and added to acc, not all products one after the other (the
 // rounding of a chain grows with its length; embeddings of 30 shapes: 2.9e-7 off 64 bits in one chain of up to 400
 // terms, 2.2e-7 in parts of 64 or 80, and 1 us of 45 more).
-template <int PREC, int MT, int DEPTH, bool PARTS = false>
-__device__ inline void tile_gemm(floatx4 (&acc)[MT], const char *A, int lda, int a_kb0, const void *W,
+template <int PREC, int MT, int DEPTH, bool PARTS = false, int RG = 0>
+__device__ inline void tile_gemm(floatx4 (&acc)[MT + RG], const char *A, int lda, int a_kb0, const void *W,
                                  int w_kblocks, int w_kb0, int kblocks, int nt)
 {
     using P = Prec<PREC>;
+    using R = TileRows<PREC, MT, RG>;
     using frag = typename P::frag;
     const int lane = lane_id();
     const size_t w0 = ((size_t)nt * w_kblocks + w_kb0) * kWave + lane;
-    const char *ap = A + (size_t)(lane & 15) * lda;
-    const int g = lane >> 4;
-    floatx4 part[MT];
+    const R rows(A, lda);
+    floatx4 part[R::kAcc];
     auto begin = [&]() {
         if constexpr (PARTS)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                part[mt] = floatx4{0, 0, 0, 0};
+            for (int i = 0; i < R::kAcc; ++i)
+                part[i] = floatx4{0, 0, 0, 0};
     };
     auto end = [&]() {
         if constexpr (PARTS)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                acc[mt] += part[mt];
+            for (int i = 0; i < R::kAcc; ++i)
+                acc[i] += part[i];
     };
     int kb = 0;
     for (; kb + DEPTH <= kblocks; kb += DEPTH) {
@@ -327,9 +393,9 @@ __device__ inline void tile_gemm(floatx4 (&acc)[MT], const char *A, int lda, int
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u) {
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const frag afrag = P::load_a(ap + (size_t)mt * 16 * lda, a_kb0 + kb + u, g);
-                P::mma(PARTS ? part[mt] : acc[mt], afrag, bfrag[u]);
+            for (int i = 0; i < R::kAcc; ++i) {
+                const frag afrag = rows.load(i, a_kb0 + kb + u);
+                R::mma(i, PARTS ? part[i] : acc[i], afrag, bfrag[u]);
             }
         }
         end();
@@ -345,9 +411,9 @@ __device__ inline void tile_gemm(floatx4 (&acc)[MT], const char *A, int lda, int
         for (int u = 0; u < DEPTH; ++u) {
             if (kb + u < kblocks) {
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const frag afrag = P::load_a(ap + (size_t)mt * 16 * lda, a_kb0 + kb + u, g);
-                    P::mma(PARTS ? part[mt] : acc[mt], afrag, bfrag[u]);
+                for (int i = 0; i < R::kAcc; ++i) {
+                    const frag afrag = rows.load(i, a_kb0 + kb + u);
+                    R::mma(i, PARTS ? part[i] : acc[i], afrag, bfrag[u]);
                 }
             }
         }
@@ -355,54 +421,20 @@ __device__ inline void tile_gemm(floatx4 (&acc)[MT], const char *A, int lda, int
     }
 }
 
-// The same for two output tiles nt1, nt2 of one weight matrix: every operand of A is read from
-// LDS once and meets the weights of both tiles (the A reads, not the matrix cores, bound these
-// small products).
-template <int PREC, int MT, int DEPTH>
-__device__ inline void tile_gemm_two(floatx4 (&acc1)[MT], floatx4 (&acc2)[MT], const char *A, int lda, int a_kb0,
-                                     const void *W, int w_kblocks, int kblocks, int nt1, int nt2)
-{
-    using P = Prec<PREC>;
-    using frag = typename P::frag;
-    const int lane = lane_id();
-    const size_t w1 = (size_t)nt1 * w_kblocks * kWave + lane;
-    const size_t w2 = (size_t)nt2 * w_kblocks * kWave + lane;
-    const char *ap = A + (size_t)(lane & 15) * lda;
-    const int g = lane >> 4;
-    for (int kb = 0; kb < kblocks; kb += DEPTH) {
-        frag b1[DEPTH], b2[DEPTH];
-#pragma unroll
-        for (int u = 0; u < DEPTH; ++u)
-            if (kb + u < kblocks) {
-                b1[u] = P::load_w(W, w1 + (size_t)(kb + u) * kWave);
-                b2[u] = P::load_w(W, w2 + (size_t)(kb + u) * kWave);
-            }
-#pragma unroll
-        for (int u = 0; u < DEPTH; ++u)
-            if (kb + u < kblocks) {
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const frag afrag = P::load_a(ap + (size_t)mt * 16 * lda, a_kb0 + kb + u, g);
-                    P::mma(acc1[mt], afrag, b1[u]);
-                    P::mma(acc2[mt], afrag, b2[u]);
-                }
-            }
-    }
-}
-
-// The same for one output tile of each of two weight matrices with equal k depth (both over all
-// k-blocks of A from 0).
-template <int PREC, int MT, int DEPTH>
-__device__ inline void tile_gemm_pair(floatx4 (&acc1)[MT], floatx4 (&acc2)[MT], const char *A, int lda,
+// The same for one output tile of each of two weight matrices (or two tiles of one) with equal k depth: every operand of A
+// is read from LDS once and meets the weights of both tiles (the A reads bound these small products where the rows are
+// many).
+template <int PREC, int MT, int DEPTH, int RG = 0>
+__device__ inline void tile_gemm_pair(floatx4 (&acc1)[MT + RG], floatx4 (&acc2)[MT + RG], const char *A, int lda, int a_kb0,
                                       const void *W1, const void *W2, int kblocks, int nt1, int nt2)
 {
     using P = Prec<PREC>;
+    using R = TileRows<PREC, MT, RG>;
     using frag = typename P::frag;
     const int lane = lane_id();
     const size_t w1 = (size_t)nt1 * kblocks * kWave + lane;
     const size_t w2 = (size_t)nt2 * kblocks * kWave + lane;
-    const char *ap = A + (size_t)(lane & 15) * lda;
-    const int g = lane >> 4;
+    const R rows(A, lda);
     for (int kb = 0; kb < kblocks; kb += DEPTH) {
         frag b1[DEPTH], b2[DEPTH];
 #pragma unroll
@@ -415,10 +447,10 @@ __device__ inline void tile_gemm_pair(floatx4 (&acc1)[MT], floatx4 (&acc2)[MT], 
         for (int u = 0; u < DEPTH; ++u)
             if (kb + u < kblocks) {
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const frag afrag = P::load_a(ap + (size_t)mt * 16 * lda, kb + u, g);
-                    P::mma(acc1[mt], afrag, b1[u]);
-                    P::mma(acc2[mt], afrag, b2[u]);
+                for (int i = 0; i < R::kAcc; ++i) {
+                    const frag afrag = rows.load(i, a_kb0 + kb + u);
+                    R::mma(i, acc1[i], afrag, b1[u]);
+                    R::mma(i, acc2[i], afrag, b2[u]);
                 }
             }
     }

@@ -112,6 +112,14 @@ def test_c1_step_locked_fp32_ragged_tiles_and_short_tail(c1):
     run(c1, "fp32", list(S.batches(c1.w.num_events, 136))[:12] + [(9990, 10)], locked=True)
 
 
+# 3 x count distinct queries over 224 compute units or more (side workgroups take up to 32): tiles of 4, 8, 16, 24 and 48
+# rows, two sizes on either side of a change, the last tiles short.  In fp32 the heights differ in which matrix
+# instructions a row's products run on; 32 rows and bf16 are covered by the other tests.
+@pytest.mark.parametrize("count", [298, 305, 597, 1100, 1290, 1790, 2600])
+def test_fp32_tile_heights(c1, count):
+    run(c1, "fp32", [(2000, count), (2000 + count, count), (2000 + 2 * count, count // 3)], locked=False, warm_at=2000)
+
+
 def test_c1_without_negatives(c1):
     run(c1, "fp32", list(S.batches(c1.w.num_events, 200))[:4], locked=False, with_neg=False)
 
