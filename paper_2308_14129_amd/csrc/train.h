@@ -36,7 +36,7 @@ struct BackParams {
     int row_bytes;            // LDS bytes per row: [DA | DB | d emb], then [d kvbar / d q~ (N1) | d s_u (Mq)]
     int ldz;                  // LDS bytes per row of d z1
     int off_z, off_meta, off_tab;
-    int rpt;                  // rows a workgroup takes, 8 .. 16 MT (the rest of its tile's rows stay empty)
+    int rpt;                  // rows a workgroup takes, 4 .. ROWS (the rest of its tile's rows stay empty)
     int slots;                // rows of the LDS table that collects the staged rows' gradients (0: none)
 };
 

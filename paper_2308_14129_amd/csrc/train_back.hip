@@ -6,7 +6,7 @@
 // LDS and leave per row only what the weight gradients contract over:
 //   k_tr_decode    per event: logits, loss terms, and the gradients of the two decoder halves' pre-activations
 //                  added to their rows (a row is shared by every event that asked for the same query)
-//   k_tr_back      16 MT query rows per workgroup: decoder halves -> embedding -> merge MLP -> attention ->
+//   k_tr_back      4 to 32 query rows per workgroup: decoder halves -> embedding -> merge MLP -> attention ->
 //                  folded query, as matrix-core products and one wavefront per row for the attention; the
 //                  gradients of state rows that this step's GRU wrote are collected in an LDS table
 //   k_tr_gru_back  16 applied winners per workgroup: gradients of the gates' pre-activations, time encoding
@@ -138,18 +138,19 @@ struct BackShape {
     static constexpr int KC = NPL >= 6 && H >= 4 ? 6 : 10;  // neighbour rows in registers at a time
 };
 
-// acc[j] += A[16 mt ..][k-blocks a_kb0 .. + n) x W[nt[j]]^T over W's k-blocks [w_kb0, w_kb0 + n), for NT output tiles
+// acc[j] += A[the tile's rows][k-blocks a_kb0 .. + n) x W[nt[j]]^T over W's k-blocks [w_kb0, w_kb0 + n), for NT output tiles
 // that share the reads of A.  With eight wavefronts on a unit a product is as long as its round trips to L2, so up to
 // DEPTH blocks of every tile's weights are requested together (a block beyond n repeats the last and is not used).
 // Products are summed two blocks (32 terms) at a time, see tile_gemm's PARTS.
-template <int MT, int NT, int DEPTH>
-__device__ inline void tile_gemm_deep(floatx4 (&acc)[NT][MT], const char *A, int lda, int a_kb0, const void *W, int w_kblocks,
+template <int MT, int RG, int NT, int DEPTH>
+__device__ inline void tile_gemm_deep(floatx4 (&acc)[NT][MT + RG], const char *A, int lda, int a_kb0, const void *W, int w_kblocks,
                                       int w_kb0, int n, const int (&nt)[NT])
 {
     using P = Prec<TIG_FP32>;
+    using TR = TileRows<TIG_FP32, MT, RG>;
     using frag = typename P::frag;
-    const int lane = lane_id(), g = lane >> 4;
-    const char *ap = A + (size_t)(lane & 15) * lda;
+    const int lane = lane_id();
+    const TR rows(A, lda);
     for (int kb = 0; kb < n; kb += DEPTH) {
         frag b[NT][DEPTH];
 #pragma unroll
@@ -163,35 +164,36 @@ __device__ inline void tile_gemm_deep(floatx4 (&acc)[NT][MT], const char *A, int
         for (int u0 = 0; u0 < DEPTH; u0 += 2) {
             if (kb + u0 >= n)  // (uniform)
                 break;
-            floatx4 part[NT][MT] = {};
+            floatx4 part[NT][TR::kAcc] = {};
 #pragma unroll
             for (int u = u0; u < u0 + 2 && u < DEPTH; ++u)
                 if (kb + u < n) {  // (uniform)
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        const frag a = P::load_a(ap + (size_t)mt * 16 * lda, a_kb0 + kb + u, g);
+                    for (int i = 0; i < TR::kAcc; ++i) {
+                        const frag a = rows.load(i, a_kb0 + kb + u);
 #pragma unroll
                         for (int j = 0; j < NT; ++j)
-                            P::mma(part[j][mt], a, b[j][u]);
+                            TR::mma(i, part[j][i], a, b[j][u]);
                     }
                 }
 #pragma unroll
             for (int j = 0; j < NT; ++j)
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[j][mt] += part[j][mt];
+                for (int i = 0; i < TR::kAcc; ++i)
+                    acc[j][i] += part[j][i];
         }
     }
 }
 
 // NPHI: 64-column pieces of a row that hold time-encoding columns (they come first).
-template <int MT, int NPL, int NPHI, int H>
+template <int ROWS, int NPL, int NPHI, int H>
 __global__ void __launch_bounds__(kBackThreads)
 k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
 {
     using P = Prec<TIG_FP32>;
     constexpr int kThreads = kBackThreads, kWaves = kThreads / kWave, KC = BackShape<NPL, H>::KC;
-    constexpr int ROWS = 16 * MT;
+    constexpr int MT = ROWS / 16, RG = ROWS % 16 / 4;
+    using TR = TileRows<TIG_FP32, MT, RG>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     char *X = smem, *Z = smem + p.off_z;
     double *row_t = (double *)(smem + p.off_meta);  // [ROWS] query time
@@ -257,47 +259,43 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
     TIG_MARK(1);
     // ---- 2. d emb = W_d1[:, :E]^T DA + W_d1[:, E:]^T DB -> X behind them
     for (int nt = wave; nt < p.Ep / 16; nt += kWaves) {
-        floatx4 acc1[1][MT];
-        clear(acc1);
-        tile_gemm_deep<MT, 1, 16>(acc1, X, p.row_bytes, 0, t.Wd1T, 2 * kbE, 0, 2 * kbE, {nt});
-        const floatx4 (&acc)[MT] = acc1[0];
+        floatx4 acc[1][TR::kAcc];
+        float d[TR::kOut];
+        clear(acc);
+        tile_gemm_deep<MT, RG, 1, 16>(acc, X, p.row_bytes, 0, t.Wd1T, 2 * kbE, 0, 2 * kbE, {nt});
+        TR::results(acc[0], d);
         const int col = nt * 16 + (lane & 15);
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = mt * 16 + 4 * (lane >> 4) + v, q = row_q[row];
-                ((float *)(X + (size_t)row * p.row_bytes))[2 * p.Ek + col] = acc[mt][v];
-                if (q >= 0 && col < p.E)
-                    t.DEMB[(size_t)q * p.E + col] = acc[mt][v];
-            }
+        for (int o = 0; o < TR::kOut; ++o) {
+            const int row = TR::row(o), q = row_q[row];
+            ((float *)(X + (size_t)row * p.row_bytes))[2 * p.Ek + col] = d[o];
+            if (q >= 0 && col < p.E)
+                t.DEMB[(size_t)q * p.E + col] = d[o];
+        }
     }
     __syncthreads();
     // ---- 3. d z1 = (W_m2^T d emb) where h1 > 0 -> Z
     for (int nt = wave; nt < p.Ep / 16; nt += kWaves) {
-        floatx4 acc1[1][MT];
-        clear(acc1);
-        const floatx4 (&acc)[MT] = acc1[0];
+        floatx4 acc[1][TR::kAcc];
+        float d[TR::kOut];
+        clear(acc);
         const int col = nt * 16 + (lane & 15);
-        float h1[MT][4];
+        float h1[TR::kOut];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int o = 0; o < TR::kOut; ++o) {
+            const int q = row_q[TR::row(o)];
+            h1[o] = t.H1[(size_t)(q >= 0 ? q : 0) * p.E + (col < p.E ? col : 0)];
+        }
+        tile_gemm_deep<MT, RG, 1, 8>(acc, X, p.row_bytes, 2 * kbE, t.Wm2T, kbE, 0, kbE, {nt});
+        TR::results(acc[0], d);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int q = row_q[mt * 16 + 4 * (lane >> 4) + v];
-                h1[mt][v] = t.H1[(size_t)(q >= 0 ? q : 0) * p.E + (col < p.E ? col : 0)];
-            }
-        tile_gemm_deep<MT, 1, 8>(acc1, X, p.row_bytes, 2 * kbE, t.Wm2T, kbE, 0, kbE, {nt});
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = mt * 16 + 4 * (lane >> 4) + v, q = row_q[row];
-                const float g = q >= 0 && col < p.E && h1[mt][v] > 0.0f ? acc[mt][v] : 0.0f;
-                ((float *)(Z + (size_t)row * p.ldz))[col] = g;
-                if (q >= 0 && col < p.E)
-                    t.DZ1[(size_t)q * p.E + col] = g;
-            }
+        for (int o = 0; o < TR::kOut; ++o) {
+            const int row = TR::row(o), q = row_q[row];
+            const float g = q >= 0 && col < p.E && h1[o] > 0.0f ? d[o] : 0.0f;
+            ((float *)(Z + (size_t)row * p.ldz))[col] = g;
+            if (q >= 0 && col < p.E)
+                t.DZ1[(size_t)q * p.E + col] = g;
+        }
     }
     __syncthreads();
     TIG_MARK(2);
@@ -306,8 +304,8 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
     {
         using frag = typename P::frag;
         constexpr int kDeep = 7;
-        const int n_nt = p.K2 / 16, g = lane >> 4;
-        const char *zp = Z + (size_t)(lane & 15) * p.ldz;
+        const int n_nt = p.K2 / 16;
+        const TR rows(Z, p.ldz);
         auto request = [&](frag (&b)[2][kDeep], int nt, int kb0) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
@@ -323,7 +321,7 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
         if (wave < n_nt)
             request(cur, wave, 0);
         for (int nt = wave; nt < n_nt; nt += 2 * kWaves) {
-            floatx4 acc[2][MT];
+            floatx4 acc[2][TR::kAcc];
             clear(acc);
             for (int kb = 0; kb < kbE; kb += kDeep) {
                 const bool last = kb + kDeep >= kbE;
@@ -332,11 +330,11 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
                 for (int u = 0; u < kDeep; ++u)
                     if (kb + u < kbE) {  // (uniform)
 #pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) {
-                            const frag a = P::load_a(zp + (size_t)mt * 16 * p.ldz, kb + u, g);
+                        for (int i = 0; i < TR::kAcc; ++i) {
+                            const frag a = rows.load(i, kb + u);
 #pragma unroll
                             for (int j = 0; j < 2; ++j)
-                                P::mma(acc[j][mt], a, cur[j][u]);
+                                TR::mma(i, acc[j][i], a, cur[j][u]);
                         }
                     }
 #pragma unroll
@@ -348,14 +346,14 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int col = (nt + j * kWaves) * 16 + (lane & 15);
+                float d[TR::kOut];
+                TR::results(acc[j], d);
                 if (nt + j * kWaves < n_nt)  // (uniform)
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int row = mt * 16 + 4 * (lane >> 4) + v;
-                            ((float *)(X + (size_t)row * p.row_bytes))[col] = col >= p.N1 || row_cnt[row] > 0 ? acc[j][mt][v] : 0.0f;
-                        }
+                    for (int o = 0; o < TR::kOut; ++o) {
+                        const int row = TR::row(o);
+                        ((float *)(X + (size_t)row * p.row_bytes))[col] = col >= p.N1 || row_cnt[row] > 0 ? d[o] : 0.0f;
+                    }
             }
         }
     }
@@ -582,15 +580,15 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
     TIG_MARK(4);
     // ---- 6. d s_u += A1^T d q~
     for (int nt = wave; nt < p.Mq / 16; nt += kWaves) {
-        floatx4 acc[1][MT];
+        floatx4 acc[1][TR::kAcc];
+        float d[TR::kOut];
         clear(acc);
-        tile_gemm_deep<MT, 1, 14>(acc, X, p.row_bytes, 0, t.A1T, p.N1 / P::KB, 0, p.N1 / P::KB, {nt});
+        tile_gemm_deep<MT, RG, 1, 14>(acc, X, p.row_bytes, 0, t.A1T, p.N1 / P::KB, 0, p.N1 / P::KB, {nt});
+        TR::results(acc[0], d);
         const int col = p.N1 + nt * 16 + (lane & 15);
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                ((float *)(X + (size_t)(mt * 16 + 4 * (lane >> 4) + v) * p.row_bytes))[col] += acc[0][mt][v];
+        for (int o = 0; o < TR::kOut; ++o)
+            ((float *)(X + (size_t)TR::row(o) * p.row_bytes))[col] += d[o];
     }
     __syncthreads();
     TIG_MARK(5);
@@ -733,16 +731,19 @@ __global__ void __launch_bounds__(kGbThreads) k_tr_gru_back(StepArgs a, PackedWe
 // ------------------------------------------------------------------------------------------
 // host side
 
-BackParams back_params(const Dims &d, int mt, int lds_limit, int *lds)
+BackParams back_params(const Dims &d, int rows, int lds_limit, int *lds)
 {
     BackParams p = {};
     p.M = d.M, p.T = d.T, p.F = d.F, p.E = d.E, p.K = d.K;
     p.dkv = d.dkv, p.dkvp = d.dkvp, p.Mq = d.Mq, p.N1 = d.N1, p.K2 = d.K2, p.Ep = d.Ep, p.Ek = d.Ek;
-    const int rows = 16 * mt, wide = d.K2 > 3 * d.Ek ? d.K2 : 3 * d.Ek;
+    const int wide = d.K2 > 3 * d.Ek ? d.K2 : 3 * d.Ek;
     p.row_bytes = lds_row_bytes(wide);
     p.ldz = lds_row_bytes(d.Ek);
     p.off_z = rows * p.row_bytes;
     p.off_meta = p.off_z + rows * p.ldz;
+    // (the wavefronts' time-encoding sums take the place of both at the end)
+    const int sums = (kBackThreads / kWave) * d.T * 8;
+    p.off_meta = p.off_meta > sums ? p.off_meta : sums;
     p.off_tab = (p.off_meta + rows * 20 + d.T * 16 + 16 + 15) / 16 * 16;
     // as many table rows as fit: hubs are few, but every row that misses the table costs device atomics
     const int slot_bytes = 8 * d.M + 4;
@@ -762,35 +763,46 @@ int back_npl(const Dims &d)
     return need <= 2 ? 2 : (need <= 4 ? 4 : (need <= 6 ? 6 : need));
 }
 
-template <int MT, int NPL, int NPHI>
+template <int ROWS, int NPL, int NPHI>
 const void *pick_back_h(int H)
 {
-    return H == 1   ? (const void *)k_tr_back<MT, NPL, NPHI, 1>
-           : H == 2 ? (const void *)k_tr_back<MT, NPL, NPHI, 2>
-                    : (const void *)k_tr_back<MT, NPL, NPHI, 4>;
+    return H == 1   ? (const void *)k_tr_back<ROWS, NPL, NPHI, 1>
+           : H == 2 ? (const void *)k_tr_back<ROWS, NPL, NPHI, 2>
+                    : (const void *)k_tr_back<ROWS, NPL, NPHI, 4>;
 }
 
-template <int MT>
+template <int ROWS>
 const void *pick_back(const Dims &d)
 {
     const bool few = d.T <= 2 * kWave;
     switch (back_npl(d)) {
-    case 2: return pick_back_h<MT, 2, 2>(d.H);
-    case 4: return few ? pick_back_h<MT, 4, 2>(d.H) : pick_back_h<MT, 4, 4>(d.H);
-    case 6: return few ? pick_back_h<MT, 6, 2>(d.H) : pick_back_h<MT, 8, 8>(d.H);
-    case 7: return few ? pick_back_h<MT, 7, 2>(d.H) : pick_back_h<MT, 8, 8>(d.H);
-    default: return few ? pick_back_h<MT, 8, 2>(d.H) : pick_back_h<MT, 8, 8>(d.H);
+    case 2: return pick_back_h<ROWS, 2, 2>(d.H);
+    case 4: return few ? pick_back_h<ROWS, 4, 2>(d.H) : pick_back_h<ROWS, 4, 4>(d.H);
+    case 6: return few ? pick_back_h<ROWS, 6, 2>(d.H) : pick_back_h<ROWS, 8, 8>(d.H);
+    case 7: return few ? pick_back_h<ROWS, 7, 2>(d.H) : pick_back_h<ROWS, 8, 8>(d.H);
+    default: return few ? pick_back_h<ROWS, 8, 2>(d.H) : pick_back_h<ROWS, 8, 8>(d.H);
     }
 }
 
-const void *back_kernel(const Dims &d, int mt) { return mt == 1 ? pick_back<1>(d) : pick_back<2>(d); }
+// rows of a workgroup's tile the kernel is compiled for
+constexpr int kBackHeights[] = {4, 8, 16, 32};
 
-// most 16-row tiles per workgroup: a second one only where the table keeps enough rows beside it
-int back_most_tiles(const Dims &d)
+const void *back_kernel(const Dims &d, int rows)
+{
+    switch (rows) {
+    case 4: return pick_back<4>(d);
+    case 8: return pick_back<8>(d);
+    case 16: return pick_back<16>(d);
+    default: return pick_back<32>(d);
+    }
+}
+
+// most rows per workgroup: a second block of sixteen only where the table keeps enough rows beside it
+int back_most_rows(const Dims &d)
 {
     int lds = 0;
-    const BackParams p = back_params(d, 2, kBackLds, &lds);
-    return lds <= kBackLds && p.slots >= 48 ? 2 : 1;
+    const BackParams p = back_params(d, 32, kBackLds, &lds);
+    return lds <= kBackLds && p.slots >= 48 ? 32 : 16;
 }
 
 GruBackParams gru_back_params(const Dims &d)
@@ -817,7 +829,7 @@ int decode_lds_bytes(const Dims &d) { return kDecWaves * (d.E + 1) * 4; }
 bool train_back_fits(const Dims &d)
 {
     int lds = 0;
-    (void)back_params(d, 1, kBackLds, &lds);
+    (void)back_params(d, 16, kBackLds, &lds);
     return lds <= kBackLds && gru_back_lds(d) <= kBackLds && d.E <= kDecCols * kWave && d.K <= kWave;
 }
 
@@ -826,10 +838,12 @@ hipError_t prepare_train_back(const Dims &d)
     hipError_t e = hipFuncSetAttribute((const void *)k_tr_decode, hipFuncAttributeMaxDynamicSharedMemorySize, decode_lds_bytes(d));
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void *)k_tr_gru_back, hipFuncAttributeMaxDynamicSharedMemorySize, gru_back_lds(d));
-    for (int mt = 1; mt <= back_most_tiles(d) && e == hipSuccess; ++mt) {
+    for (const int h : kBackHeights) {
+        if (h > back_most_rows(d) || e != hipSuccess)
+            break;
         int lds = 0;
-        (void)back_params(d, mt, kBackLds, &lds);
-        e = hipFuncSetAttribute(back_kernel(d, mt), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        (void)back_params(d, h, kBackLds, &lds);
+        e = hipFuncSetAttribute(back_kernel(d, h), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     }
     return e;
 }
@@ -844,21 +858,23 @@ hipError_t launch_train_decode(const Dims &d, const StepArgs &a, const PackedWei
 hipError_t launch_train_back(const Dims &d, const LaunchPlan &plan, const StepArgs &a, const PackedWeights &pw,
                              const TrainArrays &t, hipStream_t s)
 {
-    // one round of workgroups if 16-row tiles of the rows recent steps had fit the compute units, else taller tiles
+    // One round of workgroups: the rows recent steps had dealt evenly over the compute units, into the lowest tile that
+    // takes a unit's share (the products' time follows the tile's rows, see embed_height; the attention's the rows in use).
     const int most = 3 * a.count, rows = a.rows_est > 0 && a.rows_est < most ? a.rows_est : most;
     const int cus = plan.num_cus > 0 ? plan.num_cus : 256;
-    const int mt = (rows + 15) / 16 <= cus ? 1 : back_most_tiles(d);
+    const int even = (rows + cus - 1) / cus, tallest = back_most_rows(d);
+    int height = tallest;
+    for (const int h : kBackHeights)
+        if (h >= even && h < height)
+            height = h;
     int lds = 0;
     StepArgs aa = a;
     PackedWeights ww = pw;
     TrainArrays tt = t;
-    BackParams p = back_params(d, mt, kBackLds, &lds);
-    // (the rows dealt evenly over the compute units, eight per workgroup -- one per wavefront in the attention phase -- at
-    // least: the products' time does not depend on how many rows of a tile are in use, the attention's does)
-    const int even = (rows + cus - 1) / cus;
-    p.rpt = even < 8 ? 8 : (even > 16 * mt ? 16 * mt : even);
+    BackParams p = back_params(d, height, kBackLds, &lds);
+    p.rpt = even < 4 ? 4 : (even > height ? height : even);
     void *args[] = {&aa, &ww, &tt, &p};
-    return hipLaunchKernel(back_kernel(d, mt), dim3((most + p.rpt - 1) / p.rpt), dim3(kBackThreads), args, (size_t)lds, s);
+    return hipLaunchKernel(back_kernel(d, height), dim3((most + p.rpt - 1) / p.rpt), dim3(kBackThreads), args, (size_t)lds, s);
 }
 
 hipError_t launch_train_gru_back(const Dims &d, const StepArgs &a, const PackedWeights &pw, const TrainArrays &t, hipStream_t s)

@@ -240,6 +240,13 @@ def test_gradients_at_the_edges_of_the_kernels(dims, count):
     run_training(b, [(4000, count), (4000 + count, count // 2)], 0.0, "deferred", warm_at=4000)
 
 
+@pytest.mark.parametrize("count", [85, 341, 400, 1360, 1600])
+def test_gradients_at_each_tile_height(count):
+    # 3 x count rows over 256 compute units: tiles of 4, 4 (full), 8, 16 and 32 rows in the backward pass
+    b = Bundle(S.WORKLOADS["c1_tiny"].scaled(mem_dim=21, time_dim=13, feat_dim=6, emb_dim=35, num_neighbors=6, num_heads=2))
+    run_training(b, [(4000, count), (4000 + count, count)], 0.0, "deferred", warm_at=4000)
+
+
 @pytest.mark.parametrize("dims,count", EDGE_SHAPES)
 def test_sgd_steps_at_the_edges_of_the_kernels(dims, count):
     # the weights that a step prepares for the next one, at widths that no tile or load divides: forward pass and
