@@ -133,14 +133,17 @@ __device__ inline float wave_max_uniform(float v)
 // registers (sixteen wavefronts of 128 spilled up to 160 of them: 84 instead of 12 us for the attention phase of sixteen
 // rows of 444 columns and two heads).
 constexpr int kBackThreads = 512;
-template <int NPL, int H>
+// A tile of four rows has two wavefronts for each, which take every other neighbour slot: the attention of one row of ten
+// 444-column slots 13.4 -> 7.8 us (one wavefront's registers also spilled, 47 of them).
+template <int NPL, int H, int ROWS>
 struct BackShape {
-    static constexpr int KC = NPL >= 6 && H >= 4 ? 6 : 10;  // neighbour rows in registers at a time
+    static constexpr int KC = NPL >= 6 && (H >= 4 || ROWS == 4) ? 6 : 10;  // neighbour rows in registers at a time
 };
 
 // acc[j] += A[the tile's rows][k-blocks a_kb0 .. + n) x W[nt[j]]^T over W's k-blocks [w_kb0, w_kb0 + n), for NT output tiles
-// that share the reads of A.  With eight wavefronts on a unit a product is as long as its round trips to L2, so up to
-// DEPTH blocks of every tile's weights are requested together (a block beyond n repeats the last and is not used).
+// that share the reads of A.  With eight wavefronts on a unit a product is as long as its round trips to L2, so DEPTH
+// blocks of every tile's weights are requested together (a block beyond n repeats the last and is not used), the next
+// DEPTH while these are multiplied.
 // Products are summed two blocks (32 terms) at a time, see tile_gemm's PARTS.
 template <int MT, int RG, int NT, int DEPTH>
 __device__ inline void tile_gemm_deep(floatx4 (&acc)[NT][MT + RG], const char *A, int lda, int a_kb0, const void *W, int w_kblocks,
@@ -151,8 +154,7 @@ __device__ inline void tile_gemm_deep(floatx4 (&acc)[NT][MT + RG], const char *A
     using frag = typename P::frag;
     const int lane = lane_id();
     const TR rows(A, lda);
-    for (int kb = 0; kb < n; kb += DEPTH) {
-        frag b[NT][DEPTH];
+    auto request = [&](frag (&b)[NT][DEPTH], int kb) {
 #pragma unroll
         for (int u = 0; u < DEPTH; ++u) {
             const int kc = kb + u < n ? kb + u : n - 1;
@@ -160,6 +162,8 @@ __device__ inline void tile_gemm_deep(floatx4 (&acc)[NT][MT + RG], const char *A
             for (int j = 0; j < NT; ++j)
                 b[j][u] = P::load_w(W, ((size_t)nt[j] * w_kblocks + w_kb0 + kc) * kWave + lane);
         }
+    };
+    auto multiply = [&](const frag (&b)[NT][DEPTH], int kb) {
 #pragma unroll
         for (int u0 = 0; u0 < DEPTH; u0 += 2) {
             if (kb + u0 >= n)  // (uniform)
@@ -182,6 +186,18 @@ __device__ inline void tile_gemm_deep(floatx4 (&acc)[NT][MT + RG], const char *A
                 for (int i = 0; i < TR::kAcc; ++i)
                     acc[j][i] += part[j][i];
         }
+    };
+    frag b0[NT][DEPTH], b1[NT][DEPTH];
+    request(b0, 0);
+    for (int kb = 0; kb < n; kb += 2 * DEPTH) {
+        if (kb + DEPTH < n)  // (uniform)
+            request(b1, kb + DEPTH);
+        multiply(b0, kb);
+        if (kb + DEPTH >= n)
+            break;
+        if (kb + 2 * DEPTH < n)
+            request(b0, kb + 2 * DEPTH);
+        multiply(b1, kb + DEPTH);
     }
 }
 
@@ -191,7 +207,9 @@ __global__ void __launch_bounds__(kBackThreads)
 k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
 {
     using P = Prec<TIG_FP32>;
-    constexpr int kThreads = kBackThreads, kWaves = kThreads / kWave, KC = BackShape<NPL, H>::KC;
+    constexpr int kThreads = kBackThreads, kWaves = kThreads / kWave, KC = BackShape<NPL, H, ROWS>::KC;
+    constexpr bool PAIR = ROWS == 4;  // two wavefronts share a row's attention
+    static_assert(!PAIR || 2 * ROWS == kWaves, "");
     constexpr int MT = ROWS / 16, RG = ROWS % 16 / 4;
     using TR = TileRows<TIG_FP32, MT, RG>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -205,6 +223,7 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
     // [slots x M] sums, in double: an LDS addition of doubles takes 8 clocks for a wavefront, one of floats 192
     double *tab = (double *)(smem + p.off_tab);
     int *tag = (int *)(tab + p.slots * p.M);        // [slots] staged row held by the table's row, -1: none
+    float *pair_sd = (float *)(tag + p.slots);      // PAIR: [ROWS][2 H][64] scores and d p of every slot
 
     const int lane = lane_id(), wave = wave_id();
     int n_u = *a.qs.n_u;
@@ -323,6 +342,7 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
         for (int nt = wave; nt < n_nt; nt += 2 * kWaves) {
             floatx4 acc[2][TR::kAcc];
             clear(acc);
+            const bool two = nt + kWaves < n_nt;  // (uniform)
             for (int kb = 0; kb < kbE; kb += kDeep) {
                 const bool last = kb + kDeep >= kbE;
                 request(nxt, last ? (nt + 2 * kWaves < n_nt ? nt + 2 * kWaves : nt) : nt, last ? 0 : kb + kDeep);
@@ -334,7 +354,8 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
                             const frag a = rows.load(i, kb + u);
 #pragma unroll
                             for (int j = 0; j < 2; ++j)
-                                TR::mma(i, acc[j][i], a, cur[j][u]);
+                                if (j == 0 || two)
+                                    TR::mma(i, acc[j][i], a, cur[j][u]);
                         }
                     }
 #pragma unroll
@@ -400,18 +421,27 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
             from_e |= in_e ? 1u << n : 0u;
             from_m |= in_m ? 1u << n : 0u;
         }
+        // PAIR: wavefronts 2 r and 2 r + 1 take row r, once; slot k is the (k / 2)th of wavefront 2 r + k % 2.
+        constexpr int STEP = PAIR ? 2 : 1;
+        const int half = PAIR ? wave & 1 : 0;
+        auto slot = [&](int i) { return STEP * i + half; };  // the wavefront's slot i
         while (true) {
-            int r = 0;
-            if (lane == 0)
-                r = atomicAdd(next_row, 1);
-            r = __builtin_amdgcn_readfirstlane(r);
-            if (r >= ROWS)
-                break;
-            const int q = __builtin_amdgcn_readfirstlane(row_q[r]), cnt = __builtin_amdgcn_readfirstlane(row_cnt[r]);
-            if (q < 0)
+            int r = wave >> 1;
+            if constexpr (!PAIR) {
+                r = 0;
+                if (lane == 0)
+                    r = atomicAdd(next_row, 1);
+                r = __builtin_amdgcn_readfirstlane(r);
+                if (r >= ROWS)
+                    break;
+            }
+            const int q0 = __builtin_amdgcn_readfirstlane(row_q[r]), cnt = __builtin_amdgcn_readfirstlane(row_cnt[r]);
+            if (!PAIR && q0 < 0)
                 continue;
+            const int q = q0 < 0 ? 0 : q0;
+            const int own = (cnt - half + STEP - 1) / STEP;  // slots of this wavefront
             float *dq = t.DQT + (size_t)q * p.N1;
-            if (cnt == 0) {
+            if (!PAIR && cnt == 0) {
                 for (int j = lane; j < p.N1; j += kWave)
                     dq[j] = 0.0f;
                 continue;
@@ -429,7 +459,7 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
                 if (my_srow < 0 && (nb_v < 0 || (int64_t)nb_v >= a.num_nodes))
                     nb_v = 0;  // (not a row reference: only a corrupted table could hold it)
                 nb_e = nb_e >= 0 ? nb_e : 0;
-                if (my_srow >= 0)
+                if (my_srow >= 0 && (lane & (STEP - 1)) == half)
                     my_lds = claim(my_srow);
             }
             float *xrow = (float *)(X + (size_t)r * p.row_bytes);
@@ -445,10 +475,10 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
                     acc[h][n] = 0.0f;
                 }
             float raw[KC][NPL];
-            auto gather = [&](int c0) {  // the rows of slots c0 .. (the last filled one again beyond cnt)
+            auto gather = [&](int c0) {  // the rows of the wavefront's slots c0 .. (the last one again beyond them)
 #pragma unroll
                 for (int kk = 0; kk < KC; ++kk) {
-                    const int k = c0 + kk < cnt ? c0 + kk : cnt - 1;
+                    const int k = slot(c0 + kk < own ? c0 + kk : own - 1);
                     const int32_t v = __builtin_amdgcn_readlane(nb_v, k), e = __builtin_amdgcn_readlane(nb_e, k);
                     const float *vrow = v >= 0 ? a.mem + (size_t)v * p.M : a.staging + (size_t)(~v) * p.M;
                     const float *erow = a.edge_feat + (size_t)e * p.F;
@@ -458,7 +488,7 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
                 }
 #pragma unroll
                 for (int kk = 0; kk < KC; ++kk) {
-                    const int k = c0 + kk < cnt ? c0 + kk : cnt - 1;
+                    const int k = slot(c0 + kk < own ? c0 + kk : own - 1);
                     const double dt = readlane_f64(nb_dt, k);
 #pragma unroll
                     for (int n = 0; n < NPHI; ++n) {
@@ -474,11 +504,11 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
                 S[h] = -INFINITY;
                 D[h] = 0.0f;
             }
-            for (int c0 = 0; c0 < cnt; c0 += KC) {
+            for (int c0 = 0; c0 < own; c0 += KC) {
                 gather(c0);
 #pragma unroll
                 for (int kk = 0; kk < KC; ++kk)
-                    if (c0 + kk < cnt) {  // (uniform)
+                    if (c0 + kk < own) {  // (uniform)
                         float ps[H], pd[H];
 #pragma unroll
                         for (int h = 0; h < H; ++h) {
@@ -489,7 +519,7 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
                                 pd[h] += dv[h][n] * raw[kk][n];
                             }
                         }
-                        const bool mine = lane == c0 + kk;
+                        const bool mine = lane == slot(c0 + kk);
                         if constexpr (H % 2 == 0) {
 #pragma unroll
                             for (int h = 0; h < H; h += 2) {
@@ -513,6 +543,22 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
                         }
                     }
             }
+            if constexpr (PAIR) {  // every lane's score and d p from the wavefront that has its slot
+                float *ex = pair_sd + (size_t)r * 2 * H * kWave;
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+                    if (lane < cnt && (lane & 1) == half) {
+                        ex[h * kWave + lane] = S[h];
+                        ex[(H + h) * kWave + lane] = D[h];
+                    }
+                __syncthreads();
+#pragma unroll
+                for (int h = 0; h < H; ++h)
+                    if (lane < cnt) {
+                        S[h] = ex[h * kWave + lane];
+                        D[h] = ex[(H + h) * kWave + lane];
+                    }
+            }
             float pr[H], ds[H];
 #pragma unroll
             for (int h = 0; h < H; ++h) {
@@ -521,13 +567,13 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
                 pr[h] = ex / wave_sum_uniform(ex);
                 ds[h] = pr[h] * (D[h] - wave_sum_uniform(pr[h] * D[h]));  // gradient of <q~_h, kv_k>
             }
-            for (int c0 = 0; c0 < cnt; c0 += KC) {
-                if (cnt > KC)
+            for (int c0 = 0; c0 < own; c0 += KC) {
+                if (own > KC)
                     gather(c0);
 #pragma unroll
                 for (int kk = 0; kk < KC; ++kk)
-                    if (c0 + kk < cnt) {  // (uniform)
-                        const int k = c0 + kk;
+                    if (c0 + kk < own) {  // (uniform)
+                        const int k = slot(c0 + kk);
                         float dk[NPL];  // d kv_k = sum_h p_hk d kvbar_h + d s_hk q~_h
 #pragma unroll
                         for (int n = 0; n < NPL; ++n)
@@ -563,17 +609,33 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
                         }
                     }
             }
+            if constexpr (PAIR) {  // (both have taken d kvbar from the row before the barrier above)
+                if (half == 1)
+#pragma unroll
+                    for (int h = 0; h < H; ++h)
+#pragma unroll
+                        for (int n = 0; n < NPL; ++n)
+                            if (lane + kWave * n < p.dkvp)
+                                xrow[h * p.dkvp + lane + kWave * n] = acc[h][n];
+                __syncthreads();
+                if (half == 1)
+                    break;
+            }
 #pragma unroll
             for (int h = 0; h < H; ++h)
 #pragma unroll
                 for (int n = 0; n < NPL; ++n) {
                     const int j = lane + kWave * n;
                     if (j < p.dkvp) {
-                        const float x = j < p.dkv ? acc[h][n] : 0.0f;
+                        const float both = PAIR ? acc[h][n] + xrow[h * p.dkvp + j] : acc[h][n];
+                        const float x = j < p.dkv ? both : 0.0f;
                         xrow[h * p.dkvp + j] = x;
-                        dq[h * p.dkvp + j] = x;
+                        if (!PAIR || q0 >= 0)
+                            dq[h * p.dkvp + j] = x;
                     }
                 }
+            if constexpr (PAIR)
+                break;
         }
     }
     __syncthreads();
@@ -611,10 +673,10 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
     }
     __syncthreads();
     // ---- 8. the table's rows and the time encoding's sums to memory
-    for (int i = threadIdx.x; i < p.slots * p.M; i += kThreads) {
-        const int srow = tag[i / p.M];
-        if (srow >= 0)
-            atomicAdd(&t.D_STAG[(size_t)srow * p.M + i % p.M], (float)tab[i]);
+    for (int i = wave; i < p.slots; i += kWaves) {
+        const int srow = __builtin_amdgcn_readfirstlane(tag[i]);
+        for (int j = lane; srow >= 0 && j < p.M; j += kWave)
+            atomicAdd(&t.D_STAG[(size_t)srow * p.M + j], (float)tab[i * p.M + j]);
     }
     double *red = (double *)X;  // [waves x T], frequencies first, then phases
 #pragma unroll
@@ -745,11 +807,13 @@ BackParams back_params(const Dims &d, int rows, int lds_limit, int *lds)
     const int sums = (kBackThreads / kWave) * d.T * 8;
     p.off_meta = p.off_meta > sums ? p.off_meta : sums;
     p.off_tab = (p.off_meta + rows * 20 + d.T * 16 + 16 + 15) / 16 * 16;
-    // as many table rows as fit: hubs are few, but every row that misses the table costs device atomics
-    const int slot_bytes = 8 * d.M + 4;
-    p.slots = (lds_limit - p.off_tab) / slot_bytes;
-    p.slots = p.slots < 0 ? 0 : (p.slots > 128 ? 128 : p.slots);
-    *lds = p.off_tab + p.slots * slot_bytes;
+    // as many table rows as fit: hubs are few, but every row that misses the table costs device atomics; at most two for
+    // each that the tile can ask for
+    const int slot_bytes = 8 * d.M + 4, pair_bytes = rows == 4 ? rows * 2 * (d.H <= 2 ? d.H : 4) * kWave * 4 : 0;
+    const int most = 2 * rows * (d.K + 1) < 128 ? 2 * rows * (d.K + 1) : 128;
+    p.slots = (lds_limit - p.off_tab - pair_bytes) / slot_bytes;
+    p.slots = p.slots < 0 ? 0 : (p.slots > most ? most : p.slots);
+    *lds = p.off_tab + p.slots * slot_bytes + pair_bytes;
     return p;
 }
 
