@@ -110,9 +110,9 @@ def run_training(bundle, batches, lr, order, warm_at, then_eval=0, first_eval=()
             if not ties or len(ties) > MAX_TIES:
                 raise
 
-            def rerun(flips):
-                return T.train_step(st_before.copy(), g.src, g.dst, g.ts, g.edge_feat,
-                                    {k: v.copy() for k, v in W_before.items()}, first, count, neg, w.num_neighbors,
+            def rerun(flips):  # (the weights follow: the last call is the one with the gates that the GPU took)
+                W.update({k: v.copy() for k, v in W_before.items()})
+                return T.train_step(st_before.copy(), g.src, g.dst, g.ts, g.edge_feat, W, first, count, neg, w.num_neighbors,
                                     w.num_heads, lr, index=ix, deferred=deferred, relu_flip=flips)[2]
             worst = check_grads(got, resolve_relu_ties(got, grads, ties, rerun))
         del st_before, W_before
