@@ -9,6 +9,8 @@
 
 namespace tig {
 
+constexpr int kSumCopies = 8;
+
 // Device arrays of a training step besides the model's own.  Rows "per query" are rows of the step's query
 // set (distinct source / destination queries from 0, the negative of event b at 2 * count + b).
 struct TrainArrays {
@@ -20,8 +22,9 @@ struct TrainArrays {
     // per applied winner r, and per entry of the applied batch
     float *MSG, *GATES, *DGI, *DGH, *D_STAG;
     // sums over rows, added up with atomics and cleared by the update that reads them
-    double *TACC;                       // [2T] time-encoding gradients [frequencies | phases]
-    float *WACC;                        // [E + 1] gradients of w_d2, b_d2
+    // (every XCD's workgroups add to a copy of their own: additions of hundreds of workgroups to one address wait for each other)
+    double *TACC;                       // [copies][2T] time-encoding gradients [frequencies | phases]
+    float *WACC;                        // [copies][E + 1] gradients of w_d2, b_d2
     // transposed weights, prepared like the forward kernels' (lane-ordered, padded with zeros)
     float *Wd1T;                        // [Ep x 2Ek]   W_d1[k][n], W_d1[k][E + n]
     float *Wm2T;                        // [Ep x Ek]
@@ -43,7 +46,8 @@ struct BackParams {
 hipError_t launch_train_decode(const Dims &d, const StepArgs &a, const PackedWeights &pw, const TrainArrays &t, hipStream_t s);
 hipError_t launch_train_back(const Dims &d, const LaunchPlan &plan, const StepArgs &a, const PackedWeights &pw,
                              const TrainArrays &t, hipStream_t s);
-hipError_t launch_train_gru_back(const Dims &d, const StepArgs &a, const PackedWeights &pw, const TrainArrays &t, hipStream_t s);
+hipError_t launch_train_gru_back(const Dims &d, const LaunchPlan &plan, const StepArgs &a, const PackedWeights &pw,
+                                 const TrainArrays &t, hipStream_t s);
 hipError_t prepare_train_back(const Dims &d);
 bool train_back_fits(const Dims &d);  // the kernels' LDS and registers hold a row of this shape
 

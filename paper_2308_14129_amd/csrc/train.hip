@@ -570,12 +570,30 @@ __global__ void __launch_bounds__(256) k_tr_update(StepArgs a, UpdateJob u)
         float g = u.G[i];
         const size_t T = (size_t)u.T, tail = u.n_params - (size_t)(u.E + 1);
         if (i < 2 * T) {  // the first two arrays: frequencies, phases (Phi(0)_j = cos(b_j))
-            g = (float)(u.TACC[i] - (i >= T ? sin((double)u.P[i]) * (double)u.dphi0[i - T] : 0.0));
-            u.TACC[i] = 0.0;
+            double sum = 0.0, part[kSumCopies];
+#pragma unroll
+            for (int c = 0; c < kSumCopies; ++c)
+                part[c] = u.TACC[c * 2 * T + i];
+#pragma unroll
+            for (int c = 0; c < kSumCopies; ++c) {
+                sum += part[c];
+                u.TACC[c * 2 * T + i] = 0.0;
+            }
+            g = (float)(sum - (i >= T ? sin((double)u.P[i]) * (double)u.dphi0[i - T] : 0.0));
             u.G[i] = g;
         } else if (i >= tail) {  // the last two: w_d2, b_d2
-            g = u.WACC[i - tail];
-            u.WACC[i - tail] = 0.0f;
+            const size_t n = (size_t)(u.E + 1);
+            float part[kSumCopies];
+            double sum = 0.0;
+#pragma unroll
+            for (int c = 0; c < kSumCopies; ++c)
+                part[c] = u.WACC[c * n + i - tail];
+#pragma unroll
+            for (int c = 0; c < kSumCopies; ++c) {
+                sum += (double)part[c];
+                u.WACC[c * n + i - tail] = 0.0f;
+            }
+            g = (float)sum;
             u.G[i] = g;
         }
         float x = u.P[i];
@@ -667,8 +685,8 @@ static TrainLayout train_layout(const Dims &d, void *base)
     L.zero_lo = off;
     L.G = take(n);
     TrainArrays &t = L.t;
-    t.TACC = (double *)take(2 * 2 * T);
-    t.WACC = take(E + 1);
+    t.TACC = (double *)take(kSumCopies * 2 * 2 * T);
+    t.WACC = take(kSumCopies * (E + 1));
     t.Wd1T = take((size_t)d.Ep * 2 * d.Ek);
     t.Wm2T = take((size_t)d.Ep * d.Ek);
     t.PRT = take((size_t)d.K2 * d.Ek);
@@ -998,7 +1016,7 @@ hipError_t launch_train(const Dims &d, const LaunchPlan &plan, const StepArgs &a
     if ((e = launch_embed(d, plan, pw, a, s)) != hipSuccess || (e = launch_train_decode(d, a, pw, t, s)) != hipSuccess ||
         (e = launch_train_back(d, plan, a, pw, t, s)) != hipSuccess)
         return e;
-    if (a.msg_count > 0 && (e = launch_train_gru_back(d, a, pw, t, s)) != hipSuccess)
+    if (a.msg_count > 0 && (e = launch_train_gru_back(d, plan, a, pw, t, s)) != hipSuccess)
         return e;
     *launches += a.msg_count > 0 ? 4 : 3;
     {

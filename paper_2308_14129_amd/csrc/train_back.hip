@@ -109,7 +109,7 @@ __global__ void __launch_bounds__(kDecThreads) k_tr_decode(StepArgs a, PackedWei
         float sum = 0.0f;
         for (int v = 0; v < kDecWaves; ++v)
             sum += wsum[v * (E + 1) + j];
-        atomicAdd(&t.WACC[j], sum);
+        atomicAdd(&t.WACC[(blockIdx.x % kSumCopies) * (E + 1) + j], sum);
     }
 }
 
@@ -641,16 +641,29 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
     __syncthreads();
     TIG_MARK(4);
     // ---- 6. d s_u += A1^T d q~
-    for (int nt = wave; nt < p.Mq / 16; nt += kWaves) {
-        floatx4 acc[1][TR::kAcc];
-        float d[TR::kOut];
-        clear(acc);
-        tile_gemm_deep<MT, RG, 1, 14>(acc, X, p.row_bytes, 0, t.A1T, p.N1 / P::KB, 0, p.N1 / P::KB, {nt});
-        TR::results(acc[0], d);
-        const int col = p.N1 + nt * 16 + (lane & 15);
+    // (the tiles of the last, incomplete round are split over the wavefronts it leaves idle: eleven tiles of 172 columns
+    // took two rounds where 1.4 are needed; with few results per lane only, the parts meet by LDS additions)
+    {
+        const int n_t = p.Mq / 16, kbN = p.N1 / P::KB, rem = n_t % kWaves, whole = n_t - rem;
+        const int parts = ROWS <= 8 && rem > 0 && kbN >= kWaves ? kWaves / rem : 1;
+        for (int u = wave; u < whole + rem * parts; u += kWaves) {
+            const int nt = u < whole ? u : whole + (u - whole) % rem, part = u < whole ? 0 : (u - whole) / rem;
+            const int of = u < whole ? 1 : parts, lo = kbN * part / of, hi = kbN * (part + 1) / of;
+            floatx4 acc[1][TR::kAcc];
+            float d[TR::kOut];
+            clear(acc);
+            tile_gemm_deep<MT, RG, 1, 14>(acc, X, p.row_bytes, lo, t.A1T, kbN, lo, hi - lo, {nt});
+            TR::results(acc[0], d);
+            const int col = p.N1 + nt * 16 + (lane & 15);
 #pragma unroll
-        for (int o = 0; o < TR::kOut; ++o)
-            ((float *)(X + (size_t)TR::row(o) * p.row_bytes))[col] += d[o];
+            for (int o = 0; o < TR::kOut; ++o) {
+                float *x = (float *)(X + (size_t)TR::row(o) * p.row_bytes) + col;
+                if (ROWS <= 8 && of > 1)  // (uniform)
+                    atomicAdd(x, d[o]);
+                else
+                    *x += d[o];
+            }
+        }
     }
     __syncthreads();
     TIG_MARK(5);
@@ -692,7 +705,7 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
             double sum = 0.0;
             for (int v = 0; v < kWaves; ++v)
                 sum += red[v * p.T + j];
-            atomicAdd(&t.TACC[half * p.T + j], sum);
+            atomicAdd(&t.TACC[((int)blockIdx.x % kSumCopies * 2 + half) * p.T + j], sum);
         }
         __syncthreads();
     }
@@ -702,7 +715,11 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
 // ------------------------------------------------------------------------------------------
 // The GRU's backward pass over the applied winners, from the message rows and gates that the step's GRU launch
 // left: gradients of the gate pre-activations, and through W_i's time columns the time encoding's gradient.
-constexpr int kGbThreads = 512, kGbWaves = kGbThreads / kWave, kGbRows = 16;
+// A workgroup's chain (winners, gates, one product, the time encoding) is as long as its winners are many: tiles of 4, 8 or
+// 16, the lowest that recent steps' winners fit one workgroup per compute unit in (200 events of 172 columns 15.5 -> 9.5 us,
+// 4000 of 100 11.4 -> 8.4, both from 16 rows to 4); with more winners a workgroup takes tile after tile.
+constexpr int kGbThreads = 512, kGbWaves = kGbThreads / kWave;
+constexpr int kGbHeights[] = {4, 8, 16};
 
 __device__ inline bool win_ok(const StepArgs &a, const WinDesc &w)
 {
@@ -715,78 +732,84 @@ struct GruBackParams {
     int ldx, ldp;            // LDS bytes per row of the gate gradients / of d Phi
 };
 
+template <int ROWS>
 __global__ void __launch_bounds__(kGbThreads) k_tr_gru_back(StepArgs a, PackedWeights w, TrainArrays t, GruBackParams p)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    char *X = smem, *DP = smem + kGbRows * p.ldx;
-    double *row_dt = (double *)(DP + kGbRows * p.ldp);  // [rows]
+    char *X = smem, *DP = smem + ROWS * p.ldx;
+    double *row_dt = (double *)(DP + ROWS * p.ldp);  // [rows]
     int n_win = *a.n_win;
     n_win = n_win < 2 * a.msg_count ? n_win : 2 * a.msg_count;
-    const int r0 = (int)blockIdx.x * kGbRows;
-    if (r0 >= n_win)
-        return;
     const int lane = lane_id(), wave = wave_id();
     const int M = p.M, T = p.T, D = p.D;
-    for (int i = wave; i < kGbRows; i += kGbWaves) {
-        const int r = r0 + i;
-        float *x = (float *)(X + (size_t)i * p.ldx);
-        if (r >= n_win) {  // (uniform)
-            for (int j = lane; j < p.Kp; j += kWave)
-                x[j] = 0.0f;
+    using TR = TileRows<TIG_FP32, ROWS / 16, ROWS % 16 / 4>;
+    for (int r0 = (int)blockIdx.x * ROWS; r0 < n_win; r0 += (int)gridDim.x * ROWS) {
+        if (r0 != (int)blockIdx.x * ROWS)
+            __syncthreads();  // (the tile before is done with)
+        for (int i = wave; i < ROWS; i += kGbWaves) {
+            const int r = r0 + i;
+            float *x = (float *)(X + (size_t)i * p.ldx);
+            if (r >= n_win) {  // (uniform)
+                for (int j = lane; j < p.Kp; j += kWave)
+                    x[j] = 0.0f;
+                if (lane == 0)
+                    row_dt[i] = 0.0;
+                continue;
+            }
+            const WinDesc d = a.win[r];
+            const bool ok = win_ok(a, d);
+            const double dt = ok ? d.t - a.lu[d.node] : 0.0;
             if (lane == 0)
-                row_dt[i] = 0.0;
-            continue;
-        }
-        const WinDesc d = a.win[r];
-        const bool ok = win_ok(a, d);
-        const double dt = ok ? d.t - a.lu[d.node] : 0.0;
-        if (lane == 0)
-            row_dt[i] = dt;
-        const size_t entry = ok ? (size_t)d.entry : 0;
-        const float *gt = t.GATES + (size_t)r * 4 * M;  // r, z, n, W_hn h + b_hn
-        float *dgi = t.DGI + (size_t)r * 3 * M, *dgh = t.DGH + (size_t)r * 3 * M;
+                row_dt[i] = dt;
+            const size_t entry = ok ? (size_t)d.entry : 0;
+            const float *gt = t.GATES + (size_t)r * 4 * M;  // r, z, n, W_hn h + b_hn
+            float *dgi = t.DGI + (size_t)r * 3 * M, *dgh = t.DGH + (size_t)r * 3 * M;
 #pragma unroll 4
-        for (int j = lane; j < M; j += kWave) {
-            const float rg = gt[j], zg = gt[M + j], ng = gt[2 * M + j], ghn = gt[3 * M + j];
-            const float dh0 = t.D_STAG[entry * M + j], h = t.MSG[(size_t)r * D + j];  // s_self leads the message
-            const float dh = ok ? dh0 : 0.0f;
-            const float dn = dh * (1.0f - zg);
-            const float dz = dh * (h - ng);
-            const float dpre_n = dn * (1.0f - ng * ng);
-            const float dpre_r = dpre_n * ghn * rg * (1.0f - rg);
-            const float dpre_z = dz * zg * (1.0f - zg);
-            dgi[j] = x[j] = dpre_r;
-            dgi[M + j] = x[M + j] = dpre_z;
-            dgi[2 * M + j] = x[2 * M + j] = dpre_n;
-            dgh[j] = dpre_r;
-            dgh[M + j] = dpre_z;
-            dgh[2 * M + j] = dpre_n * rg;
+            for (int j = lane; j < M; j += kWave) {
+                const float rg = gt[j], zg = gt[M + j], ng = gt[2 * M + j], ghn = gt[3 * M + j];
+                const float dh0 = t.D_STAG[entry * M + j], h = t.MSG[(size_t)r * D + j];  // s_self leads the message
+                const float dh = ok ? dh0 : 0.0f;
+                const float dn = dh * (1.0f - zg);
+                const float dz = dh * (h - ng);
+                const float dpre_n = dn * (1.0f - ng * ng);
+                const float dpre_r = dpre_n * ghn * rg * (1.0f - rg);
+                const float dpre_z = dz * zg * (1.0f - zg);
+                dgi[j] = x[j] = dpre_r;
+                dgi[M + j] = x[M + j] = dpre_z;
+                dgi[2 * M + j] = x[2 * M + j] = dpre_n;
+                dgh[j] = dpre_r;
+                dgh[M + j] = dpre_z;
+                dgh[2 * M + j] = dpre_n * rg;
+            }
+            for (int j = 3 * M + lane; j < p.Kp; j += kWave)
+                x[j] = 0.0f;
         }
-        for (int j = 3 * M + lane; j < p.Kp; j += kWave)
-            x[j] = 0.0f;
-    }
-    __syncthreads();
-    for (int nt = wave; nt < p.Tp / 16; nt += kGbWaves) {
-        floatx4 acc[1] = {floatx4{0, 0, 0, 0}};
-        const int kb = p.Kp / Prec<TIG_FP32>::KB;
-        tile_gemm<TIG_FP32, 1, 4, true>(acc, X, p.ldx, 0, t.WiT, kb, 0, kb, nt);
+        __syncthreads();
+        for (int nt = wave; nt < p.Tp / 16; nt += kGbWaves) {
+            floatx4 acc[1][TR::kAcc] = {};
+            float d[TR::kOut];
+            const int kb = p.Kp / Prec<TIG_FP32>::KB;
+            tile_gemm_deep<ROWS / 16, ROWS % 16 / 4, 1, 12>(acc, X, p.ldx, 0, t.WiT, kb, 0, kb, {nt});
+            TR::results(acc[0], d);
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            ((float *)(DP + (size_t)(4 * (lane >> 4) + v) * p.ldp))[nt * 16 + (lane & 15)] = acc[0][v];
-    }
-    __syncthreads();
-    for (int j = threadIdx.x; j < T; j += kGbThreads) {
-        const double w_rev = w.time_w_rev[j], b_rev = w.time_b_rev[j];
-        double gw = 0.0, gb = 0.0;
-#pragma unroll
-        for (int i = 0; i < kGbRows; ++i) {  // (rows beyond the winners hold zeros)
-            const double dt = row_dt[i];
-            const float v = -time_enc_sin(w_rev, b_rev, dt) * ((const float *)(DP + (size_t)i * p.ldp))[j];
-            gw += dt * (double)v;
-            gb += (double)v;
+            for (int o = 0; o < TR::kOut; ++o)
+                ((float *)(DP + (size_t)TR::row(o) * p.ldp))[nt * 16 + (lane & 15)] = d[o];
         }
-        atomicAdd(&t.TACC[j], gw);
-        atomicAdd(&t.TACC[T + j], gb);
+        __syncthreads();
+        for (int j = threadIdx.x; j < T; j += kGbThreads) {
+            const double w_rev = w.time_w_rev[j], b_rev = w.time_b_rev[j];
+            double gw = 0.0, gb = 0.0;
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) {  // (rows beyond the winners hold zeros)
+                const double dt = row_dt[i];
+                const float v = -time_enc_sin(w_rev, b_rev, dt) * ((const float *)(DP + (size_t)i * p.ldp))[j];
+                gw += dt * (double)v;
+                gb += (double)v;
+            }
+            double *sums = t.TACC + (int)blockIdx.x % kSumCopies * 2 * T;
+            atomicAdd(&sums[j], gw);
+            atomicAdd(&sums[T + j], gb);
+        }
     }
 }
 
@@ -880,10 +903,15 @@ GruBackParams gru_back_params(const Dims &d)
     return p;
 }
 
-int gru_back_lds(const Dims &d)
+int gru_back_lds(const Dims &d, int rows)
 {
     const GruBackParams p = gru_back_params(d);
-    return kGbRows * (p.ldx + p.ldp + 8);
+    return rows * (p.ldx + p.ldp + 8);
+}
+
+const void *gru_back_kernel(int rows)
+{
+    return rows == 4 ? (const void *)k_tr_gru_back<4> : (rows == 8 ? (const void *)k_tr_gru_back<8> : (const void *)k_tr_gru_back<16>);
 }
 
 int decode_lds_bytes(const Dims &d) { return kDecWaves * (d.E + 1) * 4; }
@@ -894,14 +922,15 @@ bool train_back_fits(const Dims &d)
 {
     int lds = 0;
     (void)back_params(d, 16, kBackLds, &lds);
-    return lds <= kBackLds && gru_back_lds(d) <= kBackLds && d.E <= kDecCols * kWave && d.K <= kWave;
+    return lds <= kBackLds && gru_back_lds(d, 16) <= kBackLds && d.E <= kDecCols * kWave && d.K <= kWave;
 }
 
 hipError_t prepare_train_back(const Dims &d)
 {
     hipError_t e = hipFuncSetAttribute((const void *)k_tr_decode, hipFuncAttributeMaxDynamicSharedMemorySize, decode_lds_bytes(d));
-    if (e == hipSuccess)
-        e = hipFuncSetAttribute((const void *)k_tr_gru_back, hipFuncAttributeMaxDynamicSharedMemorySize, gru_back_lds(d));
+    for (const int h : kGbHeights)
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(gru_back_kernel(h), hipFuncAttributeMaxDynamicSharedMemorySize, gru_back_lds(d, h));
     for (const int h : kBackHeights) {
         if (h > back_most_rows(d) || e != hipSuccess)
             break;
@@ -941,11 +970,23 @@ hipError_t launch_train_back(const Dims &d, const LaunchPlan &plan, const StepAr
     return hipLaunchKernel(back_kernel(d, height), dim3((most + p.rpt - 1) / p.rpt), dim3(kBackThreads), args, (size_t)lds, s);
 }
 
-hipError_t launch_train_gru_back(const Dims &d, const StepArgs &a, const PackedWeights &pw, const TrainArrays &t, hipStream_t s)
+hipError_t launch_train_gru_back(const Dims &d, const LaunchPlan &plan, const StepArgs &a, const PackedWeights &pw,
+                                 const TrainArrays &t, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_tr_gru_back, dim3((2 * a.msg_count + kGbRows - 1) / kGbRows), dim3(kGbThreads), gru_back_lds(d), s, a, pw, t,
-                       gru_back_params(d));
-    return hipGetLastError();
+    const int most = 2 * a.msg_count, wins = a.wins_est > 0 && a.wins_est < most ? a.wins_est : most;
+    const int cus = plan.num_cus > 0 ? plan.num_cus : 256;
+    int height = 16;
+    for (const int h : kGbHeights)
+        if (h < height && (wins + h - 1) / h <= cus)
+            height = h;
+    const int tiles = (most + height - 1) / height;
+    StepArgs aa = a;
+    PackedWeights ww = pw;
+    TrainArrays tt = t;
+    GruBackParams p = gru_back_params(d);
+    void *args[] = {&aa, &ww, &tt, &p};
+    return hipLaunchKernel(gru_back_kernel(height), dim3(tiles < 2 * cus ? tiles : 2 * cus), dim3(kGbThreads), args,
+                           (size_t)gru_back_lds(d, height), s);
 }
 
 }  // namespace tig
