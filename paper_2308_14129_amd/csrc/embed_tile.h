@@ -196,7 +196,7 @@ next_tile:
     int *row_todo = next_row + 4;                 // [ROWS] 1: a negative whose neighbours phase C looks up
 
     const int lane = lane_id();
-    const int wave = wave_id();
+    const int wave = LAYER ? wave_id_uniform() : wave_id();
     const int mem_off = 4 * p.N1;
     int n_u = *a.qs.n_u;  // distinct source / destination queries; the negatives' rows follow at 2 * count
     n_u = n_u < 2 * a.count ? n_u : 2 * a.count;

@@ -225,7 +225,7 @@ k_tr_back(StepArgs a, PackedWeights w, TrainArrays t, BackParams p)
     int *tag = (int *)(tab + p.slots * p.M);        // [slots] staged row held by the table's row, -1: none
     float *pair_sd = (float *)(tag + p.slots);      // PAIR: [ROWS][2 H][64] scores and d p of every slot
 
-    const int lane = lane_id(), wave = wave_id();
+    const int lane = lane_id(), wave = wave_id_uniform();
     int n_u = *a.qs.n_u;
     n_u = n_u < 2 * a.count ? n_u : 2 * a.count;
     const int neg_row0 = 2 * a.count;
@@ -740,7 +740,7 @@ __global__ void __launch_bounds__(kGbThreads) k_tr_gru_back(StepArgs a, PackedWe
     double *row_dt = (double *)(DP + ROWS * p.ldp);  // [rows]
     int n_win = *a.n_win;
     n_win = n_win < 2 * a.msg_count ? n_win : 2 * a.msg_count;
-    const int lane = lane_id(), wave = wave_id();
+    const int lane = lane_id(), wave = wave_id_uniform();
     const int M = p.M, T = p.T, D = p.D;
     using TR = TileRows<TIG_FP32, ROWS / 16, ROWS % 16 / 4>;
     for (int r0 = (int)blockIdx.x * ROWS; r0 < n_win; r0 += (int)gridDim.x * ROWS) {
