@@ -7,9 +7,9 @@
 //   k_tr_decode    per event: logits, loss terms, and the gradients of the two decoder halves' pre-activations
 //                  added to their rows (a row is shared by every event that asked for the same query)
 //   k_tr_back      4 to 32 query rows per workgroup: decoder halves -> embedding -> merge MLP -> attention ->
-//                  folded query, as matrix-core products and one wavefront per row for the attention; the
+//                  folded query, as matrix-core products and one wavefront per row for the attention (two in tiles of four); the
 //                  gradients of state rows that this step's GRU wrote are collected in an LDS table
-//   k_tr_gru_back  16 applied winners per workgroup: gradients of the gates' pre-activations, time encoding
+//   k_tr_gru_back  4 to 16 applied winners per workgroup: gradients of the gates' pre-activations, time encoding
 // (Layer by layer as products over all rows in memory, with the key / value rows and their gradients
 // stored per slot, the same pass was two dozen launches: half of a step of 200 events was the host launching
 // them.)
