@@ -165,8 +165,9 @@ def algorithmic_bytes(w, count, rows_u, slots_u, winners):
 
 
 def mfma_flops(w, rows_u, winners, precision):
-    """Multiply-adds x 2 the matrix cores execute per launch for the padded tile shapes, and the
-    useful part (unpadded, one product per multiply instead of three for split bf16 operands)."""
+    """Multiply-adds x 2 the matrix cores execute per launch with rows padded to sixteen in all (dealt over the
+    compute units every tile pads its own: the counters' summary has what ran), and the useful part
+    (unpadded, one product per multiply instead of three for split bf16 operands)."""
     def up(x, m):
         return (x + m - 1) // m * m
     kb = 32 if precision == "bf16" else 16
