@@ -1,6 +1,7 @@
 // Launch parameters of the embedding kernels and the choice among their instances (host side).
 #pragma once
 
+#include "embed_rules.h"
 #include "tig_internal.h"
 
 namespace tig {
@@ -19,8 +20,6 @@ struct EmbedParams {
     // at least one dim of the time encoding / of the neighbour's memory / of the edge feature
     int phi_regs, mem_regs, feat_regs;
 };
-
-constexpr int kLeastRows = 8;  // of a tile that is not one of the fewest
 
 enum EmbedMode { kEmbedStep = 0, kEmbedTrain = 1, kEmbedLayer = 2 };
 

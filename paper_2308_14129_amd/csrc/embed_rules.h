@@ -1,0 +1,55 @@
+// How an embedding launch (embed_tile.h, k_embed.hip) divides its query rows over workgroups.  Plain functions, evaluated by the
+// host, by the kernel and by the tests.
+#pragma once
+
+namespace tig {
+
+constexpr int kLeastRows = 8;  // of a tile that is not one of the fewest
+
+constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
+
+// Rows a workgroup's tile can have.  fp32 products keep the matrix units busy for as long as a tile has rows (172 state
+// columns: 18 of the 43 us of a launch over 600 rows, with half of every 16-row block empty), so fp32 tiles also come in 4
+// and 8 rows and in 24 (groups of four rows, Prec<TIG_FP32>::mma_four): a step of 200 events of 172 columns 54.3 -> 36.8 us, of
+// 500 57.6 -> 46.2, of 1600 92.7 -> 79.1, a training step of 200 224 -> 203.  bf16 products take a fifth of that and are bound by the
+// weights' way from L2, which is the same for any number of rows.
+constexpr int kHeights[] = {4, 8, 16, 24, 32, 48};
+constexpr bool height_of(bool fp32, int rows) { return fp32 || (rows % 16 == 0); }
+
+// The lowest tile whose workgroups, one per compute unit at hand, take `rows` query rows: a workgroup's latency grows
+// with its rows.
+constexpr int embed_height(bool fp32, int most_mt, int rows, int units)
+{
+    for (const int h : kHeights)
+        if (height_of(fp32, h) && h < 16 * most_mt && ceil_div(rows, h) <= units)
+            return h;
+    return 16 * most_mt;
+}
+
+// Tiles of at most `height` rows that n_rows rows are dealt over: as many as there are compute units to take them (`units`)
+// while each gets eight rows, because the attention phase is as long as the rows of a compute unit are many (a row of
+// twenty 444-column slots is 2.7 us of a SIMD: 187 tiles of 32 rows took 30 us there, 223 of 27 take 26), while the
+// products cost the same for any number of rows.  A launch whose workgroups loop (`loop` of them) gives each equally many.
+constexpr int tiles_in_use(int n_rows, int height, int units, int loop)
+{
+    const int least = ceil_div(n_rows, height), most = ceil_div(n_rows, kLeastRows);
+    if (loop > 0 && least > loop)
+        return ceil_div(least, loop) * loop;
+    const int even = most < units ? most : units;
+    return least > even ? least : even;
+}
+
+// Workgroups that take the tiles of at most `most` rows, one tile each (the tiles beyond those in use return).
+constexpr int step_workgroups(int most, int height, int units) { return tiles_in_use(most, height, units, 0); }
+
+// The same for a layer of a stack, whose workgroups take tile after tile: no more than there are compute units, and no
+// fewer tiles at a time than these could take.  (Without regard to the height, a workgroup for every eight rows, tiles of
+// four rows went two by two through half of the workgroups they needed: two layers over 100 events of 172 columns 143 us
+// instead of 114, over 300 173 instead of 146; with tiles of 16 rows at least 136 and 166.)
+constexpr int layer_workgroups(int most, int height, int units)
+{
+    const int tiles = step_workgroups(most, height, units);
+    return tiles < units ? tiles : units;
+}
+
+}  // namespace tig

@@ -94,19 +94,6 @@ constexpr int regs_touching(int lo, int hi, int dims)
 static_assert(sizeof(StepArgs) % alignof(PackedWeights) == 0 && (sizeof(StepArgs) + sizeof(PackedWeights)) % alignof(EmbedParams) == 0,
               "the kernel's arguments follow each other without gaps");
 
-// Tiles of at most ROWS rows that n_rows rows are dealt over: as many as there are compute units to take them (SPREAD)
-// while each gets eight rows, because the attention phase is as long as the rows of a compute unit are many (a row of
-// twenty 444-column slots is 2.7 us of a SIMD: 187 tiles of 32 rows took 30 us there, 223 of 27 take 26), while the
-// products cost the same for any number of rows.  A launch whose workgroups loop (LOOP of them) gives each equally many.
-__device__ inline int tiles_in_use(int n_rows, int rows, int spread, int loop)
-{
-    const int least = (n_rows + rows - 1) / rows, most = (n_rows + kLeastRows - 1) / kLeastRows;
-    if (loop > 0 && least > loop)
-        return (least + loop - 1) / loop * loop;
-    const int even = most < spread ? most : spread;
-    return least > even ? least : even;
-}
-
 template <int PREC, int MODE, int ROWS, int NPL, int H, int SHAPE>
 __global__ void __launch_bounds__((EmbedShape<NPL, H>::kThreads))
 k_embed(StepArgs a_, PackedWeights w_, EmbedParams p_)

@@ -57,24 +57,6 @@ int lds_of(const Dims &d, int rows)
     return p.off_meta + rows * (4 * 4 + 8) + d.T * 16 + 16;
 }
 
-// Rows a workgroup's tile can have.  fp32 products keep the matrix units busy for as long as a tile has rows (172 state
-// columns: 18 of the 43 us of a launch over 600 rows, with half of every 16-row block empty), so fp32 tiles also come in 4
-// and 8 rows and in 24 (groups of four rows, Prec<TIG_FP32>::mma_four): a step of 200 events of 172 columns 54.3 -> 36.8 us, of
-// 500 57.6 -> 46.2, of 1600 92.7 -> 79.1, a training step of 200 224 -> 203.  bf16 products take a fifth of that and are bound by the
-// weights' way from L2, which is the same for any number of rows.
-constexpr int kHeights[] = {4, 8, 16, 24, 32, 48};
-bool height_of(bool fp32, int rows) { return fp32 || (rows % 16 == 0); }
-
-// The lowest tile whose workgroups, one per compute unit at hand, take `rows` query rows: a workgroup's latency grows
-// with its rows.
-int embed_height(bool fp32, int most_mt, int rows, int units)
-{
-    for (const int h : kHeights)
-        if (height_of(fp32, h) && h < 16 * most_mt && (rows + h - 1) / h <= units)
-            return h;
-    return 16 * most_mt;
-}
-
 }  // namespace
 
 int embed_lds_bytes(const Dims &d, int mt) { return lds_of(d, 16 * mt); }
@@ -170,11 +152,8 @@ hipError_t launch_embed(const Dims &d, const LaunchPlan &plan, const PackedWeigh
     const int rows = a.rows_est > 0 && a.rows_est < most ? a.rows_est : most;
     const int height = embed_height(train || d.prec == TIG_FP32, plan.emb_mt, rows, units);
     EmbedParams p = embed_params(d, height);
-    // tiles in use if no query repeats (tiles_in_use)
-    const int even = (most + kLeastRows - 1) / kLeastRows < units ? (most + kLeastRows - 1) / kLeastRows : units;
     p.spread = units;
-    p.n_tiles = (most + height - 1) / height;
-    p.n_tiles = p.n_tiles > even ? p.n_tiles : even;
+    p.n_tiles = step_workgroups(most, height, units);
     p.n_commit = n_commit;
     p.commit_beside = beside ? 1 : 0;
     void *args[] = {&aa, &ww, &p};
@@ -197,8 +176,7 @@ hipError_t launch_embed_layer(const Dims &d, int most_mt, int num_cus, const Pac
     const int height = embed_height(true, most_mt, rows, units);
     EmbedParams p = embed_params(d, height);
     p.spread = units;
-    p.n_tiles = (most + kLeastRows - 1) / kLeastRows;
-    p.n_tiles = p.n_tiles < units ? p.n_tiles : units;
+    p.n_tiles = layer_workgroups(most, height, units);
     void *args[] = {&aa, &ww, &p};
     const int own = lds_of(d, height);
     const int lds = a.sel.count > 0 && own < kOneLds ? kOneLds : (own < kPrepLds ? kPrepLds : own);
