@@ -409,7 +409,7 @@ PinnedStage::~PinnedStage()
     (void)hipHostFree(ptr);
 }
 
-// The two hint words of a context (see tig_ctx): places of one pinned page that contexts take and give back
+// The hint words of a context (see tig_ctx): places of one pinned page that contexts take and give back
 // (a page of its own per context cost 0.2 ms of tig_init and tig_destroy).  tig_destroy waits for the
 // context's steps, which write them, before it gives the place back.  No place left, or no page: the context
 // does without.
@@ -442,7 +442,8 @@ static void hint_words_take(int32_t **host, int32_t **dev)
     g_hint_taken |= 1ull << k;
     *host = g_hint_host + k * kHintWords;
     *dev = g_hint_dev + k * kHintWords;
-    (*host)[0] = (*host)[1] = 0;
+    for (int i = 0; i < kHintWords; ++i)  // (a former context's)
+        (*host)[i] = 0;
 }
 
 static void hint_words_give(int32_t *host)

@@ -228,6 +228,25 @@ def test_two_layers_that_prepare_each_other(name, dims, batch, order):
     c.close()
 
 
+def test_a_new_context_takes_nothing_over_from_one_that_is_gone():
+    """The first step of a context is the same bits whatever the context before it ran (contexts take over each other's
+    places in the page of hints about recent steps, which size the launches)."""
+    def first_step(count):
+        c = Case(S.WORKLOADS["c1_tiny"], INSTANCES["headline"], False, max_batch=900, layers=2)
+        c.ctx.state_import(*S.make_warm_state(c.w, c.g, 4000))
+        out = c.ctx.alloc_outputs(count)
+        c.ctx.step(4000, count, c.torch.from_numpy(S.make_negatives(c.w, c.g, 4000, count)).to("cuda:0"), out)
+        c.torch.cuda.synchronize()
+        c.close()
+        return out
+
+    first_step(10)
+    behind_small = first_step(900)
+    behind_large = first_step(900)
+    for k in ("emb", "score_pos", "score_neg"):
+        assert getattr(behind_small, k).equal(getattr(behind_large, k)), k
+
+
 def test_c2_two_layers_wide_rows_emb_narrower_than_memory():
     """E = 100 != M = 172: the second layer's rows have a width of their own."""
     w = S.WORKLOADS["c2_bipartite_medium"]
