@@ -11,7 +11,7 @@ struct EmbedParams {
     int dkv, dkvp, Mq, N1, K2, Ep, Ek;
     int row_bytes;  // LDS bytes per query row of the main buffer: [q~ / kvbar (N1) | s_u (Mq)]
     int ld1;        // row stride of the E-wide buffers, bytes
-    int off_h1, off_meta;  // byte offsets in LDS
+    int most_mt;    // sixteenths of the highest tile that LDS holds (embed_height)
     int n_tiles;    // workgroups that take row tiles
     int spread;     // tiles the rows are spread over if they are few (tiles_in_use)
     int n_commit;   // then: workgroups of the memory overwrite; the ones beyond prepare the next batch
@@ -35,9 +35,11 @@ inline int npl_for(const Dims &d)
 // must agree with EmbedShape (heads other than 1 and 2 run the 4-head kernels)
 inline int embed_threads(const Dims &d) { return npl_for(d) >= 8 && d.H > 2 ? 512 : 1024; }
 
+constexpr int kAnyRows = 0;  // a tile's rows: the kernel takes the height for the rows it finds
+
 const void *embed_kernel_bf16(const Dims &d, int rows);
-const void *embed_kernel_fp32(const Dims &d, int rows);
-const void *embed_kernel_train(const Dims &d, int rows);
-const void *embed_kernel_layer(const Dims &d, int rows);
+const void *embed_kernel_fp32(const Dims &d);
+const void *embed_kernel_train(const Dims &d);
+const void *embed_kernel_layer(const Dims &d);
 
 }  // namespace tig

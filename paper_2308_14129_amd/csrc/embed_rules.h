@@ -13,15 +13,23 @@ constexpr int ceil_div(int a, int b) { return (a + b - 1) / b; }
 // and 8 rows and in 24 (groups of four rows, Prec<TIG_FP32>::mma_four): a step of 200 events of 172 columns 54.3 -> 36.8 us, of
 // 500 57.6 -> 46.2, of 1600 92.7 -> 79.1, a training step of 200 224 -> 203.  bf16 products take a fifth of that and are bound by the
 // weights' way from L2, which is the same for any number of rows.
+// The sums of blocks of 16 rows and of groups of four differ in order.  A tile of 24 rows has both, so its last eight must not be
+// rows whose place in the set is a matter of timing: only in a launch with negatives (`negatives`), whose places are fixed, which
+// come last and which are a third of its rows or more.
 constexpr int kHeights[] = {4, 8, 16, 24, 32, 48};
-constexpr bool height_of(bool fp32, int rows) { return fp32 || (rows % 16 == 0); }
+constexpr bool height_of(bool fp32, bool negatives, int rows)
+{
+    return rows % 16 == 0 || (fp32 && (rows < 16 || negatives));
+}
 
 // The lowest tile whose workgroups, one per compute unit at hand, take `rows` query rows: a workgroup's latency grows
-// with its rows.
-constexpr int embed_height(bool fp32, int most_mt, int rows, int units)
+// with its rows.  fp32: evaluated by the kernel, from the rows that the step has (k_embed), because the heights differ in the
+// order of a product's sum and with it in the last bits.  bf16: by the host, from the rows that recent steps had; every height
+// gives the same bits there.
+constexpr int embed_height(bool fp32, bool negatives, int most_mt, int rows, int units)
 {
     for (const int h : kHeights)
-        if (height_of(fp32, h) && h < 16 * most_mt && ceil_div(rows, h) <= units)
+        if (height_of(fp32, negatives, h) && h < 16 * most_mt && ceil_div(rows, h) <= units)
             return h;
     return 16 * most_mt;
 }
@@ -39,16 +47,26 @@ constexpr int tiles_in_use(int n_rows, int height, int units, int loop)
     return least > even ? least : even;
 }
 
-// Workgroups that take the tiles of at most `most` rows, one tile each (the tiles beyond those in use return).
+// Workgroups that take the tiles of at most `most` rows in tiles of `height`, one tile each (the tiles beyond those in use
+// return).
 constexpr int step_workgroups(int most, int height, int units) { return tiles_in_use(most, height, units, 0); }
 
-// The same for a layer of a stack, whose workgroups take tile after tile: no more than there are compute units, and no
-// fewer tiles at a time than these could take.  (Without regard to the height, a workgroup for every eight rows, tiles of
+// The same where the kernel takes the height for its rows, `top` for the most of them: more tiles than compute units are in
+// use only at that height.
+constexpr int any_workgroups(int most, int top, int units)
+{
+    const int tiles = ceil_div(most, top) > units ? ceil_div(most, top) : units;
+    const int lowest = ceil_div(most, kHeights[0]);
+    return tiles < lowest ? tiles : lowest;
+}
+
+// A layer of a stack, whose workgroups take tile after tile: no more than there are compute units, and no fewer tiles at a
+// time than these could take.  (Without regard to the height, a workgroup for every eight rows, tiles of
 // four rows went two by two through half of the workgroups they needed: two layers over 100 events of 172 columns 143 us
 // instead of 114, over 300 173 instead of 146; with tiles of 16 rows at least 136 and 166.)
-constexpr int layer_workgroups(int most, int height, int units)
+constexpr int layer_workgroups(int most, int top, int units)
 {
-    const int tiles = step_workgroups(most, height, units);
+    const int tiles = any_workgroups(most, top, units);
     return tiles < units ? tiles : units;
 }
 

@@ -13,19 +13,25 @@
 //      W_d1[:, :E] emb and W_d1[:, E:] emb (merge layer 2 folded into the decoder weights)
 //      -> per-row arrays in global memory; the decode kernel pairs them up per event
 // State rows are read through row references: the memory table, or the staged GRU output for a
-// node this step updates -- so the memory overwrite M <- s_i(t) itself runs in a few extra
-// workgroups of this launch.
+// node this step updates -- so the memory overwrite M <- s_i(t) itself runs in this launch, in the
+// workgroups that prepare the next batch's queries, behind those, or in a few of its own.
 // The negatives of the batch arrive with the call; the wavefront that takes a negative's row in
 // phase C looks up its neighbours first (a chain of dependent reads that hides behind the other
 // wavefronts' rows).
 // The projections W_Q, W_K, W_V, W_O and the first merge layer are folded into A1 and P at init
 // (pack.hip), which removes the per-neighbour key/value projections.
-// The number of rows is known on the device only: the grid has a tile for every ROWS rows the
-// batch could have, and the tiles beyond those in use (tiles_in_use) return at once.  Row r of tile p is
+// The number of rows is known on the device only: the grid has a workgroup for every tile that the
+// batch could need (embed_rules.h), and those beyond the tiles in use return at once.  Row r of tile p is
 // query row p + (number of tiles in use) * r, which spreads the heavy rows (sources /
 // destinations, first in the set) over all tiles.  Workgroups beyond the tiles and the memory
 // overwrite prepare the batch expected next: one selects its last-message winners, the others
-// merge and look up its queries.
+// merge and look up its queries (and overwrite the memory if nobody else does).
+// An fp32 kernel (ROWS = kAnyRows) holds every height and takes the one for the rows that it finds: the heights
+// differ in the order of a product's sum, so a choice of the host's, from the rows of whichever earlier step had
+// ended by then, would show in the last bits.  (The host's estimate was up to an eighth too high as well: two layers over
+// 4000 events of 100 columns 126.1 -> 116.5 us, over 300 of 172 columns 177 -> 150.  A step takes what it took with a kernel
+// per height at 4 to 24 rows, 80.1 -> 80.2 us at 1600 events of 172 columns, and 2 to 3% more at 32, 168.7 -> 174.3 at 4000
+// and 49.5 -> 51.1 at 4000 of 100.)
 // MODE (EmbedMode): an ordinary step; the forward pass of a training step (TRAIN), which also keeps what the
 // backward pass reads (state rows, q~, kvbar, h1 per row of the query set); one attention layer of a stack (LAYER):
 // every row of the set, the negatives' too, has its neighbours and references already, the "memory" is the table
@@ -94,9 +100,16 @@ constexpr int regs_touching(int lo, int hi, int dims)
 static_assert(sizeof(StepArgs) % alignof(PackedWeights) == 0 && (sizeof(StepArgs) + sizeof(PackedWeights)) % alignof(EmbedParams) == 0,
               "the kernel's arguments follow each other without gaps");
 
+// distinct source / destination queries of the launch's set
+__device__ inline int distinct_queries(const StepArgs &a)
+{
+    const int n = *a.qs.n_u;
+    return n < 2 * a.count ? n : 2 * a.count;
+}
+
+// The workgroups that take tiles of ROWS rows.
 template <int PREC, int MODE, int ROWS, int NPL, int H, int SHAPE>
-__global__ void __launch_bounds__((EmbedShape<NPL, H>::kThreads))
-k_embed(StepArgs a_, PackedWeights w_, EmbedParams p_)
+__device__ __forceinline__ void embed_tiles(const StepArgs &a_, const PackedWeights &w_, const EmbedParams &p_, int n_u)
 {
     constexpr bool TRAIN = MODE == kEmbedTrain, LAYER = MODE == kEmbedLayer;
     // Steps that were computed layer by layer, without folded weights, before they came to this kernel are no further
@@ -111,55 +124,22 @@ k_embed(StepArgs a_, PackedWeights w_, EmbedParams p_)
     constexpr int MT = ROWS / 16, RG = ROWS % 16 / 4;  // blocks of 16 rows, then groups of four (TileRows)
     using TR = TileRows<PREC, MT, RG>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    if ((int)blockIdx.x >= p_.n_tiles) {
-        int x = (int)blockIdx.x - p_.n_tiles;
-        if (x < p_.n_commit) {
-            overwrite_memory(a_, p_.M, x * kEmbedWaves + wave_id(), p_.n_commit * kEmbedWaves);
-            return;
-        }
-        x -= p_.n_commit;
-        // The workgroups beyond, on compute units this launch leaves idle (launched only with
-        // 1024 threads): last-message selection and query preparation for a later step.
-        if constexpr (kEmbedThreads == kScatterThreads) {
-            TIG_MARK(0);
-            if (x == 0 && threadIdx.x == 0 && a_.rows_seen) {
-                // hints for the host (stores to its memory take a while: from a workgroup that ends
-                // long before the launch does)
-                a_.rows_seen[0] = *a_.qs.n_u + (a_.roles == 3 ? a_.count : 0);  // (a hint: not clamped)
-                if (a_.msg_count > 0)
-                    a_.rows_seen[1] = *a_.n_win;
-            }
-            if (a_.sel.count > 0) {
-                if (x == 0) {
-                    winners_block(a_, a_.sel, smem);
-                    TIG_MARK(7);
-                    return;
-                }
-                --x;
-            }
-            if (a_.ded.count > 0 && x < a_.ded.n_wgs) {
-                dedup_block(a_, a_.ded, p_.K, x, smem);
-                if (p_.commit_beside)
-                    overwrite_memory(a_, p_.M, x * kEmbedWaves + wave_id(), a_.ded.n_wgs * kEmbedWaves);
-            }
-            TIG_MARK(7);
-        }
-        return;
-    }
     int pass = (int)blockIdx.x;
 next_tile:
-    // LAYER: the arguments are read again for every tile, from a pointer that the compiler cannot see through: what it
-    // takes out of the loop otherwise (every address that does not depend on the tile) needs 250 registers and
-    // 824 bytes of scratch per lane (105 us for the first layer of 4000 events, 46 this way).
+    // fp32: the arguments are read again in every body and for every tile, from a pointer that the compiler cannot see through.
+    // What it takes out of a layer's loop otherwise (every address that does not depend on the tile) needs 250 registers and
+    // 824 bytes of scratch per lane (105 us for the first layer of 4000 events, 46 this way), and what it takes out of the
+    // bodies of a kernel that has several spills scalar registers (1 us of every step).
+    constexpr bool AGAIN = PREC == TIG_FP32;
     typedef const __attribute__((address_space(4))) char *Args;
     Args at = nullptr;
-    if constexpr (LAYER) {
+    if constexpr (AGAIN) {
         at = (Args)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(at));
     }
-    const StepArgs &a = LAYER ? *(const StepArgs *)at : a_;
-    const PackedWeights &w = LAYER ? *(const PackedWeights *)(at + sizeof(StepArgs)) : w_;
-    const EmbedParams &p = LAYER ? *(const EmbedParams *)(at + sizeof(StepArgs) + sizeof(PackedWeights)) : p_;
+    const StepArgs &a = AGAIN ? *(const StepArgs *)at : a_;
+    const PackedWeights &w = AGAIN ? *(const PackedWeights *)(at + sizeof(StepArgs)) : w_;
+    const EmbedParams &p = AGAIN ? *(const EmbedParams *)(at + sizeof(StepArgs) + sizeof(PackedWeights)) : p_;
     using P = Prec<PREC>;
     using SH = RowShape<SHAPE>;
     // segment sizes and segment-to-register maps of a key/value row, as phase C uses them
@@ -173,8 +153,8 @@ next_tile:
     constexpr int KC = NPL >= 8 ? 5 : (NPL == 4 ? 10 : 16);      // neighbour rows in flight
     constexpr int NPHI = NPL;  // registers that may hold time-encoding dims (T <= 64 * NPL)
     char *rowbuf = smem;
-    char *h1buf = smem + p.off_h1;
-    int *row_q = (int *)(smem + p.off_meta);  // [ROWS] row of the query set or -1
+    char *h1buf = smem + ROWS * p.row_bytes;
+    int *row_q = (int *)(h1buf + ROWS * p.ld1);  // [ROWS] row of the query set or -1
     int *row_cnt = row_q + ROWS;              // [ROWS]
     int *row_ref = row_cnt + ROWS;            // [ROWS] row reference of the node's own state
     double *row_t = (double *)(row_ref + ROWS);   // [ROWS] query time
@@ -183,11 +163,9 @@ next_tile:
     int *row_todo = next_row + 4;                 // [ROWS] 1: a negative whose neighbours phase C looks up
 
     const int lane = lane_id();
-    const int wave = LAYER ? wave_id_uniform() : wave_id();
+    const int wave = PREC == TIG_FP32 ? wave_id_uniform() : wave_id();
     const int mem_off = 4 * p.N1;
-    int n_u = *a.qs.n_u;  // distinct source / destination queries; the negatives' rows follow at 2 * count
-    n_u = n_u < 2 * a.count ? n_u : 2 * a.count;
-    const int neg_row0 = 2 * a.count;
+    const int neg_row0 = 2 * a.count;  // (of n_u distinct source / destination queries and the negatives)
     const int n_rows = n_u + (a.roles == 3 ? a.count : 0);
     const int n_passes = tiles_in_use(n_rows, ROWS, p.spread, LAYER ? p.n_tiles : 0);
     if (pass >= n_passes)
@@ -864,6 +842,73 @@ next_tile:
     }
 }
 
+template <int PREC, int MODE, int ROWS, int NPL, int H, int SHAPE>
+__global__ void __launch_bounds__((EmbedShape<NPL, H>::kThreads))
+k_embed(StepArgs a_, PackedWeights w_, EmbedParams p_)
+{
+    constexpr int kEmbedThreads = EmbedShape<NPL, H>::kThreads;
+    constexpr int kEmbedWaves = EmbedShape<NPL, H>::kWaves;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    if ((int)blockIdx.x >= p_.n_tiles) {
+        int x = (int)blockIdx.x - p_.n_tiles;
+        if (x < p_.n_commit) {
+            overwrite_memory(a_, p_.M, x * kEmbedWaves + wave_id(), p_.n_commit * kEmbedWaves);
+            return;
+        }
+        x -= p_.n_commit;
+        // The workgroups beyond, on compute units this launch leaves idle (launched only with
+        // 1024 threads): last-message selection and query preparation for a later step.
+        if constexpr (kEmbedThreads == kScatterThreads) {
+            TIG_MARK(0);
+            if (x == 0 && threadIdx.x == 0 && a_.rows_seen) {
+                // hints for the host (stores to its memory take a while: from a workgroup that ends
+                // long before the launch does)
+                a_.rows_seen[0] = *a_.qs.n_u + (a_.roles == 3 ? a_.count : 0);  // (a hint: not clamped)
+                if (a_.msg_count > 0)
+                    a_.rows_seen[1] = *a_.n_win;
+            }
+            if (a_.sel.count > 0) {
+                if (x == 0) {
+                    winners_block(a_, a_.sel, smem);
+                    TIG_MARK(7);
+                    return;
+                }
+                --x;
+            }
+            if (a_.ded.count > 0 && x < a_.ded.n_wgs) {
+                dedup_block(a_, a_.ded, p_.K, x, smem);
+                if (p_.commit_beside)
+                    overwrite_memory(a_, p_.M, x * kEmbedWaves + wave_id(), a_.ded.n_wgs * kEmbedWaves);
+            }
+            TIG_MARK(7);
+        }
+        return;
+    }
+    const int n_u = distinct_queries(a_);
+    if constexpr (ROWS > 0) {
+        embed_tiles<PREC, MODE, ROWS, NPL, H, SHAPE>(a_, w_, p_, n_u);
+    } else {
+        // (one word of every cache line of the arguments, which the body reads: on their way while the count is, 0.3 us)
+        typedef const __attribute__((address_space(4))) int *Words;
+        const Words arg = (Words)__builtin_amdgcn_kernarg_segment_ptr();
+        constexpr int kWords = (int)(sizeof(StepArgs) + sizeof(PackedWeights) + sizeof(EmbedParams)) / 4;
+        int touched = 0;
+#pragma unroll
+        for (int i = 0; i < kWords; i += 16)
+            touched |= arg[i];
+        asm volatile("" ::"s"(touched));
+        const int n = __builtin_amdgcn_readfirstlane(n_u);
+        switch (embed_height(true, a_.roles == 3, p_.most_mt, n + (a_.roles == 3 ? a_.count : 0), p_.spread)) {
+        case 4: embed_tiles<PREC, MODE, 4, NPL, H, SHAPE>(a_, w_, p_, n); break;
+        case 8: embed_tiles<PREC, MODE, 8, NPL, H, SHAPE>(a_, w_, p_, n); break;
+        case 16: embed_tiles<PREC, MODE, 16, NPL, H, SHAPE>(a_, w_, p_, n); break;
+        case 24: embed_tiles<PREC, MODE, 24, NPL, H, SHAPE>(a_, w_, p_, n); break;
+        case 32: embed_tiles<PREC, MODE, 32, NPL, H, SHAPE>(a_, w_, p_, n); break;
+        default: embed_tiles<PREC, MODE, 48, NPL, H, SHAPE>(a_, w_, p_, n); break;
+        }
+    }
+}
+
 template <int PREC, int MODE, int ROWS, int NPL>
 const void *pick_h(int H)
 {
@@ -882,23 +927,11 @@ constexpr int npl_of_dims(int dims)
     return npl;
 }
 
-template <int PREC, int MODE, int SHAPE>
-const void *pick_fixed(int rows)
+template <int PREC, int MODE, int ROWS, int SHAPE>
+const void *pick_fixed()
 {
     using SH = RowShape<SHAPE>;
-    constexpr int NPL = npl_of_dims(SH::T + SH::M + SH::F);
-    if constexpr (PREC == TIG_FP32)
-        switch (rows) {
-        case 4: return (const void *)k_embed<PREC, MODE, 4, NPL, SH::H, SHAPE>;
-        case 8: return (const void *)k_embed<PREC, MODE, 8, NPL, SH::H, SHAPE>;
-        case 24: return (const void *)k_embed<PREC, MODE, 24, NPL, SH::H, SHAPE>;
-        default: break;
-        }
-    switch (rows) {
-    case 16: return (const void *)k_embed<PREC, MODE, 16, NPL, SH::H, SHAPE>;
-    case 32: return (const void *)k_embed<PREC, MODE, 32, NPL, SH::H, SHAPE>;
-    default: return (const void *)k_embed<PREC, MODE, 48, NPL, SH::H, SHAPE>;
-    }
+    return (const void *)k_embed<PREC, MODE, ROWS, npl_of_dims(SH::T + SH::M + SH::F), SH::H, SHAPE>;
 }
 
 template <int SHAPE>
@@ -919,37 +952,20 @@ const void *pick_npl(int npl, int H)
     }
 }
 
-template <int PREC, int MODE>
-const void *pick_rows(int rows, int npl, int H)
-{
-    if constexpr (PREC == TIG_FP32)
-        switch (rows) {
-        case 4: return pick_npl<PREC, MODE, 4>(npl, H);
-        case 8: return pick_npl<PREC, MODE, 8>(npl, H);
-        case 24: return pick_npl<PREC, MODE, 24>(npl, H);
-        default: break;
-        }
-    switch (rows) {
-    case 16: return pick_npl<PREC, MODE, 16>(npl, H);
-    case 32: return pick_npl<PREC, MODE, 32>(npl, H);
-    default: return pick_npl<PREC, MODE, 48>(npl, H);
-    }
-}
-
 // Row shapes compiled in (RowShape; any other takes the general instances, whose widths are arguments): with their widths
 // known, which register holds what is decided at compile time and the time-encoding parameters stay in registers.  They
 // bring a training step 9% at 172 and 4% at 100 state columns (20 steps 4.85 -> 4.46 and 4.59 -> 4.43 ms) and two layers
 // over 4000 events 14% (148.6 -> 128.3 us).
-template <int PREC, int MODE>
-const void *pick(const Dims &d, int rows)
+template <int PREC, int MODE, int ROWS>
+const void *pick(const Dims &d)
 {
     if (shape_is<1>(d))
-        return pick_fixed<PREC, MODE, 1>(rows);
+        return pick_fixed<PREC, MODE, ROWS, 1>();
     if (shape_is<2>(d))
-        return pick_fixed<PREC, MODE, 2>(rows);
+        return pick_fixed<PREC, MODE, ROWS, 2>();
     if (shape_is<3>(d))
-        return pick_fixed<PREC, MODE, 3>(rows);
-    return pick_rows<PREC, MODE>(rows, npl_for(d), d.H);
+        return pick_fixed<PREC, MODE, ROWS, 3>();
+    return pick_npl<PREC, MODE, ROWS>(npl_for(d), d.H);
 }
 
 }  // namespace

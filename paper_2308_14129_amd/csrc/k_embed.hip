@@ -9,7 +9,7 @@ namespace tig {
 
 namespace {
 
-EmbedParams embed_params(const Dims &d, int rows)
+EmbedParams embed_params(const Dims &d, int most_mt)
 {
     EmbedParams p;
     p.M = d.M;
@@ -26,8 +26,7 @@ EmbedParams embed_params(const Dims &d, int rows)
     p.Ek = d.Ek;
     p.row_bytes = lds_row_bytes(d.N1 + d.Mq);
     p.ld1 = lds_row_bytes(d.Ek);
-    p.off_h1 = (rows * p.row_bytes + 15) / 16 * 16;
-    p.off_meta = p.off_h1 + rows * p.ld1;
+    p.most_mt = most_mt;
     p.n_tiles = p.spread = 0;
     p.n_commit = p.commit_beside = 0;
     p.phi_regs = p.mem_regs = p.feat_regs = 0;
@@ -44,17 +43,31 @@ EmbedParams embed_params(const Dims &d, int rows)
 }
 
 // (kernels of each precision are a translation unit of their own)
+bool any_rows(const Dims &d, bool train) { return train || d.prec == TIG_FP32; }
+
 const void *embed_kernel(const Dims &d, int rows, bool train)
 {
     if (train)
-        return embed_kernel_train(d, rows);
-    return d.prec == TIG_BF16_MFMA ? embed_kernel_bf16(d, rows) : embed_kernel_fp32(d, rows);
+        return embed_kernel_train(d);
+    return any_rows(d, train) ? embed_kernel_fp32(d) : embed_kernel_bf16(d, rows);
 }
 
 int lds_of(const Dims &d, int rows)
 {
-    const EmbedParams p = embed_params(d, rows);
-    return p.off_meta + rows * (4 * 4 + 8) + d.T * 16 + 16;
+    return rows * (lds_row_bytes(d.N1 + d.Mq) + lds_row_bytes(d.Ek) + 4 * 4 + 8) + d.T * 16 + 16;
+}
+
+hipError_t allow_lds(const Dims &d, const void *kernel, int rows)
+{
+    const int own = lds_of(d, rows);
+    const int lds = embed_threads(d) == kScatterThreads && own < kOneLds ? kOneLds : own;
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+}
+
+int launch_lds(const Dims &d, const StepArgs &a, int rows)
+{
+    const int own = lds_of(d, rows);
+    return a.sel.count > 0 && own < kOneLds ? kOneLds : (own < kPrepLds ? kPrepLds : own);
 }
 
 }  // namespace
@@ -70,35 +83,16 @@ int layer_tiles(const Dims &d, int lds_limit)
     return mt;
 }
 
-hipError_t prepare_embed_layer(const Dims &d, int most_mt)
-{
-    for (const int h : kHeights) {
-        if (!height_of(true, h) || h > 16 * most_mt)
-            continue;
-        const int own = lds_of(d, h);
-        const int lds = embed_threads(d) == kScatterThreads && own < kOneLds ? kOneLds : own;
-        const hipError_t e =
-            hipFuncSetAttribute(embed_kernel_layer(d, h), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess)
-            return e;
-    }
-    return hipSuccess;
-}
+hipError_t prepare_embed_layer(const Dims &d, int most_mt) { return allow_lds(d, embed_kernel_layer(d), 16 * most_mt); }
 
 hipError_t prepare_embed(const Dims &d, const LaunchPlan &plan, bool train)
 {
-    const int most_mt = plan.emb_mt;
-    for (const int h : kHeights) {
-        if (!height_of(train || d.prec == TIG_FP32, h) || h > 16 * most_mt)
-            continue;
-        const int own = lds_of(d, h);
-        const int lds = embed_threads(d) == kScatterThreads && own < kOneLds ? kOneLds : own;
-        const hipError_t e =
-            hipFuncSetAttribute(embed_kernel(d, h, train), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess)
-            return e;
-    }
-    return hipSuccess;
+    if (any_rows(d, train))
+        return allow_lds(d, embed_kernel(d, 0, train), 16 * plan.emb_mt);
+    hipError_t e = hipSuccess;
+    for (int mt = 1; mt <= plan.emb_mt && e == hipSuccess; ++mt)
+        e = allow_lds(d, embed_kernel(d, 16 * mt, train), 16 * mt);
+    return e;
 }
 
 // Workgroups of the preparation of a batch of `count` events.  When it shares a launch, every
@@ -145,42 +139,45 @@ hipError_t launch_embed(const Dims &d, const LaunchPlan &plan, const PackedWeigh
     }
     const int extra = n_commit + (a.sel.count > 0 ? 1 : 0) + (a.ded.count > 0 ? a.ded.n_wgs : 0);
     const int cus = plan.num_cus > 0 ? plan.num_cus : 256;
-    const int units = cus - extra > 16 ? cus - extra : 16;
-    // The tile height follows the number of distinct rows recent steps had (any height is correct:
-    // the grid covers the most rows the batch can have, and tiles beyond the actual count return).
     const int most = a.roles * a.count;
-    const int rows = a.rows_est > 0 && a.rows_est < most ? a.rows_est : most;
-    const int height = embed_height(train || d.prec == TIG_FP32, plan.emb_mt, rows, units);
-    EmbedParams p = embed_params(d, height);
+    const bool any = any_rows(d, train);
+    // Compute units for the tiles.  Where the heights differ in the last bits, as many for every kind of call with that many
+    // events: a call that prepares nothing leaves those free that another needs for it.
+    int side = extra;
+    if (any) {
+        const int per_block = 4 * (threads / kWave), overwrite = (2 * a.count + per_block - 1) / per_block;
+        const int spare = winners_in_one_launch(a.count) ? embed_spare_workgroups(d, plan, a.roles, a.count) : 0;
+        side = spare > 0 ? spare : (overwrite < 16 ? overwrite : 16);
+    }
+    const int units = cus - side > 16 ? cus - side : 16;
+    // (any height is correct: the grid covers the most rows the batch can have, and tiles beyond the actual count return)
+    const int rows = !any && a.rows_est > 0 && a.rows_est < most ? a.rows_est : most;
+    const int height = embed_height(any, a.roles == 3, plan.emb_mt, rows, units);
+    EmbedParams p = embed_params(d, plan.emb_mt);
     p.spread = units;
-    p.n_tiles = step_workgroups(most, height, units);
+    p.n_tiles = any ? any_workgroups(most, height, units) : step_workgroups(most, height, units);
     p.n_commit = n_commit;
     p.commit_beside = beside ? 1 : 0;
     void *args[] = {&aa, &ww, &p};
-    const int own = lds_of(d, height);
-    const int lds = a.sel.count > 0 && own < kOneLds ? kOneLds : (own < kPrepLds ? kPrepLds : own);
-    return hipLaunchKernel(embed_kernel(d, height, train), dim3(p.n_tiles + extra), dim3(threads), args, (size_t)lds, s);
+    return hipLaunchKernel(embed_kernel(d, height, train), dim3(p.n_tiles + extra), dim3(threads), args, (size_t)launch_lds(d, a, height), s);
 }
 
-// One attention layer over the rows of a.qs (d, pw: the layer's); a.rows_est (0: unknown) sizes the tiles.  The grid
-// fills the compute units once, its workgroups take tile after tile.
-hipError_t launch_embed_layer(const Dims &d, int most_mt, int num_cus, const PackedWeights &pw, const StepArgs &a, hipStream_t s)
+// One attention layer over the rows of a.qs (d, pw: the layer's).  The grid fills the compute units once, but for `side` of
+// them that other work of the launch may take; its workgroups take tile after tile.
+hipError_t launch_embed_layer(const Dims &d, int most_mt, int num_cus, int side, const PackedWeights &pw, const StepArgs &a, hipStream_t s)
 {
     StepArgs aa = a;
     PackedWeights ww = pw;
     const int extra = (a.sel.count > 0 ? 1 : 0) + (a.ded.count > 0 ? a.ded.n_wgs : 0);
     const int cus = num_cus > 0 ? num_cus : 256;
-    const int units = cus - extra > 16 ? cus - extra : 16;
+    const int units = cus - side > 16 ? cus - side : 16;
     const int most = a.roles * a.count;
-    const int rows = a.rows_est > 0 && a.rows_est < most ? a.rows_est : most;
-    const int height = embed_height(true, most_mt, rows, units);
-    EmbedParams p = embed_params(d, height);
+    const int top = embed_height(true, a.roles == 3, most_mt, most, units);
+    EmbedParams p = embed_params(d, most_mt);
     p.spread = units;
-    p.n_tiles = layer_workgroups(most, height, units);
+    p.n_tiles = layer_workgroups(most, top, units);
     void *args[] = {&aa, &ww, &p};
-    const int own = lds_of(d, height);
-    const int lds = a.sel.count > 0 && own < kOneLds ? kOneLds : (own < kPrepLds ? kPrepLds : own);
-    return hipLaunchKernel(embed_kernel_layer(d, height), dim3(p.n_tiles + extra), dim3(embed_threads(d)), args, (size_t)lds, s);
+    return hipLaunchKernel(embed_kernel_layer(d), dim3(p.n_tiles + extra), dim3(embed_threads(d)), args, (size_t)launch_lds(d, a, top), s);
 }
 
 }  // namespace tig

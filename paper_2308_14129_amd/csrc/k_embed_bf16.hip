@@ -10,6 +10,11 @@ extern "C" __attribute__((visibility("default"))) int tig_debug_phase_clocks_bf1
 }
 #endif
 
-const void *embed_kernel_bf16(const Dims &d, int rows) { return pick<TIG_BF16_MFMA, kEmbedStep>(d, rows); }
+const void *embed_kernel_bf16(const Dims &d, int rows)
+{
+    return rows == 16   ? pick<TIG_BF16_MFMA, kEmbedStep, 16>(d)
+           : rows == 32 ? pick<TIG_BF16_MFMA, kEmbedStep, 32>(d)
+                        : pick<TIG_BF16_MFMA, kEmbedStep, 48>(d);
+}
 
 }  // namespace tig

@@ -10,6 +10,6 @@ extern "C" __attribute__((visibility("default"))) int tig_debug_phase_clocks_fp3
 }
 #endif
 
-const void *embed_kernel_fp32(const Dims &d, int rows) { return pick<TIG_FP32, kEmbedStep>(d, rows); }
+const void *embed_kernel_fp32(const Dims &d) { return pick<TIG_FP32, kEmbedStep, kAnyRows>(d); }
 
 }  // namespace tig

@@ -3,6 +3,6 @@
 
 namespace tig {
 
-const void *embed_kernel_layer(const Dims &d, int rows) { return pick<TIG_FP32, kEmbedLayer>(d, rows); }
+const void *embed_kernel_layer(const Dims &d) { return pick<TIG_FP32, kEmbedLayer, kAnyRows>(d); }
 
 }  // namespace tig

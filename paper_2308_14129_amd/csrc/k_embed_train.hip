@@ -10,6 +10,6 @@ extern "C" __attribute__((visibility("default"))) int tig_debug_phase_clocks_tra
 }
 #endif
 
-const void *embed_kernel_train(const Dims &d, int rows) { return pick<TIG_FP32, kEmbedTrain>(d, rows); }
+const void *embed_kernel_train(const Dims &d) { return pick<TIG_FP32, kEmbedTrain, kAnyRows>(d); }
 
 }  // namespace tig

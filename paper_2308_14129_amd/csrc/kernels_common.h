@@ -115,7 +115,7 @@ __device__ inline int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ inline int wave_id() { return threadIdx.x / kWave; }
 // The same as a scalar.  What follows from wave_id() -- tiles, ranges, addresses -- is a value per lane to the compiler,
 // a condition on it a mask, and a load behind such a condition a round trip of its own.  (Not for every kernel: the
-// one-layer embedding tiles and k_mod_final are 0.5 us slower with it, out of scalar registers.)
+// bf16 embedding tiles and k_mod_final are 0.5 us slower with it, out of scalar registers.)
 __device__ inline int wave_id_uniform() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave); }
 
 template <int CTRL, int ROW_MASK, int BANK_MASK>

@@ -304,11 +304,8 @@ __global__ void __launch_bounds__(kTwoThreads) k_two_claim(StepArgs a, ModParams
     int n_u;
     const int n_rows = two_rows(a, n_u), lane = lane_id(), wave = wave_id();
     int32_t *counter = p.it.n_u + (epoch & 1u);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0)
         p.it.n_u[(epoch & 1u) ^ 1u] = 0;  // (the next step's)
-        if (a.rows_seen)
-            a.rows_seen[2] = n_rows;      // (a hint for the host)
-    }
     const int x = (int)blockIdx.x * kTwoWaves + wave;
     const bool valid = x < n_rows;  // (uniform over the wavefront)
     const int q = valid ? two_query_row(a, n_u, x) : 0;
@@ -1275,7 +1272,7 @@ hipError_t clear_two_layers(const ModParams &p, hipStream_t s)
 }
 
 hipError_t launch_two_layers(const Dims &d, int num_cus, const PackedWeights &pw, const StepArgs &a, const ModParams &p, uint32_t epoch,
-                             const int32_t *seen, hipStream_t s, int *launches)
+                             hipStream_t s, int *launches)
 {
     const int B = a.count, K = d.K;
     const int rows = a.roles * B, cus = num_cus > 0 ? num_cus : 256;
@@ -1306,7 +1303,10 @@ hipError_t launch_two_layers(const Dims &d, int num_cus, const PackedWeights &pw
     one.roles = 2;
     one.emb_u = p.h1;
     one.dec_a = one.dec_b = nullptr;
-    if ((e = launch_embed_layer(d, p.mt[0], num_cus, pw, one, s)) != hipSuccess)
+    LaunchPlan plan = {};
+    plan.num_cus = cus;
+    const int side = winners_in_one_launch(B) ? embed_spare_workgroups(d, plan, a.roles, B) : 0;
+    if ((e = launch_embed_layer(d, p.mt[0], num_cus, side, pw, one, s)) != hipSuccess)
         return e;
     StepArgs two = a;
     two.msg_count = 0;
@@ -1315,10 +1315,8 @@ hipError_t launch_two_layers(const Dims &d, int num_cus, const PackedWeights &pw
     two.qs.ref = p.ref2;
     two.qs.self_ref = p.self2;
     two.sel.count = two.ded.count = 0;
-    const int n = seen ? ((const volatile int32_t *)seen)[2] : 0;
-    two.rows_est = n > 0 ? n + n / 8 : 0;
     *launches += 3 + (n_commit + n_neg > 0 ? 1 : 0);  // (beyond embedding and closing launch)
-    return launch_embed_layer(p.d2, p.mt[1], num_cus, p.pw2, two, s);
+    return launch_embed_layer(p.d2, p.mt[1], num_cus, 0, p.pw2, two, s);
 }
 
 }  // namespace tig

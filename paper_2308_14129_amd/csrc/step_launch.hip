@@ -100,7 +100,7 @@ hipError_t launch_step(const Dims &d, const LaunchPlan &plan, const PackedWeight
         last.gru_br = pw.gru_br, last.gru_bz = pw.gru_bz, last.gru_bin = pw.gru_bin, last.gru_bhn = pw.gru_bhn;
         if (sp.mod_clear && (e = clear_two_layers(*sp.mods, s)) != hipSuccess)
             return e;
-        if ((e = launch_two_layers(d, plan.num_cus, pw, a, *sp.mods, sp.mod_epoch, sp.seen, s, sp.mod_launches)) != hipSuccess ||
+        if ((e = launch_two_layers(d, plan.num_cus, pw, a, *sp.mods, sp.mod_epoch, s, sp.mod_launches)) != hipSuccess ||
             (e = stamp()) != hipSuccess || (e = launch_closing(d, plan, last, a, sp.ahead, s)) != hipSuccess)
             return e;
         return stamp();

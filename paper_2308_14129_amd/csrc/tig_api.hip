@@ -798,7 +798,6 @@ static int step_impl(tig_ctx *ctx, const tig_batch *batch, const tig_out *out, h
     if (general) {
         sp.mods = &ctx->mods;
         sp.mod_launches = &launches;
-        sp.seen = ctx->rows_seen_host;
         if (two_layers_fused(ctx->mods)) {
             sp.mod_clear = !ctx->mod_clean || ctx->mod_epoch == 0xFFFFFFFFu;
             ctx->mod_epoch = sp.mod_clear ? 1u : ctx->mod_epoch + 1u;

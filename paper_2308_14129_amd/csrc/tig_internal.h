@@ -252,7 +252,7 @@ hipError_t launch_gru(const Dims &d, const LaunchPlan &plan, const PackedWeights
 // selection and query preparation for the batch expected next
 hipError_t launch_embed(const Dims &d, const LaunchPlan &plan, const PackedWeights &pw, const StepArgs &a,
                         hipStream_t s);
-hipError_t launch_embed_layer(const Dims &d, int most_mt, int num_cus, const PackedWeights &pw, const StepArgs &a, hipStream_t s);
+hipError_t launch_embed_layer(const Dims &d, int most_mt, int num_cus, int side, const PackedWeights &pw, const StepArgs &a, hipStream_t s);
 // scores and per-query embeddings from the distinct rows, optional inspection outputs, finishing pass
 // of the batch prepared ahead, GRU of the batch the next step applies
 hipError_t launch_closing(const Dims &d, const LaunchPlan &plan, const PackedWeights &pw, const StepArgs &a,
@@ -286,7 +286,6 @@ struct StepPlan {
     int *mod_launches;             // ... where launch_modules adds its launches
     uint32_t mod_epoch;            // two fused layers: the step's epoch
     bool mod_clear;                // ... and whether claims and counters have to be cleared first
-    const int32_t *seen;           // the context's hint words (host), or NULL
 };
 // does the step copy neighbour lists or winner flags out
 inline bool wants_inspection(const StepArgs &a)
@@ -370,7 +369,7 @@ bool two_layers_fused(const ModParams &p);
 hipError_t clear_two_layers(const ModParams &p, hipStream_t s);
 // embedding rows of two stacked layers (memory overwrite first); `epoch`: new for every call, never 0
 hipError_t launch_two_layers(const Dims &d, int num_cus, const PackedWeights &pw, const StepArgs &a, const ModParams &p, uint32_t epoch,
-                             const int32_t *seen, hipStream_t s, int *launches);
+                             hipStream_t s, int *launches);
 hipError_t launch_mean_messages(const Dims &d, const StepArgs &a, const ModParams &p, hipStream_t s);
 // everything after the state update of a step of a context with a module selection that the fused launches
 // do not cover; adds the launches it made to *launches

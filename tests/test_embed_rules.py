@@ -11,10 +11,11 @@ CSRC = os.path.join(ROOT, "paper_2308_14129_amd", "csrc")
 WRAPPERS = """
 #include "embed_rules.h"
 extern "C" {
-int height(int fp32, int most_mt, int rows, int units) { return tig::embed_height(fp32, most_mt, rows, units); }
+int height(int fp32, int neg, int most_mt, int rows, int units) { return tig::embed_height(fp32, neg, most_mt, rows, units); }
 int tiles(int n_rows, int height, int units, int loop) { return tig::tiles_in_use(n_rows, height, units, loop); }
 int step_wgs(int most, int height, int units) { return tig::step_workgroups(most, height, units); }
-int layer_wgs(int most, int height, int units) { return tig::layer_workgroups(most, height, units); }
+int any_wgs(int most, int top, int units) { return tig::any_workgroups(most, top, units); }
+int layer_wgs(int most, int top, int units) { return tig::layer_workgroups(most, top, units); }
 }
 """
 
@@ -35,28 +36,56 @@ def estimates(most):
     return sorted({most, max(1, most * 9 // 10), max(1, most // 2), max(1, most // 7)})
 
 
+def possible(most):
+    return sorted(set(range(1, most, max(1, most // 97))) | {most - 1, most} - {0})
+
+
+@pytest.mark.parametrize("neg", [0, 1])
 @pytest.mark.parametrize("most_mt", [1, 2, 3])
-def test_layer_rounds_are_what_the_compute_units_need(rules, most_mt):
+def test_layer_rounds_are_what_the_compute_units_need(rules, most_mt, neg):
     # no workgroup takes a second tile while there are compute units without one, whatever the tile's height
     for units in UNITS:
         for most in ROWS:
-            for rows in estimates(most):
-                h = rules.height(1, most_mt, rows, units)
-                loop = rules.layer_wgs(most, h, units)
-                assert 1 <= loop <= units
-                for n in {1, rows // 2, rows}:
-                    used = rules.tiles(n, h, units, loop)
-                    assert used * h >= n
-                    assert -(-used // loop) <= max(1, -(-(-(-n // h)) // units)), (units, most, rows, h, n)
+            loop = rules.layer_wgs(most, rules.height(1, neg, most_mt, most, units), units)
+            assert 1 <= loop <= units
+            for n in possible(most):
+                h = rules.height(1, neg, most_mt, n, units)
+                used = rules.tiles(n, h, units, loop)
+                assert used * h >= n
+                assert -(-used // loop) <= max(1, -(-(-(-n // h)) // units)), (units, most, h, n)
 
 
-@pytest.mark.parametrize("fp32", [0, 1])
-def test_every_row_of_a_step_has_a_workgroup(rules, fp32):
+@pytest.mark.parametrize("neg", [0, 1])
+@pytest.mark.parametrize("most_mt", [1, 2, 3])
+def test_every_row_of_a_step_has_a_workgroup_at_the_height_the_kernel_takes(rules, most_mt, neg):
+    for units in UNITS:
+        for most in ROWS:
+            top = rules.height(1, neg, most_mt, most, units)
+            wgs = rules.any_wgs(most, top, units)
+            for n in possible(most):
+                h = rules.height(1, neg, most_mt, n, units)
+                used = rules.tiles(n, h, units, 0)
+                assert h <= top and used <= wgs and used * h >= n, (units, most, h, n)
+
+
+def test_every_row_of_a_step_has_a_workgroup_at_the_height_the_host_takes(rules):
     for units in UNITS:
         for most in ROWS:
             for rows in estimates(most):
-                h = rules.height(fp32, 3, rows, units)
+                h = rules.height(0, 1, 3, rows, units)
                 wgs = rules.step_wgs(most, h, units)
                 for n in {1, rows // 2, rows, most}:
                     used = rules.tiles(n, h, units, 0)
                     assert used <= wgs and used * h >= n
+
+
+def test_only_negatives_lie_in_the_last_eight_of_24_rows(rules):
+    # (row r of tile p is row p + tiles * r of the set, negatives last; the places of the others are a matter of timing)
+    for units in UNITS:
+        for count in [1, 2, 7, 300, 597, 1021, 1100, 1250, 1790, 2000, 4099]:
+            for n_u in possible(2 * count):
+                n = n_u + count
+                assert rules.height(1, 0, 3, n, units) != 24
+                if rules.height(1, 1, 3, n, units) == 24:
+                    for loop in (0, 1, units // 2, units):
+                        assert 16 * rules.tiles(n, 24, units, loop) >= n_u, (units, count, n_u)

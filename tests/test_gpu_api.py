@@ -166,6 +166,38 @@ def test_reset_export_import_roundtrip_and_determinism(c1):
     ctx.close()
 
 
+# counts at which the number of compute units for the tiles, or the rows of an earlier step, used to decide the tiles' height
+@pytest.mark.parametrize("count", [300, 620, 900])
+def test_bits_of_a_step_do_not_depend_on_what_ran_before_or_the_kind_of_call(c1, count):
+    import torch
+    w, W, first = c1.w, c1.W, 4000
+    neg = torch.from_numpy(S.make_negatives(w, c1.g, first, count)).to("cuda:0")
+
+    def play(behind=0, static=False, last=False):
+        g = c1.g
+        if last:
+            end = first + count
+            g = S.Graph(g.num_nodes, g.src[:end], g.dst[:end], g.ts[:end], g.edge_feat[:end])
+        ctx = make_ctx(w, g, W, "fp32", max(count, 2000))
+        if behind:
+            ctx.step(1000, behind, torch.from_numpy(S.make_negatives(w, g, 1000, behind)).to("cuda:0"), ctx.alloc_outputs(behind))
+            torch.cuda.synchronize()
+        ctx.state_import(*S.make_warm_state(w, c1.g, first))
+        out = ctx.alloc_outputs(count)
+        ctx.step(first, count, neg, out, static=static)
+        torch.cuda.synchronize()
+        state = ctx.state_export()
+        ctx.close()
+        return out, state
+
+    ref, (ref_mem, ref_lu) = play()
+    for kind in (dict(), dict(behind=10), dict(behind=2000), dict(static=True), dict(last=True)):
+        out, (mem, lu) = play(**kind)
+        for name in ("emb", "score_pos", "score_neg"):
+            assert torch.equal(getattr(out, name), getattr(ref, name)), (kind, name)
+        assert np.array_equal(mem, ref_mem) and np.array_equal(lu, ref_lu), kind
+
+
 def test_launches_per_step(c1):
     """A step whose batch continues the previous one runs two kernels (its winners and queries
     were prepared inside the previous embedding launch, its GRU rows by the previous closing

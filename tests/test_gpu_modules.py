@@ -247,6 +247,25 @@ def test_a_new_context_takes_nothing_over_from_one_that_is_gone():
         assert getattr(behind_small, k).equal(getattr(behind_large, k)), k
 
 
+@pytest.mark.parametrize("count", [300, 900, 1300])
+def test_bits_of_two_layers_do_not_depend_on_the_step_before(count):
+    def play(behind):
+        c = Case(S.WORKLOADS["c1_tiny"], INSTANCES["headline"], False, max_batch=1300, layers=2)
+        for n in (behind, count):
+            c.ctx.state_import(*S.make_warm_state(c.w, c.g, 4000))
+            out = c.ctx.alloc_outputs(n)
+            c.ctx.step(4000, n, c.torch.from_numpy(S.make_negatives(c.w, c.g, 4000, n)).to("cuda:0"), out)
+            c.torch.cuda.synchronize()
+        c.close()
+        return out
+
+    ref = play(10)
+    for behind in (10, 1300):
+        out = play(behind)
+        for k in ("emb", "score_pos", "score_neg"):
+            assert getattr(out, k).equal(getattr(ref, k)), (behind, k)
+
+
 def test_c2_two_layers_wide_rows_emb_narrower_than_memory():
     """E = 100 != M = 172: the second layer's rows have a width of their own."""
     w = S.WORKLOADS["c2_bipartite_medium"]
