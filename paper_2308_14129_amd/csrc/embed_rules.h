@@ -70,4 +70,17 @@ constexpr int layer_workgroups(int most, int top, int units)
     return tiles < units ? tiles : units;
 }
 
+// Workgroups of `waves` wavefronts that the memory overwrite of `wins` winners has if it has its own.
+constexpr int overwrite_workgroups(int wins, int waves)
+{
+    const int n = ceil_div(wins, 4 * waves);
+    return n < 1 ? 1 : (n > 16 ? 16 : n);
+}
+
+// The workgroups that prepare the next batch's queries (n_prepare, 0: nothing to prepare) do the overwrite behind that: they
+// end long before the tiles do, and every workgroup of its own takes a compute unit from these.  But not if they are fewer
+// than it would have of its own, as before a short last batch: of 4000 events with eight left behind them the one workgroup
+// took until long after the tiles, 251 us a step of 200 000 nodes with few repeats and 69 with many, with sixteen of its own 60 and 39.
+constexpr bool overwrite_beside(int n_prepare, int wins, int waves) { return n_prepare >= overwrite_workgroups(wins, waves); }
+
 }  // namespace tig

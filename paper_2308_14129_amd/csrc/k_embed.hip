@@ -124,19 +124,12 @@ hipError_t launch_embed(const Dims &d, const LaunchPlan &plan, const PackedWeigh
     StepArgs aa = a;
     PackedWeights ww = pw;
     const int threads = embed_threads(d);
-    // memory overwrite: by the workgroups that prepare the next batch's queries, if there are any (they end long before the
-    // tiles do, and every workgroup of its own takes a compute unit from these), else about four winners per wavefront
-    // at the winner count recent steps had
-    int n_commit = 0;
+    // memory overwrite, at the winner count recent steps had
     const bool train = a.tr.S != nullptr;  // (a training step overwrites the memory at its end)
-    const bool commit = a.msg_count > 0 && !train, beside = commit && a.ded.count > 0;
-    if (commit && !beside) {
-        const int most = 2 * a.msg_count;
-        const int wins = a.wins_est > 0 && a.wins_est < most ? a.wins_est : most;
-        const int per_block = 4 * (threads / kWave);
-        n_commit = (wins + per_block - 1) / per_block;
-        n_commit = n_commit < 1 ? 1 : (n_commit > 16 ? 16 : n_commit);
-    }
+    const bool commit = a.msg_count > 0 && !train;
+    const int most_wins = 2 * a.msg_count, wins = a.wins_est > 0 && a.wins_est < most_wins ? a.wins_est : most_wins;
+    const bool beside = commit && overwrite_beside(a.ded.count > 0 ? a.ded.n_wgs : 0, wins, threads / kWave);
+    const int n_commit = commit && !beside ? overwrite_workgroups(wins, threads / kWave) : 0;
     const int extra = n_commit + (a.sel.count > 0 ? 1 : 0) + (a.ded.count > 0 ? a.ded.n_wgs : 0);
     const int cus = plan.num_cus > 0 ? plan.num_cus : 256;
     const int most = a.roles * a.count;
@@ -145,9 +138,8 @@ hipError_t launch_embed(const Dims &d, const LaunchPlan &plan, const PackedWeigh
     // events: a call that prepares nothing leaves those free that another needs for it.
     int side = extra;
     if (any) {
-        const int per_block = 4 * (threads / kWave), overwrite = (2 * a.count + per_block - 1) / per_block;
         const int spare = winners_in_one_launch(a.count) ? embed_spare_workgroups(d, plan, a.roles, a.count) : 0;
-        side = spare > 0 ? spare : (overwrite < 16 ? overwrite : 16);
+        side = spare > 0 ? spare : overwrite_workgroups(2 * a.count, threads / kWave);
     }
     const int units = cus - side > 16 ? cus - side : 16;
     // (any height is correct: the grid covers the most rows the batch can have, and tiles beyond the actual count return)

@@ -15,6 +15,8 @@ int height(int fp32, int neg, int most_mt, int rows, int units) { return tig::em
 int tiles(int n_rows, int height, int units, int loop) { return tig::tiles_in_use(n_rows, height, units, loop); }
 int step_wgs(int most, int height, int units) { return tig::step_workgroups(most, height, units); }
 int any_wgs(int most, int top, int units) { return tig::any_workgroups(most, top, units); }
+int overwrite_wgs(int wins, int waves) { return tig::overwrite_workgroups(wins, waves); }
+int beside(int n_prepare, int wins, int waves) { return tig::overwrite_beside(n_prepare, wins, waves); }
 int layer_wgs(int most, int top, int units) { return tig::layer_workgroups(most, top, units); }
 }
 """
@@ -89,3 +91,18 @@ def test_only_negatives_lie_in_the_last_eight_of_24_rows(rules):
                 if rules.height(1, 1, 3, n, units) == 24:
                     for loop in (0, 1, units // 2, units):
                         assert 16 * rules.tiles(n, 24, units, loop) >= n_u, (units, count, n_u)
+
+
+def test_the_overwrite_has_the_wavefronts_it_needs(rules):
+    # `left` events remain behind a batch of `count`: at most 31 workgroups prepare them, one for every sixteen entries
+    for waves in (8, 16):
+        for count in [1, 16, 200, 1000, 4000, 4096, 12000]:
+            for left in sorted({0, 1, 8, 200, count // 2, count}):
+                prepare = min(31, -(-2 * left // 16)) if left <= 4096 else 0
+                for wins in sorted({1, count // 3, count, 2 * count} - {0}):
+                    own = rules.overwrite_wgs(wins, waves)
+                    n = prepare if rules.beside(prepare, wins, waves) else own
+                    assert n >= own and 1 <= own <= 16
+                    assert wins / (n * waves) <= max(4.0, wins / (16 * waves))
+                    if left == count and count <= 4096:
+                        assert n == prepare  # (in the middle of a stream)
