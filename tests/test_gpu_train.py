@@ -247,6 +247,39 @@ def test_gradients_at_each_tile_height(count):
     run_training(b, [(4000, count), (4000 + count, count)], 0.0, "deferred", warm_at=4000)
 
 
+# more neighbours than a wavefront of k_tr_back keeps in registers at a time (ten, six at 444 columns), so that it gathers them
+# again for the second half: in tiles of four rows (two wavefronts share a row's slots), of eight and of sixteen
+@pytest.mark.parametrize("dims,count", [
+    (dict(mem_dim=172, time_dim=100, feat_dim=172, emb_dim=40, num_neighbors=20, num_heads=2), 80),
+    (dict(mem_dim=172, time_dim=100, feat_dim=172, emb_dim=40, num_neighbors=20, num_heads=2), 450),
+    (dict(mem_dim=172, time_dim=100, feat_dim=172, emb_dim=40, num_neighbors=16, num_heads=4), 80),
+    (dict(mem_dim=24, time_dim=20, feat_dim=6, emb_dim=35, num_neighbors=16, num_heads=4), 1000),
+    (dict(mem_dim=21, time_dim=13, feat_dim=6, emb_dim=35, num_neighbors=24, num_heads=1), 85),
+])
+def test_gradients_with_more_neighbours_than_registers(dims, count):
+    b = Bundle(S.WORKLOADS["c1_tiny"].scaled(**dims))
+    run_training(b, [(6000, count)], 0.0, "update_first", warm_at=6000, inspect=False)
+
+
+@pytest.mark.parametrize("heads", [1, 4])
+@pytest.mark.parametrize("count", [500, 1600])
+def test_gradients_of_one_and_four_heads_in_taller_tiles(heads, count):
+    b = Bundle(S.WORKLOADS["c1_tiny"].scaled(mem_dim=24, time_dim=12, feat_dim=6, emb_dim=35, num_neighbors=12, num_heads=heads))
+    run_training(b, [(6000, count)], 0.0, "update_first", warm_at=6000, inspect=False)
+
+
+def test_gradients_of_more_winners_than_the_launch_was_sized_for():
+    # the state update's backward pass is sized by the winners of the step before: a handful, then more than two tiles of
+    # four for every compute unit
+    w = S.WORKLOADS["c1_tiny"].scaled(mem_dim=21, time_dim=13, feat_dim=6, emb_dim=35, num_neighbors=6, num_heads=2, n_src=60000,
+                                      alpha_src=0.5)
+    b = Bundle(w)
+    batches = [(4000, 20), (4020, 1800), (5820, 30)]
+    ends = np.concatenate([b.g.src[4020:5820], b.g.dst[4020:5820]])
+    assert len(np.unique(ends)) > 2 * 256 * 4
+    run_training(b, batches, 0.0, "deferred", warm_at=4000, inspect=False)
+
+
 @pytest.mark.parametrize("dims,count", EDGE_SHAPES)
 def test_sgd_steps_at_the_edges_of_the_kernels(dims, count):
     # the weights that a step prepares for the next one, at widths that no tile or load divides: forward pass and
