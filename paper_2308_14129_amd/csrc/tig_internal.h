@@ -174,7 +174,7 @@ struct StepBase {
     int32_t *n_u_clear; // counter of a query set that no kernel reads any more (cleared by the closing launch), may be NULL
     int32_t *rows_seen; // host memory mapped into the device: the step leaves its numbers of distinct rows [0] and of winners [1] here, may be NULL
     int32_t rows_est;   // host side only: expected number of distinct rows (sizes the embedding tiles)
-    int32_t wins_est;   // host side only: expected number of winners (sizes the GRU column slices)
+    int32_t wins_est;   // host side only: expected number of winners (sizes the memory overwrite, foresees the GRU's column slices)
     // work done on compute units the embedding launch leaves idle: selection of a batch's winners
     // and preparation of a batch's queries
     SelectJob sel;

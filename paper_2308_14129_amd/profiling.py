@@ -37,7 +37,7 @@ XCDS = 8                # accelerator dies of one MI355X
 
 # the sources the step's kernels are compiled from (the partitioner, the epoch machinery, the training
 # step and the C API's host code can change without touching what the step's profiles measured)
-STEP_SOURCES = ("k_embed.hip", "embed_tile.h", "embed_rules.h", "embed_params.h", "k_gru.hip", "decode.h", "prepare.h", "lookup.h", "winners.h", "kernels_common.h",
+STEP_SOURCES = ("k_embed.hip", "embed_tile.h", "embed_rules.h", "embed_params.h", "k_gru.hip", "gru_rules.h", "decode.h", "prepare.h", "lookup.h", "winners.h", "kernels_common.h",
                 "step_small.hip", "step_launch.hip", "pack.hip")
 
 

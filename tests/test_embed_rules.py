@@ -1,4 +1,5 @@
-"""How an embedding launch divides its rows over workgroups (csrc/embed_rules.h), evaluated on the host."""
+"""How the embedding and the GRU launches divide their work over workgroups (csrc/embed_rules.h, csrc/gru_rules.h), evaluated on
+the host."""
 import ctypes
 import os
 import subprocess
@@ -10,7 +11,10 @@ CSRC = os.path.join(ROOT, "paper_2308_14129_amd", "csrc")
 
 WRAPPERS = """
 #include "embed_rules.h"
+#include "gru_rules.h"
 extern "C" {
+int gru_slices(int n_ct, int n_gru, int tiles) { return tig::column_slices(n_ct, n_gru, tiles).slices; }
+int gru_holds(int n_ct, int n_gru, int guessed, int tiles) { return tig::slices_hold(tig::column_slices(n_ct, n_gru, guessed), n_gru, tiles); }
 int height(int fp32, int neg, int most_mt, int rows, int units) { return tig::embed_height(fp32, neg, most_mt, rows, units); }
 int tiles(int n_rows, int height, int units, int loop) { return tig::tiles_in_use(n_rows, height, units, loop); }
 int step_wgs(int most, int height, int units) { return tig::step_workgroups(most, height, units); }
@@ -106,3 +110,16 @@ def test_the_overwrite_has_the_wavefronts_it_needs(rules):
                     assert wins / (n * waves) <= max(4.0, wins / (16 * waves))
                     if left == count and count <= 4096:
                         assert n == prepare  # (in the middle of a stream)
+
+
+def test_foreseen_column_slices_are_those_of_the_winners_found(rules):
+    # the kernel keeps the launch's slices exactly if it would have come to the same, whatever the winners they were for
+    for n_ct in [1, 2, 3, 7, 11, 16, 32]:
+        for most in [1, 2, 13, 100, 500, 1000]:  # tiles of winners that the batch could have
+            n_gru = min(256, most * n_ct)
+            for tiles in possible(most):
+                got = rules.gru_slices(n_ct, n_gru, tiles)
+                assert 1 <= got <= n_ct and (got == 1 or tiles * got <= n_gru)
+                for guessed in possible(most):
+                    same = rules.gru_slices(n_ct, n_gru, guessed) == got
+                    assert rules.gru_holds(n_ct, n_gru, guessed, tiles) == same, (n_ct, n_gru, tiles, guessed)

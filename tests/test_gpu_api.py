@@ -166,9 +166,10 @@ def test_reset_export_import_roundtrip_and_determinism(c1):
     ctx.close()
 
 
-# counts at which the number of compute units for the tiles, or the rows of an earlier step, used to decide the tiles' height
-@pytest.mark.parametrize("count", [300, 620, 900])
-def test_bits_of_a_step_do_not_depend_on_what_ran_before_or_the_kind_of_call(c1, count):
+# counts at which the number of compute units for the tiles, or the rows or winners of an earlier step, used to decide the
+# tiles' height or the GRU's column slices
+@pytest.mark.parametrize("precision,count", [("fp32", 300), ("fp32", 620), ("fp32", 900), ("fp32", 1260), ("bf16", 1260)])
+def test_bits_of_a_step_do_not_depend_on_what_ran_before_or_the_kind_of_call(c1, precision, count):
     import torch
     w, W, first = c1.w, c1.W, 4000
     neg = torch.from_numpy(S.make_negatives(w, c1.g, first, count)).to("cuda:0")
@@ -178,7 +179,7 @@ def test_bits_of_a_step_do_not_depend_on_what_ran_before_or_the_kind_of_call(c1,
         if last:
             end = first + count
             g = S.Graph(g.num_nodes, g.src[:end], g.dst[:end], g.ts[:end], g.edge_feat[:end])
-        ctx = make_ctx(w, g, W, "fp32", max(count, 2000))
+        ctx = make_ctx(w, g, W, precision, max(count, 2000))
         if behind:
             ctx.step(1000, behind, torch.from_numpy(S.make_negatives(w, g, 1000, behind)).to("cuda:0"), ctx.alloc_outputs(behind))
             torch.cuda.synchronize()
