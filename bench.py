@@ -164,29 +164,16 @@ def algorithmic_bytes(w, count, rows_u, slots_u, winners):
     }
 
 
-def mfma_flops(w, rows_u, winners, precision):
-    """Multiply-adds x 2 the matrix cores execute per launch with rows padded to sixteen in all (dealt over the
-    compute units every tile pads its own: the counters' summary has what ran), and the useful part
-    (unpadded, one product per multiply instead of three for split bf16 operands)."""
-    def up(x, m):
-        return (x + m - 1) // m * m
-    kb = 32 if precision == "bf16" else 16
-    split = 3 if precision == "bf16" else 1
+def mfma_flops(w, rows_u, winners):
+    """Multiply-adds x 2 of the contractions of each launch: unpadded, one product per multiply.  (What the matrix cores
+    execute follows the tiles in use and the height of each, three products per multiply of split bf16 operands: the
+    counters' summary has it.)"""
     M, T, F, E, H = w.mem_dim, w.time_dim, w.feat_dim, w.emb_dim, w.num_heads
     dkv = M + F + T
-    dkvp, Mq, Ep, Ek, Ng = up(dkv, kb), up(M, kb), up(E, 16), up(E, kb), up(M, 16)
-    Kg, Khn = up(2 * M + T + F, kb), up(M, kb)
-    rows16 = up(rows_u, 16)
-    win16 = up(winners, 16)
-    issued = {
-        "k_gru": 2 * win16 * (3 * Ng * Kg + Ng * Khn) * split,
-        "k_embed": 2 * rows16 * (H * dkvp * Mq + Ep * (H * dkvp + Mq) + 3 * Ep * Ek) * split,
-    }
-    useful = {
+    return {
         "k_gru": 2 * winners * (3 * M * (2 * M + T + F) + M * M),
         "k_embed": 2 * rows_u * (H * dkv * M + E * (H * dkv + M) + 3 * E * E),
     }
-    return issued, useful
 
 
 def train_flops(w, rows, winners):
@@ -643,14 +630,13 @@ def main():
         roofline["trace_frac"] = round(dom_bytes / (t_us * 1e-6) / 1e9 / HBM_PEAK_GBS, 5)
     if traffic:
         roofline["traffic_frac_of_peak"] = round(traffic / (float(avg_ms[dom]) * 1e-3) / 1e9 / HBM_PEAK_GBS, 5)
-    issued, useful = mfma_flops(w, rows_sum / n_prof, win_sum / n_prof, precision)
+    useful = mfma_flops(w, rows_sum / n_prof, win_sum / n_prof)
     peak_tf = BF16_PEAK_TFLOPS if precision == "bf16" else FP32_MFMA_PEAK_TFLOPS
     mfma = {}
     for n in ("k_gru", "k_embed"):
         # (in a chronological pass the GRU runs inside the closing launch of the step before)
         t_s = float(avg_ms[names.index("k_closing" if n == "k_gru" else n)]) * 1e-3
-        mfma[n] = {"issued_GFLOP": round(issued[n] / 1e9, 3), "useful_GFLOP": round(useful[n] / 1e9, 3),
-                   "issued_frac_of_peak": round(issued[n] / t_s / 1e12 / peak_tf, 5),
+        mfma[n] = {"useful_GFLOP": round(useful[n] / 1e9, 3),
                    "useful_frac_of_peak": round(useful[n] / t_s / 1e12 / peak_tf, 5)}
     mfma["peak_TFLOPs"] = peak_tf
     for k in ("k_embed_mfma_busy_frac", "k_gru_mfma_busy_frac", "k_embed_mfma_flop_per_launch",
