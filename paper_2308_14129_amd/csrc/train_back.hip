@@ -951,8 +951,9 @@ hipError_t launch_train_decode(const Dims &d, const StepArgs &a, const PackedWei
 hipError_t launch_train_back(const Dims &d, const LaunchPlan &plan, const StepArgs &a, const PackedWeights &pw,
                              const TrainArrays &t, hipStream_t s)
 {
-    // One round of workgroups: the rows recent steps had dealt evenly over the compute units, into the lowest tile that
-    // takes a unit's share (the products' time follows the tile's rows, see embed_height; the attention's the rows in use).
+    // One round of workgroups: a compute unit's share of the rows that recent steps had (the estimate is up to an eighth
+    // high, so that up to one unit in nine goes without: 221 of 256 at 5740 rows), in the lowest tile that takes it (the
+    // products' time follows the tile's rows, see kHeights; the attention's the rows in use).
     const int most = 3 * a.count, rows = a.rows_est > 0 && a.rows_est < most ? a.rows_est : most;
     const int cus = plan.num_cus > 0 ? plan.num_cus : 256;
     const int even = (rows + cus - 1) / cus, tallest = back_most_rows(d);
