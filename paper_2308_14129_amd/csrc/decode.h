@@ -39,39 +39,46 @@ __device__ inline void decode_event(const StepArgs &a, const PackedWeights &w, c
 {
     const int lane = lane_id();
     int row[3];
-    row[0] = row_of_entry(a.qs, 2 * b, 2 * a.count);
-    row[1] = row_of_entry(a.qs, 2 * b + 1, 2 * a.count);
+    row[0] = __builtin_amdgcn_readfirstlane(row_of_entry(a.qs, 2 * b, 2 * a.count));
+    row[1] = __builtin_amdgcn_readfirstlane(row_of_entry(a.qs, 2 * b + 1, 2 * a.count));
     row[2] = a.roles == 3 ? 2 * a.count + b : row[1];
     const float b2 = w.dec_b2[0];
-    // every load of a 128-dim chunk is requested before the first is used
+    // Arrays through buffer descriptors in scalar registers: a lane beyond the row (its offset lies outside every extent)
+    // reads 0 and writes nothing, so that no load or store is conditional and a lane's address is one addition.  Every
+    // load of a 128-column chunk is requested before the first is used.
+    auto rsrc = [](const float *q) { return __builtin_amdgcn_make_buffer_rsrc((void *)q, 0, kBufferAll, kBufferFlags); };
+    const __amdgpu_buffer_rsrc_t r_a = rsrc(a.dec_a), r_b = rsrc(a.dec_b), r_e = rsrc(a.emb_u), r_o = rsrc(a.emb);
+    const __amdgpu_buffer_rsrc_t r_b1 = rsrc(w.dec_b1f), r_w2 = rsrc(w.dec_w2);
+    const uint32_t dec_row = 4u * (uint32_t)p.Ep, emb_row = 4u * (uint32_t)p.E;
+    auto lane_at = [&](int j0, int u) -> uint32_t {
+        const int j = j0 + lane + kWave * u;
+        return j < p.E ? 4u * (uint32_t)j : kBufferNone;
+    };
     float part[2] = {0.0f, 0.0f};
     for (int j0 = 0; j0 < p.E; j0 += 2 * kWave) {
         float da[2], db[2][2], em[3][2], b1[2], w2[2];
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int j = j0 + lane + kWave * u;
-            const bool in = j < p.E;
-            da[u] = in ? a.dec_a[(size_t)row[0] * p.Ep + j] : 0.0f;
-            db[0][u] = in ? a.dec_b[(size_t)row[1] * p.Ep + j] : 0.0f;
-            db[1][u] = in ? a.dec_b[(size_t)row[2] * p.Ep + j] : 0.0f;
-            b1[u] = in ? w.dec_b1f[j] : 0.0f;
-            w2[u] = in ? w.dec_w2[j] : 0.0f;
+            const uint32_t at = lane_at(j0, u);
+            da[u] = buffer_load_f32(r_a, at + row[0] * dec_row);
+            db[0][u] = buffer_load_f32(r_b, at + row[1] * dec_row);
+            db[1][u] = buffer_load_f32(r_b, at + row[2] * dec_row);
+            b1[u] = buffer_load_f32(r_b1, at);
+            w2[u] = buffer_load_f32(r_w2, at);
 #pragma unroll
             for (int r = 0; r < 3; ++r)
-                em[r][u] = in ? a.emb_u[(size_t)row[r] * p.E + j] : 0.0f;
+                em[r][u] = buffer_load_f32(r_e, at + row[r] * emb_row);
         }
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            const int j = j0 + lane + kWave * u;
-            if (j < p.E) {
-                const float x = da[u] + b1[u];
-                part[0] += w2[u] * fmaxf(x + db[0][u], 0.0f);
-                part[1] += w2[u] * fmaxf(x + db[1][u], 0.0f);
+            const uint32_t at = lane_at(j0, u);
+            const float x = da[u] + b1[u];  // (0 beyond the row, where w2 is 0 too)
+            part[0] += w2[u] * fmaxf(x + db[0][u], 0.0f);
+            part[1] += w2[u] * fmaxf(x + db[1][u], 0.0f);
 #pragma unroll
-                for (int r = 0; r < 3; ++r)
-                    if (r < a.roles)
-                        a.emb[((size_t)r * a.count + b) * p.E + j] = em[r][u];
-            }
+            for (int r = 0; r < 3; ++r)
+                if (r < a.roles)  // (uniform)
+                    buffer_store_f32(em[r][u], r_o, at + (uint32_t)(r * a.count + b) * emb_row);
         }
     }
     const float s_pos = wave_sum_uniform(part[0]) + b2;
@@ -110,7 +117,7 @@ __device__ inline void closing_block(const StepArgs &a, const PackedWeights &w, 
                                      int waves)
 {
     if (blk < p.n_event_blocks) {
-        const int b = blk * waves + wave_id();
+        const int b = blk * waves + wave_id_uniform();
         if (b < a.count)
             decode_event(a, w, p, b);
         return;

@@ -46,6 +46,7 @@ constexpr int kGruThreads = 512;  // two workgroups per compute unit: the finish
 constexpr int kGruWaves = kGruThreads / kWave;
 constexpr int kPairs = kGruWaves / 2;  // wavefront pairs: (r, z) | n
 constexpr int EC = 16;                 // winners per tile
+constexpr int kPhi = 2;                // 64-column pieces of the time encoding whose parameters stay in registers
 
 struct GruParams {
     int M, T, F, Dmsg;
@@ -68,40 +69,67 @@ struct GruJob {
     const int32_t *n_win;
 };
 
-// acc1 += A x W1[nt]^T over W1's k-blocks [kb_lo, kb_hi) and acc2 += A x W2[nt]^T over W2's
-// k-blocks [kb_lo, min(kb_hi, w2_kblocks)): both weight streams are loaded DEPTH blocks ahead and
-// share the A operand.
-template <int PREC, int DEPTH>
-__device__ inline void tile_gemm2(floatx4 &acc1, floatx4 &acc2, const char *A, int lda, const void *W1,
-                                  const void *W2, int w1_kblocks, int w2_kblocks, int kb_lo, int kb_hi, int nt)
-{
+// Products of a tile of winners with two weight streams that share the reads of A: acc1 += A W1[nt]^T over W1's k-blocks
+// [kb_lo, kb_hi) and acc2 += A W2[nt]^T over W2's k-blocks [kb_lo, min(kb_hi, W2's number of blocks)).  A workgroup has
+// eight wavefronts, so few loads in flight would make every block a round trip to L2 (the compiler moves a load down to its use:
+// two in flight, 4.1 us for the 130 KB of an item of 172 columns that one compute unit can read in 0.9).  So kG blocks of both are
+// requested together, the next kG while these are multiplied, and the first two groups (start) before the rows are there;
+// the scheduler does not cross the barriers between.  A block beyond the last is the last again and is not used.
+template <int PREC, int kG>
+struct GateStream {
     using P = Prec<PREC>;
     using frag = typename P::frag;
-    const int lane = lane_id();
-    const size_t w1 = (size_t)nt * w1_kblocks * kWave + lane;
-    const size_t w2 = (size_t)nt * w2_kblocks * kWave + lane;
-    const char *ap = A + (size_t)(lane & 15) * lda;
-    const int g = lane >> 4;
-    const int kb_hi2 = kb_hi < w2_kblocks ? kb_hi : w2_kblocks;
-    for (int kb = kb_lo; kb < kb_hi; kb += DEPTH) {
-        frag b1[DEPTH], b2[DEPTH];
+    static constexpr int kBlock = kWave * P::kLaneBytes;
+    const char *w1, *w2;  // block 0 of the output tile
+    int kb_lo, kb_hi, kb_hi2, last2;
+    frag a1[kG], a2[kG], b1[kG], b2[kG];
+
+    __device__ inline void request(frag (&f1)[kG], frag (&f2)[kG], int kb) const
+    {
+        const unsigned lane_off = (unsigned)lane_id() * P::kLaneBytes;
 #pragma unroll
-        for (int u = 0; u < DEPTH; ++u) {
-            if (kb + u < kb_hi)
-                b1[u] = P::load_w(W1, w1 + (size_t)(kb + u) * kWave);
-            if (kb + u < kb_hi2)
-                b2[u] = P::load_w(W2, w2 + (size_t)(kb + u) * kWave);
+        for (int u = 0; u < kG; ++u) {
+            const int k1 = kb + u < kb_hi ? kb + u : kb_hi - 1, k2 = k1 < last2 ? k1 : last2;
+            f1[u] = P::load_w_at(w1 + (size_t)k1 * kBlock, lane_off);
+            f2[u] = P::load_w_at(w2 + (size_t)k2 * kBlock, lane_off);
         }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // (everything uniform; kb_lo < kb_hi)
+    __device__ inline void start(const void *W1, const void *W2, int w1_kblocks, int w2_kblocks, int lo, int hi, int nt)
+    {
+        w1 = (const char *)W1 + (size_t)(nt * w1_kblocks) * kBlock;
+        w2 = (const char *)W2 + (size_t)(nt * w2_kblocks) * kBlock;
+        kb_lo = lo, kb_hi = hi, last2 = w2_kblocks - 1;
+        kb_hi2 = hi < w2_kblocks ? hi : w2_kblocks;
+        request(a1, a2, lo);
+        request(b1, b2, lo + kG);
+    }
+    __device__ inline void multiply(const frag (&f1)[kG], const frag (&f2)[kG], int kb, const char *ap, floatx4 &acc1, floatx4 &acc2) const
+    {
 #pragma unroll
-        for (int u = 0; u < DEPTH; ++u)
+        for (int u = 0; u < kG; ++u)
             if (kb + u < kb_hi) {
-                const frag afrag = P::load_a(ap, kb + u, g);
-                P::mma(acc1, afrag, b1[u]);
+                const frag a = P::load_a(ap, kb + u, lane_id() >> 4);
+                P::mma(acc1, a, f1[u]);
                 if (kb + u < kb_hi2)
-                    P::mma(acc2, afrag, b2[u]);
+                    P::mma(acc2, a, f2[u]);
             }
     }
-}
+    __device__ inline void run(floatx4 &acc1, floatx4 &acc2, const char *A, int lda)
+    {
+        const char *ap = A + (size_t)(lane_id() & 15) * lda;
+        int kb = kb_lo;
+        for (; kb + 2 * kG < kb_hi; kb += 2 * kG) {
+            multiply(a1, a2, kb, ap, acc1, acc2);
+            request(a1, a2, kb + 2 * kG);
+            multiply(b1, b2, kb + kG, ap, acc1, acc2);
+            request(b1, b2, kb + 3 * kG);
+        }
+        multiply(a1, a2, kb, ap, acc1, acc2);
+        multiply(b1, b2, kb + kG, ap, acc1, acc2);
+    }
+};
 
 // KIND: an ordinary step; the state update of a module selection (mean messages, the plain recurrent cell, library
 // exp / tanh); a training step, which keeps what its backward pass reads.  Instances of their own, so that the
@@ -141,10 +169,9 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
     double *row_t = (double *)(row_e + EC);    // [EC] event time
     char *X = smem + EC * 24;                  // [EC rows x ldx bytes]
     float *part = (float *)(smem + g.off_part);  // [2 halves][kPairs][2 streams][16 x 16]
-    double *tw_tab = (double *)(part + 2 * kPairs * 2 * 256);  // [T][2] time-encoding (w_rev, b_rev)
 
     const int lane = lane_id();
-    const int wave = wave_id();
+    const int wave_u = wave_id_uniform();
 
     // the work: tiles x column slices.  The first item's descriptors are requested together with the winner
     // count, at the slice count that comes with the launch (slots beyond the count hold stale
@@ -170,10 +197,6 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
     const int items = tiles * cs;
     const int kblocks = g.Kg / P::KB;
     const int kblocks_hn = g.Khn / P::KB;
-    for (int j = threadIdx.x; j < g.T; j += kGruThreads) {  // (visible after the first barrier below)
-        tw_tab[2 * j] = w.time_w_rev[j];
-        tw_tab[2 * j + 1] = w.time_b_rev[j];
-    }
 
     for (int item = (int)blockIdx.x; item < items; item += g.n_gru) {
         // 1. this item's slice of the compacted winner list
@@ -199,75 +222,134 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
             row_e[r] = b;
             row_t[r] = t;
         }
-        __syncthreads();
+        lds_barrier();
         TIG_MARK(1);
 
-        // 2. message rows from batch-start memory; rows beyond n_rows are zero.  One wavefront per
-        //    row, lanes along the row (no index arithmetic per element); the loads of both rows of a
-        //    wavefront are requested before the first element is converted and stored.
+        // The gates' weights.  A round covers up to kPairs column tiles; with fewer, the pairs also split k.
+        GateStream<PREC, PREC == TIG_BF16_MFMA ? 1 : 2> gate;
+        const int half = wave_u / kPairs;  // 0: r and z gates, 1: n gate (input part over the whole message, hidden part over s_self)
+        const int pair = wave_u % kPairs;
+        auto begin_round = [&](int base) {
+            const int cts = ct_hi - base < kPairs ? ct_hi - base : kPairs;
+            const int ksplit = cts == 1 ? 4 : (cts == 2 ? 2 : 1), ctl = pair / ksplit;
+            const int per = (kblocks + ksplit - 1) / ksplit, kb_lo = pair % ksplit * per;
+            const int kb_hi = kblocks < kb_lo + per ? kblocks : kb_lo + per;
+            if (ctl >= cts || kb_lo >= kb_hi)
+                return;
+            if (half == 0)
+                gate.start(w.gru_Wr, w.gru_Wz, kblocks, kblocks, kb_lo, kb_hi, base + ctl);
+            else
+                gate.start(w.gru_Win, w.gru_Whn, kblocks, kblocks_hn, kb_lo, kb_hi, base + ctl);
+        };
+        // (the plain recurrent cell has one gate, whose products go another way)
+        const bool streams = !MOD || a.upd != kUpdModuleRnn;
+
+        // 2. message rows [s_self | s_other | Phi(dt) | e] from batch-start memory (mean messages: [s_self | mean]).  One
+        //    wavefront per row, segment by segment with the lanes from the segment's first column on, through buffer
+        //    descriptors in scalar registers: a lane beyond the segment reads 0, no load is conditional (such a load
+        //    is waited for at the condition's end) and no lane has an address to compute (with one per lane, chosen
+        //    among the segments, it was 900 vector instructions a wavefront, 4.7 us for rows of 616 columns).  The loads of both
+        //    of a wavefront's rows are requested before the first is stored, and behind them the first weights.
         {
-            constexpr int kRowsPerWave = EC / kGruWaves;
-            constexpr int kAhead = 6;  // 384 elements of a message row per pass
-            for (int base = 0; base < g.Kg; base += kWave * kAhead) {
-                float v[kRowsPerWave][kAhead];
-                double dt[kRowsPerWave];
+            constexpr int kRowsPerWave = EC / kGruWaves, kPieces = 3;  // 192 columns of a segment at a time
+            int lane = lane_id();
+            asm volatile("" : "+v"(lane));  // (addresses are not taken out of the loop over the items: there are no registers for them)
+            const bool means = MOD && a.mean_msg;  // (uniform)
+            const int second = means ? g.M + g.T + g.F : g.M, feats = means ? 0 : g.F;
+            const int widest = second > feats ? second : feats;
+            __amdgpu_buffer_rsrc_t rs[kRowsPerWave], ro[kRowsPerWave], rf[kRowsPerWave];
+            double since[kRowsPerWave];
 #pragma unroll
-                for (int i = 0; i < kRowsPerWave; ++i) {
-                    const int r = wave + i * kGruWaves;
-                    const bool live = r < n_rows;
-                    const int u = row_u[r], o = row_o[r];
-                    const float *self = a.mem + (size_t)u * g.M;
-                    const float *other = a.mem + (size_t)o * g.M;
-                    const float *feat = a.edge_feat + (size_t)(gj.first_eid + row_e[r]) * g.F;
-                    const float *mean = MOD && a.mean_msg ? a.mean_msg + (size_t)row_i[r] * (g.M + g.T + g.F) : nullptr;
-                    dt[i] = live ? row_t[r] - a.lu[u] : 0.0;  // since the node's last update
+            for (int i = 0; i < kRowsPerWave; ++i) {
+                const int r = wave_u + i * kGruWaves;
+                const bool live = r < n_rows;  // (a row beyond reads 0)
+                const int u = __builtin_amdgcn_readfirstlane(row_u[r]), o = __builtin_amdgcn_readfirstlane(row_o[r]);
+                const int e = __builtin_amdgcn_readfirstlane(row_e[r]), entry = __builtin_amdgcn_readfirstlane(row_i[r]);
+                const float *self = a.mem + (size_t)u * g.M;
+                const float *other = means ? a.mean_msg + (size_t)entry * second : a.mem + (size_t)o * g.M;
+                const float *feat = a.edge_feat + (size_t)(gj.first_eid + e) * g.F;
+                rs[i] = __builtin_amdgcn_make_buffer_rsrc((void *)self, 0, live ? 4 * g.M : 0, kBufferFlags);
+                ro[i] = __builtin_amdgcn_make_buffer_rsrc((void *)other, 0, live ? 4 * second : 0, kBufferFlags);
+                rf[i] = __builtin_amdgcn_make_buffer_rsrc((void *)feat, 0, live ? 4 * feats : 0, kBufferFlags);
+                since[i] = a.lu[u];
+            }
+            double tw_w[kPhi], tw_b[kPhi];  // time-encoding parameters of the lane's first columns
 #pragma unroll
-                    for (int k = 0; k < kAhead; ++k) {
-                        const int j = base + lane + kWave * k;
-                        v[i][k] = 0.0f;
-                        if (live && j < g.Dmsg) {
-                            if (j < g.M)
-                                v[i][k] = self[j];
-                            else if (MOD && mean)  // (uniform)
-                                v[i][k] = mean[j - g.M];
-                            else if (j < 2 * g.M)
-                                v[i][k] = other[j - g.M];
-                            else if (j >= 2 * g.M + g.T)
-                                v[i][k] = feat[j - 2 * g.M - g.T];
-                        }
+            for (int k = 0; k < kPhi; ++k) {
+                const int j = lane + kWave * k < g.T ? lane + kWave * k : 0;
+                tw_w[k] = w.time_w_rev[j];
+                tw_b[k] = w.time_b_rev[j];
+            }
+            for (int c0 = 0; c0 < widest; c0 += kWave * kPieces) {
+                float v[kRowsPerWave][3][kPieces];
+#pragma unroll
+                for (int i = 0; i < kRowsPerWave; ++i)
+#pragma unroll
+                    for (int k = 0; k < kPieces; ++k) {
+                        const uint32_t at = 4u * (uint32_t)(c0 + lane + kWave * k);
+                        v[i][0][k] = buffer_load_f32(rs[i], at);
+                        v[i][1][k] = buffer_load_f32(ro[i], at);
+                        v[i][2][k] = buffer_load_f32(rf[i], at);
                     }
-                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (c0 == 0 && streams)
+                    begin_round(ct_lo);
 #pragma unroll
                 for (int i = 0; i < kRowsPerWave; ++i) {
-                    const int r = wave + i * kGruWaves;
-                    const bool live = r < n_rows;
+                    const int r = wave_u + i * kGruWaves;
+                    char *const x = X + (size_t)r * g.ldx;
+                    float *const keep = TRAIN && ct_lo == 0 && r < n_rows ? a.gru_msg + (size_t)(r0 + r) * g.Dmsg : nullptr;
 #pragma unroll
-                    for (int k = 0; k < kAhead; ++k) {
-                        const int j = base + lane + kWave * k;
-                        if (j < g.Kg) {
-                            float x = v[i][k];
-                            if (live && !(MOD && a.mean_msg) && j >= 2 * g.M && j < 2 * g.M + g.T)
-                                x = time_enc(tw_tab[2 * (j - 2 * g.M)], tw_tab[2 * (j - 2 * g.M) + 1], dt[i]);
-                            P::store_a(X + (size_t)r * g.ldx, j, x);
-                            if (TRAIN && live && ct_lo == 0 && j < g.Dmsg)
-                                a.gru_msg[(size_t)(r0 + r) * g.Dmsg + j] = x;
+                    for (int seg = 0; seg < 3; ++seg) {
+                        const int width = seg == 0 ? g.M : (seg == 1 ? second : feats);
+                        const int at = seg == 0 ? 0 : (seg == 1 ? g.M : 2 * g.M + g.T);
+#pragma unroll
+                        for (int k = 0; k < kPieces; ++k) {
+                            const int j = c0 + lane + kWave * k;
+                            if (j < width) {
+                                P::store_a(x, at + j, v[i][seg][k]);
+                                if (TRAIN && keep)
+                                    keep[at + j] = v[i][seg][k];
+                            }
                         }
                     }
                 }
             }
+#pragma unroll
+            for (int i = 0; i < kRowsPerWave; ++i)
+                since[i] = row_t[wave_u + i * kGruWaves] - since[i];  // since the node's last update
+            auto phi = [&](int j, double w_rev, double b_rev) {
+#pragma unroll
+                for (int i = 0; i < kRowsPerWave; ++i) {
+                    const int r = wave_u + i * kGruWaves;
+                    const float x = time_enc(w_rev, b_rev, since[i]);
+                    P::store_a(X + (size_t)r * g.ldx, 2 * g.M + j, x);
+                    if (TRAIN && ct_lo == 0 && r < n_rows)
+                        a.gru_msg[(size_t)(r0 + r) * g.Dmsg + 2 * g.M + j] = x;
+                }
+            };
+            if (!means) {
+#pragma unroll
+                for (int k = 0; k < kPhi; ++k)
+                    if (lane + kWave * k < g.T)
+                        phi(lane + kWave * k, tw_w[k], tw_b[k]);
+                for (int j = lane + kWave * kPhi; j < g.T; j += kWave)
+                    phi(j, w.time_w_rev[j], w.time_b_rev[j]);
+            }
+#pragma unroll
+            for (int i = 0; i < kRowsPerWave; ++i)  // the k-depth's padding
+                if (lane < g.Kg - g.Dmsg)
+                    P::store_a(X + (size_t)(wave_u + i * kGruWaves) * g.ldx, g.Dmsg + lane, 0.0f);
         }
-        __syncthreads();
+        lds_barrier();
         TIG_MARK(2);
 
-        // 3. + 4. gates.  A round covers up to kPairs column tiles; with fewer, the pairs also split k.
+        // 3. + 4. gates
         for (int base = ct_lo; base < ct_hi; base += kPairs) {
             const int cts = ct_hi - base < kPairs ? ct_hi - base : kPairs;  // column tiles of this round
             const int ksplit = cts == 1 ? 4 : (cts == 2 ? 2 : 1);
-            const int pair = wave % kPairs;
-            const int half = wave / kPairs;  // 0: r and z gates, 1: n gate
             const int ctl = pair / ksplit;   // column tile of the round
             const int ks = pair % ksplit;    // k slice
-            const bool on = ctl < cts;
             // gate biases of the element this thread finishes below, requested with the weights
             float pb[4] = {0.0f, 0.0f, 0.0f, 0.0f};
             if ((int)threadIdx.x < cts * 256) {
@@ -278,21 +360,22 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                 pb[3] = w.gru_bhn[col];
             }
             floatx4 acc1 = floatx4{0, 0, 0, 0}, acc2 = floatx4{0, 0, 0, 0};
-            if (on) {
-                const int ct = base + ctl;
+            {
                 const int per = (kblocks + ksplit - 1) / ksplit;
                 const int kb_lo = ks * per;
                 const int kb_hi = kblocks < kb_lo + per ? kblocks : kb_lo + per;
-                if (MOD && a.upd == kUpdModuleRnn) {  // one gate: the halves of a pair split its k range once more
-                    floatx4 one[1] = {acc1};
-                    const int mid = kb_lo + (kb_hi - kb_lo + 1) / 2, lo = half ? mid : kb_lo, hi = half ? kb_hi : mid;
-                    tile_gemm<PREC, 1, 4>(one, X, g.ldx, lo, w.gru_Wr, kblocks, lo, hi - lo, ct);
-                    acc1 = one[0];
-                } else if (half == 0)
-                    tile_gemm2<PREC, 3>(acc1, acc2, X, g.ldx, w.gru_Wr, w.gru_Wz, kblocks, kblocks, kb_lo, kb_hi, ct);
-                else  // input part over the whole message, hidden part over s_self (the first Khn k's)
-                    tile_gemm2<PREC, 3>(acc1, acc2, X, g.ldx, w.gru_Win, w.gru_Whn, kblocks, kblocks_hn, kb_lo,
-                                        kb_hi, ct);
+                if (ctl < cts && kb_lo < kb_hi) {
+                    if (!streams) {  // one gate: the halves of a pair split its k range once more
+                        floatx4 one[1] = {acc1};
+                        const int mid = kb_lo + (kb_hi - kb_lo + 1) / 2, lo = half ? mid : kb_lo, hi = half ? kb_hi : mid;
+                        tile_gemm<PREC, 1, 4>(one, X, g.ldx, lo, w.gru_Wr, kblocks, lo, hi - lo, base + ctl);
+                        acc1 = one[0];
+                    } else {
+                        if (base != ct_lo)
+                            begin_round(base);
+                        gate.run(acc1, acc2, X, g.ldx);
+                    }
+                }
             }
             {
                 float *p1 = part + (size_t)((half * kPairs + pair) * 2) * 256;
@@ -303,7 +386,7 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                     p1[256 + e] = acc2[v];
                 }
             }
-            __syncthreads();
+            lds_barrier();
             TIG_MARK(3);
             for (int idx = threadIdx.x; idx < cts * 256; idx += kGruThreads) {
                 const int ctl2 = idx >> 8, e = idx & 255;
@@ -348,7 +431,7 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                     }
                 }
             }
-            __syncthreads();  // the partial sums (and, after the last round, the tile) are reused
+            lds_barrier();  // the partial sums (and, after the last round, the tile) are reused
         }
     }
     TIG_MARK(4);
@@ -411,7 +494,7 @@ DecodeParams no_closing(const Dims &d)
 
 int gru_lds_bytes(const Dims &d)
 {
-    return gru_params(d).off_part + 2 * kPairs * 2 * 256 * 4 + d.T * 16;
+    return gru_params(d).off_part + 2 * kPairs * 2 * 256 * 4;
 }
 
 hipError_t prepare_gru(const Dims &d, const LaunchPlan &plan)

@@ -51,6 +51,11 @@ struct Prec<TIG_FP32> {
         return frag{*(const floatx4 *)(row + (size_t)(kb * 16 + 4 * g) * 4)};
     }
     static __device__ inline frag load_w(const void *W, size_t idx) { return frag{((const floatx4 *)W)[idx]}; }
+    static constexpr int kLaneBytes = 16;  // of a weight operand
+    static __device__ inline frag load_w_at(const char *block, unsigned lane_off)
+    {
+        return frag{*(const floatx4 *)(block + lane_off)};
+    }
     static __device__ inline void mma(floatx4 &acc, const frag &a, const frag &b)
     {
         acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[0], b.v[0], acc, 0, 0, 0);
@@ -102,6 +107,11 @@ struct Prec<TIG_BF16_MFMA> {
     {
         const char *p = (const char *)W + idx * 32;
         return frag{*(const bf16x8 *)p, *(const bf16x8 *)(p + 16)};
+    }
+    static constexpr int kLaneBytes = 32;
+    static __device__ inline frag load_w_at(const char *block, unsigned lane_off)
+    {
+        return frag{*(const bf16x8 *)(block + lane_off), *(const bf16x8 *)(block + lane_off + 16)};
     }
     static __device__ inline void mma(floatx4 &acc, const frag &a, const frag &b)
     {
@@ -250,9 +260,20 @@ __device__ inline float wave_sum_four(float a, float b, float c, float d)
 // whose byte offset is not inside [0, extent - 4] reads 0.
 constexpr int kBufferFlags = 0x00020000;
 
+// An extent for arrays below 2 GiB whose offsets are valid by construction, and a lane's offset that lies outside of it, also
+// with the offset of a row added.
+constexpr int kBufferAll = 0x7ffffffc;
+constexpr uint32_t kBufferNone = 0x80000000u;
+
 __device__ inline float buffer_load_f32(__amdgpu_buffer_rsrc_t rsrc, uint32_t byte_offset)
 {
     return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)byte_offset, 0, 0));
+}
+
+// (a lane whose byte offset lies outside the extent writes nothing)
+__device__ inline void buffer_store_f32(float v, __amdgpu_buffer_rsrc_t rsrc, uint32_t byte_offset)
+{
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_int(v), rsrc, (int)byte_offset, 0, 0);
 }
 
 // value of lane `src` (wave-uniform) as a scalar
@@ -458,6 +479,15 @@ __device__ inline void tile_gemm_pair(floatx4 (&acc1)[MT + RG], floatx4 (&acc2)[
                 }
             }
     }
+}
+
+// A barrier for what the workgroup shares in LDS only: loads from memory that are on their way stay on their way
+// (__syncthreads waits for them).
+__device__ inline void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Row stride in bytes >= 4*width whose 16-byte chunk count is odd: the 16 rows read by one
