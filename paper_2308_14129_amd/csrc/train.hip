@@ -43,29 +43,54 @@ struct __attribute__((packed, aligned(4))) Floats {
     float v[N];
 };
 
+// A and B are read through buffer descriptors whose extent is the n rows: a k beyond the end reads zeros.  Two groups of
+// kU k-steps take turns, one on its way while the other is multiplied.
 template <int MI, int kU>  // kU: k-steps of 4 whose loads are issued together
 __device__ inline void multiply(const float *A, const float *B, int sa, int sb, int ao, int bo, int n, floatx4 (&acc)[MI][2],
                                 double (&sum)[MI])
 {
     constexpr int kPart = 4;  // k-steps whose products are summed on their own
-    const int g = lane_id() >> 4;
     using VA = Floats<MI>;
     using VB = Floats<2>;
-    auto products = [&](VA (&av)[kU], VB (&bv)[kU], int k) {
+    struct Group {
+        VA a[kU];
+        VB b[kU];
+    };
+    uint32_t at_a[kU], at_b[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+        at_a[u] = 4u * (uint32_t)(ao + 4 * u * sa);
+        at_b[u] = 4u * (uint32_t)(bo + 4 * u * sb);
+    }
+    auto request = [&](Group &q, int k) {
+        const int left = n - k < 4 * kU ? (n > k ? n - k : 0) : 4 * kU;
+        const auto ra = __builtin_amdgcn_make_buffer_rsrc((void *)(A + (size_t)k * sa), 0, left * sa * 4, kBufferFlags);
+        const auto rb = __builtin_amdgcn_make_buffer_rsrc((void *)(B + (size_t)k * sb), 0, left * sb * 4, kBufferFlags);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if constexpr (MI == 4)
+                q.a[u] = __builtin_bit_cast(VA, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)at_a[u], 0, 0));
+            else
+                q.a[u] = __builtin_bit_cast(VA, __builtin_amdgcn_raw_buffer_load_b64(ra, (int)at_a[u], 0, 0));
+            q.b[u] = __builtin_bit_cast(VB, __builtin_amdgcn_raw_buffer_load_b64(rb, (int)at_b[u], 0, 0));
+        }
+        __builtin_amdgcn_sched_barrier(0);  // (sunk to their use otherwise)
+    };
+    auto products = [&](const Group &q, int k) {
 #pragma unroll
         for (int u0 = 0; u0 < kU; u0 += kPart) {
+            if (k + 4 * u0 >= n)  // (uniform)
+                break;
             floatx4 part[MI][2] = {};
             float ps[MI] = {};
 #pragma unroll
             for (int u = u0; u < u0 + kPart; ++u)
-                if (k + 4 * u < n) {  // (uniform)
 #pragma unroll
-                    for (int i = 0; i < MI; ++i) {
-                        ps[i] += av[u].v[i];
+                for (int i = 0; i < MI; ++i) {
+                    ps[i] += q.a[u].v[i];
 #pragma unroll
-                        for (int j = 0; j < 2; ++j)
-                            part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u].v[i], bv[u].v[j], part[i][j], 0, 0, 0);
-                    }
+                    for (int j = 0; j < 2; ++j)
+                        part[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(q.a[u].v[i], q.b[u].v[j], part[i][j], 0, 0, 0);
                 }
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
@@ -76,35 +101,14 @@ __device__ inline void multiply(const float *A, const float *B, int sa, int sb, 
             }
         }
     };
-    int k = 0;
-    for (; k + 4 * kU <= n; k += 4 * kU) {
-        VA av[kU];
-        VB bv[kU];
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            const float *Ak = A + (size_t)(k + 4 * u) * sa, *Bk = B + (size_t)(k + 4 * u) * sb;
-            av[u] = *(const VA *)(Ak + (unsigned)ao);
-            bv[u] = *(const VB *)(Bk + (unsigned)bo);
-        }
-        products(av, bv, k);
-    }
-    if (k < n) {
-        VA av[kU];
-        VB bv[kU];
-        const float *Ak = A + (size_t)k * sa, *Bk = B + (size_t)k * sb;
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {  // (a k beyond the end reads the last one and counts as zero)
-            const int over = k + 4 * u + g - (n - 1), back = over > 0 ? over : 0;
-            av[u] = *(const VA *)(Ak + (ao + (4 * u - back) * sa));
-            bv[u] = *(const VB *)(Bk + (bo + (4 * u - back) * sb));
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-                av[u].v[i] = over <= 0 ? av[u].v[i] : 0.0f;
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-                bv[u].v[j] = over <= 0 ? bv[u].v[j] : 0.0f;
-        }
-        products(av, bv, k);
+    Group x, y;
+    request(x, 0);
+#pragma unroll 1
+    for (int k = 0; k < n; k += 8 * kU) {
+        request(y, k + 4 * kU);
+        products(x, k);
+        request(x, k + 8 * kU);
+        products(y, k + 4 * kU);
     }
 }
 
@@ -164,9 +168,9 @@ __device__ inline void store_block(const WgradJob &q, int m0, int n0, int e, flo
     }
 }
 
-// Registers: with parts, four wavefronts per SIMD spilled (12 registers with loads four deep, 106 with eight: 33 and 80 us at
-// 5700 rows of 100 columns).  SPLIT launches more workgroups than fit at once: three wavefronts, four deep (30 us, as
-// without parts); the others two, eight deep.
+// Registers: two groups of loads and 64 products' sums.  SPLIT launches more workgroups than fit at once: three wavefronts per
+// SIMD, groups of four (135 registers); the others two, groups of eight (186).  With one group, asked for when the one before was used
+// up, a training step took 212 us instead of 208.5 at 4000 events of 100 columns and 169 instead of 168 at 200 of 172.
 template <int MI, bool SPLIT>
 __global__ void __launch_bounds__(kWgWaves *kWave, SPLIT ? 3 : 2) k_tr_wgrad(StepArgs a, WgradJobs jobs)
 {
@@ -175,9 +179,7 @@ __global__ void __launch_bounds__(kWgWaves *kWave, SPLIT ? 3 : 2) k_tr_wgrad(Ste
     const int block = SPLIT ? (int)blockIdx.x / kXcds : (int)blockIdx.x;
     const int ji = job_of_block(jobs.first, block);
     const WgradJob q = jobs.j[ji];
-    // (SPLIT: as a scalar it leaves registers for a fourth workgroup on some compute units, 30.2 -> 31.4 us at 5700 rows of 100
-    // columns; the others 16.1 -> 15.6 us at 600 of 172)
-    const int w = SPLIT ? wave_id() : wave_id_uniform(), lane = lane_id();
+    const int w = wave_id_uniform(), lane = lane_id();
     const int tiles_n = (q.No + 31) / 32, tile = block - jobs.first[ji];
     const int m0 = (tile / tiles_n) * (16 * MI), n0 = (tile % tiles_n) * 32;
     int rows, gap_at = 0x7fffffff, gap = 0;  // row r lies at r, or behind a gap
