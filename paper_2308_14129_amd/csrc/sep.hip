@@ -258,31 +258,30 @@ namespace {
 //    is a count of trailing zeros;
 //  - where the balance term stays below a replica's worth (Eq. 5: at least 1), "both" beats "one" beats
 //    "none" without any arithmetic: nine edges in ten of a power-law stream end in "both", a chain of
-//    and / count zeros / shift / exclusive or, without a branch that depends on the sizes.
+//    and / count zeros / exclusive or over the two lowest levels, which stay in registers.  "Both" needs no look at the
+//    hub flags either: where a non-hub is an endpoint, its one partition is all that "both" can be.  The branches that are left
+//    are foreseen most of the time; without them (conditional moves, levels in memory) the chain is twice as long.
+//    Ids are checked and their sets requested a block of edges ahead.
 // Terms that are evaluated are the IEEE operations of Eq. 3-6 in their order, so the partitions are the
 // same bit for bit; an edge that the sets do not cover (sizes spread over kLevels values or more, terms
 // so close that rounding could make two sizes equal, centralities that are not finite and non-negative)
 // is decided by the plain evaluation (best_plain), and while the sizes are spread that far only their extremes are
-// kept.  Measured (EPYC host of the MI355X, 4 M events, 1 M nodes, 8 partitions): 36 -> 5.3 ns per edge; 5 partitions
-// and mostly non-hubs 20 -> 6.5; 16 partitions 49 -> 6.6.  Without hubs the sizes are spread from the start: 9 ns at 8
-// partitions as before (2 M events, another host), 91 with the sets rebuilt for every edge.
+// kept.  Measured per edge, 8 partitions of 4 M events and 1 M nodes, 1% hubs, before the levels were in registers and after (Xeon
+// at 2.7 GHz): 11.8 -> 5.2 ns; 16 partitions, 5% hubs 11.4 -> 5.2; 5 partitions and mostly non-hubs 12.0 -> 10.6; no hubs, where the
+// sizes are too far apart for the sets from the start, 17.6 -> 16.1.  The whole call of the first (EPYC host of the MI355X): 25.1 -> 13.8 ms.
 class EdgeLoop {
 public:
     EdgeLoop(const tig_sep_config &cfg, int64_t num_nodes, const double *cent, const uint8_t *is_hub, uint64_t *A)
-        : P_(cfg.num_parts), lam_(cfg.lambda), eps_(cfg.epsilon), N_(num_nodes), cent_(cent), A_(A)
+        : P_(cfg.num_parts), lam_(cfg.lambda), eps_(cfg.epsilon), N_(num_nodes), cent_(cent), A_(A), is_hub_(is_hub)
     {
         int odd = 0;
-        for (int64_t i = 0; i < N_; ++i) {
-            A_[i] = 0;
+        for (int64_t i = 0; i < N_; ++i)
             odd |= !(cent_[i] >= 0.0 && cent_[i] <= 1e300);
-        }
+        memset(A_, 0, sizeof(uint64_t) * (size_t)N_);
         plain_ = odd || !(lam_ <= 1e100);
         // mx < 2^31: eps moves the denominator of Eq. 6 by at least 7e-7, so the balance term of a gap below
         // kLevels is below 1 - 1e-9 * 40, and neighbouring sizes' terms are at least 9e-7 apart
         easy_ = !plain_ && lam_ >= 1e-3 && lam_ <= 1.0 && eps_ >= 1e-6 && eps_ <= 1e3;
-        hub_.assign((size_t)(N_ + 63) / 64, 0);
-        for (int64_t i = 0; i < N_; ++i)
-            hub_[(size_t)i >> 6] |= (uint64_t)(is_hub[i] != 0) << (i & 63);
         all_ = P_ == 64 ? ~0ull : (1ull << P_) - 1ull;
         for (int p = 0; p < P_; ++p)
             size_[p] = 0;
@@ -298,66 +297,125 @@ public:
     // decides `n` further edges; false: an endpoint is outside 0..N-1 (the edges before it are decided)
     bool run(const int32_t *src, const int32_t *dst, int64_t n, int32_t *part_out)
     {
-        constexpr int64_t kAhead = 24;  // edges whose endpoints' sets are requested early
-        const uint64_t *const hub = hub_.data();
+        // the ids are looked at, and their sets requested, a block ahead of the decisions
+        int64_t ok = valid(src, dst, n < kBlock ? n : kBlock);
+        for (int64_t e0 = 0; e0 < n; e0 += kBlock) {
+            const int64_t m = n - e0 < kBlock ? n - e0 : kBlock, next = e0 + m, left = n - next < kBlock ? n - next : kBlock;
+            const int64_t ahead = ok == m ? valid(src + next, dst + next, left) : 0;
+            decide_block(src + e0, dst + e0, ok, part_out + e0);
+            if (ok < m)
+                return false;
+            ok = ahead;
+        }
+        return true;
+    }
+
+    void sizes(int64_t *out) const
+    {
+        for (int p = 0; p < P_; ++p)
+            out[p] = size_[p];
+    }
+
+private:
+    static constexpr int64_t kBlock = 64;
+    static constexpr int kLevels = 16;
+    static constexpr int kRing = 1024;  // the sets move up one place whenever mn grows; moved back after so many
+    struct Terms {          // balance terms (Eq. 6) of sizes mn .. mx, mx - mn = g
+        double den;         // their denominator, -1: not computed yet
+        double of[kLevels];
+        bool distinct;      // terms of different sizes stay apart when a replica term is added
+    };
+
+    // edges before the first with an endpoint outside 0..N-1
+    int64_t valid(const int32_t *src, const int32_t *dst, int64_t n) const
+    {
+        const uint64_t N = (uint64_t)N_;
+        for (int64_t e = 0; e < n; ++e) {
+            const uint32_t i = (uint32_t)src[e], j = (uint32_t)dst[e];
+            if ((i >= N) | (j >= N))
+                return e;
+            __builtin_prefetch(A_ + i);
+            __builtin_prefetch(A_ + j);
+        }
+        return n;
+    }
+
+    void decide_block(const int32_t *src, const int32_t *dst, int64_t n, int32_t *part_out)
+    {
         uint64_t *const A = A_;
-        const uint64_t N = (uint64_t)N_, all = all_;
+        const uint64_t all = all_;
         const bool easy = easy_ && mx_ + n < ((int64_t)1 << 31);
         int64_t e = 0;
         while (e < n) {
             // as long as the sizes fit the sets: the candidates of the edge as one set, and the lowest index of
-            // its lowest level
+            // its lowest level.  The two lowest levels are kept in registers: the chain from one edge to the next is
+            // these few operations.
             uint64_t *lev = level_ + base_;
             int64_t mx = mx_, mn = mn_;
+            uint64_t l0 = lev[0], l1 = lev[1];
             const int64_t stop = !easy || mx - mn >= kLevels ? e : n;
             for (; e < stop; ++e) {
-                if (e + kAhead < n) {
-                    const uint32_t pi = (uint32_t)src[e + kAhead], pj = (uint32_t)dst[e + kAhead];
-                    __builtin_prefetch(A + (pi < N ? pi : 0));
-                    __builtin_prefetch(A + (pj < N ? pj : 0));
-                }
                 const uint32_t i = (uint32_t)src[e], j = (uint32_t)dst[e];
-                if (i >= N || j >= N)
-                    break;
-                const uint64_t ai = A[i], aj = A[j], both = ai & aj, any = ai | aj;
-                const uint64_t hi = (hub[i >> 6] >> (i & 63)) & 1u, hj = (hub[j >> 6] >> (j & 63)) & 1u;
-                // the partition of a resident non-hub is the only candidate; two of them: Case 3
-                const uint64_t x = ai & (hi - 1u), y = aj & (hj - 1u), xy = x | y;
-                const bool two = x != 0 && y != 0, apart = ai != 0 && aj != 0 && both == 0;
-                // (hubs on partitions of their own: the replicas' worths have to be compared)
-                if ((two & (x != y)) | (apart & (xy == 0)))
-                    break;
-                uint64_t set = any ? any : all;
-                set = both ? both : set;
-                set = xy ? xy : set;
-                uint64_t m = set & lev[0];
-                const uint64_t m1 = set & lev[1];
-                int64_t k = m ? 0 : 1;
-                m = m ? m : m1;
-                if (__builtin_expect(!m, 0)) {
-                    do
-                        m = set & lev[++k];
-                    while (!m);
+                const uint64_t ai = A[i], aj = A[j], both = ai & aj;
+                uint64_t set = both;
+                // (a resident non-hub has one partition: where it is an endpoint, `both` is that partition or empty)
+                if (__builtin_expect(!both, 0)) {
+                    const uint64_t any = ai | aj;
+                    // the partition of a resident non-hub is the only candidate; two of them: Case 3
+                    const uint64_t x = is_hub_[i] ? 0 : ai, y = is_hub_[j] ? 0 : aj, xy = x | y;
+                    // (two non-hubs apart; hubs on partitions of their own: the replicas' worths have to be compared)
+                    if ((x != 0 && y != 0) || (ai != 0 && aj != 0 && xy == 0))
+                        break;
+                    set = xy ? xy : (any ? any : all);
                 }
-                const uint64_t bit = m & (0ull - m);
-                const int p = __builtin_ctzll(m);
+                const uint64_t m0 = set & l0;
+                uint64_t bit;
+                int64_t k = 0;
+                if (__builtin_expect(m0 != 0, 1)) {
+                    bit = m0 & (0ull - m0);
+                    l0 ^= bit;
+                    l1 |= bit;
+                } else {
+                    uint64_t m = set & l1;
+                    if (m) {
+                        k = 1;
+                        bit = m & (0ull - m);
+                        l1 ^= bit;
+                        lev[2] |= bit;
+                    } else {
+                        k = 2;
+                        while (!(m = set & lev[k]))
+                            ++k;
+                        bit = m & (0ull - m);
+                        lev[k] ^= bit;
+                        lev[k + 1] |= bit;
+                    }
+                }
+                const int p = __builtin_ctzll(bit);
                 part_out[e] = p;
-                if (!(both & bit)) {
-                    A[i] |= bit;
-                    A[j] |= bit;
+                if (!both) {
+                    A[i] = ai | 1ull << p;
+                    A[j] |= 1ull << p;
                 }
                 ++size_[p];
-                lev[k] ^= bit;
-                lev[k + 1] |= bit;
                 mx += mn + k == mx;
-                const int64_t up = lev[0] == 0;  // (the smallest size had one partition left)
-                mn += up;
-                lev += up;
-                if (__builtin_expect(lev >= level_ + kRing || mx - mn >= kLevels, 0)) {
+                if (l0 == 0) {  // (the smallest size had one partition left)
+                    ++mn;
+                    *lev++ = 0;
+                    l0 = l1;
+                    l1 = lev[1];
+                    if (__builtin_expect(lev >= level_ + kRing, 0)) {
+                        ++e;
+                        break;
+                    }
+                }
+                if (__builtin_expect(mx - mn >= kLevels, 0)) {
                     ++e;
                     break;
                 }
             }
+            lev[0] = l0;
+            lev[1] = l1;
             mx_ = mx;
             mn_ = mn;
             base_ = (int)(lev - level_);
@@ -365,14 +423,7 @@ public:
                 levels_from_sizes();
             // one edge of any kind, or all of them while the sizes are too far apart for the sets
             while (e < n) {
-                if (e + kAhead < n) {
-                    const uint32_t pi = (uint32_t)src[e + kAhead], pj = (uint32_t)dst[e + kAhead];
-                    __builtin_prefetch(A + (pi < N ? pi : 0));
-                    __builtin_prefetch(A + (pj < N ? pj : 0));
-                }
                 const int64_t i = src[e], j = dst[e];
-                if (i < 0 || i >= N_ || j < 0 || j >= N_)
-                    return false;
                 const int p = decide(i, j);
                 part_out[e] = p;
                 if (p >= 0) {
@@ -385,27 +436,11 @@ public:
                     break;
             }
         }
-        return true;
     }
-
-    void sizes(int64_t *out) const
-    {
-        for (int p = 0; p < P_; ++p)
-            out[p] = size_[p];
-    }
-
-private:
-    static constexpr int kLevels = 16;
-    static constexpr int kRing = 1024;  // the sets move up one place whenever mn grows; moved back after so many
-    struct Terms {          // balance terms (Eq. 6) of sizes mn .. mx, mx - mn = g
-        double den;         // their denominator, -1: not computed yet
-        double of[kLevels];
-        bool distinct;      // terms of different sizes stay apart when a replica term is added
-    };
 
     int decide(int64_t i, int64_t j)
     {
-        const bool hi = (hub_[(size_t)i >> 6] >> (i & 63)) & 1u, hj = (hub_[(size_t)j >> 6] >> (j & 63)) & 1u;
+        const bool hi = is_hub_[i] != 0, hj = is_hub_[j] != 0;
         const uint64_t ai = A_[i], aj = A_[j];
         if (ai && aj) {
             if (hi != hj)                                     // Case 1: where the non-hub resides
@@ -542,7 +577,7 @@ private:
     const int64_t N_;
     const double *const cent_;
     uint64_t *const A_;
-    std::vector<uint64_t> hub_;  // one bit per node
+    const uint8_t *const is_hub_;
     bool plain_, easy_;
     uint64_t all_, level_[kRing + kLevels + 1];  // level k: level_[base_ + k], 0 <= k <= kLevels; all zero above
     int base_;
