@@ -81,9 +81,9 @@ __global__ void k_fill_csr(const EventRecord *__restrict__ rec, int64_t num_entr
 // per entry beyond the few heaviest nodes, and writes another for its `pos`.)  An entry's place is followed
 // instead of scattered: a pass leaves every entry's destination at its source position, where two
 // passes are composed by a read whose neighbours go to neighbouring places (k_sort_pos).
-// Per pass: digit counts per workgroup (k_sort_count), their prefix sums (k_sort_scan), and the move (k_sort_move), no workgroup
-// waiting for another.  25 M entries of 0.5 M nodes (Zipf 1.5), with the times' and ids' check: 1.62 -> 1.11 ms (moves 486 and 282 us, counts
-// 44 and 116, positions 125, bounds 40); a sub-graph's whole rebuilding 3.19 -> 2.65 ms.  More nodes than 2^22 would need a third pass and a second copy of the entries; they take the sort above.
+// Per pass: digit counts per workgroup (k_sort_count), their prefix sums (k_sort_scan), and the move (k_sort_events, k_sort_entries), no workgroup
+// waiting for another.  25 M entries of 0.5 M nodes (Zipf 1.5), with the times' and ids' check: 1.62 -> 0.86 ms (moves 309 and 293 us, counts
+// 41 and 45, positions 127, bounds 36); a sub-graph's whole rebuilding 3.19 -> 2.41 ms.  More nodes than 2^22 would need a third pass and a second copy of the entries; they take the sort above.
 constexpr int kSortThreads = 512, kSortWaves = kSortThreads / 64;
 constexpr int kSortRounds = 16;                       // entries per lane and tile
 constexpr int kSortTile = kSortThreads * kSortRounds;
@@ -101,6 +101,7 @@ struct SortPass {
     int32_t *place;       // destination of the entry at source position q (LAST after another pass: over node_in)
     uint32_t *counts;     // [workgroups][bins], then their prefix sums within a bin
     uint32_t *totals;     // [bins]
+    uint32_t *bounds;     // [bins + 2] last pass: first entry of every digit, NULL otherwise
     int32_t *flags;
     int64_t n, num_nodes;
     int64_t chunk;        // entries per workgroup, whole tiles
@@ -129,8 +130,16 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_count(SortPass p)
         }
 #pragma unroll
         for (int u = 0; u < kTurn; ++u)
-            if (q0 + u * kSortThreads < hi)
-                atomicAdd(&count[(node[u] >> p.shift) & (kBins - 1)], 1u);
+            if (q0 + u * kSortThreads < hi) {
+                // the first lane's digit is counted at once: most lanes share it where a few nodes have most of the entries, and
+                // additions to one address take turns (25 M entries of which 97% have one digit: 116 us a lane at a time)
+                const uint32_t d = (node[u] >> p.shift) & (kBins - 1), lead = __builtin_amdgcn_readfirstlane(d);
+                const unsigned long long same = __ballot(d == lead);
+                if (d != lead)
+                    atomicAdd(&count[d], 1u);
+                else if (__builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u)) == 0)
+                    atomicAdd(&count[d], (uint32_t)__popcll(same));
+            }
     }
     __syncthreads();
     for (int d = threadIdx.x; d < kBins; d += kSortThreads)
@@ -162,81 +171,237 @@ __global__ void __launch_bounds__(1024) k_sort_scan(uint32_t *counts, uint32_t *
     }
 }
 
-// The move of a workgroup's entries, a tile at a time, in order.  Every wavefront takes a run of the tile, 64 entries a
-// round: lanes with the same digit find each other by a ballot per bit, the wavefront counts its digits in LDS, and
-// the counts of the wavefronts before it complete an entry's rank.  FIRST also checks the graph: flags[0] an id out of
-// range, [1] times that decrease, [2] a self-loop (whatever the ids, a digit is one of the bins).
-template <int BITS, bool FIRST, bool LAST>
-__global__ void __launch_bounds__(kSortThreads, 4) k_sort_move(SortPass p)
+// Lanes with the same digit: entries of it in the lanes before, and in all of them (`on`: the lanes that count).
+template <int BITS>
+__device__ inline void match_digit(uint32_t d, bool on, uint32_t &before, uint32_t &all)
 {
-    constexpr int kBins = 1 << BITS;
-    constexpr int kPer = (kBins + kSortThreads - 1) / kSortThreads;  // bins of a thread
+    unsigned long long same = __ballot(on);
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        const bool bit = (d >> b) & 1u;
+        const unsigned long long set = __ballot(bit);
+        same &= bit ? set : ~set;
+    }
+    before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
+    all = (uint32_t)__popcll(same);
+}
+
+// Sum over the threads before this one; `sums`: [wavefronts] of LDS that nobody else uses, whose readers may still be
+// reading on return.
+__device__ inline uint32_t sum_before(uint32_t x, uint32_t *sums, int wave, int lane)
+{
+    uint32_t incl = x;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t up = __shfl_up(incl, off, 64);
+        incl += lane >= off ? up : 0u;
+    }
+    if (lane == 63)
+        sums[wave] = incl;
+    __syncthreads();
+    uint32_t run = incl - x;
+    for (int w = 0; w < wave; ++w)
+        run += sums[w];
+    return run;
+}
+
+template <int BITS>
+struct SortBins {
+    static constexpr int kBins = 1 << BITS;
+    static constexpr int kPer = (kBins + kSortThreads - 1) / kSortThreads;  // bins of a thread
     static_assert(kBins % kSortThreads == 0 || kBins < kSortThreads, "");
-    __shared__ __attribute__((aligned(16))) uint16_t mine[kSortWaves][kBins];  // digits of a wavefront's run, then those of the wavefronts before it
-    __shared__ uint32_t base[kBins];              // where the next entry of a digit goes
-    __shared__ uint32_t wave_sum[kSortWaves];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int d0 = (int)threadIdx.x * kPer;
-    {   // first place of every digit: the totals of the digits before it, and of this digit in the workgroups before
+    // where the workgroup's first entry of each of the thread's digits goes: behind all entries of smaller digits, and those of
+    // the digit in the workgroups before
+    static __device__ inline void first_places(const SortPass &p, uint32_t *sums, int wave, int lane, uint32_t (&place)[kPer])
+    {
+        const int d0 = (int)threadIdx.x * kPer;
         uint32_t tot[kPer], sum = 0;
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
             tot[i] = d0 + i < kBins ? p.totals[d0 + i] : 0u;
             sum += tot[i];
         }
-        uint32_t incl = sum;
+        uint32_t run = sum_before(sum, sums, wave, lane);
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t up = __shfl_up(incl, off, 64);
-            incl += lane >= off ? up : 0u;
-        }
-        if (lane == 63)
-            wave_sum[wave] = incl;
-        __syncthreads();
-        uint32_t run = incl - sum;
-        for (int w = 0; w < wave; ++w)
-            run += wave_sum[w];
-#pragma unroll
-        for (int i = 0; i < kPer; ++i)
+        for (int i = 0; i < kPer; ++i) {
+            place[i] = 0;
             if (d0 + i < kBins) {
-                base[d0 + i] = run + p.counts[(size_t)blockIdx.x * kBins + d0 + i];
+                place[i] = run + p.counts[(size_t)blockIdx.x * kBins + d0 + i];
+                if (p.bounds && blockIdx.x == 0)
+                    p.bounds[d0 + i] = run;
                 run += tot[i];
             }
+        }
+        if (p.bounds && blockIdx.x == 0 && threadIdx.x < 2)
+            p.bounds[kBins + threadIdx.x] = (uint32_t)p.n;
     }
+};
+
+// The move of a workgroup's entries, a tile at a time, in order.  Every wavefront takes a run of the tile, 64 entries a
+// round: lanes with the same digit find each other by a ballot per bit, the wavefront counts its digits in LDS, and
+// the counts of the wavefronts before it complete an entry's rank.
+//
+// The first pass, from the event stream: a tile's events stay in LDS, and its entries leave in the order of their
+// digits, so that neighbouring lanes write neighbouring places (written from where they were read, 16 and 4 bytes a lane to as many
+// places, 25 M entries of 0.5 M nodes took 486 us instead of 309).  Also checks the graph: flags[0] an id out of
+// range, [1] times that decrease, [2] a self-loop (whatever the ids, a digit is one of the bins).
+template <int BITS, bool LAST>
+__global__ void __launch_bounds__(kSortThreads, 4) k_sort_events(SortPass p)
+{
+    using Bins = SortBins<BITS>;
+    constexpr int kBins = Bins::kBins, kPer = Bins::kPer, kRounds = 8, kTile = kSortThreads * kRounds;
+    static_assert(kSortTile % kTile == 0, "");
+    __shared__ EntryWords event[kTile / 2];                              // src, dst, time
+    __shared__ __attribute__((aligned(16))) uint16_t mine[kSortWaves][kBins];  // digits of a wavefront's run, then first ranks
+    __shared__ uint16_t at_rank[kTile];
+    __shared__ uint32_t shift_of[kBins];  // destination less rank, per digit  (two workgroups of 11 bits fill the unit's LDS)
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int d0 = (int)threadIdx.x * kPer;
+    uint32_t place[kPer];
+    Bins::first_places(p, shift_of, wave, lane, place);
     const int64_t lo = (int64_t)blockIdx.x * p.chunk, hi = lo + p.chunk < p.n ? lo + p.chunk : p.n;
     int bad = 0;  // bit f: flags[f]
-    for (int64_t t0 = lo; t0 < hi; t0 += kSortTile) {  // (t0 is even)
+    for (int64_t t0 = lo; t0 < hi; t0 += kTile) {  // (t0 and hi are even)
+        const int left = hi - t0 < kTile ? (int)(hi - t0) : kTile;
+        const int64_t e0 = t0 >> 1;
+        constexpr int kEvents = kTile / 2 / kSortThreads;
+        __syncthreads();  // (the tile before is done with)
+        for (int i = threadIdx.x; i < kSortWaves * kBins / 2; i += kSortThreads)
+            ((uint32_t *)mine)[i] = 0;
+        int32_t s[kEvents], d[kEvents];
+        double t[kEvents], earlier[kEvents];
+#pragma unroll
+        for (int u = 0; u < kEvents; ++u) {
+            const int x = (int)threadIdx.x + u * kSortThreads, ev = 2 * x < left ? x : left / 2 - 1;
+            s[u] = (p.src + e0)[(unsigned)ev];
+            d[u] = (p.dst + e0)[(unsigned)ev];
+            t[u] = (p.ts + e0)[(unsigned)ev];
+            earlier[u] = p.ts[e0 + ev > 0 ? e0 + ev - 1 : 0];
+        }
+#pragma unroll
+        for (int u = 0; u < kEvents; ++u) {
+            const int x = (int)threadIdx.x + u * kSortThreads;
+            bad |= (s[u] < 0 || s[u] >= p.num_nodes || d[u] < 0 || d[u] >= p.num_nodes ? 1 : 0) | (s[u] == d[u] ? 4 : 0);
+            bad |= e0 + x > 0 && 2 * x < left && !(earlier[u] <= t[u]) ? 2 : 0;
+            event[x] = EntryWords{s[u], d[u], __double2loint(t[u]), __double2hiint(t[u])};
+        }
+        __syncthreads();
+        uint32_t node[kRounds], rank[kRounds];
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int at = wave * (64 * kRounds) + 64 * u + lane;
+            node[u] = ((const uint32_t *)event)[4 * (at >> 1) + (at & 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const bool on = wave * (64 * kRounds) + 64 * u + lane < left;
+            const uint32_t dig = (node[u] >> p.shift) & (kBins - 1);
+            uint32_t before, all;
+            match_digit<BITS>(dig, on, before, all);
+            const uint32_t had = mine[wave][dig];
+            rank[u] = had + before;
+            if (on && before + 1 == all)
+                mine[wave][dig] = (uint16_t)(had + all);
+        }
+        __syncthreads();
+        {   // ranks of the tile: digit by digit, within a digit wavefront by wavefront
+            uint32_t tot[kPer], sum = 0;
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                tot[i] = 0;
+                if (d0 + i < kBins)
+#pragma unroll
+                    for (int w = 0; w < kSortWaves; ++w)
+                        tot[i] += mine[w][d0 + i];
+                sum += tot[i];
+            }
+            uint32_t run = sum_before(sum, shift_of, wave, lane);
+            __syncthreads();  // (the sums have been read)
+#pragma unroll
+            for (int i = 0; i < kPer; ++i)
+                if (d0 + i < kBins) {
+                    shift_of[d0 + i] = place[i] - run;
+                    place[i] += tot[i];
+#pragma unroll
+                    for (int w = 0; w < kSortWaves; ++w) {
+                        const uint32_t x = mine[w][d0 + i];
+                        mine[w][d0 + i] = (uint16_t)run;
+                        run += x;
+                    }
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int at = wave * (64 * kRounds) + 64 * u + lane;
+            const uint32_t dig = (node[u] >> p.shift) & (kBins - 1), r = mine[wave][dig] + rank[u];
+            if (at < left) {
+                at_rank[r] = (uint16_t)at;
+                (p.place + t0)[(unsigned)at] = (int32_t)(shift_of[dig] + r);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kRounds; ++u) {
+            const int r = (int)threadIdx.x + u * kSortThreads;
+            if (r < left) {
+                const int at = at_rank[r];
+                const EntryWords x = event[at >> 1];
+                const bool role = at & 1;
+                const uint32_t me = (uint32_t)(role ? x[1] : x[0]);
+                const uint32_t to = shift_of[(me >> p.shift) & (kBins - 1)] + (uint32_t)r;
+                ((EntryWords *)p.out)[to] = EntryWords{role ? x[0] : x[1], (int32_t)((t0 + at) >> (LAST ? 1 : 0)), x[2], x[3]};
+                if (!LAST)
+                    p.node_out[to] = me;
+            }
+        }
+    }
+#pragma unroll
+    for (int f = 0; f < 3; ++f)
+        if (bad >> f & 1)
+            p.flags[f] = 1;
+}
+
+// The second pass: entries that are in the order of their low digits already, so that those of one high digit leave in long runs
+// by themselves where a few nodes have most of them.
+template <int BITS>
+__global__ void __launch_bounds__(kSortThreads, 4) k_sort_entries(SortPass p)
+{
+    using Bins = SortBins<BITS>;
+    constexpr int kBins = Bins::kBins, kPer = Bins::kPer;
+    __shared__ __attribute__((aligned(16))) uint16_t mine[kSortWaves][kBins];  // digits of a wavefront's run, then of those before it
+    __shared__ uint32_t base[kBins];                                          // where the next entry of a digit goes
+    __shared__ uint32_t sums[kSortWaves];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int d0 = (int)threadIdx.x * kPer;
+    {
+        uint32_t place[kPer];
+        Bins::first_places(p, sums, wave, lane, place);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i)
+            if (d0 + i < kBins)
+                base[d0 + i] = place[i];
+    }
+    const int64_t lo = (int64_t)blockIdx.x * p.chunk, hi = lo + p.chunk < p.n ? lo + p.chunk : p.n;
+    for (int64_t t0 = lo; t0 < hi; t0 += kSortTile) {
         const int left = hi - t0 < kSortTile ? (int)(hi - t0) : kSortTile;
-        int at0 = wave * (64 * kSortRounds) + lane;  // of the tile; beyond its end the last of the same role stands in
+        int at0 = wave * (64 * kSortRounds) + lane;  // of the tile; beyond its end the last entry stands in
         asm volatile("" : "+v"(at0));                // (sixteen rounds' places, kept over the tiles, spill)
-        const int stand_in = left - 2 + (lane & 1);
-        const int32_t *const src = p.src + (t0 >> 1), *const dst = p.dst + (t0 >> 1);
-        const int32_t *const own = (lane & 1) ? dst : src, *const opposite = (lane & 1) ? src : dst;
-        const double *const ts = p.ts + (t0 >> 1);
         const uint32_t *const node_in = p.node_in + t0;
         for (int i = threadIdx.x; i < kSortWaves * kBins / 2; i += kSortThreads)
             ((uint32_t *)mine)[i] = 0;
         uint32_t node[kSortRounds];
         uint16_t rank[kSortRounds];
 #pragma unroll
-        for (int u = 0; u < kSortRounds; ++u) {
-            const int at = at0 + 64 * u < left ? at0 + 64 * u : stand_in;
-            node[u] = FIRST ? (uint32_t)own[(unsigned)at >> 1] : node_in[(unsigned)at];
-        }
+        for (int u = 0; u < kSortRounds; ++u)
+            node[u] = node_in[(unsigned)(at0 + 64 * u < left ? at0 + 64 * u : left - 1)];
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < kSortRounds; ++u) {
             const bool on = at0 + 64 * u < left;
             const uint32_t d = (node[u] >> p.shift) & (kBins - 1);
-            unsigned long long same = __ballot(on);
-#pragma unroll
-            for (int b = 0; b < BITS; ++b) {
-                const bool bit = (d >> b) & 1u;
-                const unsigned long long set = __ballot(bit);
-                same &= bit ? set : ~set;
-            }
-            const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0u));
-            const uint32_t all = (uint32_t)__popcll(same);
+            uint32_t before, all;
+            match_digit<BITS>(d, on, before, all);
             const uint32_t had = mine[wave][d];
             rank[u] = (uint16_t)(had + before);
             if (on && before + 1 == all)
@@ -260,21 +425,12 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_sort_move(SortPass p)
 #pragma unroll
         for (int u0 = 0; u0 < kSortRounds; u0 += kTurn) {
             EntryWords e[kTurn];
-            asm volatile("" : "+v"(at0), "+v"(bad) : : "memory");  // (a turn at a time: all turns' loads together spill)
+            asm volatile("" : "+v"(at0) : : "memory");  // (a turn at a time: all turns' loads together spill)
 #pragma unroll
             for (int v = 0; v < kTurn; ++v) {
-                const int at = at0 + 64 * (u0 + v) < left ? at0 + 64 * (u0 + v) : stand_in;
-                if (FIRST) {
-                    const unsigned ev = (unsigned)at >> 1;
-                    const bool some = t0 + at > 1;  // not the stream's first event
-                    const int32_t me = (int32_t)node[u0 + v], other = opposite[ev];
-                    const double t = ts[ev], earlier = (ts - (some ? 1 : 0))[ev];
-                    bad |= (me < 0 || (int64_t)me >= p.num_nodes ? 1 : 0) | (some && !(earlier <= t) ? 2 : 0) | (me == other ? 4 : 0);
-                    e[v] = EntryWords{other, (int32_t)((t0 + at) >> (LAST ? 1 : 0)), __double2loint(t), __double2hiint(t)};
-                } else {
-                    e[v] = ((const EntryWords *)(p.in + t0))[(unsigned)at];
-                    e[v][1] = (int32_t)((uint32_t)e[v][1] >> 1);  // (the role has done its service)
-                }
+                const int at = at0 + 64 * (u0 + v);
+                e[v] = ((const EntryWords *)(p.in + t0))[(unsigned)(at < left ? at : left - 1)];
+                e[v][1] = (int32_t)((uint32_t)e[v][1] >> 1);  // (the role has done its service)
             }
 #pragma unroll
             for (int v = 0; v < kTurn; ++v) {
@@ -283,8 +439,6 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_sort_move(SortPass p)
                 const uint32_t to = base[d] + mine[wave][d] + rank[u];
                 if (at < left) {
                     ((EntryWords *)p.out)[to] = e[v];
-                    if (!LAST)
-                        p.node_out[to] = node[u];
                     (p.place + t0)[(unsigned)at] = (int32_t)to;
                 }
             }
@@ -294,12 +448,6 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_sort_move(SortPass p)
         for (int i = 0; i < kPer; ++i)
             if (d0 + i < kBins)
                 base[d0 + i] += tile[i];
-    }
-    if (FIRST) {
-#pragma unroll
-        for (int f = 0; f < 3; ++f)
-            if (bad >> f & 1)
-                p.flags[f] = 1;
     }
 }
 
@@ -324,13 +472,13 @@ __global__ void __launch_bounds__(kThreads) k_sort_pos(int32_t *__restrict__ pos
 }
 
 // indptr[n] = entries of nodes below n, n = 0..N, where the nodes are not kept beside the entries: an entry's node is its
-// event's other endpoint
+// event's other endpoint.  bounds: first entry of every value of the node's upper digit
 __global__ void k_indptr_of_entries(const CsrEntry *__restrict__ csr, const int32_t *__restrict__ src, const int32_t *__restrict__ dst,
-                                    int64_t num_entries, int64_t num_nodes, int64_t *__restrict__ indptr)
+                                    const uint32_t *__restrict__ bounds, int shift, int64_t num_nodes, int64_t *__restrict__ indptr)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n <= num_nodes; n += stride) {
-        int64_t lo = 0, hi = num_entries;
+        int64_t lo = bounds[n >> shift], hi = bounds[(n >> shift) + 1];
         while (lo < hi) {
             const int64_t mid = lo + ((hi - lo) >> 1);
             const CsrEntry x = csr[mid];
@@ -395,20 +543,20 @@ hipError_t sort_passes(SortPass first, SortPass second, int blocks, int bits, hi
     scan();
     if (bits <= BITS) {
         first.out = second.out;
-        hipLaunchKernelGGL((k_sort_move<BITS, true, true>), grid, threads, 0, s, first);
+        first.bounds = second.bounds;
+        hipLaunchKernelGGL((k_sort_events<BITS, true>), grid, threads, 0, s, first);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((k_sort_move<BITS, true, false>), grid, threads, 0, s, first);
-    second.shift = BITS;
+    hipLaunchKernelGGL((k_sort_events<BITS, false>), grid, threads, 0, s, first);
     hipLaunchKernelGGL((k_sort_count<BITS, false>), grid, threads, 0, s, second);
     scan();
-    hipLaunchKernelGGL((k_sort_move<BITS, false, true>), grid, threads, 0, s, second);
+    hipLaunchKernelGGL(k_sort_entries<BITS>, grid, threads, 0, s, second);
     const int64_t turns = (first.n + 4 * kThreads - 1) / (4 * kThreads);
     hipLaunchKernelGGL(k_sort_pos, dim3((unsigned)turns), dim3(kThreads), 0, s, first.place, second.place, first.n);
     return hipGetLastError();
 }
 
-// scratch: [entries | nodes, then destinations | counts per workgroup and digit | totals], within csr_build_scratch_bytes
+// scratch: [entries | nodes, then destinations | counts per workgroup and digit | totals | bounds], within csr_build_scratch_bytes
 hipError_t sort_adjacency(const int32_t *src, const int32_t *dst, const double *ts, int64_t num_events, int64_t num_nodes,
                           int64_t *indptr, CsrEntry *csr, int32_t *pos, int32_t *flags, char *scratch, size_t scratch_bytes,
                           int bits, hipStream_t s)
@@ -420,7 +568,8 @@ hipError_t sort_adjacency(const int32_t *src, const int32_t *dst, const double *
     const int half = bits <= kDigitBits ? bits : (bits + 1) / 2, digit = half < 8 ? 8 : half;
     const size_t entries = align_up(sizeof(CsrEntry) * (size_t)n2), nodes = align_up(sizeof(uint32_t) * (size_t)n2);
     const size_t counts = align_up(sizeof(uint32_t) * (size_t)blocks << digit);
-    if (entries + nodes + counts + (sizeof(uint32_t) << digit) > scratch_bytes)
+    const size_t totals = align_up(sizeof(uint32_t) << digit), bounds = totals + 256;
+    if (entries + nodes + counts + totals + bounds > scratch_bytes)
         return hipErrorOutOfMemory;
     SortPass a = {};
     a.src = src, a.dst = dst, a.ts = ts;
@@ -436,6 +585,8 @@ hipError_t sort_adjacency(const int32_t *src, const int32_t *dst, const double *
     b.in = a.out, b.node_in = a.node_out;
     b.out = csr, b.node_out = nullptr;
     b.place = (int32_t *)a.node_out;
+    b.bounds = (uint32_t *)(scratch + entries + nodes + counts + totals);
+    b.shift = digit;
     hipError_t e;
     switch (digit) {
     case 8: e = sort_passes<8>(a, b, blocks, bits, s); break;
@@ -445,7 +596,8 @@ hipError_t sort_adjacency(const int32_t *src, const int32_t *dst, const double *
     }
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(k_indptr_of_entries, dim3(grid_for(num_nodes + 1)), dim3(kThreads), 0, s, csr, src, dst, n2, num_nodes, indptr);
+    hipLaunchKernelGGL(k_indptr_of_entries, dim3(grid_for(num_nodes + 1)), dim3(kThreads), 0, s, csr, src, dst, b.bounds,
+                       bits <= digit ? 0 : digit, num_nodes, indptr);
     return hipGetLastError();
 }
 
