@@ -22,30 +22,66 @@ constexpr int kScanThreads = 1024;
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 // A node with replicas in more than one part resides in every part (node loop of Alg. 1).
-__device__ inline bool is_member(const uint64_t *node_parts, int64_t num_nodes, int64_t v, uint64_t group)
+__device__ inline bool is_member(uint64_t parts, uint64_t group)
 {
-    if (v < 0 || v >= num_nodes)
-        return false;
-    const uint64_t m = node_parts[v];
-    return __popcll(m) > 1 ? group != 0ull : (m & group) != 0ull;
+    return __popcll(parts) > 1 ? group != 0ull : (parts & group) != 0ull;
 }
+
+__device__ inline bool inside(int32_t v, int64_t num_nodes) { return v >= 0 && (int64_t)v < num_nodes; }
+
+// Consecutive items of a thread, tested together: all ids are there in two loads, and all their masks on their way before the first is
+// looked at (one item after the other, two dependent reads each, 16 M events took 114 us; with the counts' scan in wavefronts and one wait for both
+// compactions a sub-graph's rebuilding takes 2305 instead of 2408 us).
+struct __attribute__((packed, aligned(4))) EightIds {
+    int32_t v[kCompPer];
+};
 
 struct EventPred {
     const int32_t *src, *dst;
     const uint64_t *node_parts;
     int64_t num_nodes;
     uint64_t group;
-    __device__ bool operator()(int64_t e) const
+    __device__ unsigned operator()(int64_t i0, int64_t n) const
     {
-        return is_member(node_parts, num_nodes, src[e], group) && is_member(node_parts, num_nodes, dst[e], group);
+        EightIds s, d;
+        if (i0 + kCompPer <= n) {
+            s = *(const EightIds *)(src + i0);
+            d = *(const EightIds *)(dst + i0);
+        } else {
+            for (int u = 0; u < kCompPer; ++u) {
+                s.v[u] = i0 + u < n ? src[i0 + u] : -1;
+                d.v[u] = i0 + u < n ? dst[i0 + u] : -1;
+            }
+        }
+        uint64_t ms[kCompPer], md[kCompPer];
+#pragma unroll
+        for (int u = 0; u < kCompPer; ++u) {
+            ms[u] = node_parts[inside(s.v[u], num_nodes) ? s.v[u] : 0];
+            md[u] = node_parts[inside(d.v[u], num_nodes) ? d.v[u] : 0];
+        }
+        unsigned bits = 0;
+#pragma unroll
+        for (int u = 0; u < kCompPer; ++u)
+            if (inside(s.v[u], num_nodes) && inside(d.v[u], num_nodes) && is_member(ms[u], group) && is_member(md[u], group))
+                bits |= 1u << u;
+        return bits;
     }
 };
 
 struct NodePred {
     const uint64_t *node_parts;
-    int64_t num_nodes;
     uint64_t group;
-    __device__ bool operator()(int64_t v) const { return is_member(node_parts, num_nodes, v, group); }
+    __device__ unsigned operator()(int64_t i0, int64_t n) const
+    {
+        unsigned bits = 0;
+#pragma unroll
+        for (int u = 0; u < kCompPer; ++u) {
+            const uint64_t m = node_parts[i0 + u < n ? i0 + u : n - 1];
+            if (i0 + u < n && is_member(m, group))
+                bits |= 1u << u;
+        }
+        return bits;
+    }
 };
 
 // The count pass also leaves the verdicts of a thread's 8 consecutive items as one byte, so the
@@ -59,18 +95,12 @@ __global__ void __launch_bounds__(kCompThreads) k_comp_count(Pred pred, int64_t 
         total = 0;
     __syncthreads();
     const int64_t i0 = (int64_t)blockIdx.x * kCompBlock + (int64_t)threadIdx.x * kCompPer;
-    int c = 0;
-    unsigned bits = 0;
-#pragma unroll
-    for (int u = 0; u < kCompPer; ++u)
-        if (i0 + u < n && pred(i0 + u)) {
-            ++c;
-            bits |= 1u << u;
-        }
-    if (i0 < n)
+    if (i0 < n) {
+        const unsigned bits = pred(i0, n);
         keep_bits[i0 / kCompPer] = (uint8_t)bits;
-    if (c)
-        atomicAdd(&total, c);
+        if (bits)
+            atomicAdd(&total, __popc(bits));
+    }
     __syncthreads();
     if (threadIdx.x == 0)
         block_counts[blockIdx.x] = total;
@@ -80,26 +110,30 @@ __global__ void __launch_bounds__(kCompThreads) k_comp_count(Pred pred, int64_t 
 __global__ void __launch_bounds__(kScanThreads) k_comp_scan(const int32_t *block_counts, int64_t n_blocks,
                                                             int64_t *block_offsets, int64_t *total)
 {
-    __shared__ int64_t part[kScanThreads];
+    __shared__ int64_t part[kScanThreads / kWave];
     const int64_t per = (n_blocks + kScanThreads - 1) / kScanThreads;
     const int64_t lo = (int64_t)threadIdx.x * per;
     const int64_t hi = lo + per < n_blocks ? lo + per : n_blocks;
     int64_t s = 0;
     for (int64_t b = lo; b < hi; ++b)
         s += block_counts[b];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int64_t run = 0;
-        for (int t = 0; t < kScanThreads; ++t) {
-            const int64_t c = part[t];
-            part[t] = run;
-            run += c;
-        }
-        *total = run;
+    // (one thread adding up the threads' sums was 15 of 18 us)
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    int64_t incl = s;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int64_t up = __shfl_up(incl, off, kWave);
+        if (lane >= off)
+            incl += up;
     }
+    if (lane == kWave - 1)
+        part[wave] = incl;
     __syncthreads();
-    int64_t run = part[threadIdx.x];
+    int64_t run = incl - s;
+    for (int w = 0; w < wave; ++w)
+        run += part[w];
+    if (threadIdx.x == kScanThreads - 1)
+        *total = run + s;
     for (int64_t b = lo; b < hi; ++b) {
         block_offsets[b] = run;
         run += block_counts[b];
@@ -274,31 +308,25 @@ CompScratch comp_scratch(int64_t n_max, void *base)
     return c;
 }
 
+// (enqueues; *total is device memory)
 template <class Pred>
 hipError_t compact(Pred pred, int64_t n, const CompScratch &c, int64_t capacity, int32_t *out, int32_t *rank_of,
-                   int64_t *total_host, hipStream_t s)
+                   int64_t *total, hipStream_t s)
 {
     const int64_t nb = (n + kCompBlock - 1) / kCompBlock;
-    if (nb == 0) {
-        *total_host = 0;
-        return hipSuccess;
-    }
+    if (nb == 0)
+        return launch_fill_zero(total, sizeof(int64_t), s);
     hipLaunchKernelGGL(k_comp_count<Pred>, dim3((unsigned)nb), dim3(kCompThreads), 0, s, pred, n, c.block_counts,
                        c.keep_bits);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(k_comp_scan, dim3(1), dim3(kScanThreads), 0, s, c.block_counts, nb, c.block_offsets, c.total);
+    hipLaunchKernelGGL(k_comp_scan, dim3(1), dim3(kScanThreads), 0, s, c.block_counts, nb, c.block_offsets, total);
     if ((e = hipGetLastError()) != hipSuccess)
         return e;
     hipLaunchKernelGGL(k_comp_write, dim3((unsigned)nb), dim3(kCompThreads), 0, s, c.keep_bits, n, c.block_offsets,
                        capacity, out, rank_of);
-    if ((e = hipGetLastError()) != hipSuccess)
-        return e;
-    e = hipMemcpyAsync(total_host, c.total, sizeof(int64_t), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s);
-    return e;
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -338,10 +366,14 @@ int tig_pac_subgraph(const int32_t *src, const int32_t *dst, int64_t num_events,
     hipStream_t s = (hipStream_t)hip_stream;
     const CompScratch c = comp_scratch(num_events > num_nodes ? num_events : num_nodes, scratch);
     hipError_t e = compact(EventPred{src, dst, node_parts, num_nodes, group}, num_events, c, num_events, eid_out,
-                           nullptr, &counts_out[0], s);
+                           nullptr, c.total, s);
     if (e != hipSuccess)
         return fail_global("tig_pac_subgraph: event compaction", e);
-    e = compact(NodePred{node_parts, num_nodes, group}, num_nodes, c, 0, nullptr, local_out, &counts_out[1], s);
+    e = compact(NodePred{node_parts, group}, num_nodes, c, 0, nullptr, local_out, c.total + 1, s);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(counts_out, c.total, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(s);
     return e == hipSuccess ? TIG_OK : fail_global("tig_pac_subgraph: node compaction", e);
 }
 
