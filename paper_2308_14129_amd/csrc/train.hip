@@ -314,21 +314,22 @@ struct CopyJob {  // dst element (r, c), r < rows, c < cols, = src[r * rs + c * 
     int kbs;      // k-blocks per output tile of a prepared operand, 0: a plain vector (c only)
     int r0, c0, rows, cols, rs, cs, rs2, cols2;
 };
-constexpr int kMaxCopy = 20;
+constexpr int kMaxCopy = 22;
 struct SmallJobs {
     int first[kMaxSmall];  // as in WgradJobs
     SmallJob j[kMaxSmall];
     int n, tiles;  // jobs, their workgroups
     int T, MF;     // key / value row: time encoding, state + features
 };
+// A thread takes four columns of a row (16 bytes of a prepared operand); first[i]: first workgroup of job i, as in WgradJobs.
 struct CopyJobs {
+    int first[kMaxCopy];
     CopyJob j[kMaxCopy];
-    int n;
+    int n, blocks;
     const float *time_w, *time_b;
     double *time_w_rev, *time_b_rev;
     int T;
 };
-constexpr int kCopyX = 32;  // workgroups per copy
 
 __device__ inline size_t packed_index(int r, int c, int kbs)  // fp32 operand, 16-deep k-blocks
 {
@@ -354,7 +355,7 @@ __device__ inline int map_index(int i, int how, int T, int MF)
 
 constexpr int kSmallThreads = 512, kSmallWaves = kSmallThreads / kWave, kSmallPer = 1024 / kSmallThreads;
 
-__device__ void copy_block(const CopyJobs &jobs, int x, int y);
+__device__ void copy_block(const CopyJobs &jobs, int block);
 
 struct __attribute__((packed, aligned(4))) Four {
     float v[4];
@@ -431,13 +432,12 @@ __device__ inline void small_multiply(const SmallJob &q, const int (&ao)[2], con
     }
 }
 
-// The workgroups beyond the products' take the copies, jobs.copy_x of them per job.
+// The workgroups beyond the products' take the copies.
 __global__ void __launch_bounds__(kSmallThreads, 4) k_tr_small(SmallJobs jobs, CopyJobs copies)
 {
     __shared__ float red[kSmallWaves][1024];
     if ((int)blockIdx.x >= jobs.tiles) {
-        const int x = (int)blockIdx.x - jobs.tiles;
-        copy_block(copies, x % kCopyX, x / kCopyX);
+        copy_block(copies, (int)blockIdx.x - jobs.tiles);
         return;
     }
     const int block = (int)blockIdx.x;
@@ -515,26 +515,46 @@ __global__ void __launch_bounds__(kSmallThreads, 4) k_tr_small(SmallJobs jobs, C
     }
 }
 
-__device__ void copy_block(const CopyJobs &jobs, int x, int y)
+// One group of four per thread, all of its loads together (a fixed number of workgroups per matrix, element by element, was a chain of
+// seven loads and scattered stores for the widest ones; with the order of the unfolding's jobs, a training step of 200 events of 172
+// columns 168 -> 164.5 us, of 4000 of 100 as before).
+__device__ void copy_block(const CopyJobs &jobs, int block)
 {
-    const size_t stride = (size_t)kCopyX * kSmallThreads;
-    const size_t i0 = (size_t)x * kSmallThreads + threadIdx.x;
-    if (y >= jobs.n) {
-        for (size_t i = i0; i < (size_t)2 * jobs.T; i += stride) {
-            const bool phase = i >= (size_t)jobs.T;
-            const size_t j = phase ? i - jobs.T : i;
+    const int y = job_of_block(jobs.first, block);
+    if (y >= jobs.n) {  // the time encoding's parameters in revolutions
+        const int i = (block - jobs.first[y]) * kSmallThreads + (int)threadIdx.x;
+        if (i < 2 * jobs.T) {
+            const bool phase = i >= jobs.T;
+            const int j = phase ? i - jobs.T : i;
             (phase ? jobs.time_b_rev : jobs.time_w_rev)[j] = (double)(phase ? jobs.time_b : jobs.time_w)[j] / 6.283185307179586476925286766559;
         }
         return;
     }
-    const CopyJob &q = jobs.j[y];
-    for (size_t i = i0; i < (size_t)q.rows * q.cols; i += stride) {
-        // (the faster index of the source varies fastest)
-        const int r = q.cs == 1 ? (int)(i / q.cols) : (int)(i % q.rows), c = q.cs == 1 ? (int)(i % q.cols) : (int)(i / q.rows);
-        float v = q.src[(size_t)r * q.rs + (size_t)c * q.cs];
-        if (q.src2 && c < q.cols2)
-            v += q.src2[(size_t)r * q.rs2 + c];
-        q.dst[q.kbs ? packed_index(q.r0 + r, q.c0 + c, q.kbs) : (size_t)c] = v;
+    const CopyJob q = jobs.j[y];
+    const int groups = (q.cols + 3) / 4, i = (block - jobs.first[y]) * kSmallThreads + (int)threadIdx.x;
+    if (i >= q.rows * groups)
+        return;
+    // (the faster index of the source varies fastest)
+    const int r = q.cs == 1 ? i / groups : i % q.rows, c = 4 * (q.cs == 1 ? i % groups : i / q.rows);
+    floatx4 v, v2 = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int ce = c + e < q.cols ? c + e : c;
+        v[e] = q.src[(size_t)r * q.rs + (size_t)ce * q.cs];
+        if (q.src2)
+            v2[e] = q.src2[(size_t)r * q.rs2 + (ce < q.cols2 ? ce : 0)];
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        v[e] += q.src2 && c + e < q.cols2 ? v2[e] : 0.0f;
+    float *const dst = q.dst + (q.kbs ? packed_index(q.r0 + r, q.c0 + c, q.kbs) : (size_t)c);
+    if (q.kbs && c + 4 <= q.cols) {
+        *(floatx4 *)dst = v;  // (c0 is a multiple of four: one lane's share of an operand)
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (c + e < q.cols)
+                dst[e] = v[e];
     }
 }
 
@@ -786,7 +806,7 @@ struct SmallList {
     hipError_t launch(hipStream_t s, const CopyJobs *copies = nullptr) const
     {
         const CopyJobs none = {};
-        const int blocks = jobs.tiles + (copies ? (copies->n + 1) * kCopyX : 0);
+        const int blocks = jobs.tiles + (copies ? copies->blocks : 0);
         hipLaunchKernelGGL(k_tr_small, dim3(blocks), dim3(kSmallThreads), 0, s, jobs, copies ? *copies : none);
         return hipGetLastError();
     }
@@ -865,6 +885,11 @@ hipError_t fold_weights(const Dims &d, const TrainLayout &L, const PackedWeights
     vec(pw.dec_b2, w.b_d2, 1);
     c.time_w = w.time_w, c.time_b = w.time_b, c.T = T;
     c.time_w_rev = (double *)pw.time_w_rev, c.time_b_rev = (double *)pw.time_b_rev;
+    for (int i = 0; i < kMaxCopy; ++i) {
+        c.first[i] = i <= c.n ? c.blocks : 0x7fffffff;
+        const int items = i < c.n ? c.j[i].rows * ((c.j[i].cols + 3) / 4) : (i == c.n ? 2 * T : 0);
+        c.blocks += (items + kSmallThreads - 1) / kSmallThreads;
+    }
     (void)F;
     const hipError_t e = one.launch(s, &c);
     return e == hipSuccess ? two.launch(s) : e;
@@ -877,21 +902,22 @@ hipError_t unfold_gradients(const Dims &d, const TrainLayout &L, hipStream_t s)
     const int M = d.M, T = d.T, E = d.E, H = d.H, da = d.da, dh = d.dh, dkv = d.dkv, ld_m1 = da + M, ldA = M + 1;
     const double scale = 1.0 / sqrt((double)dh);
     SmallList one(d), two(d);
+    // Two workgroups fit a compute unit, and the first 256 spread over all: those of the longest sums (over key / value columns)
+    // in the middle, so that the ones that share a unit with another, the first and the last, have the shorter sums.
+    for (int h = 0; h < H; ++h) {   // dW_K,h = scale (W_Q,h[:, :M] dA1_h^T + cQ_h (x) da1_h)
+        const float *WQ = w.W_Q + (size_t)h * dh * da, *gA = L.gA1 + (size_t)h * d.dkvp * ldA;
+        SmallJob &q = one.add((float *)g.W_K + (size_t)h * dh * dkv, dkv, WQ, da, 1, gA, 1, ldA, dh, dkv, M, scale);
+        q.bn = kToKernel;
+        q.u = L.cQ + h * dh, q.us = 1, q.v = gA + M, q.vs = ldA;
+        q.u_scale = scale;
+    }
     for (int h = 0; h < H; ++h) {
-        const float *WK = w.W_K + (size_t)h * dh * dkv, *WV = w.W_V + (size_t)h * dh * dkv, *WQ = w.W_Q + (size_t)h * dh * da;
+        const float *WK = w.W_K + (size_t)h * dh * dkv, *WV = w.W_V + (size_t)h * dh * dkv;
         const float *gP = L.gP + h * d.dkvp, *gA = L.gA1 + (size_t)h * d.dkvp * ldA;
         {   // dG_h = dP_h W_V,h^T + dc (x) b_V,h
             SmallJob &q = one.add(L.gG + h * dh, da, gP, d.N1, 1, WV, 1, dkv, E, dh, dkv);
             one.k_to_model(q, q.b_k);
             q.u = L.gc, q.us = 1, q.v = w.b_V + h * dh, q.vs = 1;
-        }
-        // dW_V,h = G_h^T dP_h
-        one.add((float *)g.W_V + (size_t)h * dh * dkv, dkv, L.Gm + h * dh, 1, da, gP, d.N1, 1, dh, dkv, E).bn = kToKernel;
-        {   // dW_K,h = scale (W_Q,h[:, :M] dA1_h^T + cQ_h (x) da1_h)
-            SmallJob &q = one.add((float *)g.W_K + (size_t)h * dh * dkv, dkv, WQ, da, 1, gA, 1, ldA, dh, dkv, M, scale);
-            q.bn = kToKernel;
-            q.u = L.cQ + h * dh, q.us = 1, q.v = gA + M, q.vs = ldA;
-            q.u_scale = scale;
         }
         {   // [dW_Q,h[:, :M] | d cQ_h] = scale W_K,h [dA1_h | da1_h];  d b_Q = d cQ
             SmallJob &q = one.add((float *)g.W_Q + (size_t)h * dh * da, da, WK, dkv, 1, gA, ldA, 1, dh, M + 1, dkv, scale);
@@ -899,6 +925,8 @@ hipError_t unfold_gradients(const Dims &d, const TrainLayout &L, hipStream_t s)
             q.split = M, q.C_hi = (float *)g.b_Q + h * dh;
         }
     }
+    for (int h = 0; h < H; ++h)     // dW_V,h = G_h^T dP_h
+        one.add((float *)g.W_V + (size_t)h * dh * dkv, dkv, L.Gm + h * dh, 1, da, L.gP + h * d.dkvp, d.N1, 1, dh, dkv, E).bn = kToKernel;
     // d b_V = G^T dc
     one.add((float *)g.b_V, 1, L.Gm, 1, da, L.gc, 1, 1, da, 1, E);
     {   // dW_m1[:, :da] = dG W_O^T + dc (x) b_O
