@@ -40,17 +40,23 @@ __device__ inline int row_of_entry_tr(const QuerySet &qs, int i, int entries)
 }
 
 // ------------------------------------------------------------------------------------------
-// One wavefront per event, sixteen events per workgroup.  y = W_a emb_src + W_b emb_other + b1 comes from
+// One wavefront per event, sixteen consecutive events per workgroup, an eighth of the batch per XCD.  y = W_a emb_src + W_b emb_other + b1 comes from
 // the per-row halves that the forward pass left; d y goes to the source's row of DA and the other's row
-// of DB (a negative's row belongs to its event alone: stored, not added).
+// of DB (a negative's row belongs to its event alone: stored, not added).  Events of one moment share a hub's row: their workgroups'
+// additions come from one XCD, and a workgroup adds each of its rows once (an addition of its own for every event, from
+// all XCDs in turn, at 4000 events of 100 columns of which 44% touch one node: 12.2 us instead of 10.4).
 constexpr int kDecThreads = 1024, kDecWaves = kDecThreads / kWave;
 constexpr int kDecCols = 8;  // 64-column pieces of a row at most
+constexpr int kDecXcds = 8;
 
 __global__ void __launch_bounds__(kDecThreads) k_tr_decode(StepArgs a, PackedWeights w, TrainArrays t, int E, int Ep)
 {
     extern __shared__ float wsum[];  // [waves x (E + 1)] the wavefronts' shares of the gradients of w_d2 and b_d2
-    const int B = a.count, lane = lane_id(), wave = wave_id();
-    const int b = (int)blockIdx.x * kDecWaves + wave;
+    float *const share = wsum + kDecWaves * (E + 1);  // [2][waves x E] what the events add to DA, to DB
+    __shared__ int s_row[2][kDecWaves];
+    const int B = a.count, lane = lane_id(), wave = wave_id_uniform();
+    const int per_xcd = ((int)gridDim.x + kDecXcds - 1) / kDecXcds;  // (a launch's workgroups go round the XCDs)
+    const int b = ((int)blockIdx.x % kDecXcds * per_xcd + (int)blockIdx.x / kDecXcds) * kDecWaves + wave;
     const bool on = b < B;  // (uniform over the wavefront)
     const int bb = on ? b : 0;
     const int row[3] = {row_of_entry_tr(a.qs, 2 * bb, 2 * B), row_of_entry_tr(a.qs, 2 * bb + 1, 2 * B), 2 * B + bb};
@@ -94,17 +100,35 @@ __global__ void __launch_bounds__(kDecThreads) k_tr_decode(StepArgs a, PackedWei
             const int j = c * kWave + lane;
             if (j < E) {
                 wsum[wave * (E + 1) + j] = dl[0] * g[0][c] + dl[1] * g[1][c];
-                if (on) {
-                    const float dp = g[0][c] > 0.0f ? dl[0] * w2[c] : 0.0f, dn = g[1][c] > 0.0f ? dl[1] * w2[c] : 0.0f;
-                    atomicAdd(&t.DA[(size_t)row[0] * E + j], dp + dn);
-                    atomicAdd(&t.DB[(size_t)row[1] * E + j], dp);
+                const float dp = g[0][c] > 0.0f ? dl[0] * w2[c] : 0.0f, dn = g[1][c] > 0.0f ? dl[1] * w2[c] : 0.0f;
+                share[wave * E + j] = dp + dn;
+                share[(kDecWaves + wave) * E + j] = dp;
+                if (on)
                     t.DB[(size_t)row[2] * E + j] = dn;
-                }
             }
         }
-    if (lane == 0)
+    if (lane == 0) {
         wsum[wave * (E + 1) + E] = dl[0] + dl[1];
+        s_row[0][wave] = on ? row[0] : -1;
+        s_row[1][wave] = on ? row[1] : -1;
+    }
     __syncthreads();
+    // the first event of the workgroup with a row adds for all of them
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int mine = __builtin_amdgcn_readfirstlane(s_row[p][wave]);
+        const int theirs = lane < kDecWaves ? s_row[p][lane] : -1;
+        const unsigned long long same = __ballot(theirs == mine && lane < kDecWaves);
+        if (mine < 0 || __builtin_ctzll(same) != wave)
+            continue;
+        float *const dst = (p == 0 ? t.DA : t.DB) + (size_t)mine * E;
+        for (int j = lane; j < E; j += kWave) {
+            float sum = 0.0f;
+            for (unsigned long long m = same; m; m &= m - 1)  // (uniform)
+                sum += share[(p * kDecWaves + __builtin_ctzll(m)) * E + j];
+            atomicAdd(&dst[j], sum);
+        }
+    }
     for (int j = threadIdx.x; j <= E; j += kDecThreads) {
         float sum = 0.0f;
         for (int v = 0; v < kDecWaves; ++v)
@@ -914,7 +938,7 @@ const void *gru_back_kernel(int rows)
     return rows == 4 ? (const void *)k_tr_gru_back<4> : (rows == 8 ? (const void *)k_tr_gru_back<8> : (const void *)k_tr_gru_back<16>);
 }
 
-int decode_lds_bytes(const Dims &d) { return kDecWaves * (d.E + 1) * 4; }
+int decode_lds_bytes(const Dims &d) { return kDecWaves * (3 * d.E + 1) * 4; }
 
 }  // namespace
 
@@ -943,7 +967,7 @@ hipError_t prepare_train_back(const Dims &d)
 
 hipError_t launch_train_decode(const Dims &d, const StepArgs &a, const PackedWeights &pw, const TrainArrays &t, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_tr_decode, dim3((a.count + kDecWaves - 1) / kDecWaves), dim3(kDecThreads), decode_lds_bytes(d), s, a, pw, t,
+    hipLaunchKernelGGL(k_tr_decode, dim3(((a.count + kDecWaves - 1) / kDecWaves + kDecXcds - 1) / kDecXcds * kDecXcds), dim3(kDecThreads), decode_lds_bytes(d), s, a, pw, t,
                        d.E, d.Ep);
     return hipGetLastError();
 }
