@@ -82,7 +82,7 @@ __global__ void k_fill_csr(const EventRecord *__restrict__ rec, int64_t num_entr
 // instead of scattered: a pass leaves every entry's destination at its source position, where two
 // passes are composed by a read whose neighbours go to neighbouring places (k_sort_pos).
 // Per pass: digit counts per workgroup (k_sort_count), their prefix sums (k_sort_scan), and the move (k_sort_events, k_sort_entries), no workgroup
-// waiting for another.  25 M entries of 0.5 M nodes (Zipf 1.5), with the times' and ids' check: 1.62 -> 0.86 ms (moves 309 and 293 us, counts
+// waiting for another.  31.7 M entries of 0.5 M nodes (Zipf 1.5), with the times' and ids' check: 1.62 -> 0.86 ms (moves 309 and 293 us, counts
 // 41 and 45, positions 127, bounds 36); a sub-graph's whole rebuilding 3.19 -> 2.41 ms.  More nodes than 2^22 would need a third pass and a second copy of the entries; they take the sort above.
 constexpr int kSortThreads = 512, kSortWaves = kSortThreads / 64;
 constexpr int kSortRounds = 16;                       // entries per lane and tile
@@ -132,7 +132,7 @@ __global__ void __launch_bounds__(kSortThreads) k_sort_count(SortPass p)
         for (int u = 0; u < kTurn; ++u)
             if (q0 + u * kSortThreads < hi) {
                 // the first lane's digit is counted at once: most lanes share it where a few nodes have most of the entries, and
-                // additions to one address take turns (25 M entries of which 97% have one digit: 116 us a lane at a time)
+                // additions to one address take turns (31.7 M entries of which 97% have one digit: 116 us a lane at a time)
                 const uint32_t d = (node[u] >> p.shift) & (kBins - 1), lead = __builtin_amdgcn_readfirstlane(d);
                 const unsigned long long same = __ballot(d == lead);
                 if (d != lead)
@@ -243,7 +243,7 @@ struct SortBins {
 //
 // The first pass, from the event stream: a tile's events stay in LDS, and its entries leave in the order of their
 // digits, so that neighbouring lanes write neighbouring places (written from where they were read, 16 and 4 bytes a lane to as many
-// places, 25 M entries of 0.5 M nodes took 486 us instead of 309).  Also checks the graph: flags[0] an id out of
+// places, 31.7 M entries of 0.5 M nodes took 486 us instead of 309).  Also checks the graph: flags[0] an id out of
 // range, [1] times that decrease, [2] a self-loop (whatever the ids, a digit is one of the bins).
 template <int BITS, bool LAST>
 __global__ void __launch_bounds__(kSortThreads, 4) k_sort_events(SortPass p)
