@@ -186,6 +186,16 @@ __device__ inline void match_digit(uint32_t d, bool on, uint32_t &before, uint32
     all = (uint32_t)__popcll(same);
 }
 
+// Orders a wavefront's own LDS accesses: what a lane has stored is what the other lanes load next.  (The counters of
+// match_digit's rounds go from the digit's last lane to whichever lanes have it a round later; LDS operations of a
+// wavefront are carried out in order anyway, so that this only binds the compiler: the same instructions, no wait added.)
+__device__ inline void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 // Sum over the threads before this one; `sums`: [wavefronts] of LDS that nobody else uses, whose readers may still be
 // reading on return.
 __device__ inline uint32_t sum_before(uint32_t x, uint32_t *sums, int wave, int lane)
@@ -302,6 +312,7 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_sort_events(SortPass p)
             rank[u] = had + before;
             if (on && before + 1 == all)
                 mine[wave][dig] = (uint16_t)(had + all);
+            wave_lds_order();
         }
         __syncthreads();
         {   // ranks of the tile: digit by digit, within a digit wavefront by wavefront
@@ -406,6 +417,7 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_sort_entries(SortPass p)
             rank[u] = (uint16_t)(had + before);
             if (on && before + 1 == all)
                 mine[wave][d] = (uint16_t)(had + all);
+            wave_lds_order();
         }
         __syncthreads();
         uint32_t tile[kPer];
