@@ -78,3 +78,11 @@ def test_a_graph_that_is_not_one_is_refused(n, event):
     late = ts.copy()
     late[event] = 20_000.0 if event < 9999 else -1.0
     assert refused(src, dst, late) == tig.TIG_EUNSORTED
+
+
+# more than 1024 tiles, so that workgroups carry their digits' places from tile to tile, with two and four bins a thread: one pass of 11
+# bits, two of 9, 10 and 11; whole runs of tiles, a shorter last run, a last tile of two entries
+@pytest.mark.parametrize("n,e,alpha", [(2000, 4_300_000, 1.3), ((1 << 17) + 1, 4_296_000, 1.2), ((1 << 19) + 1, 4_300_000, 1.3),
+                                       ((1 << 21) + 1, 4_300_000, 1.1), ((1 << 21) + 1, 4_300_801, 0.0)])
+def test_places_carried_from_tile_to_tile(n, e, alpha):
+    test_adjacency_is_the_stable_sort(n, e, alpha)
