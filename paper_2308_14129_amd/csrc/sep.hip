@@ -15,8 +15,6 @@
 
 #include <cmath>
 #include <cstring>
-#include <new>
-#include <vector>
 
 #include "tig_internal.h"
 
@@ -266,7 +264,7 @@ namespace {
 // same bit for bit; an edge that the sets do not cover (sizes spread over kLevels values or more, terms
 // so close that rounding could make two sizes equal, centralities that are not finite and non-negative)
 // is decided by the plain evaluation (best_plain), and while the sizes are spread that far only their extremes are
-// kept.  Measured per edge, 8 partitions of 4 M events and 1 M nodes, 1% hubs, before the levels were in registers and after (Xeon
+// kept.  Nothing is allocated, so that the C entries have no exception to hold back.  Measured per edge, 8 partitions of 4 M events and 1 M nodes, 1% hubs, before the levels were in registers and after (Xeon
 // at 2.7 GHz): 11.8 -> 5.2 ns; 16 partitions, 5% hubs 11.4 -> 5.2; 5 partitions and mostly non-hubs 12.0 -> 10.6; no hubs, where the
 // sizes are too far apart for the sets from the start, 17.6 -> 16.1.  The whole call of the first (EPYC host of the MI355X): 25.1 -> 13.8 ms.
 class EdgeLoop {
@@ -606,14 +604,10 @@ int tig_sep_assign(const tig_sep_config *cfg, const int32_t *src, const int32_t 
     if (num_nodes < 1 || num_events < 0 || !cent || !is_hub || !node_parts_out || !part_edges_out ||
         (num_events > 0 && (!src || !dst || !edge_part_out)))
         return TIG_EINVAL;
-    try {
-        EdgeLoop loop(*cfg, num_nodes, cent, is_hub, node_parts_out);
-        if (!loop.run(src, dst, num_events, edge_part_out))
-            return TIG_ERANGE;
-        loop.sizes(part_edges_out);
-    } catch (const std::bad_alloc &) {
-        return TIG_ENOMEM;
-    }
+    EdgeLoop loop(*cfg, num_nodes, cent, is_hub, node_parts_out);
+    if (!loop.run(src, dst, num_events, edge_part_out))
+        return TIG_ERANGE;
+    loop.sizes(part_edges_out);
     return TIG_OK;
 }
 
@@ -692,20 +686,16 @@ int tig_sep_partition(const tig_sep_config *cfg, const int32_t *src, const int32
     if (he == hipSuccess)
         he = request(0);
     int status = TIG_OK;
-    try {
-        EdgeLoop loop(*cfg, num_nodes, cent_out, is_hub_out, node_parts_out);
-        for (int64_t k = 0; he == hipSuccess && status == TIG_OK && k * piece < num_events; ++k) {
-            if ((he = request(k + 1)) != hipSuccess || (he = hipEventSynchronize(ready.e[k & 1])) != hipSuccess)
-                break;
-            const int64_t e0 = k * piece, n = num_events - e0 < piece ? num_events - e0 : piece;
-            const int32_t *const d = buf + (k & 1) * 2 * piece;
-            if (!loop.run(d, d + piece, n, edge_part_out + e0))
-                status = TIG_ERANGE;
-        }
-        loop.sizes(part_edges_out);
-    } catch (const std::bad_alloc &) {
-        status = TIG_ENOMEM;
+    EdgeLoop loop(*cfg, num_nodes, cent_out, is_hub_out, node_parts_out);
+    for (int64_t k = 0; he == hipSuccess && status == TIG_OK && k * piece < num_events; ++k) {
+        if ((he = request(k + 1)) != hipSuccess || (he = hipEventSynchronize(ready.e[k & 1])) != hipSuccess)
+            break;
+        const int64_t e0 = k * piece, n = num_events - e0 < piece ? num_events - e0 : piece;
+        const int32_t *const d = buf + (k & 1) * 2 * piece;
+        if (!loop.run(d, d + piece, n, edge_part_out + e0))
+            status = TIG_ERANGE;
     }
+    loop.sizes(part_edges_out);
     // (nothing is in flight into the pinned buffer when it is given back)
     const hipError_t last = hipStreamSynchronize(s);
     return he != hipSuccess || last != hipSuccess ? TIG_EHIP : status;
