@@ -43,8 +43,10 @@ struct __attribute__((packed, aligned(4))) Floats {
     float v[N];
 };
 
-// A and B are read through buffer descriptors whose extent is the n rows: a k beyond the end reads zeros.  Two groups of
-// kU k-steps take turns, one on its way while the other is multiplied.
+// A and B are read through buffer descriptors whose extent is the n rows: a k beyond the end reads zeros.  Where a width is no
+// multiple of a lane's two or four columns, its load of the last row reaches beyond the extent: such loads are checked dword
+// by dword, so that the columns inside arrive and those outside, which are no columns of the matrix, read zero; nothing behind
+// an array is read.  Two groups of kU k-steps take turns, one on its way while the other is multiplied.
 template <int MI, int kU>  // kU: k-steps of 4 whose loads are issued together
 __device__ inline void multiply(const float *A, const float *B, int sa, int sb, int ao, int bo, int n, floatx4 (&acc)[MI][2],
                                 double (&sum)[MI])
@@ -119,8 +121,7 @@ __device__ inline void multiply(const float *A, const float *B, int sa, int sb, 
 // that goes with a weight gradient), by the workgroups of the first block column.
 // The wavefronts' and XCDs' parts are added in double.
 // Bound by the matrix units of the compute unit a block lies on: blocks of 64 rows where these fill the chip, of 32
-// otherwise.  A block's operands are read to the end of a lane's two or four columns, up to 12 bytes
-// beyond the last row: in the workspace, where every array is followed by another.  SPLIT: many rows and few blocks -- every XCD takes an eighth of the rows (and reads
+// otherwise.  SPLIT: many rows and few blocks -- every XCD takes an eighth of the rows (and reads
 // each of them once: with the blocks spread over the XCDs, every L2 fetched nearly all of the operands, 200 MB in
 // 52 us at 5700 rows of 100 columns) and leaves its part of every block for k_tr_wgrad_sum.
 constexpr int kWgWaves = 4;
