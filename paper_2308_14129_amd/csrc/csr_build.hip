@@ -83,7 +83,7 @@ __global__ void k_fill_csr(const EventRecord *__restrict__ rec, int64_t num_entr
 // passes are composed by a read whose neighbours go to neighbouring places (k_sort_pos).
 // Per pass: digit counts per workgroup (k_sort_count), their prefix sums (k_sort_scan), and the move (k_sort_events, k_sort_entries), no workgroup
 // waiting for another.  31.7 M entries of 0.5 M nodes (Zipf 1.5), with the times' and ids' check: 1.62 -> 0.86 ms (moves 309 and 293 us, counts
-// 41 and 45, positions 127, bounds 36); a sub-graph's whole rebuilding 3.19 -> 2.41 ms.  More nodes than 2^22 would need a third pass and a second copy of the entries; they take the sort above.
+// 41 and 45, positions 127, list bounds 22); a sub-graph's whole rebuilding 3.19 -> 2.41 ms.  More nodes than 2^22 would need a third pass and a second copy of the entries; they take the sort above.
 constexpr int kSortThreads = 512, kSortWaves = kSortThreads / 64;
 constexpr int kSortRounds = 16;                       // entries per lane and tile
 constexpr int kSortTile = kSortThreads * kSortRounds;
@@ -102,6 +102,8 @@ struct SortPass {
     uint32_t *counts;     // [workgroups][bins], then their prefix sums within a bin
     uint32_t *totals;     // [bins]
     uint32_t *bounds;     // [bins + 2] last pass: first entry of every digit, NULL otherwise
+    uint32_t *sample;     // LAST after another pass: node of every entry whose place is a multiple of 2^sample_shift
+    int sample_shift;
     int32_t *flags;
     int64_t n, num_nodes;
     int64_t chunk;        // entries per workgroup, whole tiles
@@ -452,6 +454,8 @@ __global__ void __launch_bounds__(kSortThreads, 4) k_sort_entries(SortPass p)
                 if (at < left) {
                     ((EntryWords *)p.out)[to] = e[v];
                     (p.place + t0)[(unsigned)at] = (int32_t)to;
+                    if ((to & ((1u << p.sample_shift) - 1u)) == 0u)
+                        p.sample[to >> p.sample_shift] = node[u];
                 }
             }
         }
@@ -483,19 +487,47 @@ __global__ void __launch_bounds__(kThreads) k_sort_pos(int32_t *__restrict__ pos
             pos[i0 + u * kThreads] = at[u];
 }
 
-// indptr[n] = entries of nodes below n, n = 0..N, where the nodes are not kept beside the entries: an entry's node is its
-// event's other endpoint.  bounds: first entry of every value of the node's upper digit
+// indptr[n] = entries of nodes below n, n = 0..N.  bounds: first entry of every value of the last pass's digit.  After one pass the
+// digit is the node.  After two the nodes are not kept beside the entries: a list's bound is searched among those that the
+// second pass left of every 2^sample_shift-th entry, and between two of them by the entries, whose node is their event's other
+// endpoint.  Bound by these last steps' memory lines, which nobody else wants.  Flat endpoints of 16 M events over 2.6 M nodes: 234 us
+// with the node of every fourth entry, which costs the second pass 70 (of every eighth 320 and 40; with all steps among the
+// entries 624 us, which made the whole build slower than the library's sort, 2310 -> 2514 us; now 2180).  Zipf 1.5 over
+// 1 M nodes: 38 -> 22 us.
+__global__ void k_bounds_to_indptr(const uint32_t *__restrict__ bounds, int64_t num_nodes, int64_t *__restrict__ indptr)
+{
+    const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (n <= num_nodes)
+        indptr[n] = bounds[n];
+}
+
 __global__ void k_indptr_of_entries(const CsrEntry *__restrict__ csr, const int32_t *__restrict__ src, const int32_t *__restrict__ dst,
-                                    const uint32_t *__restrict__ bounds, int shift, int64_t num_nodes, int64_t *__restrict__ indptr)
+                                    const uint32_t *__restrict__ bounds, const uint32_t *__restrict__ sample, int sample_shift, int shift,
+                                    int64_t num_nodes, int64_t *__restrict__ indptr)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n <= num_nodes; n += stride) {
         int64_t lo = bounds[n >> shift], hi = bounds[(n >> shift) + 1];
+        // the samples of the list: places first, first + 1, ... in units of 2^sample_shift, below hi
+        const int64_t round = ((int64_t)1 << sample_shift) - 1, first = (lo + round) >> sample_shift;
+        int64_t a = first, b = (hi + round) >> sample_shift;
+        while (a < b) {
+            const int64_t mid = a + ((b - a) >> 1);
+            if ((int64_t)sample[mid] < n)
+                a = mid + 1;
+            else
+                b = mid;
+        }
+        // sample a, if it lies in the list, is the first whose node is not below n; the one before it is below
+        hi = (a << sample_shift) < hi ? a << sample_shift : hi;
+        lo = a > first ? ((a - 1) << sample_shift) + 1 : lo;
         while (lo < hi) {
             const int64_t mid = lo + ((hi - lo) >> 1);
             const CsrEntry x = csr[mid];
-            const int32_t s = src[x.eid], d = dst[x.eid];
-            if ((int64_t)(s == x.nbr ? d : s) < n)
+            int32_t node = src[x.eid];
+            if (node == x.nbr)
+                node = dst[x.eid];
+            if ((int64_t)node < n)
                 lo = mid + 1;
             else
                 hi = mid;
@@ -568,7 +600,8 @@ hipError_t sort_passes(SortPass first, SortPass second, int blocks, int bits, hi
     return hipGetLastError();
 }
 
-// scratch: [entries | nodes, then destinations | counts per workgroup and digit | totals | bounds], within csr_build_scratch_bytes
+// scratch: [entries | nodes, then destinations | counts per workgroup and digit | totals | bounds | samples], within
+// csr_build_scratch_bytes
 hipError_t sort_adjacency(const int32_t *src, const int32_t *dst, const double *ts, int64_t num_events, int64_t num_nodes,
                           int64_t *indptr, CsrEntry *csr, int32_t *pos, int32_t *flags, char *scratch, size_t scratch_bytes,
                           int bits, hipStream_t s)
@@ -581,7 +614,14 @@ hipError_t sort_adjacency(const int32_t *src, const int32_t *dst, const double *
     const size_t entries = align_up(sizeof(CsrEntry) * (size_t)n2), nodes = align_up(sizeof(uint32_t) * (size_t)n2);
     const size_t counts = align_up(sizeof(uint32_t) * (size_t)blocks << digit);
     const size_t totals = align_up(sizeof(uint32_t) << digit), bounds = totals + 256;
-    if (entries + nodes + counts + totals + bounds > scratch_bytes)
+    const size_t before = entries + nodes + counts + totals + bounds;
+    // The samples take what is left of the scratch memory: every fourth entry up to some 55 million of them, and
+    // every 256th of the 2^31 that there can be.  (Every second one: 1268 -> 1218 us for 8 M flat events over 4 M nodes, but
+    // 533 -> 551 for 4 M over 0.3 M; every eighth 1328 and 534.)
+    int sample_shift = 2;
+    while (bits > digit && sample_shift < 30 && before + 4 * (((size_t)n2 >> sample_shift) + 1) > scratch_bytes)
+        ++sample_shift;
+    if (before + (bits > digit ? 4 * (((size_t)n2 >> sample_shift) + 1) : 0) > scratch_bytes)
         return hipErrorOutOfMemory;
     SortPass a = {};
     a.src = src, a.dst = dst, a.ts = ts;
@@ -599,6 +639,8 @@ hipError_t sort_adjacency(const int32_t *src, const int32_t *dst, const double *
     b.place = (int32_t *)a.node_out;
     b.bounds = (uint32_t *)(scratch + entries + nodes + counts + totals);
     b.shift = digit;
+    b.sample = (uint32_t *)(scratch + before);
+    b.sample_shift = sample_shift;
     hipError_t e;
     switch (digit) {
     case 8: e = sort_passes<8>(a, b, blocks, bits, s); break;
@@ -608,8 +650,11 @@ hipError_t sort_adjacency(const int32_t *src, const int32_t *dst, const double *
     }
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(k_indptr_of_entries, dim3(grid_for(num_nodes + 1)), dim3(kThreads), 0, s, csr, src, dst, b.bounds,
-                       bits <= digit ? 0 : digit, num_nodes, indptr);
+    if (bits <= digit)
+        hipLaunchKernelGGL(k_bounds_to_indptr, dim3((unsigned)(num_nodes / kThreads + 1)), dim3(kThreads), 0, s, b.bounds, num_nodes, indptr);
+    else
+        hipLaunchKernelGGL(k_indptr_of_entries, dim3(grid_for(num_nodes + 1)), dim3(kThreads), 0, s, csr, src, dst, b.bounds, b.sample,
+                           sample_shift, digit, num_nodes, indptr);
     return hipGetLastError();
 }
 

@@ -86,3 +86,23 @@ def test_a_graph_that_is_not_one_is_refused(n, event):
                                        ((1 << 21) + 1, 4_300_000, 1.1), ((1 << 21) + 1, 4_300_801, 0.0)])
 def test_places_carried_from_tile_to_tile(n, e, alpha):
     test_adjacency_is_the_stable_sort(n, e, alpha)
+
+
+@pytest.mark.parametrize("n,e", [(3_000_001, 60_000_000), (70_000, 60_000_000)])
+def test_list_bounds_between_wider_samples(n, e):
+    # so many entries that the scratch memory holds the node of every sixteenth only
+    import torch
+    gen = torch.Generator(device="cuda:0").manual_seed(n)
+    src = torch.randint(0, n, (e,), device="cuda:0", generator=gen, dtype=torch.int32)
+    dst = torch.randint(0, n // 50, (e,), device="cuda:0", generator=gen, dtype=torch.int32)
+    dst = torch.where(dst == src, (src + 1) % n, dst).to(torch.int32)
+    ts = torch.arange(e, device="cuda:0", dtype=torch.float64)
+    ctx = tig.TigContext(tig.make_config(4, 4, 1, 4, 5, 1, 8), n, src, dst, ts, torch.zeros((e, 1), device="cuda:0"), None)
+    at = 0
+    for size in (4 * e, 4 * e, 8 * e, 4 * e):
+        at = (at + size + 255) // 256 * 256
+    indptr = ctx.persistent[at:at + 8 * (n + 1)].view(torch.int64)
+    count = torch.bincount(torch.cat([src, dst]).long(), minlength=n)
+    assert indptr[0].item() == 0
+    assert torch.equal(indptr[1:], torch.cumsum(count, 0))
+    ctx.close()
