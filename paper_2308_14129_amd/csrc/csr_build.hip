@@ -87,7 +87,10 @@ __global__ void k_fill_csr(const EventRecord *__restrict__ rec, int64_t num_entr
 constexpr int kSortThreads = 512, kSortWaves = kSortThreads / 64;
 constexpr int kSortRounds = 16;                       // entries per lane and tile
 constexpr int kSortTile = kSortThreads * kSortRounds;
-constexpr int kSortBlocks = 1024;                     // four workgroups per compute unit, all resident
+// At most so many workgroups.  Registers leave two of either move to a compute unit (LDS two or three), so that 1024 are two
+// rounds; the counts' fit four.  512, one round: 16 M Zipf events of 1 M nodes 1106 -> 1124 us for the whole build, 4 M flat
+// ones of 0.3 M nodes 555 -> 542; 2048: 1105 -> 1089 and 561 -> 557; the others within one percent either way.
+constexpr int kSortBlocks = 1024;
 constexpr int kDigitBits = 11;
 
 struct SortPass {
