@@ -88,8 +88,8 @@ constexpr int kSortThreads = 512, kSortWaves = kSortThreads / 64;
 constexpr int kSortRounds = 16;                       // entries per lane and tile
 constexpr int kSortTile = kSortThreads * kSortRounds;
 // At most so many workgroups.  Registers leave two of either move to a compute unit (LDS two or three), so that 1024 are two
-// rounds; the counts' fit four.  512, one round: 16 M Zipf events of 1 M nodes 1106 -> 1124 us for the whole build, 4 M flat
-// ones of 0.3 M nodes 555 -> 542; 2048: 1105 -> 1089 and 561 -> 557; the others within one percent either way.
+// rounds; the counts' fit four.  512, one round: 16 M Zipf events of 1 M and of 2.6 M nodes take 1.6% longer for the whole build, 4 M
+// flat ones of 0.3 M nodes 2.4% less; 2048: the Zipf graphs 1.5% and 2% less, flat ones up to 1.4% less.
 constexpr int kSortBlocks = 1024;
 constexpr int kDigitBits = 11;
 
