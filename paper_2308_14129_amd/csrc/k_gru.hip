@@ -131,15 +131,17 @@ struct GateStream {
     }
 };
 
-// KIND: an ordinary step; the state update of a module selection (mean messages, the plain recurrent cell, library
-// exp / tanh); a training step, which keeps what its backward pass reads.  Instances of their own, so that the
-// ordinary one carries nothing of the others (in one kernel they cost a step 2 us and 1 us).
-enum GruKind { kGruPlain, kGruModules, kGruTraining };
+// KIND: an ordinary step; the state update of a module selection (the plain recurrent cell, library exp / tanh), with last
+// messages and with mean ones; a training step, which keeps what its backward pass reads.  Instances of their own, so that the
+// ordinary one carries nothing of the others (in one kernel they cost a step 2 us and 1 us; last and mean messages in one
+// instance spilled 104 scalar registers instead of 69 and 83, and steps of 200 to 2000 events took 0.5 to 1.3 us more: mean messages,
+// GRU, attention 38.4 -> 37.7 at 200 narrow events, 63.2 -> 61.9 at 2000 of 100 columns; last, RNN, projection 14.3 -> 13.8).
+enum GruKind { kGruPlain, kGruModules, kGruMeans, kGruTraining };
 template <int PREC, GruKind KIND>
 __global__ void __launch_bounds__(kGruThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))  // 128 registers: two workgroups per unit
 k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
 {
-    constexpr bool MOD = KIND == kGruModules, TRAIN = KIND == kGruTraining;
+    constexpr bool means = KIND == kGruMeans, MOD = KIND == kGruModules || means, TRAIN = KIND == kGruTraining;
     TIG_MARK(0);
     if (blockIdx.x == 0 && threadIdx.x == 0 && g.clear)
         *g.clear = 0;
@@ -254,9 +256,9 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
             constexpr int kRowsPerWave = EC / kGruWaves, kPieces = 3;  // 192 columns of a segment at a time
             int lane = lane_id();
             asm volatile("" : "+v"(lane));  // (addresses are not taken out of the loop over the items: there are no registers for them)
-            const bool means = MOD && a.mean_msg;  // (uniform)
-            const int second = means ? g.M + g.T + g.F : g.M, feats = means ? 0 : g.F;
-            const int widest = second > feats ? second : feats;
+            // (a mean's columns are taken as two segments, so that their loads are in flight together)
+            const int mean = g.M + g.T + g.F, second = means ? (mean + 1) / 2 : g.M, third = means ? mean - second : g.F;
+            const int wider = second > third ? second : third, widest = means && g.M > wider ? g.M : wider;
             __amdgpu_buffer_rsrc_t rs[kRowsPerWave], ro[kRowsPerWave], rf[kRowsPerWave];
             double since[kRowsPerWave];
 #pragma unroll
@@ -266,12 +268,12 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                 const int u = __builtin_amdgcn_readfirstlane(row_u[r]), o = __builtin_amdgcn_readfirstlane(row_o[r]);
                 const int e = __builtin_amdgcn_readfirstlane(row_e[r]), entry = __builtin_amdgcn_readfirstlane(row_i[r]);
                 const float *self = a.mem + (size_t)u * g.M;
-                const float *other = means ? a.mean_msg + (size_t)entry * second : a.mem + (size_t)o * g.M;
-                const float *feat = a.edge_feat + (size_t)(gj.first_eid + e) * g.F;
+                const float *other = means ? a.mean_msg + (size_t)entry * mean : a.mem + (size_t)o * g.M;
+                const float *feat = means ? other + second : a.edge_feat + (size_t)(gj.first_eid + e) * g.F;
                 rs[i] = __builtin_amdgcn_make_buffer_rsrc((void *)self, 0, live ? 4 * g.M : 0, kBufferFlags);
                 ro[i] = __builtin_amdgcn_make_buffer_rsrc((void *)other, 0, live ? 4 * second : 0, kBufferFlags);
-                rf[i] = __builtin_amdgcn_make_buffer_rsrc((void *)feat, 0, live ? 4 * feats : 0, kBufferFlags);
-                since[i] = a.lu[u];
+                rf[i] = __builtin_amdgcn_make_buffer_rsrc((void *)feat, 0, live ? 4 * third : 0, kBufferFlags);
+                since[i] = means ? 0.0 : a.lu[u];
             }
             double tw_w[kPhi], tw_b[kPhi];  // time-encoding parameters of the lane's first columns
 #pragma unroll
@@ -301,8 +303,8 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
                     float *const keep = TRAIN && ct_lo == 0 && r < n_rows ? a.gru_msg + (size_t)(r0 + r) * g.Dmsg : nullptr;
 #pragma unroll
                     for (int seg = 0; seg < 3; ++seg) {
-                        const int width = seg == 0 ? g.M : (seg == 1 ? second : feats);
-                        const int at = seg == 0 ? 0 : (seg == 1 ? g.M : 2 * g.M + g.T);
+                        const int width = seg == 0 ? g.M : (seg == 1 ? second : third);
+                        const int at = seg == 0 ? 0 : (seg == 1 ? g.M : (means ? g.M + second : 2 * g.M + g.T));
 #pragma unroll
                         for (int k = 0; k < kPieces; ++k) {
                             const int j = c0 + lane + kWave * k;
@@ -457,13 +459,15 @@ GruParams gru_params(const Dims &d)
     return g;
 }
 
-const void *gru_kernel(const Dims &d, int upd, bool train)
+const void *gru_kernel(const Dims &d, int upd, bool means, bool train)
 {
     if (train)
         return (const void *)k_gru<TIG_FP32, kGruTraining>;
     if (d.prec == TIG_BF16_MFMA)  // (module selections run in fp32 contexts)
         return (const void *)k_gru<TIG_BF16_MFMA, kGruPlain>;
-    return upd == kUpdGru ? (const void *)k_gru<TIG_FP32, kGruPlain> : (const void *)k_gru<TIG_FP32, kGruModules>;
+    if (upd == kUpdGru)
+        return (const void *)k_gru<TIG_FP32, kGruPlain>;
+    return means ? (const void *)k_gru<TIG_FP32, kGruMeans> : (const void *)k_gru<TIG_FP32, kGruModules>;
 }
 
 // GRU workgroups and column slices for a batch of `count` events with about `wins_est` winners.
@@ -499,8 +503,8 @@ int gru_lds_bytes(const Dims &d)
 
 hipError_t prepare_gru(const Dims &d, const LaunchPlan &plan)
 {
-    for (int i = 0; i < 3; ++i) {
-        const void *const kernel = gru_kernel(d, i == 1 ? kUpdModuleGru : kUpdGru, i == 2 && d.prec == TIG_FP32);
+    for (int i = 0; i < 4; ++i) {
+        const void *const kernel = gru_kernel(d, i == 1 || i == 3 ? kUpdModuleGru : kUpdGru, i == 3, i == 2 && d.prec == TIG_FP32);
         const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, gru_lds_bytes(d));
         if (e != hipSuccess)
             return e;
@@ -531,7 +535,7 @@ hipError_t launch_gru(const Dims &d, const LaunchPlan &plan, const PackedWeights
     if (blocks == 0)
         return hipSuccess;  // nothing to apply, nothing to finish
     void *args[] = {&aa, &gj, &ww, &g, &dp};
-    return hipLaunchKernel(gru_kernel(d, a.upd, a.gru_gates != nullptr), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
+    return hipLaunchKernel(gru_kernel(d, a.upd, a.mean_msg != nullptr, a.gru_gates != nullptr), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
 }
 
 // The closing launch of a step: scores and embedding rows of its events, inspection outputs, the
@@ -560,7 +564,7 @@ hipError_t launch_closing(const Dims &d, const LaunchPlan &plan, const PackedWei
     int blocks = g.n_gru + p.n_event_blocks + p.n_expand_blocks + p.n_fin_row_blocks + p.n_fin_slot_blocks;
     blocks = blocks > 0 ? blocks : 1;  // (block 0 clears the counter whatever else there is to do)
     void *args[] = {&aa, &gj, &ww, &g, &p};
-    return hipLaunchKernel(gru_kernel(d, a.upd, false), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
+    return hipLaunchKernel(gru_kernel(d, a.upd, a.mean_msg != nullptr, false), dim3(blocks), dim3(kGruThreads), args, (size_t)gru_lds_bytes(d), s);
 }
 
 }  // namespace tig

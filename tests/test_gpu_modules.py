@@ -385,3 +385,15 @@ def test_two_layers_errors_against_64_bits():
         c.close()
     print(f"medians: embeddings {np.median(emb):.3g}, scores {np.median(score):.3g}", flush=True)
     assert np.median(emb) < TWO_LAYER_EMB and np.median(score) < TWO_LAYER_SCORE, (emb, score)
+
+
+# a mean message's columns are gathered as two halves beside the state row: the fewest columns, an odd number of them, halves and
+# state rows on either side of what one round of a wavefront's loads takes (192 columns)
+@pytest.mark.parametrize("name,dims", [("mean_rnn_projection", dict(mem_dim=2, time_dim=2, feat_dim=1)),
+                                       ("mean_gru_identity", dict(mem_dim=200, time_dim=8, feat_dim=3)),
+                                       ("mean_gru_attention", dict(mem_dim=150, time_dim=150, feat_dim=151)),
+                                       ("mean_rnn_projection", dict(mem_dim=192, time_dim=100, feat_dim=92))])
+def test_mean_messages_in_two_halves(name, dims):
+    c = Case(S.WORKLOADS["c1_tiny"].scaled(**dims), INSTANCES[name], False)
+    c.run([(3000, 150), (3150, 150)], warm_at=3000)
+    c.close()
