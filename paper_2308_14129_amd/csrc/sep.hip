@@ -258,15 +258,17 @@ namespace {
 //    "none" without any arithmetic: nine edges in ten of a power-law stream end in "both", a chain of
 //    and / count zeros / exclusive or over the two lowest levels, which stay in registers.  "Both" needs no look at the
 //    hub flags either: where a non-hub is an endpoint, its one partition is all that "both" can be.  The branches that are left
-//    are foreseen most of the time; without them (conditional moves, levels in memory) the chain is twice as long.
-//    Ids are checked and their sets requested a block of edges ahead.
+//    are foreseen most of the time; without them (conditional moves, levels in memory) the chain is twice as long.  An edge
+//    that is not "both" has one more, whether it leaves the sets: in a flat stream none can be foreseen.
+//    Sets and hub flags are requested some edges ahead, one edge's with every decision, so that their misses run beside it.
 // Terms that are evaluated are the IEEE operations of Eq. 3-6 in their order, so the partitions are the
 // same bit for bit; an edge that the sets do not cover (sizes spread over kLevels values or more, terms
 // so close that rounding could make two sizes equal, centralities that are not finite and non-negative)
 // is decided by the plain evaluation (best_plain), and while the sizes are spread that far only their extremes are
-// kept.  Nothing is allocated, so that the C entries have no exception to hold back.  Measured per edge, 8 partitions of 4 M events and 1 M nodes, 1% hubs, before the levels were in registers and after (Xeon
-// at 2.7 GHz): 11.8 -> 5.2 ns; 16 partitions, 5% hubs 11.4 -> 5.2; 5 partitions and mostly non-hubs 12.0 -> 10.6; no hubs, where the
-// sizes are too far apart for the sets from the start, 17.6 -> 16.1.  The whole call of the first (EPYC host of the MI355X): 25.1 -> 13.8 ms.
+// kept.  Nothing is allocated, so that the C entries have no exception to hold back.  Measured per edge (Xeon at 2.7 GHz), with every level in memory
+// and no test for "both", with ids checked and sets requested 64 edges at a time ahead of 64 decisions, and now: 4 M events, 1 M nodes
+// (Zipf 1.5), 8 partitions 12.0, 5.6, 5.1 ns; 16 partitions, 5% hubs 12.2, 5.8, 5.3; 2 M events of 2.6 M nodes (Zipf 1.1), 8
+// partitions 20.4, 25.7, 15.1; 0.6 M events of 1 M nodes (Zipf 0.8) 25.7, 40.8, 22.8.
 class EdgeLoop {
 public:
     EdgeLoop(const tig_sep_config &cfg, int64_t num_nodes, const double *cent, const uint8_t *is_hub, uint64_t *A)
@@ -295,53 +297,18 @@ public:
     // decides `n` further edges; false: an endpoint is outside 0..N-1 (the edges before it are decided)
     bool run(const int32_t *src, const int32_t *dst, int64_t n, int32_t *part_out)
     {
-        // the ids are looked at, and their sets requested, a block ahead of the decisions
-        int64_t ok = valid(src, dst, n < kBlock ? n : kBlock);
-        for (int64_t e0 = 0; e0 < n; e0 += kBlock) {
-            const int64_t m = n - e0 < kBlock ? n - e0 : kBlock, next = e0 + m, left = n - next < kBlock ? n - next : kBlock;
-            const int64_t ahead = ok == m ? valid(src + next, dst + next, left) : 0;
-            decide_block(src + e0, dst + e0, ok, part_out + e0);
-            if (ok < m)
-                return false;
-            ok = ahead;
-        }
-        return true;
-    }
-
-    void sizes(int64_t *out) const
-    {
-        for (int p = 0; p < P_; ++p)
-            out[p] = size_[p];
-    }
-
-private:
-    static constexpr int64_t kBlock = 64;
-    static constexpr int kLevels = 16;
-    static constexpr int kRing = 1024;  // the sets move up one place whenever mn grows; moved back after so many
-    struct Terms {          // balance terms (Eq. 6) of sizes mn .. mx, mx - mn = g
-        double den;         // their denominator, -1: not computed yet
-        double of[kLevels];
-        bool distinct;      // terms of different sizes stay apart when a replica term is added
-    };
-
-    // edges before the first with an endpoint outside 0..N-1
-    int64_t valid(const int32_t *src, const int32_t *dst, int64_t n) const
-    {
-        const uint64_t N = (uint64_t)N_;
-        for (int64_t e = 0; e < n; ++e) {
-            const uint32_t i = (uint32_t)src[e], j = (uint32_t)dst[e];
-            if ((i >= N) | (j >= N))
-                return e;
-            __builtin_prefetch(A_ + i);
-            __builtin_prefetch(A_ + j);
-        }
-        return n;
-    }
-
-    void decide_block(const int32_t *src, const int32_t *dst, int64_t n, int32_t *part_out)
-    {
+        constexpr int64_t kAhead = 24;  // edges whose endpoints' sets and hub flags are requested early
         uint64_t *const A = A_;
-        const uint64_t all = all_;
+        const uint8_t *const hub = is_hub_;
+        // (whatever the ids are: a request is a hint, and an address of nothing is passed over)
+        const auto request = [A, hub](int32_t i, int32_t j) {
+            const uintptr_t a = (uintptr_t)A, h = (uintptr_t)hub, u = (uint32_t)i, v = (uint32_t)j;
+            __builtin_prefetch((const void *)(a + sizeof(uint64_t) * u));
+            __builtin_prefetch((const void *)(a + sizeof(uint64_t) * v));
+            __builtin_prefetch((const void *)(h + u));
+            __builtin_prefetch((const void *)(h + v));
+        };
+        const uint64_t N = (uint64_t)N_, all = all_;
         const bool easy = easy_ && mx_ + n < ((int64_t)1 << 31);
         int64_t e = 0;
         while (e < n) {
@@ -353,18 +320,24 @@ private:
             uint64_t l0 = lev[0], l1 = lev[1];
             const int64_t stop = !easy || mx - mn >= kLevels ? e : n;
             for (; e < stop; ++e) {
+                if (e + kAhead < n)
+                    request(src[e + kAhead], dst[e + kAhead]);
                 const uint32_t i = (uint32_t)src[e], j = (uint32_t)dst[e];
+                if (i >= N || j >= N)
+                    break;
                 const uint64_t ai = A[i], aj = A[j], both = ai & aj;
                 uint64_t set = both;
                 // (a resident non-hub has one partition: where it is an endpoint, `both` is that partition or empty)
                 if (__builtin_expect(!both, 0)) {
                     const uint64_t any = ai | aj;
                     // the partition of a resident non-hub is the only candidate; two of them: Case 3
-                    const uint64_t x = is_hub_[i] ? 0 : ai, y = is_hub_[j] ? 0 : aj, xy = x | y;
+                    const uint64_t x = ai & ((uint64_t)(hub[i] != 0) - 1u), y = aj & ((uint64_t)(hub[j] != 0) - 1u), xy = x | y;
                     // (two non-hubs apart; hubs on partitions of their own: the replicas' worths have to be compared)
-                    if ((x != 0 && y != 0) || (ai != 0 && aj != 0 && xy == 0))
+                    const bool two = (x != 0) & (y != 0), apart = (ai != 0) & (aj != 0) & (xy == 0);
+                    if (two | apart)
                         break;
-                    set = xy ? xy : (any ? any : all);
+                    set = any ? any : all;
+                    set = xy ? xy : set;
                 }
                 const uint64_t m0 = set & l0;
                 uint64_t bit;
@@ -421,7 +394,11 @@ private:
                 levels_from_sizes();
             // one edge of any kind, or all of them while the sizes are too far apart for the sets
             while (e < n) {
+                if (e + kAhead < n)
+                    request(src[e + kAhead], dst[e + kAhead]);
                 const int64_t i = src[e], j = dst[e];
+                if (i < 0 || i >= N_ || j < 0 || j >= N_)
+                    return false;
                 const int p = decide(i, j);
                 part_out[e] = p;
                 if (p >= 0) {
@@ -434,7 +411,23 @@ private:
                     break;
             }
         }
+        return true;
     }
+
+    void sizes(int64_t *out) const
+    {
+        for (int p = 0; p < P_; ++p)
+            out[p] = size_[p];
+    }
+
+private:
+    static constexpr int kLevels = 16;
+    static constexpr int kRing = 1024;  // the sets move up one place whenever mn grows; moved back after so many
+    struct Terms {          // balance terms (Eq. 6) of sizes mn .. mx, mx - mn = g
+        double den;         // their denominator, -1: not computed yet
+        double of[kLevels];
+        bool distinct;      // terms of different sizes stay apart when a replica term is added
+    };
 
     int decide(int64_t i, int64_t j)
     {

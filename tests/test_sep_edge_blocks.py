@@ -38,3 +38,17 @@ def test_blocks_against_one_edge_at_a_time(n, parts):
     assert part.tolist() == list(ref_part)
     assert masks.tolist() == [sum(1 << p for p in a) for a in A]
     assert sizes.tolist() == list(ref_sizes)
+
+
+@pytest.mark.parametrize("n", [23, 24, 25, 26, 49])  # endpoints are requested 24 edges ahead, whatever they are
+def test_ends_of_what_is_requested_ahead(n):
+    src, dst, cent, hub = _stream(n, 300, n)
+    part, masks, _ = sep.assign(sep.make_config(3, 0.0, 0.0, 1.0, 1e-3), src, dst, 300, cent, hub)
+    ref_part, A, _, _ = P.assign_stream(src, dst, 300, cent, np.flatnonzero(hub).tolist(), 3, 1.0, 1e-3)
+    assert part.tolist() == list(ref_part)
+    assert masks.tolist() == [sum(1 << p for p in a) for a in A]
+    for bad in (-1, -2**31, 2**31 - 1):
+        dst[n - 1] = bad
+        with pytest.raises(tig.TigError) as err:
+            sep.assign(sep.make_config(3, 0.0, 0.0, 1.0, 1e-3), src, dst, 300, cent, hub)
+        assert err.value.status == tig.TIG_ERANGE
