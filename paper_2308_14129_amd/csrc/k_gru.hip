@@ -136,6 +136,8 @@ struct GateStream {
 // ordinary one carries nothing of the others (in one kernel they cost a step 2 us and 1 us; last and mean messages in one
 // instance spilled 104 scalar registers instead of 69 and 83, and steps of 200 to 2000 events took 0.5 to 1.3 us more: mean messages,
 // GRU, attention 38.4 -> 37.7 at 200 narrow events, 63.2 -> 61.9 at 2000 of 100 columns; last, RNN, projection 14.3 -> 13.8).
+// Spilled in the others: 35 scalar registers (bf16), 53 (fp32), 79 (training), to lanes of vector registers, and none of these: a
+// wavefront's six row descriptors, the weights' bases and the closing work's arguments are alive together.
 enum GruKind { kGruPlain, kGruModules, kGruMeans, kGruTraining };
 template <int PREC, GruKind KIND>
 __global__ void __launch_bounds__(kGruThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))  // 128 registers: two workgroups per unit

@@ -40,23 +40,27 @@ __device__ inline int row_of_entry_tr(const QuerySet &qs, int i, int entries)
 }
 
 // ------------------------------------------------------------------------------------------
-// One wavefront per event, sixteen consecutive events per workgroup, an eighth of the batch per XCD.  y = W_a emb_src + W_b emb_other + b1 comes from
+// One wavefront per event, sixteen consecutive events per workgroup.  y = W_a emb_src + W_b emb_other + b1 comes from
 // the per-row halves that the forward pass left; d y goes to the source's row of DA and the other's row
-// of DB (a negative's row belongs to its event alone: stored, not added).  Events of one moment share a hub's row: their workgroups'
-// additions come from one XCD, and a workgroup adds each of its rows once (an addition of its own for every event, from
-// all XCDs in turn, at 4000 events of 100 columns of which 44% touch one node: 12.2 us instead of 10.4).
+// of DB (a negative's row belongs to its event alone: stored, not added).
+// MERGE: events of one moment share a hub's row, and additions to one row take turns.  An eighth of the batch per XCD, so that a
+// row's come from one of them, and a workgroup adds each of its rows once (merge_rows: when).
 constexpr int kDecThreads = 1024, kDecWaves = kDecThreads / kWave;
 constexpr int kDecCols = 8;  // 64-column pieces of a row at most
 constexpr int kDecXcds = 8;
 
+template <bool MERGE>
 __global__ void __launch_bounds__(kDecThreads) k_tr_decode(StepArgs a, PackedWeights w, TrainArrays t, int E, int Ep)
 {
     extern __shared__ float wsum[];  // [waves x (E + 1)] the wavefronts' shares of the gradients of w_d2 and b_d2
-    float *const share = wsum + kDecWaves * (E + 1);  // [2][waves x E] what the events add to DA, to DB
+    float *const share = wsum + kDecWaves * (E + 1);  // MERGE: [2][waves x E] what the events add to DA, to DB
     __shared__ int s_row[2][kDecWaves];
     const int B = a.count, lane = lane_id(), wave = wave_id_uniform();
     const int per_xcd = ((int)gridDim.x + kDecXcds - 1) / kDecXcds;  // (a launch's workgroups go round the XCDs)
-    const int b = ((int)blockIdx.x % kDecXcds * per_xcd + (int)blockIdx.x / kDecXcds) * kDecWaves + wave;
+    const int block = MERGE ? (int)blockIdx.x % kDecXcds * per_xcd + (int)blockIdx.x / kDecXcds : (int)blockIdx.x;
+    const int b = block * kDecWaves + wave;
+    if (MERGE && block * kDecWaves >= B)  // (the grid is whole rounds over the XCDs)
+        return;
     const bool on = b < B;  // (uniform over the wavefront)
     const int bb = on ? b : 0;
     const int row[3] = {row_of_entry_tr(a.qs, 2 * bb, 2 * B), row_of_entry_tr(a.qs, 2 * bb + 1, 2 * B), 2 * B + bb};
@@ -101,21 +105,28 @@ __global__ void __launch_bounds__(kDecThreads) k_tr_decode(StepArgs a, PackedWei
             if (j < E) {
                 wsum[wave * (E + 1) + j] = dl[0] * g[0][c] + dl[1] * g[1][c];
                 const float dp = g[0][c] > 0.0f ? dl[0] * w2[c] : 0.0f, dn = g[1][c] > 0.0f ? dl[1] * w2[c] : 0.0f;
-                share[wave * E + j] = dp + dn;
-                share[(kDecWaves + wave) * E + j] = dp;
+                if (MERGE) {
+                    share[wave * E + j] = dp + dn;
+                    share[(kDecWaves + wave) * E + j] = dp;
+                } else if (on) {
+                    atomicAdd(&t.DA[(size_t)row[0] * E + j], dp + dn);
+                    atomicAdd(&t.DB[(size_t)row[1] * E + j], dp);
+                }
                 if (on)
                     t.DB[(size_t)row[2] * E + j] = dn;
             }
         }
     if (lane == 0) {
         wsum[wave * (E + 1) + E] = dl[0] + dl[1];
-        s_row[0][wave] = on ? row[0] : -1;
-        s_row[1][wave] = on ? row[1] : -1;
+        if (MERGE) {
+            s_row[0][wave] = on ? row[0] : -1;
+            s_row[1][wave] = on ? row[1] : -1;
+        }
     }
     __syncthreads();
     // the first event of the workgroup with a row adds for all of them
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
+    for (int p = 0; MERGE && p < 2; ++p) {
         const int mine = __builtin_amdgcn_readfirstlane(s_row[p][wave]);
         const int theirs = lane < kDecWaves ? s_row[p][lane] : -1;
         const unsigned long long same = __ballot(theirs == mine && lane < kDecWaves);
@@ -938,7 +949,20 @@ const void *gru_back_kernel(int rows)
     return rows == 4 ? (const void *)k_tr_gru_back<4> : (rows == 8 ? (const void *)k_tr_gru_back<8> : (const void *)k_tr_gru_back<16>);
 }
 
-int decode_lds_bytes(const Dims &d) { return kDecWaves * (3 * d.E + 1) * 4; }
+int decode_lds_bytes(const Dims &d, bool merge) { return kDecWaves * ((merge ? 3 : 1) * d.E + 1) * 4; }
+
+// Turns at shared rows count where they are more than the launch's latency hides: many events of wide rows, and few rows for
+// them (by the steps before, whose rows are estimated up to an eighth high: a negative's for every event, and at most one
+// more; then two to three endpoints ask for the same row).  And two workgroups have to fit a compute unit's LDS, up
+// to 425 columns.  Every event on its own and merged, 100 columns, 44% of the endpoints at one node: 4000 events 12.1 and 10.2 us,
+// 3000 10.5 and 9.4, 2000 9.1 and 8.9, 1000 7.7 and 8.8; of a quarter as many events a moment, 4000 10.4 and 10.2, 2000 7.9 and 8.8; a
+// sixteenth, 4000 10.1 and 10.7; 32 columns, 4000 7.4 and 8.1; 400 columns, 2000 17.4 and 16.7; one workgroup a unit, 5000 events of 512 columns
+// 33 and 43.
+bool merge_rows(const Dims &d, const StepArgs &a)
+{
+    const size_t lds = (size_t)decode_lds_bytes(d, true) + 2 * kDecWaves * sizeof(int);
+    return a.rows_est > 0 && a.rows_est <= 2 * a.count && (int64_t)a.count * d.E >= (1 << 18) && lds <= 80 * 1024;
+}
 
 }  // namespace
 
@@ -951,7 +975,9 @@ bool train_back_fits(const Dims &d)
 
 hipError_t prepare_train_back(const Dims &d)
 {
-    hipError_t e = hipFuncSetAttribute((const void *)k_tr_decode, hipFuncAttributeMaxDynamicSharedMemorySize, decode_lds_bytes(d));
+    hipError_t e = hipFuncSetAttribute((const void *)k_tr_decode<false>, hipFuncAttributeMaxDynamicSharedMemorySize, decode_lds_bytes(d, false));
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void *)k_tr_decode<true>, hipFuncAttributeMaxDynamicSharedMemorySize, decode_lds_bytes(d, true));
     for (const int h : kGbHeights)
         if (e == hipSuccess)
             e = hipFuncSetAttribute(gru_back_kernel(h), hipFuncAttributeMaxDynamicSharedMemorySize, gru_back_lds(d, h));
@@ -967,8 +993,12 @@ hipError_t prepare_train_back(const Dims &d)
 
 hipError_t launch_train_decode(const Dims &d, const StepArgs &a, const PackedWeights &pw, const TrainArrays &t, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_tr_decode, dim3(((a.count + kDecWaves - 1) / kDecWaves + kDecXcds - 1) / kDecXcds * kDecXcds), dim3(kDecThreads), decode_lds_bytes(d), s, a, pw, t,
-                       d.E, d.Ep);
+    const int blocks = (a.count + kDecWaves - 1) / kDecWaves;
+    if (merge_rows(d, a))
+        hipLaunchKernelGGL(k_tr_decode<true>, dim3((blocks + kDecXcds - 1) / kDecXcds * kDecXcds), dim3(kDecThreads), decode_lds_bytes(d, true), s,
+                           a, pw, t, d.E, d.Ep);
+    else
+        hipLaunchKernelGGL(k_tr_decode<false>, dim3(blocks), dim3(kDecThreads), decode_lds_bytes(d, false), s, a, pw, t, d.E, d.Ep);
     return hipGetLastError();
 }
 

@@ -352,3 +352,13 @@ def test_training_needs_fp32_negatives_and_a_workspace(c1):
         half.train_attach(W)
     assert ei.value.status == tig.TIG_EINVAL
     half.close()
+
+
+# the loss's gradients merged per workgroup: enough events times columns, and rows that several endpoints ask for by the step before
+# (the first step of each run is not merged); 425 columns are the most that are merged, and 650 and 2701 events leave
+# workgroups of the grid without an event, the latter one with a single event
+@pytest.mark.parametrize("emb,count", [(100, 2701), (425, 650), (426, 650)])
+def test_gradients_of_rows_that_many_events_share(emb, count):
+    w5 = S.WORKLOADS["c5_gpu_partition"]
+    b = Bundle(w5.scaled(num_events=40000, n_src=20000, span=float(int(w5.span * 40000 / w5.num_events)), emb_dim=emb))
+    run_training(b, [(30000, count), (30000 + count, count)], 0.0, "deferred", warm_at=30000, inspect=False)
