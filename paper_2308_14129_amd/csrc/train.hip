@@ -46,7 +46,8 @@ struct __attribute__((packed, aligned(4))) Floats {
 // A and B are read through buffer descriptors whose extent is the n rows: a k beyond the end reads zeros.  Where a width is no
 // multiple of a lane's two or four columns, its load of the last row reaches beyond the extent: such loads are checked dword
 // by dword, so that the columns inside arrive and those outside, which are no columns of the matrix, read zero; nothing behind
-// an array is read.  Two groups of kU k-steps take turns, one on its way while the other is multiplied.
+// an array is read.  Two groups of kU k-steps take turns, one on its way while the other is multiplied; where the rows end with the
+// first group, nothing more is asked for (three groups of loads for the few rows of 16 events: k_tr_wgrad 5.7 instead of 5.1 us).
 template <int MI, int kU>  // kU: k-steps of 4 whose loads are issued together
 __device__ inline void multiply(const float *A, const float *B, int sa, int sb, int ao, int bo, int n, floatx4 (&acc)[MI][2],
                                 double (&sum)[MI])
@@ -109,6 +110,8 @@ __device__ inline void multiply(const float *A, const float *B, int sa, int sb, 
     for (int k = 0; k < n; k += 8 * kU) {
         request(y, k + 4 * kU);
         products(x, k);
+        if (k + 4 * kU >= n)  // (uniform)
+            break;
         request(x, k + 8 * kU);
         products(y, k + 4 * kU);
     }
