@@ -136,8 +136,9 @@ struct GateStream {
 // ordinary one carries nothing of the others (in one kernel they cost a step 2 us and 1 us; last and mean messages in one
 // instance spilled 104 scalar registers instead of 69 and 83, and steps of 200 to 2000 events took 0.5 to 1.3 us more: mean messages,
 // GRU, attention 38.4 -> 37.7 at 200 narrow events, 63.2 -> 61.9 at 2000 of 100 columns; last, RNN, projection 14.3 -> 13.8).
-// Spilled in the others: 35 scalar registers (bf16), 53 (fp32), 79 (training), to lanes of vector registers, and none of these: a
-// wavefront's six row descriptors, the weights' bases and the closing work's arguments are alive together.
+// Spilled in the others: 35 scalar registers (bf16), 58 (fp32), 79 (training), to lanes of vector registers, and none of these: a
+// wavefront's six row descriptors, the weights' bases and the closing work's arguments are alive together.  (Arguments read again
+// where they are used, from a pointer that the compiler cannot see through: none spilled, and every step 0.8 to 1.4 us longer.)
 enum GruKind { kGruPlain, kGruModules, kGruMeans, kGruTraining };
 template <int PREC, GruKind KIND>
 __global__ void __launch_bounds__(kGruThreads) __attribute__((amdgpu_waves_per_eu(4, 4)))  // 128 registers: two workgroups per unit
@@ -326,6 +327,10 @@ k_gru(StepArgs a, GruJob gj, PackedWeights w, GruParams g, DecodeParams dp)
 #pragma unroll
                 for (int i = 0; i < kRowsPerWave; ++i) {
                     const int r = wave_u + i * kGruWaves;
+                    // (uniform; what stands in a row beyond reaches no other.  Computed for all sixteen rows: steps of 1 to 16 events 0.2 us
+                    // more; left out in the other instances, 0 to 0.4 us more)
+                    if (KIND == kGruPlain && PREC == TIG_FP32 && r >= n_rows)
+                        continue;
                     const float x = time_enc(w_rev, b_rev, since[i]);
                     P::store_a(X + (size_t)r * g.ldx, 2 * g.M + j, x);
                     if (TRAIN && ct_lo == 0 && r < n_rows)
